@@ -213,8 +213,8 @@ int svdq_debug_act(const svdq_layer_dev *layer, const void *workspace, int M,
 
 /*
  * Exact int32 group sums A_g[m, n] = sum_{k in g} qx[m, k] qw[k, n] for the window
- * m0 <= m < m1, n0 <= n < n1, all g, produced by the GEMM kernel itself (the same instantiation
- * of the MFMA loop with an extra store), from the codes in `workspace`.
+ * m0 <= m < m1, n0 <= n < n1, all g, produced by the GEMM kernel of large launches itself (the same
+ * MFMA loop with an extra store), from the codes in `workspace`.
  *   out device int32 [(m1 - m0) x (n1 - n0) x G].
  */
 int svdq_debug_group_acc(const svdq_layer_dev *layer, const void *workspace, int M,

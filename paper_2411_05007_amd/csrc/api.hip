@@ -116,6 +116,11 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     const bool lowrank = s.rank > 0 && !(opts & SVDQ_OPT_SKIP_LOWRANK);
     const bool unfused = opts & SVDQ_OPT_UNFUSED;
 
+    // small launches: the kernel whose wavefronts share K, unless the caller's options force a K split.  All others: tile
+    // count and K split follow the plan the workspace was sized for
+    const int kpar = svdq::plan_kpar_int4(M, s.N, s.K / svdq::kGroup, ksplit_override());
+    const svdq::GemmPlan plan = svdq::plan_gemm(M, s.N, s.K / svdq::kGroup, ksplit_force > 0 ? ksplit_force : ksplit_override());
+
     svdq::ActParams a{};
     a.X = static_cast<const uint16_t *>(X);
     a.rinv = static_cast<const float *>(L->rinv);
@@ -126,13 +131,11 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     a.hfrag = ws + w.hfrag_off;
     a.M = M; a.K = s.K; a.G = s.K / svdq::kGroup; a.Mpad = w.Mpad; a.rank = s.rank;
     a.zero_words = reinterpret_cast<uint32_t *>(ws + w.counters_off);
-    a.n_zero = w.n_counters;
+    a.n_zero = kpar ? 0 : w.n_counters;
     a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
     a.whole = w.act.whole; a.chunks0 = w.act.chunks0; a.gchunk0 = w.act.gchunk0;
     a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
     a.arrived = reinterpret_cast<unsigned long long *>(ws + w.aflags_off);
-    // tile count and K split follow the plan the workspace was sized for
-    const svdq::GemmPlan plan = svdq::plan_gemm(M, s.N, s.K / svdq::kGroup, ksplit_force > 0 ? ksplit_force : ksplit_override());
 
     hipError_t e;
     if (!unfused) {
@@ -143,8 +146,9 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
             if (e != hipSuccess) return hip_fail(e);
         }
         svdq::GemmW4Params g = gemm_params(L, ws, w, M, Y, lowrank ? s.rank : 0);
-        g.ksplit = plan.ksplit;
-        g.tail = plan.tail;
+        g.ksplit = kpar ? 1 : plan.ksplit;
+        g.tail = kpar ? 0 : plan.tail;
+        g.kpar = kpar;
         e = svdq::launch_gemm_w4a4(g, stream);
         if (e != hipSuccess) return hip_fail(e);
     } else {
@@ -160,8 +164,9 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
             if (e != hipSuccess) return hip_fail(e);
         }
         svdq::GemmW4Params g = gemm_params(L, ws, w, M, Y, 0);
-        g.ksplit = plan.ksplit;
-        g.tail = plan.tail;
+        g.ksplit = kpar ? 1 : plan.ksplit;
+        g.tail = kpar ? 0 : plan.tail;
+        g.kpar = kpar;
         e = svdq::launch_gemm_w4a4(g, stream);
         if (e != hipSuccess) return hip_fail(e);
         if (lowrank) {
@@ -224,6 +229,10 @@ int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
         const svdq::GemmPlan pl = svdq::plan_gemm(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.tail; out[10] = pl.ksplit; out[11] = pl.tiles - pl.tail + pl.tail * pl.ksplit;
+        if (const int kpar = svdq::plan_kpar_int4(M, s->N, G, ksplit_override())) {
+            out[8] = out[11] = ((M + svdq::kpar_rows(kpar) - 1) / svdq::kpar_rows(kpar)) * ((s->N + 63) / 64);
+            out[9] = 0; out[10] = 1;
+        }
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else {
         return SVDQ_EUNSUPPORTED;
@@ -251,16 +260,15 @@ int svdq_linear_forward_static(const svdq_layer_dev *L, const void *X, int M, vo
     if (got != SVDQ_OK) return got;
     const svdq_shape &s = L->shape;
     // the plan the caller's options ask for if its workspace fits the array, else the same forward without parked partial
-    // results (no K split in the GEMM, one activation-kernel workgroup per 16 tokens); a batch whose activation blocks
-    // alone do not fit is refused
+    // tiles (no K split in the GEMM), else without any parked results (one activation-kernel workgroup per 16 tokens
+    // too); a batch whose activation blocks alone do not fit is refused
     int kforce = 0, aforce = 0;
-    if (svdq::workspace_layout(M, s.K, s.N, s.rank, ksplit_override(), act_override()).total > kStaticScratchBytes) {
-        kforce = 1;
-        aforce = svdq::kActChunkWhole;
-    }
-    if (svdq::workspace_layout(M, s.K, s.N, s.rank, kforce > 0 ? kforce : ksplit_override(), aforce > 0 ? aforce : act_override()).total >
-        kStaticScratchBytes)
-        return SVDQ_ENOSPACE;
+    auto bytes = [&]() {
+        return svdq::workspace_layout(M, s.K, s.N, s.rank, kforce > 0 ? kforce : ksplit_override(), aforce > 0 ? aforce : act_override()).total;
+    };
+    if (bytes() > kStaticScratchBytes) kforce = 1;
+    if (bytes() > kStaticScratchBytes) aforce = svdq::kActChunkWhole;
+    if (bytes() > kStaticScratchBytes) return SVDQ_ENOSPACE;
     return forward_int4(L, X, M, Y, ws, kStaticScratchBytes, hip_stream, kforce, aforce);
 }
 

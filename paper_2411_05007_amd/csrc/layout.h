@@ -176,10 +176,35 @@ struct WorkspaceFp4 {
 };
 
 
+// Variants of the GEMM for launches of few tiles: (32 RB) x 64 tiles, KS wavefronts per workgroup that share K.
+enum KparVariant { kKparNone = 0, kKpar1x8, kKpar2x8, kKpar2x4, kKpar4x8, kKpar4x4, kKparVariants };
+// INT4.  Small tiles where the launch is short of workgroups, larger ones where it is not (fewer bytes from the L2 per
+// product); eight wavefronts while one such workgroup per CU is all there is, four (two workgroups per CU) beyond.
+// Measured, us per forward at rank 32 with the kernel of 128 x 256 tiles (K loops split over workgroups) first:
+//   M = 256, K = N = 1152 (72 tiles of 64 x 64): 27.8; 1x8 11.6, 2x8 12.5, 2x4 13.3.   M = 64, K = 12288, N = 3072 (48): 49.9; 1x8 20.7, 2x8 24.5
+//   M = 300, K = 3072, N = 2064 (165): 35.6; 1x8 17.5, 2x8 15.6, 2x4 17.1.              M = 128, K = 3072, N = 9216 (288): 31.5; 2x8 19.1, 2x4 17.3
+//   M = 512, K = N = 3072 (384): 32.3; 2x8 20.3, 2x4 18.9, 4x8 19.3, 4x4 21.7.           M = 512, K = 12288, N = 3072 (384), rank 128: 63.4; 2x4 45.2, 4x8 43.6
+//   M = 512, K = 3072, N = 9216 (1152): 40.5; 2x4 34.0, 4x4 36.9.                       M = 4096, K = 4608, N = 1152 (1152): 59.6; 2x4 51.5, 4x4 54.2
+//   M = 2048, K = N = 3072 (1536): 47.6; 2x4 42.9, 4x4 39.6.                            M = 1024, K = 3072, N = 9216 (2304): 59.1; 2x4 53.1, 4x4 52.7
+//   M = 4608, K = N = 3072 (3456): 69.5; 2x4 84.9, 4x4 77.0.                            M = 4096, K = 1152, N = 4608 (4608): 47.5; 2x4 55.8, 4x4 51.0
+inline int kpar_rows(int variant) { return variant == kKpar1x8 ? 32 : variant == kKpar2x8 || variant == kKpar2x4 ? 64 : 128; }
+inline int plan_kpar_int4(int M, int N, int G, int ksplit_override = 0) {
+    if (ksplit_override > 0) return kKparNone;
+    const long tn = (N + 63) / 64, t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
+    if (t32 <= 256) return kKpar1x8;
+    if (t64 <= 256) return kKpar2x8;
+    if (t128 <= 256 && G >= 128) return kKpar4x8;
+    if (t64 > 2304) return kKparNone;
+    const long rest = t128 % 512;      // 128-row tiles where their last round of 512 places is at least half full
+    return t128 > 256 && (rest == 0 || rest >= 256) ? kKpar4x4 : kKpar2x4;
+}
+
 // How the W4A4 GEMM of an M x N x (64 G) layer is launched.  Tiles are 128 x 256, two workgroups per CU (512 places).
-// A launch with at most one workgroup per CU has the K loop of every tile split over up to eight workgroups (at least
+// The K loops of a launch with at most one workgroup per CU can be split over up to eight workgroups per tile (at least
 // twelve groups each): every one of them writes its fp32 partial tile to the workspace, and the one that finishes last
-// adds them up (in split order, so the result does not depend on who is last) and stores Y.
+// adds them up (in split order, so the result does not depend on who is last) and stores Y.  Left to themselves such
+// launches run the kernel whose wavefronts share K instead (plan_kpar_int4) and park nothing; the workspace keeps room
+// for the split, which a caller can ask for (SVDQ_OPT_KSPLIT).
 // The kernel can also split only the last `tail` tiles of the launch order (the partly filled last round of a large
 // launch); measured on the FLUX.1 shapes that gains nothing, because parked tiles travel with device-scope accesses,
 // past the L2, at a fraction of the ordinary bandwidth: 1728 tiles with the last 192 split two ways ran 192.9 us

@@ -1,0 +1,41 @@
+"""The GEMM of launches with few output tiles, whose wavefronts share K (csrc/gemm_*kpar*): every variant that the
+launch rule can pick, at the sizes where its indexing can go wrong - rows and columns off its tiles, a K of fewer groups
+than wavefronts, group counts off the wavefront count, ranks with more steps than wavefronts - against the oracle, with
+the bounds of the large kernel's tests (one bf16 rounding plus fp32 summation order)."""
+import numpy as np
+import pytest
+
+from oracle import svdq_oracle as O
+from paper_2411_05007_amd import svdq as S
+from tests.test_gpu_parity import _run_and_compare, torch  # noqa: F401 (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(rng, K, N, r):
+    G = K // 64
+    rinv = np.exp2(rng.uniform(-1, 1, K)).astype(np.float32)
+    qw = rng.integers(-7, 8, size=(K, N)).astype(np.int8)
+    sw = rng.uniform(5e-4, 4e-3, size=(G, N)).astype(np.float16)
+    l1 = O.bf16_round((rng.standard_normal((K, r)) * 0.02).astype(np.float32))
+    l2 = O.bf16_round((rng.standard_normal((r, N)) * 0.05).astype(np.float32))
+    return S.svdq_pack(rinv, l1, l2, qw, sw, rng.standard_normal(N).astype(np.float32))
+
+
+# rows per tile of the variant that the rule picks, and its tile count, follow each shape
+@pytest.mark.parametrize("M,K,N,r,rows", [
+    (1, 64, 16, 16, 32), (33, 128, 80, 16, 32), (31, 576, 1040, 144, 32), (64, 1088, 272, 0, 32),             # 32 rows, 8 wavefronts
+    (290, 192, 2064, 32, 64), (257, 704, 3072, 144, 64), (320, 64, 2032, 16, 64),                             # 64 rows, 8 wavefronts
+    (610, 192, 2064, 48, 64), (577, 832, 2320, 32, 64), (129, 64, 6160, 16, 64),                              # 64 rows, 4 wavefronts
+    (520, 8256, 1984, 32, 128), (385, 8192, 3072, 160, 128),                                                  # 128 rows, 8 wavefronts
+    (1000, 192, 3088, 80, 128), (897, 320, 3056, 16, 128), (1030, 64, 2736, 32, 128)])                        # 128 rows, 4 wavefronts
+def test_every_variant_at_its_edges(torch, M, K, N, r, rows):  # noqa: F811
+    rng = np.random.default_rng(5200 + M + K + N)
+    prep = _layer(rng, K, N, min(r, K // 16 * 16, N))
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x[:, rng.choice(K, max(1, K // 100), replace=False)] *= 50
+    plan = S.svdq_debug_launch_plan(M, prep.shape)
+    assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // rows) * -(-N // 64), 1)
+    print(f"small launch: M={M} K={K} N={N} r={prep.shape.rank}, {rows}-row tiles", flush=True)
+    sample = np.unique(np.concatenate([np.arange(min(M, 40)), np.arange(max(0, M - 40), M), rng.integers(0, M, 60)]))
+    _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"small {M}x{K}x{N}", window=False)
