@@ -148,7 +148,7 @@ def bench_w4a16(args, np, torch, S, hip):
         "dtype": "int4 codes widened to fp32, fp32 FMA and accumulate, bf16 out", "data": "synthetic",
         "config": {"workload": f"FLUX.1 modulation linear: M={M} K={K} N={N} r={r} g=64, weights rotated over {nsets} copies"},
         "kernels": {"projection_us": proj_us, "w4a16_us": main_us},
-        "roofline": {"bound": "hbm", "kernel": "w4a16_stream_kernel" if M <= 2 else "w4a16_kernel",
+        "roofline": {"bound": "hbm", "kernel": "w4a16_mfma_kernel",
                      "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None},
     }), flush=True)
 

@@ -317,8 +317,8 @@ int svdq_fp4_debug_act(const svdq_layer_dev *layer, const void *workspace, int M
  * i.e. Eq. 5 without quantizing the activations.  Arguments, stream and errors as for svdq_linear_forward; the
  * workspace holds only H and its bf16 parts: svdq_w4a16_workspace_bytes(M, shape) bytes (a workspace sized for
  * svdq_linear_forward is larger and does as well).  A weight-streaming kernel meant for the handful of rows these layers
- * see; any M is accepted (eight rows per pass over the weights).  Enqueues two kernels (down projection, then the
- * weight stream).
+ * see; any M is accepted (sixteen rows per pass over the weights).  Enqueues one kernel up to rank 64, two beyond (down
+ * projection, then the weight stream).
  */
 size_t svdq_w4a16_workspace_bytes(int M, const svdq_shape *shape);
 int svdq_w4a16_forward(const svdq_layer_dev *layer, const void *X, int M, void *Y,

@@ -431,8 +431,10 @@ int svdq_w4a16_forward(const svdq_layer_dev *L, const void *X, int M, void *Y, v
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const bool lowrank = s.rank > 0 && !(g_options & SVDQ_OPT_SKIP_LOWRANK);
     hipError_t e = hipSuccess;
-    if (lowrank && M <= svdq::kW4A16ProjRows) {
-        // a handful of rows: the projection kernel shaped for them (the activation kernel gives 16 tokens to a workgroup)
+    if (lowrank && svdq::w4a16_makes_h(s.K, s.rank)) {
+        // the weight kernel makes H itself
+    } else if (lowrank && M <= svdq::kW4A16ProjRows) {
+        // few rows: the projection kernel shaped for them (the activation kernel gives 16 tokens and all columns to a workgroup)
         e = svdq::launch_w4a16_proj(static_cast<const uint16_t *>(X), static_cast<const uint16_t *>(L->l1s),
                                     reinterpret_cast<float *>(ws + w.h_off), M, s.K, s.rank, stream);
         if (e != hipSuccess) return hip_fail(e);
@@ -456,6 +458,7 @@ int svdq_w4a16_forward(const svdq_layer_dev *L, const void *X, int M, void *Y, v
     q.rinv = static_cast<const float *>(L->rinv);
     q.wcodes = static_cast<const uint8_t *>(L->wcodes);
     q.sw = static_cast<const uint16_t *>(L->wscales);
+    q.l1s = static_cast<const uint16_t *>(L->l1s);
     q.H = reinterpret_cast<const float *>(ws + w.h_off);
     q.l2t = static_cast<const uint16_t *>(L->l2);
     q.bias = static_cast<const float *>(L->bias);

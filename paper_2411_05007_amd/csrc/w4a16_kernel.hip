@@ -3,15 +3,27 @@
 //
 //   Y = X^ Q(R) + H L2 + bias,   X^ = bf16(x) * (1 / lambda) in fp32,   Q(R) = s_w[g, n] * codes        (Eq. 5 without Q(X^))
 //
-// These layers see a handful of rows (one conditioning vector per image), so the kernels are weight-streaming ones:
-// every 4-bit code is read once and turned into a float on the vector ALU (the 16 bytes of one operand lane of the
-// GEMM's weight blocks are spread to the 6-bit float form with four AND / AND-OR operations per 16 codes and
-// converted 32 at a time by v_cvt_scalef32_pk32_f32_fp6); the matrix cores are not used.  Codes are summed
-// against X^ in fp32 per group and scaled once per group; partial sums of wavefronts are added in wavefront order
-// (deterministic); then H L2 (H from w4a16_proj_kernel below, or from the activation kernel for many rows), bias, bf16.
-//   * one or two rows: w4a16_stream_kernel, one workgroup per compute unit, X^ in registers;
-//   * more rows: w4a16_kernel, a workgroup per 32 or 64 columns and 4 or 8 rows (further rows take further passes
-//     over the weights), X^ through a wavefront-private LDS block and back as broadcast reads.
+// These layers see a handful of rows (one conditioning vector per image), so the kernel streams the weights: the weight
+// blocks of the INT4 GEMM are read as they are, once per sixteen rows, and everything else rides along.
+//
+// Rows go through the matrix core sixteen at a time.  Codes become bf16 (exact: the 16 bytes of one operand lane are
+// spread to the 6-bit float form with four AND / AND-OR operations per 16 codes and converted 32 at a time by
+// v_cvt_scalef32_pk32_bf16_fp6); X^ is fp32 and goes in as three bf16 parts, each the next eight bits of its significand
+// (exact: 24 bits), so that group sums are fp32 sums of exact products, as a vector-ALU kernel's would be.  Up to five
+// rows, the three parts of a row are three rows of ONE operand (STACK); more rows take one operand per part.
+// Lanes: a lane of a weight block holds 32 codes, channels 32 h .. of column l % 32 (h = l / 32).  v_permlane16_swap
+// turns two registers of such lanes (channels 8 j .. and 16 + 8 j .. of all 32 columns, j = 0, 1) into B operands of
+// v_mfma_f32_16x16x32_bf16 for columns 0-15 and 16-31 whose k quarter q = l / 16 holds channels 16 q + 8 j .. + 7 of the
+// group - the order in which l1s is stored.  X is read to match: a lane takes 16 neighbouring channels of one row, and
+// the same registers multiply l1s: H = X l1s of the workgroup's rows comes out of the same loop.
+// Work split: a workgroup owns 32 CB columns, wavefront w takes groups w, w + W, ... for all of them, the operands of
+// its next group requested while it works on this one; a group's scale is one FMA per output; behind the loop the
+// wavefronts' shares of H meet in LDS, H L2 is one or two more steps of the same MFMA, and the wavefronts' sums meet in
+// LDS, both in wavefront order (deterministic).
+// Bound: the vector ALU (about 250 instructions per wavefront, group and 96 columns, half of them X^'s parts) and the fixed
+// parts around the loop; us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
+// launch of its own) -> now: N = 18432: 1 row 13.7 -> 12.6, 2 rows 24 -> 12.7, 16 rows 63.5 -> 15.9, 64 rows 175 -> 43;
+// N = 9216: 16 rows 44 -> 11.8; N = 3072: 1 row 11.5 -> 7.9.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -22,362 +34,336 @@
 namespace svdq {
 namespace {
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-
 typedef uint32_t u32x6 __attribute__((ext_vector_type(6)));
-typedef float floatx32 __attribute__((ext_vector_type(32)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 
-// The 32 codes of one operand lane of a weight block (16 bytes: channels 32 h .. 32 h + 31 of a group for one
-// column, layout.h) as floats.  The stored bits are spread to the 6-bit form sign | 00 | magnitude, whose value as an
-// E2M3 float is code / 8; the conversion's scale of 8 returns the code itself.
-__device__ __forceinline__ floatx32 decode_lane(uint4 q) {
-    u32x6 t;
-    t[0] = q.x & ~kW4Z0;
-    t[1] = q.y & ~kW4Z1;
-    t[2] = (q.x & kW4Z0) | (q.y & kW4Z1);
-    t[3] = q.z & ~kW4Z0;
-    t[4] = q.w & ~kW4Z1;
-    t[5] = (q.z & kW4Z0) | (q.w & kW4Z1);
-    return __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(t, 8.0f);
-}
-// byte offset of operand lane (half h, column n) of group g's weight blocks
-__device__ __forceinline__ size_t lane_offset(int g, int Npad, int n, int h) {
-    return w4_b_block(g, Npad, n) + 1024 * ((n % 64) / 32) + 16 * (32 * h + n % 32);
-}
+constexpr int kStackRows = 5;
+// LDS of the loop: 1 / lambda of all channels, and behind it the wavefronts' shares of H [wave][16 rows][16 RK + 4]
+constexpr int mfma_loop_bytes(int K, int rk, int waves) { return K * 4 + (rk > 0 ? waves * 16 * (16 * rk + 4) * 4 : 0); }
+constexpr int mfma_sums_bytes(int cb, int waves) { return waves * cb * 2 * 16 * 17 * 4; }
 
-// ROWS rows and CW columns per workgroup; a wavefront's lanes are (column, part): PARTS = 64 / CW lanes share one
-// column and split its 64 codes of a group into halves of 32 (CW = 32) or take them all (CW = 64).  UNROLL groups are
-// loaded before the first is used.
-template <int ROWS, int WAVES, int CW, int UNROLL>
-__global__ __launch_bounds__(WAVES * 64) void w4a16_kernel(W4A16Params p) {
-    constexpr int PARTS = 64 / CW, HALVES = 2 / PARTS;      // operand lanes (halves of a group) per lane
-    static_assert(CW == 32 || CW == 64, "a lane takes one or both halves of its column's group");
-    __shared__ __attribute__((aligned(16))) float xs[WAVES][ROWS][64];   // per wavefront: the group's slice of X^
-    __shared__ float part[WAVES][PARTS][ROWS][CW];                       // partial sums of every (wavefront, part)
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = lane % CW, pt = lane / CW;
-    const int n = blockIdx.x * CW + col;                                 // < Npad: CW divides 64, which divides Npad
-    const int m0 = blockIdx.y * ROWS;
-    const int G = p.K / 64;
-    // The thread that will finish output o = threadIdx.x (row o / CW, column o % CW) forms its low-rank term and bias
-    // first, so that those loads overlap the weight stream instead of trailing it.
-    static_assert(ROWS * CW <= WAVES * 64, "one output per thread at most");
-    const int o_m = threadIdx.x / CW, o_c = threadIdx.x % CW, o_row = m0 + o_m, o_n = blockIdx.x * CW + o_c;
-    const bool o_live = o_m < ROWS && o_row < p.M && o_n < p.N;
-    float low = 0.f, bias = 0.f;
-    if (o_live) {
-        bias = p.bias[o_n];
-        const uint4 *lp = reinterpret_cast<const uint4 *>(p.l2t + (size_t)o_n * p.rank);     // rank is a multiple of 16
-        const float4 *hp = reinterpret_cast<const float4 *>(p.H + (size_t)o_row * p.rank);
-        for (int j8 = 0; j8 < p.rank / 8; ++j8) {
-            const uint4 l = lp[j8];
-            const float4 ha = hp[2 * j8], hb = hp[2 * j8 + 1];
-            low = __builtin_fmaf(ha.x, __uint_as_float(l.x << 16), low);
-            low = __builtin_fmaf(ha.y, __uint_as_float(l.x & 0xffff0000u), low);
-            low = __builtin_fmaf(ha.z, __uint_as_float(l.y << 16), low);
-            low = __builtin_fmaf(ha.w, __uint_as_float(l.y & 0xffff0000u), low);
-            low = __builtin_fmaf(hb.x, __uint_as_float(l.z << 16), low);
-            low = __builtin_fmaf(hb.y, __uint_as_float(l.z & 0xffff0000u), low);
-            low = __builtin_fmaf(hb.z, __uint_as_float(l.w << 16), low);
-            low = __builtin_fmaf(hb.w, __uint_as_float(l.w & 0xffff0000u), low);
+template <bool STACK, int CB, int RK, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // 1 / lambda of all channels, later the wavefronts' sums
+    constexpr int SETS = STACK ? 1 : 3, RM = STACK ? kStackRows : 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int n0 = blockIdx.x * CB * 32, m0 = blockIdx.y * RM, G = p.K / 64;
+    const int part = STACK ? l16 / kStackRows : 0;      // (operand row 15 carries nothing: part 3, dropped twice, never added)
+    const uint32_t drop1 = part >= 1 ? 0xffff0000u : 0u, drop2 = part >= 2 ? 0xffff0000u : 0u;
+    const int m_lane = m0 + (STACK ? l16 % kStackRows : l16), row = m_lane < p.M ? m_lane : p.M - 1;      // rows past M repeat the last row; never stored
+    // eight fp32 values of a row as the operand registers of the SETS MFMAs
+    auto split8 = [&](const float (&x)[8], u32x4 (&a)[SETS]) {
+        float t[8], u[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            t[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & (STACK ? drop1 : 0xffff0000u));
+            u[e] = t[e] - __uint_as_float(__float_as_uint(t[e]) & (STACK ? drop2 : 0xffff0000u));
         }
-    }
-    const uint16_t *xrow[ROWS];
+        auto top = [](float lo, float hi) { return (uint32_t)__builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302); };
 #pragma unroll
-    for (int m = 0; m < ROWS; ++m) xrow[m] = p.X + (size_t)(m0 + m < p.M ? m0 + m : p.M - 1) * p.K + lane;   // rows past M repeat the last row; never stored
-    float acc[ROWS];
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m) acc[m] = 0.f;
-    for (int g0 = wave; g0 < G; g0 += UNROLL * WAVES) {
-        uint4 words[UNROLL][HALVES];
-        uint16_t xr[UNROLL][ROWS];
-        float rinv[UNROLL], s[UNROLL];
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int g = g0 + u * WAVES < G ? g0 + u * WAVES : g0;      // past the end: a valid group, loaded and ignored
-#pragma unroll
-            for (int hh = 0; hh < HALVES; ++hh)
-                words[u][hh] = *reinterpret_cast<const uint4 *>(p.wcodes + lane_offset(g, p.Npad, n, PARTS == 2 ? pt : hh));
-            s[u] = (float)__builtin_bit_cast(_Float16, p.sw[(size_t)g * p.Npad + n]);
-            rinv[u] = p.rinv[g * 64 + lane];
-#pragma unroll
-            for (int m = 0; m < ROWS; ++m) xr[u][m] = xrow[m][g * 64];
-        }
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            if (g0 + u * WAVES >= G) break;                               // uniform over the wavefront
-            // X^ of the group: lane k holds channel 64 g + k of every row.  The LDS block is private to the wavefront,
-            // whose LDS operations complete in order: no workgroup barrier.
-#pragma unroll
-            for (int m = 0; m < ROWS; ++m) xs[wave][m][lane] = bf16_bits_to_f32(xr[u][m]) * rinv[u];
-            __builtin_amdgcn_wave_barrier();
-            float sum[ROWS];
-#pragma unroll
-            for (int m = 0; m < ROWS; ++m) sum[m] = 0.f;
-#pragma unroll
-            for (int hh = 0; hh < HALVES; ++hh) {
-                const floatx32 code = decode_lane(words[u][hh]);      // element e = channel 32 h + e of the group
-                const int h = PARTS == 2 ? pt : hh;
-#pragma unroll
-                for (int m = 0; m < ROWS; ++m) {
-                    const float4 *xp = reinterpret_cast<const float4 *>(&xs[wave][m][32 * h]);
-#pragma unroll
-                    for (int e4 = 0; e4 < 8; ++e4) {
-                        const float4 xa = xp[e4];
-                        sum[m] = __builtin_fmaf(xa.x, code[4 * e4], sum[m]);
-                        sum[m] = __builtin_fmaf(xa.y, code[4 * e4 + 1], sum[m]);
-                        sum[m] = __builtin_fmaf(xa.z, code[4 * e4 + 2], sum[m]);
-                        sum[m] = __builtin_fmaf(xa.w, code[4 * e4 + 3], sum[m]);
-                    }
-                }
+        for (int e = 0; e < 4; ++e) {
+            a[SETS - 1][e] = top(u[2 * e], u[2 * e + 1]);
+            if (!STACK) {
+                a[0][e] = top(x[2 * e], x[2 * e + 1]);
+                a[SETS / 2][e] = top(t[2 * e], t[2 * e + 1]);
             }
-#pragma unroll
-            for (int m = 0; m < ROWS; ++m) acc[m] = __builtin_fmaf(s[u], sum[m], acc[m]);
-            __builtin_amdgcn_wave_barrier();
         }
-    }
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m) part[wave][pt][m][col] = acc[m];
-    __syncthreads();
-    // one thread per output: partial sums in (wavefront, part) order, low-rank term, bias, bf16
-    if (o_live) {
-        float y = 0.f;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-#pragma unroll
-            for (int q = 0; q < PARTS; ++q) y += part[w][q][o_m][o_c];
-        y = (y + low) + bias;
-        p.Y[(size_t)o_row * p.N + o_n] = __builtin_bit_cast(uint16_t, (__bf16)y);
-    }
-}
-
-// One or two rows.  The layer's columns are dealt out in runs of 32 * CB, CB chosen on the host so that the workgroups
-// fill the compute units evenly (one 16-wavefront workgroup per unit when the layer is wide enough).  A lane is
-// (column c of 32, half h of the group): it reads the 16 bytes of ITS operand lane of the weight block, 32 codes, per
-// group and block of 32 columns - a wavefront's load is one contiguous kilobyte - and keeps the matching 32 channels
-// of X^ of its wavefront's current group in registers for all the columns of the run: no LDS in the loop.  Wavefront
-// w of nw takes groups w, w + nw, ...; the codes of the next group are requested while the current one is summed.
-// The two halves and the wavefronts are added in a fixed order through LDS.
-constexpr int kStreamCbMax = 3;      // 32-column blocks per workgroup, at most
-
-template <int ROWS>
-__global__ __launch_bounds__(1024) void w4a16_stream_kernel(W4A16Params p, int CB) {
-    constexpr int CBMAX = kStreamCbMax;
-    __shared__ float part[16][2][ROWS][CBMAX * 32];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    const int c32 = lane & 31, h = lane >> 5;
-    const int n0 = blockIdx.x * CB * 32;
-    // byte offsets into the block and scale tensors stay below 2^31 (checked on the host): buffer loads, a per-lane
-    // offset that never changes plus a uniform one; reads past the end of a buffer return zero
-    const int G = p.K / 64;
+    };
     const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(p.wcodes, w4_b_bytes(G, p.Npad));
     const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(p.sw, (size_t)G * p.Npad * 2);
-    const int w_voff = 16 * lane, s_voff = c32 * 2;      // operand lane 32 h + c32 of a 32-column half block is its bytes 16 lane .. + 15
-    const int m0 = blockIdx.y * ROWS;
-    // the thread that finishes output (row o_m, column n0 + o_c) forms its low-rank term and bias first
-    const int o_m = threadIdx.x / (CBMAX * 32), o_c = threadIdx.x % (CBMAX * 32), o_row = m0 + o_m, o_n = n0 + o_c;
-    const bool o_live = o_m < ROWS && o_c < CB * 32 && o_row < p.M && o_n < p.N;
-    float low = 0.f, bias = 0.f;
-    if (o_live) {
-        bias = p.bias[o_n];
-        const uint4 *lp = reinterpret_cast<const uint4 *>(p.l2t + (size_t)o_n * p.rank);
-        const float4 *hp = reinterpret_cast<const float4 *>(p.H + (size_t)o_row * p.rank);
-        for (int j8 = 0; j8 < p.rank / 8; ++j8) {
-            const uint4 l = lp[j8];
-            const float4 ha = hp[2 * j8], hb = hp[2 * j8 + 1];
-            low = __builtin_fmaf(ha.x, __uint_as_float(l.x << 16), low);
-            low = __builtin_fmaf(ha.y, __uint_as_float(l.x & 0xffff0000u), low);
-            low = __builtin_fmaf(ha.z, __uint_as_float(l.y << 16), low);
-            low = __builtin_fmaf(ha.w, __uint_as_float(l.y & 0xffff0000u), low);
-            low = __builtin_fmaf(hb.x, __uint_as_float(l.z << 16), low);
-            low = __builtin_fmaf(hb.y, __uint_as_float(l.z & 0xffff0000u), low);
-            low = __builtin_fmaf(hb.z, __uint_as_float(l.w << 16), low);
-            low = __builtin_fmaf(hb.w, __uint_as_float(l.w & 0xffff0000u), low);
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.X, (size_t)p.M * p.K * 2);
+    const int vx = (int)(((uint32_t)row * (uint32_t)p.K + 16u * (uint32_t)q4) * 2u);
+    // a block past N reads the run's first block: multiplied, never stored
+    int first[CB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) first[cb] = n0 + (n0 + cb * 32 < p.N ? cb * 32 : 0);
+    const int rb = p.rank / 16;
+    const __amdgpu_buffer_rsrc_t rs_l = make_rsrc(p.l1s, (size_t)p.K * p.rank * 2);
+    struct Batch { u32x4 x[2], w[CB], l[RK > 0 ? 2 * RK : 1]; uint16_t s[CB][2]; };
+    auto load = [&](int g) {
+        Batch t;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            t.w[cb] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_w, 16 * lane, (int)(w4_b_block(g, p.Npad, first[cb]) + 1024 * ((first[cb] % 64) / 32)), 0));
+#pragma unroll
+            for (int c = 0; c < 2; ++c) t.s[cb][c] = __builtin_amdgcn_raw_buffer_load_b16(rs_s, 2 * l16, (g * p.Npad + first[cb] + 16 * c) * 2, 0);
         }
-    }
-    float acc[CBMAX][ROWS];
 #pragma unroll
-    for (int cb = 0; cb < CBMAX; ++cb)
+        for (int j = 0; j < 2; ++j) t.x[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_x, vx + 16 * j, g * 128, 0));
 #pragma unroll
-        for (int m = 0; m < ROWS; ++m) acc[cb][m] = 0.f;
-    // codes and scales of one group for the run's blocks; a block past the run or past N repeats the run's first block (uniform)
-    struct Batch { uint4 codes[CBMAX]; uint16_t sc[CBMAX]; };
-    auto load_batch = [&](int g) {
-        Batch q;
-#pragma unroll
-        for (int cb = 0; cb < CBMAX; ++cb) {
-            const bool live = cb < CB && n0 + cb * 32 < p.N;
-            const int first = n0 + (live ? cb * 32 : 0);                  // a multiple of 32, below Npad
-            q.codes[cb] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff, (int)(w4_b_block(g, p.Npad, first) + 1024 * ((first % 64) / 32)), 0));
-            q.sc[cb] = __builtin_amdgcn_raw_buffer_load_b16(rs_s, s_voff, (g * p.Npad + first) * 2, 0);
+        for (int i = 0; i < 2 * RK; ++i) {      // blocks past the rank repeat the last one; what they give is dropped
+            const int c = i / 2 < rb ? i / 2 : rb - 1;
+            t.l[RK > 0 ? i : 0] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_l, 16 * lane, ((g * 2 + i % 2) * rb + c) * 1024, 0));
         }
-        return q;
+        return t;
     };
-    Batch cur = load_batch(wave < G ? wave : 0);
-    for (int g = wave; g < G; g += nw) {
-        // X^ of this group: channels 64 g + 32 h .. + 31 of every row (rows past M repeat the last row; never stored)
-        float xh[ROWS][32];
+    Batch cur = load(wave < G ? wave : G - 1);
+    // Everything else that comes from memory is requested right behind: the bias of the outputs this thread will finish,
+    // the operands of the wavefront's first low-rank step, 1 / lambda.
+    constexpr int kOut = (RM * CB * 32 + WAVES * 64 - 1) / (WAVES * 64);
+    float bias[kOut];
 #pragma unroll
-        for (int q4 = 0; q4 < 8; ++q4) {
-            const float4 r = *reinterpret_cast<const float4 *>(p.rinv + g * 64 + 32 * h + 4 * q4);
+    for (int i = 0; i < kOut; ++i) {
+        const int n = n0 + (int)(threadIdx.x + i * WAVES * 64) % (CB * 32);
+        bias[i] = p.bias[n < p.Npad ? n : 0];
+    }
+    // low-rank term: 32 columns of H per step, step s by wavefront s % W; the rank is a multiple of 16, its upper end is cut
+    // off by zeros
+    // (RK > 0: H of the workgroup's rows is made here, behind the loop)
+    struct LowRank { float4 h[2]; u32x4 l[CB][2]; };
+    const int steps = (p.rank + 31) / 32;
+    auto load_lowrank = [&](int s) {
+        LowRank t;
+        const int j = 32 * s + 8 * q4, jc = j < p.rank ? j : 0;
+        if (RK == 0) {
+            const float4 *hp = reinterpret_cast<const float4 *>(p.H + (size_t)row * p.rank + jc);
+            t.h[0] = hp[0];
+            t.h[1] = hp[1];
+        }
 #pragma unroll
-            for (int m = 0; m < ROWS; ++m) {
-                const int row = m0 + m < p.M ? m0 + m : p.M - 1;
-                const uint2 xv = *reinterpret_cast<const uint2 *>(p.X + (size_t)row * p.K + g * 64 + 32 * h + 4 * q4);
-                xh[m][4 * q4] = __uint_as_float(xv.x << 16) * r.x;
-                xh[m][4 * q4 + 1] = __uint_as_float(xv.x & 0xffff0000u) * r.y;
-                xh[m][4 * q4 + 2] = __uint_as_float(xv.y << 16) * r.z;
-                xh[m][4 * q4 + 3] = __uint_as_float(xv.y & 0xffff0000u) * r.w;
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) t.l[cb][c] = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4 *>(p.l2t + (size_t)(first[cb] + 16 * c + l16) * p.rank + jc));      // < Npad columns
+        return t;
+    };
+    LowRank low;
+    if (wave < steps) low = load_lowrank(wave);
+    float *lrinv = reinterpret_cast<float *>(lds);
+    for (int k = 4 * threadIdx.x; k < p.K; k += 4 * WAVES * 64) *reinterpret_cast<float4 *>(lrinv + k) = *reinterpret_cast<const float4 *>(p.rinv + k);
+    floatx4 acc[CB][2];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[cb][0] = acc[cb][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto mfma = [](u32x4 a, u32x4 b, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0); };
+    auto add_lowrank = [&](int s) {
+        const bool live = 32 * s + 8 * q4 < p.rank;
+        u32x4 a[SETS];
+        const float4 ha = low.h[0], hb = low.h[1];
+        const float x[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+        split8(x, a);
+        if (!live)
+#pragma unroll
+            for (int st = 0; st < SETS; ++st) a[st] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int st = 0; st < SETS; ++st) acc[cb][c] = mfma(a[st], low.l[cb][c], acc[cb][c]);
+    };
+    __syncthreads();
+    if (RK == 0)
+        for (int s = wave; s < steps; s += WAVES) {
+            if (s >= WAVES) low = load_lowrank(s);
+            add_lowrank(s);
+        }
+    floatx4 hacc[RK > 0 ? RK : 1];
+#pragma unroll
+    for (int c = 0; c < RK; ++c) hacc[RK > 0 ? c : 0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int g = wave; g < G; g += WAVES) {
+        const Batch nxt = load(g + WAVES < G ? g + WAVES : g);      // past the end: this group again, loaded and ignored
+#pragma unroll
+        for (int i = 0; i < 2 * RK; ++i) hacc[RK > 0 ? i / 2 : 0] = mfma(cur.x[i % 2], cur.l[RK > 0 ? i : 0], hacc[RK > 0 ? i / 2 : 0]);
+        u32x4 a[2][SETS];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float4 *rp = reinterpret_cast<const float4 *>(lrinv + 64 * g + 16 * q4 + 8 * j);
+            const float4 r0 = rp[0], r1 = rp[1];
+            {
+                const u32x4 w = cur.x[j];
+                const float x[8] = {__uint_as_float(w.x << 16) * r0.x, __uint_as_float(w.x & 0xffff0000u) * r0.y, __uint_as_float(w.y << 16) * r0.z, __uint_as_float(w.y & 0xffff0000u) * r0.w,
+                                    __uint_as_float(w.z << 16) * r1.x, __uint_as_float(w.z & 0xffff0000u) * r1.y, __uint_as_float(w.w << 16) * r1.z, __uint_as_float(w.w & 0xffff0000u) * r1.w};
+                split8(x, a[j]);
             }
         }
-        const Batch nxt = load_batch(g + nw < G ? g + nw : g);          // past the end: this group again, loaded and ignored
 #pragma unroll
-        for (int cb = 0; cb < CBMAX; ++cb) {
-            if (cb >= CB) break;                                          // uniform
-            const floatx32 code = decode_lane(cur.codes[cb]);
-            const float sc = (float)__builtin_bit_cast(_Float16, cur.sc[cb]);
+        for (int cb = 0; cb < CB; ++cb) {
+            const u32x4 q = cur.w[cb];
+            u32x6 t;
+            t[0] = q.x & ~kW4Z0;
+            t[1] = q.y & ~kW4Z1;
+            t[2] = (q.x & kW4Z0) | (q.y & kW4Z1);
+            t[3] = q.z & ~kW4Z0;
+            t[4] = q.w & ~kW4Z1;
+            t[5] = (q.z & kW4Z0) | (q.w & kW4Z1);
+            const u32x16 c = __builtin_bit_cast(u32x16, __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(t, 8.0f));
+            u32x4 op[2][2];      // [k step][columns 0-15, 16-31]
 #pragma unroll
-            for (int m = 0; m < ROWS; ++m) {
-                float sum = 0.f;
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
-                for (int e = 0; e < 32; ++e) sum = __builtin_fmaf(xh[m][e], code[e], sum);
-                acc[cb][m] = __builtin_fmaf(sc, sum, acc[cb][m]);
+                for (int e = 0; e < 4; ++e) {
+                    const auto sw = __builtin_amdgcn_permlane16_swap(c[4 * j + e], c[8 + 4 * j + e], false, false);
+                    op[j][0][e] = sw[0];
+                    op[j][1][e] = sw[1];
+                }
+#pragma unroll
+            for (int cc = 0; cc < 2; ++cc) {
+                const float sc = (float)__builtin_bit_cast(_Float16, cur.s[cb][cc]);
+                floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int st = 0; st < SETS; ++st) sum = mfma(a[j][st], op[j][cc], sum);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[cb][cc][v] = __builtin_fmaf(sc, sum[v], acc[cb][cc][v]);
             }
         }
         cur = nxt;
     }
+    if (RK > 0) {
+        // H: the wavefronts' shares meet in LDS behind 1 / lambda; the wavefront of a low-rank step adds up the 32 columns it
+        // needs, in wavefront order, as it reads its operand
+        constexpr int kHRow = 16 * (RK > 0 ? RK : 1) + 4;
+        float *hs = lrinv + p.K;      // [wave][16 rows][kHRow]
 #pragma unroll
-    for (int cb = 0; cb < CBMAX; ++cb)
+        for (int c = 0; c < RK; ++c)
 #pragma unroll
-        for (int m = 0; m < ROWS; ++m) part[wave][h][m][cb * 32 + c32] = acc[cb][m];
+            for (int v = 0; v < 4; ++v) hs[(wave * 16 + 4 * q4 + v) * kHRow + 16 * c + l16] = hacc[RK > 0 ? c : 0][v];
+        __syncthreads();
+        if (wave < steps) {      // (RK <= 4: at most two steps)
+            const int j = 32 * wave + 8 * q4, jc = j < p.rank ? j : 0;
+            float4 ha = make_float4(0.f, 0.f, 0.f, 0.f), hb = ha;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const float4 *hp = reinterpret_cast<const float4 *>(hs + (w * 16 + (STACK ? l16 % kStackRows : l16)) * kHRow + jc);
+                const float4 ta = hp[0], tb = hp[1];
+                ha.x += ta.x; ha.y += ta.y; ha.z += ta.z; ha.w += ta.w;
+                hb.x += tb.x; hb.y += tb.y; hb.z += tb.z; hb.w += tb.w;
+            }
+            low.h[0] = ha;
+            low.h[1] = hb;
+            add_lowrank(wave);
+        }
+    }
+    __syncthreads();      // nobody reads 1 / lambda (or the shares of H) any more
+    float *sums = reinterpret_cast<float *>(lds);      // [wave][cb][columns 0-15, 16-31][16 rows][17]
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) sums[(((wave * CB + cb) * 2 + c) * 16 + 4 * q4 + v) * 17 + l16] = acc[cb][c][v];
     __syncthreads();
-    if (o_live) {
-        float y = 0.f;
-        for (int w = 0; w < nw; ++w) y += part[w][0][o_m][o_c] + part[w][1][o_m][o_c];
-        y = (y + low) + bias;
-        p.Y[(size_t)o_row * p.N + o_n] = __builtin_bit_cast(uint16_t, (__bf16)y);
+    float y[kOut];
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+        const int o = threadIdx.x + i * WAVES * 64, cl = o % (CB * 32), m = o / (CB * 32) < RM ? o / (CB * 32) : RM - 1;
+        y[i] = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const float *s = sums + ((w * CB * 2 + cl / 16) * 16 + m) * 17 + cl % 16;
+            y[i] += STACK ? s[0] + (s[kStackRows * 17] + s[2 * kStackRows * 17]) : s[0];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+        const int o = threadIdx.x + i * WAVES * 64, n = n0 + o % (CB * 32), m = o / (CB * 32);
+        if (m < RM && m0 + m < p.M && n < p.N) p.Y[(size_t)(m0 + m) * p.N + n] = __builtin_bit_cast(uint16_t, (__bf16)(y[i] + bias[i]));
     }
 }
 
 // Down projection for a handful of rows: H[m][j] = sum_k bf16(x[m][k]) * l1s[k][j] in fp32 (Sec. 4.2: the 16-bit branch,
-// lambda^-1 folded into l1s).  The activation kernel gives a whole workgroup to 16 tokens and walks K serially, which
-// for one row means one workgroup reading all of l1s; here a workgroup of 16 wavefronts takes one block of 16 columns
-// and one or two rows (more rows: more workgroups), wavefront w the groups w, w + 16, ..., three groups' operands requested at a time;  l1s is read in its stored fragment order (lane l of a
-// fragment: column l % 16, channels 16 (l / 16) + 8 s + e of the group for k step s), one 16-byte load per lane and
-// step; the four 16-channel quarters and the wavefronts are added in a fixed order through LDS.
-template <int ROWS>
+// lambda^-1 folded into l1s).  The activation kernel gives a whole workgroup to 16 tokens and all columns of H; here a
+// workgroup of 16 wavefronts takes 16 rows and 16 columns, wavefront w the groups w, w + 16, ..., three groups' operands
+// requested at a time.  l1s is read in its stored fragment order, which with X read to match (lane l: row l % 16,
+// channels 16 (l / 16) + 8 s + e of the group for k step s) is the B operand of v_mfma_f32_16x16x32_bf16 as it is; the
+// wavefronts' sums are added in wavefront order through LDS.
 __global__ __launch_bounds__(1024) void w4a16_proj_kernel(const uint16_t *X, const uint16_t *l1s, float *H, int M, int K, int rank) {
     constexpr int GPW = 3;                                // groups per wavefront whose operands are requested together
-    __shared__ float part[16][4][ROWS][16];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = lane & 15, quarter = lane >> 4;
-    const int c = blockIdx.x, m0 = blockIdx.y * ROWS, G = K / 64, cb = rank / 16;
-    const uint16_t *xrow[ROWS];
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m) xrow[m] = X + (size_t)(m0 + m < M ? m0 + m : M - 1) * K + 16 * quarter;   // rows past M repeat the last row; never stored
-    float acc[ROWS];
-#pragma unroll
-    for (int m = 0; m < ROWS; ++m) acc[m] = 0.f;
-    for (int gb = 0; gb < G; gb += 16 * GPW) {
-        uint4 f[GPW][2], xv[GPW][2][ROWS];
+    __shared__ float part[16][16][17];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, quarter = lane >> 4;
+    const int c = blockIdx.x, m0 = blockIdx.y * 16, G = K / 64, cb = rank / 16;
+    const uint16_t *xrow = X + (size_t)(m0 + l16 < M ? m0 + l16 : M - 1) * K + 16 * quarter;      // rows past M repeat the last row; never stored
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int gb = wave; gb < G; gb += 16 * GPW) {
+        uint4 f[GPW][2], xv[GPW][2];
 #pragma unroll
         for (int u = 0; u < GPW; ++u) {
-            const int g = gb + wave + 16 * u < G ? gb + wave + 16 * u : G - 1;      // past the end: a valid group, loaded and ignored
+            const int g = gb + 16 * u < G ? gb + 16 * u : G - 1;      // past the end: a valid group, loaded and ignored
 #pragma unroll
-            for (int sidx = 0; sidx < 2; ++sidx) {
-                f[u][sidx] = *reinterpret_cast<const uint4 *>(l1s + ((((size_t)g * 2 + sidx) * cb + c) * 64 + lane) * 8);
-#pragma unroll
-                for (int m = 0; m < ROWS; ++m) xv[u][sidx][m] = *reinterpret_cast<const uint4 *>(xrow[m] + g * 64 + 8 * sidx);
+            for (int s = 0; s < 2; ++s) {
+                f[u][s] = *reinterpret_cast<const uint4 *>(l1s + ((((size_t)g * 2 + s) * cb + c) * 64 + lane) * 8);
+                xv[u][s] = *reinterpret_cast<const uint4 *>(xrow + g * 64 + 8 * s);
             }
         }
 #pragma unroll
         for (int u = 0; u < GPW; ++u) {
-            if (gb + wave + 16 * u >= G) break;                                      // uniform over the wavefront
+            if (gb + 16 * u >= G) break;                                      // uniform over the wavefront
 #pragma unroll
-            for (int sidx = 0; sidx < 2; ++sidx) {
-                const uint4 w4 = f[u][sidx];
-                const float w[8] = {__uint_as_float(w4.x << 16), __uint_as_float(w4.x & 0xffff0000u), __uint_as_float(w4.y << 16), __uint_as_float(w4.y & 0xffff0000u),
-                                    __uint_as_float(w4.z << 16), __uint_as_float(w4.z & 0xffff0000u), __uint_as_float(w4.w << 16), __uint_as_float(w4.w & 0xffff0000u)};
-#pragma unroll
-                for (int m = 0; m < ROWS; ++m) {
-                    const uint4 x4 = xv[u][sidx][m];
-                    float a = acc[m];
-                    a = __builtin_fmaf(__uint_as_float(x4.x << 16), w[0], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.x & 0xffff0000u), w[1], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.y << 16), w[2], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.y & 0xffff0000u), w[3], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.z << 16), w[4], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.z & 0xffff0000u), w[5], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.w << 16), w[6], a);
-                    a = __builtin_fmaf(__uint_as_float(x4.w & 0xffff0000u), w[7], a);
-                    acc[m] = a;
-                }
-            }
+            for (int s = 0; s < 2; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xv[u][s]), __builtin_bit_cast(bf16x8, f[u][s]), acc, 0, 0, 0);
         }
     }
 #pragma unroll
-    for (int m = 0; m < ROWS; ++m) part[wave][quarter][m][col] = acc[m];
+    for (int v = 0; v < 4; ++v) part[wave][4 * quarter + v][l16] = acc[v];
     __syncthreads();
     const int o_m = threadIdx.x / 16, o_c = threadIdx.x % 16;
-    if (o_m < ROWS && m0 + o_m < M) {
+    if (o_m < 16 && m0 + o_m < M) {
         float h = 0.f;
 #pragma unroll
-        for (int w = 0; w < 16; ++w)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) h += part[w][q][o_m][o_c];
+        for (int w = 0; w < 16; ++w) h += part[w][o_m][o_c];
         H[(size_t)(m0 + o_m) * rank + 16 * c + o_c] = h;
     }
 }
 
-// ---- host side: the shape of the chip-filling launch ----
-struct StreamPlan { int cb, nw, wgs; };
-
-StreamPlan plan_stream(int N, int G, int passes) {
-    const int blocks = (N + 31) / 32, kCUs = 256;
-    StreamPlan best{1, 16, blocks};
-    long best_cost = -1;
-    for (int cb = 1; cb <= kStreamCbMax; ++cb) {
-        const int wgs = (blocks + cb - 1) / cb;
-        const long cost = (long)(((long)wgs * passes + kCUs - 1) / kCUs) * cb;      // rounds of one workgroup per unit x its length
-        if (best_cost < 0 || cost <= best_cost) { best_cost = cost; best.cb = cb; best.wgs = wgs; }    // ties: the longer run (X^ is loaded once per run)
-    }
-    long best_t = -1;
-    for (int nw = 8; nw <= 16; nw += 4) {
-        const long t = (long)((nw + 3) / 4) * ((G + nw - 1) / nw);                   // wavefronts per SIMD x groups per wavefront
-        if (best_t < 0 || t <= best_t) { best_t = t; best.nw = nw; }
-    }
-    return best;
+// ---- host side ----------------------------------------------------------------------------------------------------
+template <bool STACK, int CB, int RK, int WAVES>
+hipError_t launch_mfma(const W4A16Params &p, hipStream_t stream) {
+    auto k = w4a16_mfma_kernel<STACK, CB, RK, WAVES>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesPerCU);
+    if (attr != hipSuccess) return attr;
+    const int rows = STACK ? kStackRows : 16;
+    const int loop = mfma_loop_bytes(p.K, RK, WAVES), sums = mfma_sums_bytes(CB, WAVES), bytes = loop > sums ? loop : sums;
+    if (bytes > kLdsBytesPerCU) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k, dim3((p.N + 32 * CB - 1) / (32 * CB), (p.M + rows - 1) / rows), dim3(WAVES * 64), bytes, stream, p);
+    return hipGetLastError();
 }
-
-template <int ROWS, int WAVES, int CW, int UNROLL>
-void launch_one(const W4A16Params &p, int row_blocks, hipStream_t stream) {
-    hipLaunchKernelGGL((w4a16_kernel<ROWS, WAVES, CW, UNROLL>), dim3((p.N + CW - 1) / CW, row_blocks), dim3(WAVES * 64), 0, stream, p);
+template <bool STACK, int RK>
+hipError_t launch_mfma_shape(const W4A16Params &p, hipStream_t stream) {
+    // Columns per workgroup: a round of workgroups (one per CU; up to two short ones share a CU, so beyond two rounds parts of
+    // rounds count) lasts about 1.2 + CB of what one more 32-column block adds, the 1.2 being X^'s.  (Measured, us, CB = 1,
+    // 2, 3, K = 3072, rank 32: 16 rows, N = 18432 21.9, 18.8, 15.9; N = 9216 14.7, 11.8, 15.1; N = 3072 8.8, 10.7, 13.4; 32 rows,
+    // N = 18432 34.0, 26.9, 29.5.)
+    const int rows = STACK ? kStackRows : 16, passes = (p.M + rows - 1) / rows, blocks = (p.N + 31) / 32;
+    int cb = 1;
+    double best = 0.0;
+    for (int c = 1; c <= 3; ++c) {
+        const long wgs = (long)((blocks + c - 1) / c) * passes;
+        const double cost = (wgs > 512 && c < 3 ? wgs / 256.0 : (double)((wgs + 255) / 256)) * (1.2 + c);
+        if (c == 1 || cost < best) { best = cost; cb = c; }
+    }
+    // sixteen wavefronts where a long K meets few columns (K = 12288, N = 3072: 24.6 -> 21.7 us; at K = 3072 eight are as fast)
+    if (cb == 1 && p.K >= 6144 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU) return launch_mfma<STACK, 1, RK, 16>(p, stream);
+    return cb == 1 ? launch_mfma<STACK, 1, RK, 8>(p, stream) : cb == 2 ? launch_mfma<STACK, 2, RK, 8>(p, stream) : launch_mfma<STACK, 3, RK, 8>(p, stream);
+}
+template <bool STACK>
+hipError_t launch_mfma_rank(const W4A16Params &p, hipStream_t stream) {
+    if (p.rank == 0 || !w4a16_makes_h(p.K, p.rank)) return launch_mfma_shape<STACK, 0>(p, stream);
+    return p.rank <= 32 ? launch_mfma_shape<STACK, 2>(p, stream) : launch_mfma_shape<STACK, 4>(p, stream);
 }
 
 }  // namespace
 
+// Up to rank 64 every workgroup makes H of its rows itself (l1s comes from the L2 beside the weights: K * rank * 2 bytes per
+// workgroup), which saves a launch and its wait: one row, N = 18432, rank 32 14.1 -> 12.6 us, rank 64 14.2 -> 13.8;
+// sixteen rows 18.2 -> 15.9 and 18.3 (rank 48) -> 16.0.  Wider branches leave H to a launch of its own.
+bool w4a16_makes_h(int K, int rank) { return rank <= 64 && mfma_loop_bytes(K, rank <= 32 ? 2 : 4, 8) <= kLdsBytesPerCU; }
+
 hipError_t launch_w4a16_proj(const uint16_t *X, const uint16_t *l1s, float *H, int M, int K, int rank, hipStream_t stream) {
     if (M <= 0 || rank <= 0) return hipSuccess;
     if (K <= 0 || K % 64 || rank % 16) return hipErrorInvalidValue;
-    if (M == 1) hipLaunchKernelGGL(w4a16_proj_kernel<1>, dim3(rank / 16, 1), dim3(1024), 0, stream, X, l1s, H, M, K, rank);
-    else hipLaunchKernelGGL(w4a16_proj_kernel<2>, dim3(rank / 16, (M + 1) / 2), dim3(1024), 0, stream, X, l1s, H, M, K, rank);
+    hipLaunchKernelGGL(w4a16_proj_kernel, dim3(rank / 16, (M + 15) / 16), dim3(1024), 0, stream, X, l1s, H, M, K, rank);
     return hipGetLastError();
 }
 
 hipError_t launch_w4a16(const W4A16Params &p, hipStream_t stream) {
     if (p.M <= 0) return hipSuccess;
     if (p.K <= 0 || p.K % 64 || p.Npad % kRowPad || p.Npad < p.N || p.rank < 0) return hipErrorInvalidValue;
-    if (p.M <= 2) {
-        const int rows = p.M, passes = 1;
-        const StreamPlan sp = plan_stream(p.N, p.K / 64, passes);
-        if (rows == 1) hipLaunchKernelGGL(w4a16_stream_kernel<1>, dim3(sp.wgs, passes), dim3(sp.nw * 64), 0, stream, p, sp.cb);
-        else hipLaunchKernelGGL(w4a16_stream_kernel<2>, dim3(sp.wgs, passes), dim3(sp.nw * 64), 0, stream, p, sp.cb);
-        return hipGetLastError();
-    }
-    // more rows: the 64-lanes-per-group kernel, whose cost per row is lower (the widening is shared by the rows)
-    if (p.M <= 4) launch_one<4, 16, 32, 3>(p, 1, stream);
-    else launch_one<8, 8, 64, 3>(p, (p.M + 7) / 8, stream);
-    return hipGetLastError();
+    if (p.N % 16 || (p.rank > 0 && (!p.l1s || !p.l2t || (!p.H && !w4a16_makes_h(p.K, p.rank))))) return hipErrorInvalidValue;
+    return p.M <= kStackRows ? launch_mfma_rank<true>(p, stream) : launch_mfma_rank<false>(p, stream);
 }
 
 }  // namespace svdq

@@ -39,3 +39,17 @@ def test_every_variant_at_its_edges(torch, M, K, N, r, rows):  # noqa: F811
     print(f"small launch: M={M} K={K} N={N} r={prep.shape.rank}, {rows}-row tiles", flush=True)
     sample = np.unique(np.concatenate([np.arange(min(M, 40)), np.arange(max(0, M - 40), M), rng.integers(0, M, 60)]))
     _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"small {M}x{K}x{N}", window=False)
+
+
+@pytest.mark.parametrize("M,K,N,r", [(5, 64, 16, 16), (6, 64, 48, 48), (17, 576, 1008, 64), (33, 1088, 9232, 32), (4, 704, 18448, 48),     # one, two, three column blocks
+                                     (2, 6208, 80, 80), (19, 6144, 1040, 32), (3, 6208, 272, 0),                                        # sixteen wavefronts
+                                     (16, 320, 400, 256), (70, 256, 144, 96),                                                            # H from a launch of its own
+                                     (2, 32768, 16, 16), (7, 32768, 32, 32)])                                                            # 1 / lambda fills the LDS
+def test_w4a16_at_its_edges(torch, M, K, N, r):  # noqa: F811
+    """Rows off the five and sixteen of a pass, column tails, fewer groups than wavefronts, every launch variant; bound:
+    one bf16 rounding plus the fp32 summation of K products (test_gpu_w4a16.py)."""
+    from tests.test_gpu_w4a16 import _run
+    rng = np.random.default_rng(5300 + M + K + N)
+    r = min(r, N // 16 * 16, K // 16 * 16)
+    print(f"w4a16 edges: M={M} K={K} N={N} r={r}", flush=True)
+    _run(torch, O.bf16_round(rng.standard_normal((M, K)).astype(np.float32)), _layer(rng, K, N, r), f"w4a16 {M}x{K}x{N} r{r}")
