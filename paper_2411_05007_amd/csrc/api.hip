@@ -218,24 +218,27 @@ int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
     const int G = s->K / svdq::kGroup;
     svdq::ActPlan a;
     size_t parked_bytes = 0, total = 0;
+    int kpar = 0;
     if (s->group == svdq::kFp4Block) {
         const svdq::WorkspaceFp4 w = svdq::workspace_layout_fp4(M, s->K, s->N, s->rank, ksplit_override(), act_override());
         const svdq::GemmPlanFp4 pl = svdq::plan_gemm_fp4(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.ksplit > 1 ? pl.tiles : 0; out[10] = pl.ksplit; out[11] = pl.tiles * pl.ksplit;
+        kpar = svdq::plan_kpar_blocks(false, M, s->N, G, ksplit_override());
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else if (s->group == svdq::kGroup) {
         const svdq::Workspace w = svdq::workspace_layout(M, s->K, s->N, s->rank, ksplit_override(), act_override());
         const svdq::GemmPlan pl = svdq::plan_gemm(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.tail; out[10] = pl.ksplit; out[11] = pl.tiles - pl.tail + pl.tail * pl.ksplit;
-        if (const int kpar = svdq::plan_kpar_int4(M, s->N, G, ksplit_override())) {
-            out[8] = out[11] = ((M + svdq::kpar_rows(kpar) - 1) / svdq::kpar_rows(kpar)) * ((s->N + 63) / 64);
-            out[9] = 0; out[10] = 1;
-        }
+        kpar = svdq::plan_kpar_int4(M, s->N, G, ksplit_override());
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else {
         return SVDQ_EUNSUPPORTED;
+    }
+    if (kpar) {
+        out[8] = out[11] = ((M + svdq::kpar_rows(kpar) - 1) / svdq::kpar_rows(kpar)) * ((s->N + 63) / 64);
+        out[9] = 0; out[10] = 1;
     }
     const int slices = (M + 15) / 16;
     const int ca = a.chunks0 > 1 ? a.chunks0 : 1, cb = a.chunks > 1 ? a.chunks : 1;
@@ -329,6 +332,7 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const bool lowrank = s.rank > 0 && !(g_options & SVDQ_OPT_SKIP_LOWRANK);
+    const int kpar = svdq::plan_kpar_blocks(false, M, s.N, s.K / svdq::kGroup, ksplit_override());
 
     svdq::ActParams a{};
     a.X = static_cast<const uint16_t *>(X);
@@ -341,7 +345,7 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     a.M = M; a.K = s.K; a.G = s.K / svdq::kGroup; a.Mpad = w.Mpad; a.rank = s.rank;
     a.fmt = 1;
     a.zero_words = reinterpret_cast<uint32_t *>(ws + w.counters_off);      // arrival counters of a split K loop start at zero
-    a.n_zero = w.n_counters;
+    a.n_zero = kpar ? 0 : w.n_counters;
     a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
     a.whole = w.act.whole; a.chunks0 = w.act.chunks0; a.gchunk0 = w.act.gchunk0;
     a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
@@ -366,7 +370,8 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     g.rank = lowrank ? s.rank : 0;
     const svdq::GemmPlanFp4 plan = svdq::plan_gemm_fp4(M, s.N, s.K / svdq::kGroup, ksplit_override());
     g.tile = plan.tile;
-    g.ksplit = plan.ksplit;
+    g.kpar = kpar;
+    g.ksplit = kpar ? 1 : plan.ksplit;
     g.partial = reinterpret_cast<float *>(ws + w.partial_off);
     g.counters = reinterpret_cast<uint32_t *>(ws + w.counters_off);
     e = svdq::launch_gemm_fp4(g, stream);
@@ -509,7 +514,8 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     a.M = M; a.K = s.K; a.G = s.K / svdq::kGroup; a.Mpad = w.Mpad; a.rank = s.rank;
     a.fmt = 2;
     a.zero_words = reinterpret_cast<uint32_t *>(ws + w.counters_off);      // the arrival counters of the GEMM's split K loop
-    a.n_zero = w.n_counters;
+    const int kpar = svdq::plan_kpar_blocks(true, M, s.N, s.K / svdq::kGroup, ksplit_override());
+    a.n_zero = kpar ? 0 : w.n_counters;
     hipError_t e;
     if (w.act_cut) {
         a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
@@ -538,7 +544,8 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     g.Y = static_cast<uint16_t *>(Y);
     g.M = M; g.N = s.N; g.K = s.K; g.Mpad = w.Mpad; g.Npad = svdq::round_up(s.N, svdq::kRowPad);
     g.rank = lowrank ? s.rank : 0;
-    g.ksplit = w.ksplit;
+    g.kpar = kpar;
+    g.ksplit = kpar ? 1 : w.ksplit;
     g.partial = reinterpret_cast<int32_t *>(ws + w.partial_off);
     g.counters = reinterpret_cast<uint32_t *>(ws + w.counters_off);
     e = svdq::launch_gemm_w8a8(g, stream);

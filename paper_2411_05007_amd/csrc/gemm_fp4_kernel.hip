@@ -306,6 +306,7 @@ hipError_t launch_gemm_fp4(const GemmFp4Params &p, hipStream_t stream) {
     if (p.G <= 0 || p.K != p.G * kGroup || p.Mpad % kRowPad || p.Npad % kRowPad || p.Mpad < p.M || p.Npad < p.N || p.rank % 16 ||
         (size_t)p.G * p.Mpad * kFp4RowBytes >= (size_t)1 << 31 || (size_t)p.G * p.Npad * kFp4RowBytes >= (size_t)1 << 31)
         return hipErrorInvalidValue;
+    if (p.kpar > 0) return launch_gemm_fp4_kpar(p, stream);
     if (p.ksplit < 1 || (p.ksplit > 1 && (!p.partial || !p.counters || p.tile != 0))) return hipErrorInvalidValue;
     // every split must own at least one step (splits are multiples of four steps)
     if (p.ksplit > 1 && (size_t)(p.ksplit - 1) * (((p.G + p.ksplit - 1) / p.ksplit + 3) / 4 * 4) >= (size_t)p.G) return hipErrorInvalidValue;

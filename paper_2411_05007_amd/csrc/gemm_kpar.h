@@ -40,17 +40,24 @@ struct KparLds {
     static_assert(RB % kPR == 0 && kBytes <= 160 * 1024, "");
 };
 
-// acc[r][c][v]: the wavefront's partial tile in the accumulator layout of the 32 x 32 MFMAs (register v of lane l is row
-// 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32).  One or two row blocks at a time, every wavefront leaves its partial
-// blocks in LDS in register order (16 bytes per lane: no bank conflicts), and each then adds up an equal share of the
-// outputs over the wavefronts, in wavefront order, rounds to bf16 (RNE) and stores whole runs of its rows after a turn
-// through LDS.
+// acc[r][c][v] (32-bit words, fp32 or int32): the wavefront's partial tile in the accumulator layout of the 32 x 32 MFMAs
+// (register v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32).  One or two row blocks at a time, every
+// wavefront leaves its partial blocks in LDS in register order (16 bytes per lane: no bank conflicts), and each then
+// adds up an equal share of the outputs over the wavefronts, in wavefront order:
+//   take(p0, k, c, s): s = the sums of rows 8 (oct % 4) + 4 (l / 32) .. + 3 of row block p0 + oct / 4, column 32 (c0 + c) + l % 32,
+//   where oct, c0 = kpar_share(wave, k);   done(p0): behind the last of a phase.
 template <int RB, int CB, int KS>
-__device__ __forceinline__ void kpar_reduce_store(const float (&acc)[RB][CB][16], unsigned char *lds, uint16_t *Y, int M, int N, int gm0, int gn0,
-                                                  int wave, int lane) {
+__device__ __forceinline__ void kpar_share(int wave, int k, int &oct, int &c0) {
     using T = KparLds<RB, CB, KS>;
-    const int li = lane & 31, lh = lane >> 5;
-    unsigned char *ob = lds + T::kPart + wave * (T::kOPW * 8 * T::kOutRow);
+    oct = (wave / T::kWPO) * T::kOPW + k;
+    c0 = (wave % T::kWPO) * T::kCPW;
+}
+template <typename E> struct alignas(16) Kpar4 { E x, y, z, w; };
+template <int RB, int CB, int KS, typename E, typename Take, typename Done>
+__device__ __forceinline__ void kpar_meet(const E (&acc)[RB][CB][16], unsigned char *lds, int wave, int lane, Take take, Done done) {
+    using T = KparLds<RB, CB, KS>;
+    // (a struct, not a vector type: a vector would tie the accumulators to runs of four registers through the whole K loop)
+    using e4 = Kpar4<E>;
 #pragma unroll
     for (int p0 = 0; p0 < RB; p0 += T::kPR) {
         if (p0 > 0) __syncthreads();      // the partial blocks of the phase before have been read
@@ -60,42 +67,66 @@ __device__ __forceinline__ void kpar_reduce_store(const float (&acc)[RB][CB][16]
             for (int c = 0; c < CB; ++c)
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<float4 *>(lds + (((wave * T::kPR + pr) * 4 + q) * CB + c) * 1024 + lane * 16) =
-                        make_float4(acc[p0 + pr][c][4 * q], acc[p0 + pr][c][4 * q + 1], acc[p0 + pr][c][4 * q + 2], acc[p0 + pr][c][4 * q + 3]);
+                    *reinterpret_cast<e4 *>(lds + (((wave * T::kPR + pr) * 4 + q) * CB + c) * 1024 + lane * 16) =
+                        e4{acc[p0 + pr][c][4 * q], acc[p0 + pr][c][4 * q + 1], acc[p0 + pr][c][4 * q + 2], acc[p0 + pr][c][4 * q + 3]};
         __syncthreads();
-        const int c0 = (wave % T::kWPO) * T::kCPW;      // this wavefront's first column block
 #pragma unroll
         for (int k = 0; k < T::kOPW; ++k) {
-            const int oct = (wave / T::kWPO) * T::kOPW + k;      // rows 8 (oct % 4) .. + 7 of row block oct / 4 of the phase
+            int oct, c0;
+            kpar_share<RB, CB, KS>(wave, k, oct, c0);
 #pragma unroll
             for (int c = 0; c < T::kCPW; ++c) {
-                float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+                e4 s{};
 #pragma unroll
                 for (int w = 0; w < KS; ++w) {
-                    const float4 t = *reinterpret_cast<const float4 *>(lds + ((w * T::kOctets + oct) * CB + c0 + c) * 1024 + lane * 16);
+                    const e4 t = *reinterpret_cast<const e4 *>(lds + ((w * T::kOctets + oct) * CB + c0 + c) * 1024 + lane * 16);
                     s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
                 }
-                const uint32_t a = bf16_rne_pair(s.x, s.y), b = bf16_rne_pair(s.z, s.w);
-                unsigned char *o = ob + (k * 8 + 4 * lh) * T::kOutRow + (c * 32 + li) * 2;
-                *reinterpret_cast<uint16_t *>(o) = (uint16_t)a;
-                *reinterpret_cast<uint16_t *>(o + T::kOutRow) = (uint16_t)(a >> 16);
-                *reinterpret_cast<uint16_t *>(o + 2 * T::kOutRow) = (uint16_t)b;
-                *reinterpret_cast<uint16_t *>(o + 3 * T::kOutRow) = (uint16_t)(b >> 16);
+                take(p0, k, c, s);
             }
         }
-        // only this wavefront touches its block, and the LDS queue of a wavefront is in order: no barrier
+        done(p0);
+    }
+}
+
+// How a wavefront's share of the finished outputs leaves for memory: rounded to bf16 (RNE), whole runs of its rows after
+// a turn through its own block of LDS (behind the partial blocks; the LDS queue of a wavefront is in order: no barrier).
+template <int RB, int CB, int KS>
+struct KparStore {
+    using T = KparLds<RB, CB, KS>;
+    unsigned char *ob;
+    int wave, lane;
+    __device__ __forceinline__ KparStore(unsigned char *lds, int wave_, int lane_) : ob(lds + T::kPart + wave_ * (T::kOPW * 8 * T::kOutRow)), wave(wave_), lane(lane_) {}
+    __device__ __forceinline__ void put(int k, int c, Kpar4<float> s) {
+        const uint32_t a = bf16_rne_pair(s.x, s.y), b = bf16_rne_pair(s.z, s.w);
+        unsigned char *o = ob + (k * 8 + 4 * (lane >> 5)) * T::kOutRow + (c * 32 + (lane & 31)) * 2;
+        *reinterpret_cast<uint16_t *>(o) = (uint16_t)a;
+        *reinterpret_cast<uint16_t *>(o + T::kOutRow) = (uint16_t)(a >> 16);
+        *reinterpret_cast<uint16_t *>(o + 2 * T::kOutRow) = (uint16_t)b;
+        *reinterpret_cast<uint16_t *>(o + 3 * T::kOutRow) = (uint16_t)(b >> 16);
+    }
+    __device__ __forceinline__ void store(int p0, uint16_t *Y, int M, int N, int gm0, int gn0) {
         constexpr int kChunks = T::kOPW * 8 * T::kCPW * 4;      // 16-byte chunks; N is a multiple of 16, so a chunk is whole
 #pragma unroll
         for (int j = 0; j < (kChunks + 63) / 64; ++j) {
             const int q = lane + 64 * j;
             if (kChunks % 64 && q >= kChunks) break;
             const int row = q / (T::kCPW * 4), ch = q % (T::kCPW * 4);
-            const int oct = (wave / T::kWPO) * T::kOPW + row / 8;
+            int oct, c0;
+            kpar_share<RB, CB, KS>(wave, row / 8, oct, c0);
             const int grow = gm0 + (p0 + oct / 4) * 32 + 8 * (oct % 4) + row % 8, gcol = gn0 + c0 * 32 + 8 * ch;
             const uint4 v = *reinterpret_cast<const uint4 *>(ob + row * T::kOutRow + ch * 16);
             if (grow < M && gcol < N) *reinterpret_cast<uint4 *>(Y + (size_t)grow * N + gcol) = v;
         }
     }
+};
+
+// fp32 partial tiles whose sum is the output
+template <int RB, int CB, int KS>
+__device__ __forceinline__ void kpar_reduce_store(const float (&acc)[RB][CB][16], unsigned char *lds, uint16_t *Y, int M, int N, int gm0, int gn0,
+                                                  int wave, int lane) {
+    KparStore<RB, CB, KS> out(lds, wave, lane);
+    kpar_meet<RB, CB, KS>(acc, lds, wave, lane, [&](int, int k, int c, Kpar4<float> s) { out.put(k, c, s); }, [&](int p0) { out.store(p0, Y, M, N, gm0, gn0); });
 }
 
 }  // namespace svdq

@@ -97,8 +97,12 @@ struct GemmFp4Params {
     int ksplit;              // workgroups per tile along K (1 = no split); splits are multiples of four steps
     float *partial;          // ksplit > 1: fp32 [tile][split][128 * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per tile, zero when the kernel starts
+    int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
 };
 hipError_t launch_gemm_fp4(const GemmFp4Params &p, hipStream_t stream);
+// small launches (p.kpar > 0): the same product by workgroups whose wavefronts share the K of one small tile
+// (gemm_kpar_blocks_kernel.hip); p.ksplit must be 1
+hipError_t launch_gemm_fp4_kpar(const GemmFp4Params &p, hipStream_t stream);
 
 // register-only matrix-core loops (measurement): kind 0 = int8 32x32x32, kind 1 = 6-bit operands 32x32x64;
 // kPeakProbeGrid workgroups of 256 threads, each wavefront `iters` rounds of 8 MFMAs; sink: kPeakProbeGrid * 256 floats
@@ -138,8 +142,10 @@ struct GemmW8Params {
     int ksplit;              // workgroups per tile along K (1 = no split); splits are multiples of eight steps of 32 channels
     int32_t *partial;        // ksplit > 1: int32 [tile][split][128 * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per tile, zero when the kernel starts
+    int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
 };
 hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream);
+hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &p, hipStream_t stream);      // small launches, as launch_gemm_fp4_kpar
 
 struct DebugActW8Params {
     const uint8_t *codes;

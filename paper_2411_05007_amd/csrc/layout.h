@@ -199,6 +199,25 @@ inline int plan_kpar_int4(int M, int N, int G, int ksplit_override = 0) {
     return t128 > 256 && (rest == 0 || rest >= 256) ? kKpar4x4 : kKpar2x4;
 }
 
+// MXFP4 and INT8 (gemm_kpar_blocks_kernel.hip): one MFMA per block and step and nothing behind it, so these variants are bound
+// by what a CU's load unit delivers, (RB + 2) KB for 2 RB MFMAs, and give way to the 128 x 256 tiles, which share their
+// operands through LDS, as soon as those fill the CUs.  us per forward, rank 32 / 16, with the large-tile kernels first:
+//   M = 1, K = 3072, N = 9216 (144 tiles of 32 x 64): MXFP4 24.8; 1x8 13.2, 2x4 13.7.       INT8 30.3; 1x8 17.3, 2x8 19.3
+//   M = 16, K = N = 12288 (192): 38.5; 1x8 24.3, 2x8 26.6.                                   51.6; 1x8 38.2, 2x8 40.8
+//   M = 300, K = 3072, N = 2064 (165 of 64 x 64): 28.3; 1x8 19.2, 2x8 15.1, 2x4 14.8.        34.2; 1x8 23.2, 2x8 20.6, 2x4 21.4
+//   M = 512, K = N = 3072 (192 of 128 x 64): 26.4; 2x4 18.1, 4x8 17.8, 4x4 18.3.             32.4; 2x4 24.5, 4x8 25.6, 4x4 27.2
+//   M = 512, K = 12288, N = 3072 (192): 38.6; 2x4 38.6, 4x8 34.9, 4x4 38.1.                  52.4; 2x4 50.4, 4x8 47.5, 4x4 52.4
+//   M = 1024, K = N = 3072 (384): 28.6; 2x4 24.6, 4x8 28.0, 4x4 24.4.                        42.8; 2x4 37.1, 4x8 39.8, 4x4 33.5
+//   M = 512, K = 3072, N = 9216 (576): 27.9; 2x4 31.0, 4x4 29.8.                             39.6; 2x4 41.6, 4x4 43.3
+inline int plan_kpar_blocks(bool i8, int M, int N, int G, int ksplit_override = 0) {
+    if (ksplit_override > 0) return kKparNone;
+    const long tn = (N + 63) / 64, t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
+    if (t32 <= 256) return kKpar1x8;
+    if (t64 <= 256) return i8 ? kKpar2x8 : kKpar2x4;
+    if (t128 <= 256) return i8 && G < 128 ? kKpar2x4 : kKpar4x8;
+    return t128 <= 512 ? kKpar4x4 : kKparNone;
+}
+
 // How the W4A4 GEMM of an M x N x (64 G) layer is launched.  Tiles are 128 x 256, two workgroups per CU (512 places).
 // The K loops of a launch with at most one workgroup per CU can be split over up to eight workgroups per tile (at least
 // twelve groups each): every one of them writes its fp32 partial tile to the workspace, and the one that finishes last

@@ -301,6 +301,7 @@ hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream) {
         return hipErrorInvalidValue;
     // what a split K loop needs: its buffers, the 128 x 256 tile (whose partial tiles the workspace is sized for), and at
     // least one step for every split (splits are multiples of four steps of 64 channels)
+    if (p.kpar > 0) return launch_gemm_w8a8_kpar(p, stream);
     if (p.ksplit < 1 || (p.ksplit > 1 && (!p.partial || !p.counters))) return hipErrorInvalidValue;
     const int G = p.K / kGroup;
     if (p.ksplit > 1 && (size_t)(p.ksplit - 1) * (((G + p.ksplit - 1) / p.ksplit + 3) / 4 * 4) >= (size_t)G) return hipErrorInvalidValue;

@@ -1,4 +1,4 @@
-"""The GEMM of launches with few output tiles, whose wavefronts share K (csrc/gemm_*kpar*): every variant that the
+"""The GEMMs of launches with few output tiles, whose wavefronts share K (csrc/gemm_*kpar*): every variant that the
 launch rule can pick, at the sizes where its indexing can go wrong - rows and columns off its tiles, a K of fewer groups
 than wavefronts, group counts off the wavefront count, ranks with more steps than wavefronts - against the oracle, with
 the bounds of the large kernel's tests (one bf16 rounding plus fp32 summation order)."""
@@ -53,3 +53,33 @@ def test_w4a16_at_its_edges(torch, M, K, N, r):  # noqa: F811
     r = min(r, N // 16 * 16, K // 16 * 16)
     print(f"w4a16 edges: M={M} K={K} N={N} r={r}", flush=True)
     _run(torch, O.bf16_round(rng.standard_normal((M, K)).astype(np.float32)), _layer(rng, K, N, r), f"w4a16 {M}x{K}x{N} r{r}")
+
+
+# (the rule of the two block formats; the last column: rows per tile for MXFP4 and for INT8)
+@pytest.mark.parametrize("M,K,N,r,rows", [
+    (1, 64, 16, 16, (32, 32)), (33, 128, 80, 16, (32, 32)), (31, 576, 1040, 144, (32, 32)), (64, 1088, 272, 0, (32, 32)),
+    (290, 192, 2064, 32, (64, 64)), (257, 704, 3072, 144, (64, 64)), (320, 64, 2032, 16, (64, 64)),
+    (610, 192, 2064, 48, (128, 64)), (577, 832, 2320, 32, (128, 64)), (129, 64, 6160, 16, (128, 64)),
+    (520, 8256, 1984, 32, (128, 128)), (1000, 192, 3088, 80, (128, 128)), (897, 320, 3056, 16, (128, 128))])
+@pytest.mark.parametrize("fmt", ["fp4", "w8a8"])
+def test_block_formats_at_their_edges(torch, fmt, M, K, N, r, rows):  # noqa: F811
+    """Bounds: those of test_gpu_fp4.py and test_gpu_w8a8.py (exact codes and scales, one bf16 rounding plus fp32 summation order)."""
+    from tests import test_gpu_fp4, test_gpu_w8a8
+    rng = np.random.default_rng(5400 + M + K + N)
+    r = min(r, K // 16 * 16, N)
+    rinv = np.exp2(rng.uniform(-1, 1, K)).astype(np.float32)
+    l1 = O.bf16_round((rng.standard_normal((K, r)) * 0.02).astype(np.float32))
+    l2 = O.bf16_round((rng.standard_normal((r, N)) * 0.05).astype(np.float32))
+    bias = rng.standard_normal(N).astype(np.float32)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x[:, rng.choice(K, max(1, K // 100), replace=False)] *= 50
+    sample = np.unique(np.concatenate([np.arange(min(M, 40)), np.arange(max(0, M - 40), M), rng.integers(0, M, 60)]))
+    print(f"small launch: {fmt} M={M} K={K} N={N} r={r}", flush=True)
+    if fmt == "fp4":
+        prep = S.svdq_fp4_pack(rinv, l1, l2, rng.integers(0, 16, size=(K, N)).astype(np.uint8), rng.integers(110, 118, size=(K // 32, N)).astype(np.uint8), bias)
+        plan = S.svdq_debug_launch_plan(M, prep.shape)
+        assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // rows[0]) * -(-N // 64), 1)
+        test_gpu_fp4._run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"fp4 small {M}x{K}x{N}")
+    else:
+        prep = S.svdq_w8a8_pack(rinv, l1, l2, rng.integers(-127, 128, size=(K, N)).astype(np.int8), rng.uniform(5e-5, 4e-4, N).astype(np.float16), bias)
+        test_gpu_w8a8._run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"w8a8 small {M}x{K}x{N}")
