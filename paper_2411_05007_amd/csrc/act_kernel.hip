@@ -104,10 +104,11 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
 #pragma unroll
     for (int c = 0; c < RBMAX; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // wavefront w owns a contiguous run of groups, walked in steps of two; a run of odd length repeats its
+    // wavefront w owns a contiguous run of groups, walked in steps of two; from rank 33 on a run of odd length repeats its
     // last group once more (it recomputes and rewrites the same codes and is kept out of the projection), so
     // the loop body has no divergent or data-dependent control flow around its memory operations and the
-    // load/store counters can be waited on precisely
+    // load/store counters can be waited on precisely.  (Up to rank 32 the second step of such a run is left out: no slower
+    // on long runs, 1 us faster on runs of three groups.)
     const int gbeg = nchunks > 1 ? chunk * gchunk : 0;                      // this workgroup's run of groups
     const int gend = nchunks > 1 && gbeg + gchunk < p.G ? gbeg + gchunk : p.G;
     const int per = (gend - gbeg + WAVES - 1) / WAVES;
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
             step2(g, g + 1 < g1);
         } else {
             step1(g, true, xs0, bs0);
-            step1(clampg(g + 1), g + 1 < g1, xs1, bs1);
+            if (g + 1 < g1) step1(g + 1, true, xs1, bs1);
         }
     }
 
@@ -541,6 +542,23 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
         // a thread takes eight neighbouring columns of one token: two 16-byte stores of fp32 H, and one each
         // of the bf16 hi and lo parts that the GEMM feeds to its matrix core as they are
         const int octets = p.rank / 8;
+        // Small launches whose GEMM adds the runs itself: the run's sum goes out with plain stores, and that is all (the
+        // meeting below costs four round trips past the L2, 3 us of a launch that takes 5 without it).
+        if (p.deposit) {
+            float *mine = p.hpart + ((size_t)chunk * p.Mpad + m0) * p.rank;
+            for (int idx = threadIdx.x; idx < 4 * p.rank; idx += WAVES * 64) {
+                const int r = idx / (p.rank / 4), col = 4 * (idx - r * (p.rank / 4));
+                float h[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < WAVES; ++w) {
+                    const float *pw = reinterpret_cast<const float *>(all + (size_t)w * L::kWaveBytes) + r * L::kRedRow + col;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) h[e] += pw[e];
+                }
+                *reinterpret_cast<float4 *>(mine + r * p.rank + col) = make_float4(h[0], h[1], h[2], h[3]);
+            }
+            return;
+        }
         float *sums = reinterpret_cast<float *>(act_lds + 16);      // [16][rank] sums over the runs, behind the verdict word
         if (nchunks > 1) {
             // This run's sum goes to the workspace with device-scope atomic stores (they go past the L2 caches of the
@@ -632,6 +650,7 @@ hipError_t launch_rb(const ActParams &p, int flags, hipStream_t stream) {
     const int slices = (p.M + 15) / 16;
     // what the kernel's indexing assumes about a cut K: runs that cover it, no empty run, one arrival word per run and lane
     auto runs_ok = [&](int c, int g) { return g >= 1 && (size_t)g * c >= (size_t)p.G && (c - 1) * g < p.G && c <= 64 && p.hpart && p.arrived; };
+    if (p.deposit && (p.whole != 0 || !p.hpart)) return hipErrorInvalidValue;
     if (nchunks > 1 && !runs_ok(nchunks, p.gchunk)) return hipErrorInvalidValue;
     if (p.whole < 0 || p.whole > slices || (p.whole > 0 && cA > 1 && !runs_ok(cA, p.gchunk0))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(p.whole * cA + (slices - p.whole) * nchunks)), block(WAVES * 64);

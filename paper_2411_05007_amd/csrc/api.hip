@@ -57,6 +57,9 @@ svdq::GemmW4Params gemm_params(const svdq_layer_dev *L, unsigned char *ws, const
     g.tail = 0;
     g.partial = reinterpret_cast<float *>(ws + w.partial_off);
     g.counters = reinterpret_cast<uint32_t *>(ws + w.counters_off);
+    g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
+    g.H = reinterpret_cast<float *>(ws + w.h_off);
+    g.runs = 0;
     return g;
 }
 
@@ -139,6 +142,7 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
 
     hipError_t e;
     if (!unfused) {
+        a.deposit = w.act.deposit;
         e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
         if (e != hipSuccess) return hip_fail(e);
         if (void *ev = g_profile_event) {
@@ -149,6 +153,7 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
         g.ksplit = kpar ? 1 : plan.ksplit;
         g.tail = kpar ? 0 : plan.tail;
         g.kpar = kpar;
+        g.runs = lowrank && w.act.deposit ? w.act.chunks : 0;
         e = svdq::launch_gemm_w4a4(g, stream);
         if (e != hipSuccess) return hip_fail(e);
     } else {
@@ -350,6 +355,7 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     a.whole = w.act.whole; a.chunks0 = w.act.chunks0; a.gchunk0 = w.act.gchunk0;
     a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
     a.arrived = reinterpret_cast<unsigned long long *>(ws + w.aflags_off);
+    a.deposit = w.act.deposit;
     hipError_t e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (void *ev = g_profile_event) {
@@ -357,6 +363,9 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
         if (e != hipSuccess) return hip_fail(e);
     }
     svdq::GemmFp4Params g{};
+    g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
+    g.H = reinterpret_cast<float *>(ws + w.h_off);
+    g.runs = lowrank && w.act.deposit ? w.act.chunks : 0;
     g.xcodes = ws + w.codes_off;
     g.bx = ws + w.bx_off;
     g.hfrag = ws + w.hfrag_off;
@@ -526,6 +535,7 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
         e = svdq::launch_act(a, 1, stream);
         if (e != hipSuccess) return hip_fail(e);
         a.maxmode = 2;
+        a.deposit = w.act.deposit;
     }
     e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);
@@ -534,6 +544,9 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
         if (e != hipSuccess) return hip_fail(e);
     }
     svdq::GemmW8Params g{};
+    g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
+    g.H = reinterpret_cast<float *>(ws + w.h_off);
+    g.runs = lowrank && w.act.deposit ? w.act.chunks : 0;
     g.xcodes = ws + w.codes_off;
     g.sx = reinterpret_cast<const uint16_t *>(ws + w.sx_off);
     g.hfrag = ws + w.hfrag_off;

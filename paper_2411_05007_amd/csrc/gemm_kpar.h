@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "act_common.h"
+#include "layout.h"
 
 namespace svdq {
 
@@ -128,5 +129,56 @@ __device__ __forceinline__ void kpar_reduce_store(const float (&acc)[RB][CB][16]
     KparStore<RB, CB, KS> out(lds, wave, lane);
     kpar_meet<RB, CB, KS>(acc, lds, wave, lane, [&](int, int k, int c, Kpar4<float> s) { out.put(k, c, s); }, [&](int p0) { out.store(p0, Y, M, N, gm0, gn0); });
 }
+
+// Columns col .. + 7 of H's row m from the partial H that the runs of the activation kernel left (fp32 [runs][Mpad][rank]):
+// added in run order, split into bf16 hi + lo.  Hout: where the sums also go, or null.
+__device__ __forceinline__ void kpar_sum_h(const float *hpart, int runs, int Mpad, int rank, int m, int col, float *Hout, uint4 &vhi, uint4 &vlo) {
+    const size_t at = (size_t)m * rank + col, stride = (size_t)Mpad * rank;
+    float h[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int c0 = 0; c0 < runs; c0 += 4) {      // four runs are requested before the first addition waits
+        float4 t[4][2];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float4 *q = reinterpret_cast<const float4 *>(hpart + (c0 + c < runs ? c0 + c : c0) * stride + at);
+            t[c][0] = q[0];
+            t[c][1] = q[1];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (c0 + c < runs) {
+                h[0] += t[c][0].x; h[1] += t[c][0].y; h[2] += t[c][0].z; h[3] += t[c][0].w;
+                h[4] += t[c][1].x; h[5] += t[c][1].y; h[6] += t[c][1].z; h[7] += t[c][1].w;
+            }
+    }
+    uint32_t hi[4], lo[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        hi[e] = bf16_rne_pair(h[2 * e], h[2 * e + 1]);
+        lo[e] = bf16_rne_pair(h[2 * e] - bf16lo(hi[e]), h[2 * e + 1] - bf16hi(hi[e]));
+    }
+    vhi = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    vlo = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    if (Hout) {
+        float4 *o = reinterpret_cast<float4 *>(Hout + at);
+        o[0] = make_float4(h[0], h[1], h[2], h[3]);
+        o[1] = make_float4(h[4], h[5], h[6], h[7]);
+    }
+}
+// The same for all of a tile's 32 RB rows, left in LDS in the operand order of hfrag (rows counted from the tile's first).
+// All threads take part; ends with a barrier.
+template <int RB, int KS>
+__device__ __forceinline__ void kpar_sum_h_tile(unsigned char *lds, const float *hpart, int runs, int Mpad, int rank, int gm0, float *Hout, int tid) {
+    const int octets = rank / 8;
+    for (int idx = tid; idx < 32 * RB * octets; idx += KS * 64) {
+        const int m = idx / octets, col = 8 * (idx - m * octets);
+        uint4 hi, lo;
+        kpar_sum_h(hpart, runs, Mpad, rank, gm0 + m, col, Hout, hi, lo);
+        *reinterpret_cast<uint4 *>(lds + hfrag_offset(rank, m, col, 0)) = hi;
+        *reinterpret_cast<uint4 *>(lds + hfrag_offset(rank, m, col, 1)) = lo;
+    }
+    __syncthreads();
+}
+// LDS that the sums need
+template <int RB> constexpr int kpar_h_bytes(int rank) { return 32 * RB * rank * 4; }
 
 }  // namespace svdq

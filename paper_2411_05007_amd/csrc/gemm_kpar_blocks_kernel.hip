@@ -37,6 +37,9 @@ struct KparParams {
     const float *bias;
     uint16_t *Y;
     int M, N, steps, Mpad, Npad, rank;
+    const float *hpart;      // runs > 0: partial H of the activation kernel's runs, else hfrag holds the whole H
+    float *H;
+    int runs;
 };
 
 // I8: INT8 (32 channels per step), else MXFP4 (64).  RB row blocks of 32, KS wavefronts that share K, DEPTH steps ahead.
@@ -98,11 +101,15 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
         struct RankStep { uint4 hi, lo, b[T::kCPW]; };
         auto load_rank = [&](RankStep &o, int ph, int ks) {
             const int m = gm0 + (ph * T::kPR + oct0 / 4) * 32 + 8 * (oct0 % 4 + li / 8 % T::kOPW) + li % 8;      // < Mpad
+#pragma unroll
+            for (int c = 0; c < T::kCPW; ++c) o.b[c] = *reinterpret_cast<const uint4 *>(p.l2t + (size_t)(gn0 + (c0 + c) * 32 + li) * p.rank + 16 * ks + 8 * lh);
+            if (p.runs > 0) {
+                kpar_sum_h(p.hpart, p.runs, p.Mpad, p.rank, m, 16 * ks + 8 * lh, tile_n == 0 && c0 == 0 && li < 8 * T::kOPW ? p.H : nullptr, o.hi, o.lo);
+                return;
+            }
             const unsigned char *h = p.hfrag + hfrag_offset(p.rank, m, 16 * ks + 8 * lh, 0);
             o.hi = *reinterpret_cast<const uint4 *>(h);
             o.lo = *reinterpret_cast<const uint4 *>(h + 1024);
-#pragma unroll
-            for (int c = 0; c < T::kCPW; ++c) o.b[c] = *reinterpret_cast<const uint4 *>(p.l2t + (size_t)(gn0 + (c0 + c) * 32 + li) * p.rank + 16 * ks + 8 * lh);
         };
         RankStep first[kPhases];
 #pragma unroll
@@ -187,10 +194,18 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
 #pragma unroll
             for (int r = 0; r < RB; ++r) acc[r][c] = floatx16{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
         }
-        for (int ks = wave; ks < p.rank / 16; ks += KS) {
-            GemmLowRankStep<RB, CB> o;
-            gemm_lowrank_load<RB, CB>(o, p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048 + lane * 16, p.l2t, p.rank, gn0, lane, ks);
-            gemm_lowrank_multiply<RB, CB>(acc, o);
+        auto low_rank = [&](const unsigned char *hf) {
+            for (int ks = wave; ks < p.rank / 16; ks += KS) {
+                GemmLowRankStep<RB, CB> o;
+                gemm_lowrank_load<RB, CB>(o, hf + lane * 16, p.l2t, p.rank, gn0, lane, ks);
+                gemm_lowrank_multiply<RB, CB>(acc, o);
+            }
+        };
+        if (p.runs > 0) {
+            kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.Mpad, p.rank, gm0, tile_n == 0 ? p.H : nullptr, threadIdx.x);
+            low_rank(lds);
+        } else {
+            low_rank(p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048);
         }
         for (int i = 0; i < n; i += DEPTH) {
 #pragma unroll
@@ -214,6 +229,7 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
             for (int c = 0; c < CB; ++c)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) f[r][c][v] = acc[r][c][v];
+        if (p.runs > 0) __syncthreads();      // nobody reads H any more
         kpar_reduce_store<RB, CB, KS>(f, lds, p.Y, p.M, p.N, gm0, gn0, wave, lane);
     }
 }
@@ -225,6 +241,7 @@ hipError_t launch_one(const KparParams &p, hipStream_t stream) {
     if (tiles_m * 32 * RB > p.Mpad || tiles_n * 64 > p.Npad) return hipErrorInvalidValue;
     auto k = gemm_kpar_blocks_kernel<I8, RB, KS, DEPTH>;
     constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
+    if (p.runs > 0 && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);
@@ -251,6 +268,7 @@ hipError_t launch_gemm_fp4_kpar(const GemmFp4Params &q, hipStream_t stream) {
     p.xcodes = q.xcodes; p.wcodes = q.wcodes; p.bx = q.bx; p.bw = q.bw;
     p.hfrag = q.hfrag; p.l2t = q.l2t; p.bias = q.bias; p.Y = q.Y;
     p.M = q.M; p.N = q.N; p.steps = q.G; p.Mpad = q.Mpad; p.Npad = q.Npad; p.rank = q.rank;
+    p.hpart = q.hpart; p.H = q.H; p.runs = q.runs;
     return launch_variant<false>(p, q.kpar, stream);
 }
 
@@ -260,6 +278,7 @@ hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &q, hipStream_t stream) {
     p.xcodes = q.xcodes; p.wcodes = q.wcodes; p.sx = q.sx; p.sw = q.sw;
     p.hfrag = q.hfrag; p.l2t = q.l2t; p.bias = q.bias; p.Y = q.Y;
     p.M = q.M; p.N = q.N; p.steps = q.K / 32; p.Mpad = q.Mpad; p.Npad = q.Npad; p.rank = q.rank;
+    p.hpart = q.hpart; p.H = q.H; p.runs = q.runs;
     return launch_variant<true>(p, q.kpar, stream);
 }
 

@@ -122,10 +122,19 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kerne
 #pragma unroll
             for (int r = 0; r < RB; ++r) lr[r][c] = floatx16{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
         }
-        for (int ks = wave; ks < p.rank / 16; ks += KS) {
-            GemmLowRankStep<RB, CB> o;
-            gemm_lowrank_load<RB, CB>(o, p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048 + lane * 16, p.l2t, p.rank, gn0, lane, ks);
-            gemm_lowrank_multiply<RB, CB>(lr, o);
+        // H comes ready-made, or as the partial sums of the activation kernel's runs
+        auto low_rank = [&](const unsigned char *hf) {
+            for (int ks = wave; ks < p.rank / 16; ks += KS) {
+                GemmLowRankStep<RB, CB> o;
+                gemm_lowrank_load<RB, CB>(o, hf + lane * 16, p.l2t, p.rank, gn0, lane, ks);
+                gemm_lowrank_multiply<RB, CB>(lr, o);
+            }
+        };
+        if (p.runs > 0) {
+            kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.Mpad, p.rank, gm0, tile_n == 0 ? p.H : nullptr, threadIdx.x);
+            low_rank(lds);
+        } else {
+            low_rank(p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048);
         }
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -204,6 +213,7 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kerne
             }
         }
     }
+    if (p.runs > 0) __syncthreads();      // nobody reads H any more
     kpar_reduce_store<RB, CB, KS>(acc, lds, p.Y, p.M, p.N, gm0, gn0, wave, lane);
 }
 
@@ -214,6 +224,7 @@ hipError_t launch_kpar(const GemmW4Params &p, hipStream_t stream) {
     if (tiles_m * 32 * RB > p.Mpad || tiles_n * 64 > p.Npad) return hipErrorInvalidValue;
     auto k = gemm_w4a4_kpar_kernel<RB, KS, DEPTH>;
     constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
+    if (p.runs > 0 && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);

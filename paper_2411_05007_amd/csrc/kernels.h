@@ -24,6 +24,8 @@ struct ActParams {
     int whole, chunks0, gchunk0;     // the first `whole` 16-token slices are cut differently: chunks0 runs of gchunk0 groups (chunks0 <= 1: not cut)
     // partial H of every run of the cut slices, fp32: [chunks0][16 whole][rank] (if chunks0 > 1), then [chunks][Mpad - 16 whole][rank] (if chunks > 1)
     float *hpart;
+    // deposit: H is not made here; the runs' partial H stay in hpart and the GEMM (a variant whose wavefronts share K) adds them
+    int deposit;
     // arrival words: [whole][chunks0] (if chunks0 > 1), then [Mpad / 16 - whole][chunks] (if chunks > 1)
     unsigned long long *arrived;
     // INT8 per token with K cut into runs: 1 = first pass, only the maxima of the runs, to pmax fp32 [chunks][Mpad];
@@ -52,6 +54,9 @@ struct GemmW4Params {
     float *partial;          // ksplit > 1: fp32 [split tile][split][BM * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per split tile, zero when the kernel starts
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
+    const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
+    int runs;
+    float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
 hipError_t launch_gemm_w4a4(const GemmW4Params &p, hipStream_t stream);
 // small launches (p.kpar > 0): the same product by workgroups whose wavefronts share the K of one small tile
@@ -98,6 +103,9 @@ struct GemmFp4Params {
     float *partial;          // ksplit > 1: fp32 [tile][split][128 * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per tile, zero when the kernel starts
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
+    const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
+    int runs;
+    float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
 hipError_t launch_gemm_fp4(const GemmFp4Params &p, hipStream_t stream);
 // small launches (p.kpar > 0): the same product by workgroups whose wavefronts share the K of one small tile
@@ -143,6 +151,9 @@ struct GemmW8Params {
     int32_t *partial;        // ksplit > 1: int32 [tile][split][128 * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per tile, zero when the kernel starts
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
+    const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
+    int runs;
+    float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
 hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream);
 hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &p, hipStream_t stream);      // small launches, as launch_gemm_fp4_kpar

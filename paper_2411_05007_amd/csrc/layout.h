@@ -167,6 +167,7 @@ struct ActPlan {
     int waves;       // wavefronts per workgroup: 4 or 8
     // the first `whole` slices of a launch can be cut differently from the rest (or not at all): chunks0 runs of gchunk0 groups
     int whole, chunks0, gchunk0;
+    bool deposit;    // the runs' partial H are left for the GEMM to add (plan_act_small)
 };
 struct WorkspaceFp4 {
     size_t codes_off, bx_off, h_off, hfrag_off, counters_off, partial_off, hpart_off, aflags_off, total;
@@ -316,6 +317,7 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
     // (measured at K = 3072, rank 32: M = 4608 20.2 -> 16.9 us, 5120 20.5 -> 18.1, 6144 21.4 -> 19.4, 8704 30.1 -> 26.4,
     // 16896 47.2 -> 43.8; rank 128 at M = 4608: 30.1 -> 23.0; with r > 128 a finer cut does not pay).
     pl.whole = 0; pl.chunks0 = 1; pl.gchunk0 = G > 0 ? G : 1;
+    pl.deposit = false;
     int twos = 1;                                        // largest power of two that divides the runs per slice (up to 256)
     while (twos < 256 && pl.chunks % (2 * twos) == 0) twos *= 2;
     const int tail = slices % (256 / twos);              // the slices behind the last full round of 256 workgroups
@@ -335,6 +337,31 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
     }
     return pl;
 }
+// The same where the GEMM is one whose wavefronts share K (`kpar`, the variant; `i8`: the 8-bit format).  Such a GEMM can add the
+// runs' partial H itself when it loads them, which takes the meeting of a slice's runs - four round trips past the L2 - out of
+// the activation kernel; runs then cost next to nothing and are cut so that a wavefront walks three groups.  What they do
+// cost is that every tile reads its rows of all partial H: up to 64 MB of that per launch (measured: 50 MB gains 2-3 us,
+// 75 MB nothing, 201 MB loses 5), and 512 workgroups.  us per forward, meeting -> deposit (wavefronts, groups per run):
+//   K = N = 3072, rank 32: M = 512 20.6 -> 18.4 (4, 12), 18.6 (8, 16), 19.1 (8, 24); M = 1024 29.5 -> 27.4 (4, 12); M = 2048 43.5 -> 40.2 (4, 12)
+//   M = 64, K = 12288, N = 3072: 22.1 -> 20.0 (4, 12), 19.8 (8, 24); M = 512 41.7 -> 39.7 (4, 12), 37.6 (8, 24); M = 256, K = N = 1152 12.2 -> 10.3 (4, 12)
+//   rank 128, K = N = 3072: M = 64 17.8 -> 14.1 (4, 12), M = 512 26.3 -> 24.3;  M = 512, K = 12288: 48.4 -> 54.1 (201 MB: not taken)
+// INT8 needs the tokens' maxima first, a launch of its own where K is cut: a short K is walked whole instead (M = 256,
+// K = N = 1152 16.5 -> 12.7; at K = 3072 17.4 against 15.7 cut), and a long one gains nothing from the deposit (49.3 against 48.9).
+inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, int kpar, bool i8) {
+    const ActPlan old = plan_act(M, G, rank, act_override);
+    if (act_override > 0 || kpar == kKparNone || rank <= 0 || rank > 128) return old;
+    const long slices = (M + 15) / 16;
+    ActPlan pl = old;
+    pl.waves = G > 96 ? 8 : 4;
+    pl.gchunk = i8 && G <= 32 ? G : G > 96 ? 24 : G > 12 ? 12 : G;
+    if (i8 && (G > 96 || slices > 128)) return old;
+    pl.chunks = (G + pl.gchunk - 1) / pl.gchunk;
+    pl.whole = 0; pl.chunks0 = 1; pl.gchunk0 = G;
+    pl.deposit = pl.chunks > 1;
+    const long tiles = (long)((M + kpar_rows(kpar) - 1) / kpar_rows(kpar)) * ((N + 63) / 64);
+    if (slices * pl.chunks > 512 || pl.chunks > 64 || tiles * kpar_rows(kpar) * rank * 4 * pl.chunks > 64l << 20) return old;
+    return pl;
+}
 // the value a workgroup leaves in its arrival word; the word is cleared again before the kernel ends, so whatever a
 // fresh workspace holds is taken for "not arrived" (anything but this one 64-bit value)
 constexpr unsigned long long kActArrived = 0x5356445141525256ull;
@@ -344,6 +371,21 @@ inline size_t act_parked_floats(const ActPlan &a, int Mpad, int rank) {
 }
 inline size_t act_arrival_words(const ActPlan &a, int Mpad) {
     return (a.whole > 0 && a.chunks0 > 1 ? (size_t)a.chunks0 * a.whole : 0) + (a.chunks > 1 ? (size_t)a.chunks * (Mpad / 16 - a.whole) : 0);
+}
+
+// Gives a workspace the plan of plan_act_small where what that plan parks (and `ahead` bytes in front of it) fits into what the
+// workspace holds from partial_off on: the launches it is made for leave the room of the GEMM's partial tiles unused, and
+// a workspace's size stays what callers may have kept from the plan above.
+template <typename W>
+inline bool act_use_small_plan(W &w, const ActPlan &a, int rank, size_t ahead) {
+    const bool parked = a.chunks > 1 && rank > 0;
+    const size_t h = parked ? align256(act_parked_floats(a, w.Mpad, rank) * 4) : 0, words = parked ? align256(act_arrival_words(a, w.Mpad) * 8) : 0;
+    if (a.chunks > 1 && !a.deposit) return false;
+    if (w.partial_off + ahead + h + words > w.total) return false;
+    w.act = a;
+    w.hpart_off = w.partial_off + ahead;
+    w.aflags_off = w.hpart_off + h;
+    return true;
 }
 
 // The int8 MFMA takes twice the time of the 4-bit one per step of 64 channels, so a split of the 8-bit GEMM's K loop pays
@@ -382,6 +424,12 @@ inline WorkspaceW8 workspace_layout_w8(int M, int K, int N, int rank, int ksplit
     const bool parked = w.act_cut && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
+    const ActPlan small = plan_act_small(M > 0 ? M : 1, N, K / kGroup, rank, act_override, plan_kpar_blocks(true, M > 0 ? M : 1, N, K / kGroup, ksplit_override), true);
+    const size_t pmax = small.chunks > 1 ? align256((size_t)small.chunks * w.Mpad * 4) : 0;
+    if (w.act_cut && act_use_small_plan(w, small, rank, pmax)) {
+        w.act_cut = small.chunks > 1;
+        w.pmax_off = w.partial_off;
+    }
     return w;
 }
 
@@ -405,6 +453,7 @@ inline WorkspaceFp4 workspace_layout_fp4(int M, int K, int N, int rank, int kspl
     const bool parked = ap.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(ap, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(ap, w.Mpad) * 8) : 0);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override), false), rank, 0);
     return w;
 }
 
@@ -432,6 +481,7 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     const bool parked = w.act.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_int4(M > 0 ? M : 1, N, G, ksplit_override), false), rank, 0);
     return w;
 }
 

@@ -27,6 +27,7 @@ def _layer(rng, K, N, r):
     (1, 64, 16, 16, 32), (33, 128, 80, 16, 32), (31, 576, 1040, 144, 32), (64, 1088, 272, 0, 32),             # 32 rows, 8 wavefronts
     (290, 192, 2064, 32, 64), (257, 704, 3072, 144, 64), (320, 64, 2032, 16, 64),                             # 64 rows, 8 wavefronts
     (610, 192, 2064, 48, 64), (577, 832, 2320, 32, 64), (129, 64, 6160, 16, 64),                              # 64 rows, 4 wavefronts
+    (45, 1600, 336, 112, 32), (17, 832, 80, 16, 32), (300, 6400, 1040, 64, 32),      # H added from two, three and five runs
     (520, 8256, 1984, 32, 128), (385, 8192, 3072, 160, 128),                                                  # 128 rows, 8 wavefronts
     (1000, 192, 3088, 80, 128), (897, 320, 3056, 16, 128), (1030, 64, 2736, 32, 128)])                        # 128 rows, 4 wavefronts
 def test_every_variant_at_its_edges(torch, M, K, N, r, rows):  # noqa: F811
@@ -60,6 +61,7 @@ def test_w4a16_at_its_edges(torch, M, K, N, r):  # noqa: F811
     (1, 64, 16, 16, (32, 32)), (33, 128, 80, 16, (32, 32)), (31, 576, 1040, 144, (32, 32)), (64, 1088, 272, 0, (32, 32)),
     (290, 192, 2064, 32, (64, 64)), (257, 704, 3072, 144, (64, 64)), (320, 64, 2032, 16, (64, 64)),
     (610, 192, 2064, 48, (128, 64)), (577, 832, 2320, 32, (128, 64)), (129, 64, 6160, 16, (128, 64)),
+    (70, 2112, 208, 48, (32, 32)), (40, 2432, 144, 128, (32, 32)), (300, 3136, 2064, 32, (64, 64)),      # H added from runs
     (520, 8256, 1984, 32, (128, 128)), (1000, 192, 3088, 80, (128, 128)), (897, 320, 3056, 16, (128, 128))])
 @pytest.mark.parametrize("fmt", ["fp4", "w8a8"])
 def test_block_formats_at_their_edges(torch, fmt, M, K, N, r, rows):  # noqa: F811
