@@ -39,8 +39,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Tile configuration: 2 x 2 wavefronts, each RB x CB MFMA blocks of 32 x 32.  <2, 4>: 128 x 256 workgroup tile;
 // <3, 3>: 192 x 192 (nine MFMAs per six operand blocks instead of eight; used where it makes the tile count a whole
-// number of rounds of the chip's 512 workgroup places, e.g. 24 x 64 = 1536 tiles for M = 4608, N = 12288).
-// Both have 12 operand blocks per step: three direct-to-LDS loads per wavefront.
+// number of rounds of the chip's 512 workgroup places, e.g. 24 x 64 = 1536 tiles for M = 4608, N = 12288);
+// <3, 2>: 192 x 128 and <2, 2>: 128 x 128, which load more per MFMA and are used where they spread a launch better over
+// the CUs (layout.h, plan_gemm_fp4).
+// 12, 12, 10, 8 operand blocks per step: two or three direct-to-LDS loads per wavefront.
 template <int RB, int CB>
 struct Fp4Tile {
     static constexpr int kRB = RB, kCB = CB;
@@ -48,11 +50,12 @@ struct Fp4Tile {
     static constexpr int kBM = 2 * kWM, kBN = 2 * kWN;               // workgroup tile
     static constexpr int kOutRow = kWN * 2 + 16;                     // epilogue staging: one row of bf16 + 16 bytes pad
     static constexpr int kFragsA = kBM / 32, kFragsB = kBN / 32;
-    static constexpr int kStageBytes = (kFragsA + kFragsB) * 1024;   // one stage = the operand blocks of one 64-channel step
+    static constexpr int kReq = (kFragsA + kFragsB + 3) / 4;         // direct loads per wavefront and step
+    static constexpr int kStageBytes = kReq * 4 * 1024;              // one stage = the operand blocks of one step, a place for every direct load
     static constexpr int kRingBytes = 4 * kStageBytes;               // four stages
     static constexpr int kOutBytes = 4 * 32 * kOutRow;
     static constexpr int kLdsBytes = kRingBytes > kOutBytes ? kRingBytes : kOutBytes;
-    static_assert(kFragsA + kFragsB == 12 && RB + CB == 6, "three direct loads per wavefront and step, six operand blocks per wavefront");
+    static_assert(RB + CB >= 4 && RB + CB <= 6, "four to six operand blocks per wavefront");
 };
 typedef __attribute__((address_space(3))) void *lds_ptr;
 constexpr int kFmtE2M1 = 4;                  // operand format selector of the instruction
@@ -63,7 +66,7 @@ __device__ __forceinline__ intx8 as_operand(u32x4 v) {
 }
 
 template <int RB, int CB>
-__global__ __launch_bounds__(256, 2) void gemm_fp4_kernel(GemmFp4Params p) {
+__global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(GemmFp4Params p) {
     using T = Fp4Tile<RB, CB>;
     constexpr int kRB = RB, kCB = CB, kWM = T::kWM, kWN = T::kWN, kBM = T::kBM, kBN = T::kBN;
     constexpr int kFragsA = T::kFragsA, kStageBytes = T::kStageBytes, kOutRowFp4 = T::kOutRow;
@@ -124,22 +127,23 @@ __global__ __launch_bounds__(256, 2) void gemm_fp4_kernel(GemmFp4Params p) {
     // dealt to the four wavefronts, blocks w, w + 4 and w + 8 to wavefront w (one kilobyte each; lane l's 16 bytes
     // land at l * 16 of the block, which is the operand order).  Which operand a block belongs to is uniform per wavefront.
     const int glast = g_end - 1;
-    __amdgpu_buffer_rsrc_t rs_d[3];
-    int d_base[3], d_stride[3];
+    __amdgpu_buffer_rsrc_t rs_d[3];      // (of which the first T::kReq)
+    int d_base[3], d_stride[3], d_lane[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < T::kReq; ++i) {
         const int j = wave + 4 * i;
+        d_lane[i] = j < kFragsA + T::kFragsB ? lane * 16 : (int)0x80000000u;      // no such block: beyond the buffer (smaller than 2^31 bytes)
         const bool is_a = j < kFragsA;
         rs_d[i] = is_a ? make_rsrc(p.xcodes, (size_t)p.G * p.Mpad * kFp4RowBytes) : make_rsrc(p.wcodes, (size_t)p.G * p.Npad * kFp4RowBytes);
         d_base[i] = is_a ? gm0 * kFp4RowBytes + j * 1024 : gn0 * kFp4RowBytes + (j - kFragsA) * 1024;
         d_stride[i] = is_a ? a_stride : b_stride;
     }
     auto dma = [&](int g, int stage) {
-        const int gc = g < glast ? g : glast;      // past the end: the last step once more (never read), so that every step issues three requests
+        const int gc = g < glast ? g : glast;      // past the end: the last step once more (never read), so that every step issues as many requests
         unsigned char *st = lds + stage * kStageBytes + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_d[i], (lds_ptr)(st + i * 4096), 16, lane * 16, d_base[i] + gc * d_stride[i], 0, 0);
+        for (int i = 0; i < T::kReq; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_d[i], (lds_ptr)(st + i * 4096), 16, d_lane[i], d_base[i] + gc * d_stride[i], 0, 0);
     };
     // LDS -> registers.  These reads are written as instructions of their own, with explicit waits, because the
     // compiler would make every LDS read wait for ALL outstanding memory-to-LDS requests, also those of later stages.
@@ -147,12 +151,15 @@ __global__ __launch_bounds__(256, 2) void gemm_fp4_kernel(GemmFp4Params p) {
     const uint32_t rd_a = lds_base + lane * 16 + (wm0 / 32) * 1024;
     const uint32_t rd_b = lds_base + lane * 16 + (kFragsA + wn0 / 32) * 1024;
 #define SVDQ_LDS_READ(F, I, STAGE) \
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[I]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) - kRB) * 1024))
+    if ((I) < RB + CB) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[I]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) - kRB) * 1024))
 #define SVDQ_READ_STAGE(F, STAGE) \
     SVDQ_LDS_READ(F, 0, STAGE); SVDQ_LDS_READ(F, 1, STAGE); SVDQ_LDS_READ(F, 2, STAGE); \
     SVDQ_LDS_READ(F, 3, STAGE); SVDQ_LDS_READ(F, 4, STAGE); SVDQ_LDS_READ(F, 5, STAGE);
     // all LDS reads of this wavefront have returned; tied to the registers they fill, so that nothing that uses them moves above
-#define SVDQ_READS_DONE(F) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[4]), "+v"(F.f[5]))
+#define SVDQ_READS_DONE(F)                                                                                                                    \
+    if (RB + CB == 6) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 2]), "+v"(F.f[kRB + kCB - 1])); \
+    else if (RB + CB == 5) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 1])); \
+    else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]))
 
     const int q_begin = g_begin / 4, q_end = (g_end + 3) / 4;
     Frags f0, f1;
@@ -188,8 +195,8 @@ __global__ __launch_bounds__(256, 2) void gemm_fp4_kernel(GemmFp4Params p) {
     SVDQ_READS_DONE(f0);
 #define SVDQ_FP4_STEP(SEL, cur, nxt)                                                                                  \
     if (g0 + SEL < g_end) {                                                                                           \
-        if (SEL == 1 || SEL == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 + kRB + kCB) : "memory");                \
-        else asm volatile("s_waitcnt vmcnt(6)" ::: "memory");                                                         \
+        if (SEL == 1 || SEL == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq + kRB + kCB) : "memory");                \
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq) : "memory");                                                         \
         __builtin_amdgcn_s_barrier();                                                                                 \
         SVDQ_READ_STAGE(nxt, (SEL + 1) & 3)                                                                           \
         if (SEL == 0) load_scales(sn, q + 1 < q_end ? q + 1 : q);                                                     \
@@ -313,6 +320,8 @@ hipError_t launch_gemm_fp4(const GemmFp4Params &p, hipStream_t stream) {
     switch (p.tile) {
         case 0: return launch_fp4_tile<2, 4>(p, stream);
         case 1: return launch_fp4_tile<3, 3>(p, stream);
+        case 2: return launch_fp4_tile<3, 2>(p, stream);
+        case 3: return launch_fp4_tile<2, 2>(p, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -129,7 +129,7 @@ inline __host__ __device__ size_t fp4_scale_bytes(int G, int rows_pad) { return 
 // saves; at 192 steps four splits halve the time, eight are slower again); the partial tiles meet in the
 // workspace as in the INT4 kernel.
 struct GemmPlanFp4 {
-    int tile;        // 0: 128 x 256, 1: 192 x 192
+    int tile;        // 0: 128 x 256, 1: 192 x 192, 2: 192 x 128, 3: 128 x 128
     int tiles, ksplit;
 };
 inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, int min_steps = 32) {
@@ -155,6 +155,26 @@ inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, i
         if (tm * 192 <= round_up(M, kRowPad) && tn * 192 <= round_up(N, kRowPad) && rounds192 * 9 < rounds128 * 8) {
             pl.tile = 1;
             pl.tiles = (int)t192;
+        }
+    }
+    // What a launch takes follows the CU with the most tiles: tiles per CU times MFMAs per step of a tile, weighted with what the
+    // tile loads per MFMA, and a fifth more where no CU has a second tile to fill the first one's waits.  192 x 128 (six
+    // MFMAs) and 128 x 128 (four) are taken where that comes out 5 % below the 128 x 256 tile (eight).
+    // us per forward, 128 x 256 | 192 x 128 | 128 x 128, the rule's choice in brackets; MXFP4 rank 32, INT8 rank 16:
+    //   M = 1337, K = 3072, N = 9216 (396 | 504 | 792 tiles)   43.2 [40.4] 47.4     70.4 [59.2] 65.9
+    //   M = 2048, K = N = 3072 (192 | - | 384)                 31.8   -   [29.0]    44.4   -   [41.5]
+    //   M = 4096, K = 4608, N = 1152 (160 | - | 288)           46.0   -   [38.2]    61.0   -   [53.6]
+    //   M = 1800, K = 3072, N = 12288 (720 | 960 | 1440)       60.7  61.8 [59.2]    [89.8] 94.0  90.8
+    //   M = 4608, K = N = 3072 (432 | 576 | 864)               [43.8] 51.3  49.9    [71.0] 82.3  74.4
+    //   M = 3000, K = 3072, N = 9216 (864 | 1152 | 1728)       [70.5] 74.9  71.7    [110] 115  107
+    if (pl.ksplit == 1 && pl.tile == 0) {
+        auto cost = [](long tiles, int products, double traffic) { return (double)((tiles + 255) / 256 * products) * traffic * (tiles <= 256 ? 1.2 : 1.0); };
+        const double c0 = cost(pl.tiles, 8, 1.0);
+        const long t2 = (long)((M + 191) / 192) * ((N + 127) / 128), t3 = (long)((M + 127) / 128) * ((N + 127) / 128);
+        const double c2 = (M + 191) / 192 * 192 <= round_up(M, kRowPad) ? cost(t2, 6, 1.06) : 1e30, c3 = cost(t3, 4, 1.12);
+        if ((c2 < c3 ? c2 : c3) < 0.95 * c0) {
+            pl.tile = c2 < c3 ? 2 : 3;
+            pl.tiles = (int)(c2 < c3 ? t2 : t3);
         }
     }
     return pl;

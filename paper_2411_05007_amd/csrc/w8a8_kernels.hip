@@ -28,10 +28,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Tile configuration: 2 x 2 wavefronts, each RB x CB MFMA blocks of 32 x 32.  <2, 4>: 128 x 256 workgroup tile;
-// <3, 3>: 192 x 192 (nine MFMAs per six operand blocks instead of eight; used where it makes the tile count a whole
-// number of rounds of the chip's 512 workgroup places, e.g. 24 x 64 = 1536 tiles for M = 4608, N = 12288).
-// Both have 12 operand blocks per step: three direct-to-LDS loads per wavefront.
+// Tile configuration: 2 x 2 wavefronts, each RB x CB MFMA blocks of 32 x 32; the MXFP4 GEMM's tiles (gemm_fp4_kernel.hip)
 template <int RB, int CB>
 struct W8Tile {
     static constexpr int kRB = RB, kCB = CB;
@@ -39,11 +36,12 @@ struct W8Tile {
     static constexpr int kBM = 2 * kWM, kBN = 2 * kWN;               // workgroup tile
     static constexpr int kOutRow = kWN * 2 + 16;                     // epilogue staging: one row of bf16 + 16 bytes pad
     static constexpr int kFragsA = kBM / 32, kFragsB = kBN / 32;
-    static constexpr int kStageBytes = (kFragsA + kFragsB) * 1024;   // one stage = the operand blocks of one 64-channel step
+    static constexpr int kReq = (kFragsA + kFragsB + 3) / 4;         // direct loads per wavefront and step
+    static constexpr int kStageBytes = kReq * 4 * 1024;              // one stage = the operand blocks of one step, a place for every direct load
     static constexpr int kRingBytes = 4 * kStageBytes;               // four stages
     static constexpr int kOutBytes = 4 * 32 * kOutRow;
     static constexpr int kLdsBytes = kRingBytes > kOutBytes ? kRingBytes : kOutBytes;
-    static_assert(kFragsA + kFragsB == 12 && RB + CB == 6, "three direct loads per wavefront and step, six operand blocks per wavefront");
+    static_assert(RB + CB >= 4 && RB + CB <= 6, "four to six operand blocks per wavefront");
 };
 typedef __attribute__((address_space(3))) void *lds_ptr;
 constexpr int kI8RowBytes = 32;      // bytes of one row of one 32-channel step
@@ -59,7 +57,7 @@ __global__ void debug_act_w8_kernel(DebugActW8Params p) {
 }
 
 template <int RB, int CB>
-__global__ __launch_bounds__(256, 2) void gemm_w8a8_kernel(GemmW8Params p) {
+__global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_w8a8_kernel(GemmW8Params p) {
     using T = W8Tile<RB, CB>;
     constexpr int kRB = RB, kCB = CB, kWM = T::kWM, kWN = T::kWN, kBM = T::kBM, kBN = T::kBN;
     constexpr int kFragsA = T::kFragsA, kStageBytes = T::kStageBytes, kOutRowW8 = T::kOutRow;
@@ -103,22 +101,23 @@ __global__ __launch_bounds__(256, 2) void gemm_w8a8_kernel(GemmW8Params p) {
     // dealt to the four wavefronts, blocks w, w + 4 and w + 8 to wavefront w (one kilobyte each; lane l's 16 bytes
     // land at l * 16 of the block, which is the operand order).  Which operand a block belongs to is uniform per wavefront.
     const int glast = g_end - 1;
-    __amdgpu_buffer_rsrc_t rs_d[3];
-    int d_base[3], d_stride[3];
+    __amdgpu_buffer_rsrc_t rs_d[3];      // (of which the first T::kReq)
+    int d_base[3], d_stride[3], d_lane[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < T::kReq; ++i) {
         const int j = wave + 4 * i;
+        d_lane[i] = j < kFragsA + T::kFragsB ? lane * 16 : (int)0x80000000u;      // no such block: beyond the buffer (smaller than 2^31 bytes)
         const bool is_a = j < kFragsA;
         rs_d[i] = is_a ? make_rsrc(p.xcodes, (size_t)p.K * p.Mpad) : make_rsrc(p.wcodes, (size_t)p.K * p.Npad);
         d_base[i] = is_a ? gm0 * kI8RowBytes + j * 1024 : gn0 * kI8RowBytes + (j - kFragsA) * 1024;
         d_stride[i] = is_a ? a_stride : b_stride;
     }
     auto dma = [&](int g, int stage) {
-        const int gc = g < glast ? g : glast;      // past the end: the last step once more (never read), so that every step issues three requests
+        const int gc = g < glast ? g : glast;      // past the end: the last step once more (never read), so that every step issues as many requests
         unsigned char *st = lds + stage * kStageBytes + wave * 1024;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_d[i], (lds_ptr)(st + i * 4096), 16, lane * 16, d_base[i] + gc * d_stride[i], 0, 0);
+        for (int i = 0; i < T::kReq; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_d[i], (lds_ptr)(st + i * 4096), 16, d_lane[i], d_base[i] + gc * d_stride[i], 0, 0);
     };
     // LDS -> registers.  These reads are written as instructions of their own, with explicit waits, because the
     // compiler would make every LDS read wait for ALL outstanding memory-to-LDS requests, also those of later stages.
@@ -126,12 +125,15 @@ __global__ __launch_bounds__(256, 2) void gemm_w8a8_kernel(GemmW8Params p) {
     const uint32_t rd_a = lds_base + lane * 16 + (wm0 / 32) * 1024;
     const uint32_t rd_b = lds_base + lane * 16 + (kFragsA + wn0 / 32) * 1024;
 #define SVDQ_LDS_READ(F, I, STAGE) \
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[I]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) - kRB) * 1024))
+    if ((I) < RB + CB) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[I]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) - kRB) * 1024))
 #define SVDQ_READ_STAGE(F, STAGE) \
     SVDQ_LDS_READ(F, 0, STAGE); SVDQ_LDS_READ(F, 1, STAGE); SVDQ_LDS_READ(F, 2, STAGE); \
     SVDQ_LDS_READ(F, 3, STAGE); SVDQ_LDS_READ(F, 4, STAGE); SVDQ_LDS_READ(F, 5, STAGE);
     // all LDS reads of this wavefront have returned; tied to the registers they fill, so that nothing that uses them moves above
-#define SVDQ_READS_DONE(F) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[4]), "+v"(F.f[5]))
+#define SVDQ_READS_DONE(F)                                                                                                                    \
+    if (RB + CB == 6) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 2]), "+v"(F.f[kRB + kCB - 1])); \
+    else if (RB + CB == 5) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 1])); \
+    else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]))
 
     const int q_begin = g_begin / 4, q_end = (g_end + 3) / 4;
     Frags f0, f1;
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(256, 2) void gemm_w8a8_kernel(GemmW8Params p) {
     SVDQ_READS_DONE(f0);
 #define SVDQ_W8_STEP(SEL, cur, nxt)                                                                                  \
     if (g0 + SEL < g_end) {                                                                                           \
-        asm volatile("s_waitcnt vmcnt(6)" ::: "memory");                                                              \
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq) : "memory");                                                              \
         __builtin_amdgcn_s_barrier();                                                                                 \
         SVDQ_READ_STAGE(nxt, (SEL + 1) & 3)                                                                           \
         dma(g0 + SEL + 4, SEL);                                                                             \
@@ -306,9 +308,15 @@ hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream) {
     const int G = p.K / kGroup;
     if (p.ksplit > 1 && (size_t)(p.ksplit - 1) * (((G + p.ksplit - 1) / p.ksplit + 3) / 4 * 4) >= (size_t)G) return hipErrorInvalidValue;
     if (p.ksplit > 1) return launch_w8_tile<2, 4>(p, stream);
-    // the tile shape follows the MXFP4 GEMM's rule (192 x 192 where it saves a round of workgroup places)
+    // the tile shape follows the MXFP4 GEMM's rule
     const GemmPlanFp4 plan = plan_gemm_fp4(p.M, p.N, G, 1);
-    return plan.tile == 1 ? launch_w8_tile<3, 3>(p, stream) : launch_w8_tile<2, 4>(p, stream);
+    switch (plan.tile) {
+        case 0: return launch_w8_tile<2, 4>(p, stream);
+        case 1: return launch_w8_tile<3, 3>(p, stream);
+        case 2: return launch_w8_tile<3, 2>(p, stream);
+        case 3: return launch_w8_tile<2, 2>(p, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace svdq

@@ -66,6 +66,17 @@ def test_w4a16_at_its_edges(torch, M, K, N, r):  # noqa: F811
 @pytest.mark.parametrize("fmt", ["fp4", "w8a8"])
 def test_block_formats_at_their_edges(torch, fmt, M, K, N, r, rows):  # noqa: F811
     """Bounds: those of test_gpu_fp4.py and test_gpu_w8a8.py (exact codes and scales, one bf16 rounding plus fp32 summation order)."""
+    _block_format(torch, fmt, M, K, N, r, (rows[0], 64))
+
+
+# tiles of the launches that fill the chip: 192 x 128, 128 x 128 (K off four steps, fewer steps than the ring has stages, ragged M and N)
+@pytest.mark.parametrize("M,K,N,r,tile", [(1337, 192, 9040, 32, (192, 128)), (1300, 64, 9232, 0, (192, 128)), (1000, 320, 9040, 48, (128, 128)), (970, 64, 9104, 16, (128, 128))])
+@pytest.mark.parametrize("fmt", ["fp4", "w8a8"])
+def test_block_formats_on_smaller_tiles(torch, fmt, M, K, N, r, tile):  # noqa: F811
+    _block_format(torch, fmt, M, K, N, r, tile)
+
+
+def _block_format(torch, fmt, M, K, N, r, tile):  # noqa: F811
     from tests import test_gpu_fp4, test_gpu_w8a8
     rng = np.random.default_rng(5400 + M + K + N)
     r = min(r, K // 16 * 16, N)
@@ -76,11 +87,11 @@ def test_block_formats_at_their_edges(torch, fmt, M, K, N, r, rows):  # noqa: F8
     x = rng.standard_normal((M, K)).astype(np.float32)
     x[:, rng.choice(K, max(1, K // 100), replace=False)] *= 50
     sample = np.unique(np.concatenate([np.arange(min(M, 40)), np.arange(max(0, M - 40), M), rng.integers(0, M, 60)]))
-    print(f"small launch: {fmt} M={M} K={K} N={N} r={r}", flush=True)
+    print(f"block formats: {fmt} M={M} K={K} N={N} r={r}", flush=True)
     if fmt == "fp4":
         prep = S.svdq_fp4_pack(rinv, l1, l2, rng.integers(0, 16, size=(K, N)).astype(np.uint8), rng.integers(110, 118, size=(K // 32, N)).astype(np.uint8), bias)
         plan = S.svdq_debug_launch_plan(M, prep.shape)
-        assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // rows[0]) * -(-N // 64), 1)
+        assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // tile[0]) * -(-N // tile[1]), 1)
         test_gpu_fp4._run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"fp4 small {M}x{K}x{N}")
     else:
         prep = S.svdq_w8a8_pack(rinv, l1, l2, rng.integers(-127, 128, size=(K, N)).astype(np.int8), rng.uniform(5e-5, 4e-4, N).astype(np.float16), bias)
