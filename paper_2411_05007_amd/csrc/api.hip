@@ -510,8 +510,9 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const bool lowrank = s.rank > 0 && !(g_options & SVDQ_OPT_SKIP_LOWRANK);
 
-    // one kernel: per-token maxima, then smoothing + INT8 codes + the down projection H = X L1s in one walk over X;
-    // small launches: the same kernel twice over K cut into runs (the maxima of the runs, then everything else)
+    // one kernel: per-token maxima, smoothing + INT8 codes + the down projection H = X L1s, in one pass over X that a
+    // workgroup holds in registers (act_w8_one_pass) or in two walks over it;
+    // small launches with a longer K: the walking kernel twice over K cut into runs (the maxima of the runs, then everything else)
     svdq::ActParams a{};
     a.X = static_cast<const uint16_t *>(X);
     a.rinv = static_cast<const float *>(L->rinv);
@@ -526,7 +527,8 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     const int kpar = svdq::plan_kpar_blocks(true, M, s.N, s.K / svdq::kGroup, ksplit_override());
     a.n_zero = kpar ? 0 : w.n_counters;
     hipError_t e;
-    if (w.act_cut) {
+    const bool one_pass = act_override() == 0 && svdq::act_w8_one_pass(M, s.K, s.rank);
+    if (!one_pass && w.act_cut) {
         a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
         a.pmax = reinterpret_cast<float *>(ws + w.pmax_off);
         a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
@@ -535,18 +537,14 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
         e = svdq::launch_act(a, 1, stream);
         if (e != hipSuccess) return hip_fail(e);
         a.maxmode = 2;
-        a.deposit = w.act.deposit;
     }
-    e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
+    e = one_pass ? svdq::launch_act_w8(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (void *ev = g_profile_event) {
         e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);
         if (e != hipSuccess) return hip_fail(e);
     }
     svdq::GemmW8Params g{};
-    g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
-    g.H = reinterpret_cast<float *>(ws + w.h_off);
-    g.runs = lowrank && w.act.deposit ? w.act.chunks : 0;
     g.xcodes = ws + w.codes_off;
     g.sx = reinterpret_cast<const uint16_t *>(ws + w.sx_off);
     g.hfrag = ws + w.hfrag_off;

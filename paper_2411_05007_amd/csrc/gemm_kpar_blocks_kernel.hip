@@ -37,7 +37,7 @@ struct KparParams {
     const float *bias;
     uint16_t *Y;
     int M, N, steps, Mpad, Npad, rank;
-    const float *hpart;      // runs > 0: partial H of the activation kernel's runs, else hfrag holds the whole H
+    const float *hpart;      // MXFP4, runs > 0: partial H of the activation kernel's runs, else hfrag holds the whole H
     float *H;
     int runs;
 };
@@ -103,10 +103,6 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
             const int m = gm0 + (ph * T::kPR + oct0 / 4) * 32 + 8 * (oct0 % 4 + li / 8 % T::kOPW) + li % 8;      // < Mpad
 #pragma unroll
             for (int c = 0; c < T::kCPW; ++c) o.b[c] = *reinterpret_cast<const uint4 *>(p.l2t + (size_t)(gn0 + (c0 + c) * 32 + li) * p.rank + 16 * ks + 8 * lh);
-            if (p.runs > 0) {
-                kpar_sum_h(p.hpart, p.runs, p.Mpad, p.rank, m, 16 * ks + 8 * lh, tile_n == 0 && c0 == 0 && li < 8 * T::kOPW ? p.H : nullptr, o.hi, o.lo);
-                return;
-            }
             const unsigned char *h = p.hfrag + hfrag_offset(p.rank, m, 16 * ks + 8 * lh, 0);
             o.hi = *reinterpret_cast<const uint4 *>(h);
             o.lo = *reinterpret_cast<const uint4 *>(h + 1024);
@@ -278,7 +274,6 @@ hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &q, hipStream_t stream) {
     p.xcodes = q.xcodes; p.wcodes = q.wcodes; p.sx = q.sx; p.sw = q.sw;
     p.hfrag = q.hfrag; p.l2t = q.l2t; p.bias = q.bias; p.Y = q.Y;
     p.M = q.M; p.N = q.N; p.steps = q.K / 32; p.Mpad = q.Mpad; p.Npad = q.Npad; p.rank = q.rank;
-    p.hpart = q.hpart; p.H = q.H; p.runs = q.runs;
     return launch_variant<true>(p, q.kpar, stream);
 }
 

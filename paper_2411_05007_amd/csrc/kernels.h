@@ -36,6 +36,9 @@ struct ActParams {
 
 // flags: bit 0 = quantize (codes + scales), bit 1 = down projection (H)
 hipError_t launch_act(const ActParams &p, int flags, hipStream_t stream);
+// the 8-bit format in one pass over X, for the sizes that act_w8_one_pass names (act_w8_kernel.hip)
+hipError_t launch_act_w8(const ActParams &p, int flags, hipStream_t stream);
+bool act_w8_one_pass(int M, int K, int rank);
 
 // W4A4 GEMM on the block-scaled matrix instruction: INT4 codes as 6-bit float operands, exact fp32 group sums,
 // scale tiles from an f16 MFMA, one FMA per partial sum (gemm_w4a4_kernel.hip; layouts in layout.h)
@@ -151,9 +154,6 @@ struct GemmW8Params {
     int32_t *partial;        // ksplit > 1: int32 [tile][split][128 * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per tile, zero when the kernel starts
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
-    const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
-    int runs;
-    float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
 hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream);
 hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &p, hipStream_t stream);      // small launches, as launch_gemm_fp4_kpar

@@ -357,7 +357,7 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
     }
     return pl;
 }
-// The same where the GEMM is one whose wavefronts share K (`kpar`, the variant; `i8`: the 8-bit format).  Such a GEMM can add the
+// The same where the GEMM is one whose wavefronts share K (`kpar`, the variant).  Such a GEMM can add the
 // runs' partial H itself when it loads them, which takes the meeting of a slice's runs - four round trips past the L2 - out of
 // the activation kernel; runs then cost next to nothing and are cut so that a wavefront walks three groups.  What they do
 // cost is that every tile reads its rows of all partial H: up to 64 MB of that per launch (measured: 50 MB gains 2-3 us,
@@ -365,16 +365,13 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
 //   K = N = 3072, rank 32: M = 512 20.6 -> 18.4 (4, 12), 18.6 (8, 16), 19.1 (8, 24); M = 1024 29.5 -> 27.4 (4, 12); M = 2048 43.5 -> 40.2 (4, 12)
 //   M = 64, K = 12288, N = 3072: 22.1 -> 20.0 (4, 12), 19.8 (8, 24); M = 512 41.7 -> 39.7 (4, 12), 37.6 (8, 24); M = 256, K = N = 1152 12.2 -> 10.3 (4, 12)
 //   rank 128, K = N = 3072: M = 64 17.8 -> 14.1 (4, 12), M = 512 26.3 -> 24.3;  M = 512, K = 12288: 48.4 -> 54.1 (201 MB: not taken)
-// INT8 needs the tokens' maxima first, a launch of its own where K is cut: a short K is walked whole instead (M = 256,
-// K = N = 1152 16.5 -> 12.7; at K = 3072 17.4 against 15.7 cut), and a long one gains nothing from the deposit (49.3 against 48.9).
-inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, int kpar, bool i8) {
+inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, int kpar) {
     const ActPlan old = plan_act(M, G, rank, act_override);
     if (act_override > 0 || kpar == kKparNone || rank <= 0 || rank > 128) return old;
     const long slices = (M + 15) / 16;
     ActPlan pl = old;
     pl.waves = G > 96 ? 8 : 4;
-    pl.gchunk = i8 && G <= 32 ? G : G > 96 ? 24 : G > 12 ? 12 : G;
-    if (i8 && (G > 96 || slices > 128)) return old;
+    pl.gchunk = G > 96 ? 24 : G > 12 ? 12 : G;
     pl.chunks = (G + pl.gchunk - 1) / pl.gchunk;
     pl.whole = 0; pl.chunks0 = 1; pl.gchunk0 = G;
     pl.deposit = pl.chunks > 1;
@@ -393,17 +390,17 @@ inline size_t act_arrival_words(const ActPlan &a, int Mpad) {
     return (a.whole > 0 && a.chunks0 > 1 ? (size_t)a.chunks0 * a.whole : 0) + (a.chunks > 1 ? (size_t)a.chunks * (Mpad / 16 - a.whole) : 0);
 }
 
-// Gives a workspace the plan of plan_act_small where what that plan parks (and `ahead` bytes in front of it) fits into what the
-// workspace holds from partial_off on: the launches it is made for leave the room of the GEMM's partial tiles unused, and
+// Gives a workspace the plan of plan_act_small where what that plan parks fits into what the workspace holds from
+// partial_off on: the launches it is made for leave the room of the GEMM's partial tiles unused, and
 // a workspace's size stays what callers may have kept from the plan above.
 template <typename W>
-inline bool act_use_small_plan(W &w, const ActPlan &a, int rank, size_t ahead) {
+inline bool act_use_small_plan(W &w, const ActPlan &a, int rank) {
     const bool parked = a.chunks > 1 && rank > 0;
     const size_t h = parked ? align256(act_parked_floats(a, w.Mpad, rank) * 4) : 0, words = parked ? align256(act_arrival_words(a, w.Mpad) * 8) : 0;
     if (a.chunks > 1 && !a.deposit) return false;
-    if (w.partial_off + ahead + h + words > w.total) return false;
+    if (w.partial_off + h + words > w.total) return false;
     w.act = a;
-    w.hpart_off = w.partial_off + ahead;
+    w.hpart_off = w.partial_off;
     w.aflags_off = w.hpart_off + h;
     return true;
 }
@@ -444,12 +441,6 @@ inline WorkspaceW8 workspace_layout_w8(int M, int K, int N, int rank, int ksplit
     const bool parked = w.act_cut && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
-    const ActPlan small = plan_act_small(M > 0 ? M : 1, N, K / kGroup, rank, act_override, plan_kpar_blocks(true, M > 0 ? M : 1, N, K / kGroup, ksplit_override), true);
-    const size_t pmax = small.chunks > 1 ? align256((size_t)small.chunks * w.Mpad * 4) : 0;
-    if (w.act_cut && act_use_small_plan(w, small, rank, pmax)) {
-        w.act_cut = small.chunks > 1;
-        w.pmax_off = w.partial_off;
-    }
     return w;
 }
 
@@ -473,7 +464,7 @@ inline WorkspaceFp4 workspace_layout_fp4(int M, int K, int N, int rank, int kspl
     const bool parked = ap.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(ap, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(ap, w.Mpad) * 8) : 0);
-    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override), false), rank, 0);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override)), rank);
     return w;
 }
 
@@ -501,7 +492,7 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     const bool parked = w.act.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
-    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_int4(M > 0 ? M : 1, N, G, ksplit_override), false), rank, 0);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_int4(M > 0 ? M : 1, N, G, ksplit_override)), rank);
     return w;
 }
 

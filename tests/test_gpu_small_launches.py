@@ -61,6 +61,7 @@ def test_w4a16_at_its_edges(torch, M, K, N, r):  # noqa: F811
     (1, 64, 16, 16, (32, 32)), (33, 128, 80, 16, (32, 32)), (31, 576, 1040, 144, (32, 32)), (64, 1088, 272, 0, (32, 32)),
     (290, 192, 2064, 32, (64, 64)), (257, 704, 3072, 144, (64, 64)), (320, 64, 2032, 16, (64, 64)),
     (610, 192, 2064, 48, (128, 64)), (577, 832, 2320, 32, (128, 64)), (129, 64, 6160, 16, (128, 64)),
+    (33, 3136, 80, 16, (32, 32)), (20, 6080, 144, 32, (32, 32)), (50, 2048, 272, 64, (32, 32)),      # groups off the wavefronts that hold K in registers
     (70, 2112, 208, 48, (32, 32)), (40, 2432, 144, 128, (32, 32)), (300, 3136, 2064, 32, (64, 64)),      # H added from runs
     (520, 8256, 1984, 32, (128, 128)), (1000, 192, 3088, 80, (128, 128)), (897, 320, 3056, 16, (128, 128))])
 @pytest.mark.parametrize("fmt", ["fp4", "w8a8"])
