@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "layout.h"
+
 namespace svdq {
 
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -92,6 +94,65 @@ __device__ __forceinline__ void w4_run48(const act_u32x6 &r, int j, uint32_t &lo
         lo = r[w];
         hi = r[w + 1] & 0xffffu;
     }
+}
+
+
+// Where the codes and scales of a wavefront's 16 tokens of one group meet in LDS, in the byte order of the activation block
+// (kActOutStage bytes in three runs: the two k-halves and the scales), and how they leave.  Lane 8 r8 + c8 holds channels
+// 8 c8 .. + 7 of tokens r8 and r8 + 8: half of one 16-channel triple (three registers of the GEMM's 6-bit operand form,
+// layout.h).  The even lane of a pair stores the triple's first two dwords, the odd lane the third, and then lane c8 = 1
+// the token's scale dword, the other odd lanes the third dword once more (same value to the same address).
+struct W4Stage {
+    int a, b, a2, b2, c8;
+    __device__ __forceinline__ W4Stage(int r8, int c8_) : c8(c8_) {
+        a = 384 * (c8 >> 2) + 24 * r8 + 12 * ((c8 & 3) >> 1) + ((c8 & 1) ? 8 : 0);
+        b = a + 24 * 8;
+        a2 = (c8 & 1) ? (c8 == 1 ? 768 + 4 * r8 : a) : a + 4;
+        b2 = (c8 & 1) ? (c8 == 1 ? 768 + 4 * (r8 + 8) : b) : b + 4;
+    }
+    // the 48 bits of codes and the scale of token r8 (alo, ahi, sa) and of token r8 + 8
+    __device__ __forceinline__ void put(unsigned char *stage, uint32_t alo, uint32_t ahi, uint32_t sa, uint32_t blo, uint32_t bhi, uint32_t sb) const {
+        // Two neighbouring lanes hold the 16 codes of one triple = 96 bits: dword 0 is the even lane's low word,
+        // dword 1 the even lane's high 16 bits and the odd lane's low 16, dword 2 the rest of the odd lane.
+        const uint32_t na = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)alo, 0xB1, 0xf, 0xf, true);      // the pair's other lane
+        const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)blo, 0xB1, 0xf, 0xf, true);
+        const bool odd = c8 & 1;
+        const uint32_t a1 = odd ? ((alo >> 16) | (ahi << 16)) : alo;                // first store: dword 2 (odd) or dword 0 (even)
+        const uint32_t b1 = odd ? ((blo >> 16) | (bhi << 16)) : blo;
+        *reinterpret_cast<uint32_t *>(stage + a) = a1;
+        *reinterpret_cast<uint32_t *>(stage + b) = b1;
+        *reinterpret_cast<uint32_t *>(stage + a2) = odd ? (c8 == 1 ? sa : a1) : (ahi | (na << 16));         // second: the scale, dword 2 again, or dword 1
+        *reinterpret_cast<uint32_t *>(stage + b2) = odd ? (c8 == 1 ? sb : b1) : (bhi | (nb << 16));
+    }
+};
+// where lane l's 16 bytes of such a stage belong in the group's activation blocks (lanes below kActOutStage / 16)
+__device__ __forceinline__ int w4_stage_out(int m0, int lane) {
+    const int half16 = (m0 >> 4) & 1;
+    return (m0 / 32) * kW4ABlock + (lane < 24 ? 384 * half16 + 16 * lane : lane < 48 ? 768 + 384 * half16 + 16 * (lane - 24) : kW4ACodes + 64 * half16 + 16 * (lane - 48));
+}
+
+// Eq. 1 for one MXFP4 block (the 32 channels held by 4 neighbouring lanes): the scale is the smallest power
+// of two s = 2^e >= 2^-126 with max|x| <= 6 s, found from the exponent and mantissa bits of the maximum
+// (max|x| = 1.m * 2^(E - 127) <= 1.5 * 2^(e + 2)  <=>  e = E - 129, one more if 1.m > 1.5), stored as the
+// byte e + 127 (0 for an all-zero block); the codes come from the hardware conversion, which divides by
+// the scale's power of two and rounds to the nearest E2M1 element, ties to even, saturating.
+__device__ __forceinline__ void fp4_encode(const float (&xh)[8], uint32_t &word, uint32_t &sbyte) {
+    float amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(xh[e]));
+    amax = max_over_4_lanes(amax);
+    const uint32_t bits = __float_as_uint(amax);
+    int byte = (int)(bits >> 23) - 2 + ((bits & 0x7fffffu) > 0x400000u ? 1 : 0);
+    byte = byte < 1 ? 1 : (byte > 254 ? 254 : byte);
+    const bool zero = !(amax > 0.f);
+    sbyte = zero ? 0u : (uint32_t)byte;
+    const float scale = __uint_as_float((zero ? 127u : (uint32_t)byte) << 23);
+    uint32_t w = 0u;
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[0], xh[1], scale, 0);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[2], xh[3], scale, 1);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[4], xh[5], scale, 2);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[6], xh[7], scale, 3);
+    word = w;
 }
 
 }  // namespace svdq

@@ -53,13 +53,6 @@ struct ActLds {
     static __host__ __device__ size_t wave_bytes() { return (size_t)WAVES * kWaveBytes; }
 };
 
-// Byte offsets inside one group's run of activation blocks (layout.h): the first dword a lane stores for token m
-// (dword 0 of its triple for an even c8, dword 2 for an odd one), and the token's scale dword.
-__device__ __forceinline__ int w4_triple_offset(int m, int c8) {
-    return (m / 32) * kW4ABlock + 24 * (32 * (c8 >> 2) + m % 32) + 12 * ((c8 & 3) >> 1) + ((c8 & 1) ? 8 : 0);
-}
-__device__ __forceinline__ int w4_scale_offset(int m) { return (m / 32) * kW4ABlock + kW4ACodes + 4 * (m % 32); }
-
 // Workgroups that must fit a CU together (this caps the registers): four of four wavefronts up to rank 64, fewer
 // where the rank's accumulators and fragments need the room.
 constexpr int act_min_workgroups(int rbmax, int waves, bool stage) {
@@ -126,27 +119,15 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
     const int vxa = (int)(((uint32_t)(ma < p.M ? ma : p.M - 1) * (uint32_t)p.K + 8u * (uint32_t)c8) * 2u);
     const int vxb = (int)(((uint32_t)(mb < p.M ? mb : p.M - 1) * (uint32_t)p.K + 8u * (uint32_t)c8) * 2u);
     // MXFP4: a lane's 8 channels are a quarter of block c8 / 4 of its token; its 8 codes are one dword
-    // INT4: the lane's 8 channels are half of one 16-channel triple (three registers of the GEMM's 6-bit operand form,
-    // layout.h) of operand lane 32 (c8 / 4) + m % 32; the even lane of a pair stores the triple's first two dwords,
-    // the odd lane the third, and lane c8 = 1 also the token's scale dword (w4_int4_offsets below)
     // INT8: the lane's 8 channels are half of a 16-byte operand chunk of v_mfma_i32_32x32x32_i8: 32-channel step c8 / 4 of
     // the group, lane half (c8 % 4) / 2, bytes 8 (c8 % 2) .. + 7 (layout.h, i8_code_offset)
     const int vca = FMT == 2 ? (int)i8_code_offset(8 * c8, p.Mpad, ma)
-                  : FMT == 1 ? (int)fp4_code_offset(0, p.Mpad, ma, c8 >> 2) + 4 * (c8 & 3) : w4_triple_offset(ma, c8);
+                  : (int)fp4_code_offset(0, p.Mpad, ma, c8 >> 2) + 4 * (c8 & 3);
     const int vcb = FMT == 2 ? (int)i8_code_offset(8 * c8, p.Mpad, mb)
-                  : FMT == 1 ? (int)fp4_code_offset(0, p.Mpad, mb, c8 >> 2) + 4 * (c8 & 3) : w4_triple_offset(mb, c8);
+                  : (int)fp4_code_offset(0, p.Mpad, mb, c8 >> 2) + 4 * (c8 & 3);
     const int vsx = FMT == 1 ? (int)fp4_scale_offset(0, p.Mpad, (c8 & 1) ? mb : ma, c8 >> 2) : 0;
-    // second INT4 store of a lane: the triple's second dword (even lanes), the token's scale (lane c8 = 1), or the
-    // third dword once more (the other odd lanes: same value to the same address)
-    // (INT4: these are offsets into the wavefront's staging block, tokens r8 and r8 + 8 of its 16; the second word of
-    // a lane is the triple's second dword (even lanes), the token's scale (lane c8 = 1), or the third dword once more)
-    const int lca = 384 * (c8 >> 2) + 24 * r8 + 12 * ((c8 & 3) >> 1) + ((c8 & 1) ? 8 : 0), lcb = lca + 24 * 8;
-    const int lca2 = (c8 & 1) ? (c8 == 1 ? 768 + 4 * r8 : lca) : lca + 4;
-    const int lcb2 = (c8 & 1) ? (c8 == 1 ? 768 + 4 * (r8 + 8) : lcb) : lcb + 4;
-    // where lane l's 16 bytes of the staging block belong in the activation block of the slice's 32 tokens
-    const int half16 = (m0 >> 4) & 1;
-    const int vout = (m0 / 32) * kW4ABlock + (lane < 24 ? 384 * half16 + 16 * lane
-                                                : lane < 48 ? 768 + 384 * half16 + 16 * (lane - 24) : kW4ACodes + 64 * half16 + 16 * (lane - 48));
+    const W4Stage w4(r8, c8);                  // the wavefront's staging block, and
+    const int vout = w4_stage_out(m0, lane);   // where lane l's 16 bytes of it belong
     struct XStage { uint4 x0, x1; };                   // 8 bf16 activations of token r8 and of token r8 + 8
     struct BStage { uint4 b[PROJ ? 2 * RBMAX : 1]; };  // L1s fragments: k steps 0 and 1 of every 16-column block
     // STAGE: the fragments of the next two groups wait in registers (at rank 128 this fills the register file
@@ -354,34 +335,11 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
         }
         return o;
     };
-    // Eq. 1 for one MXFP4 block (the 32 channels held by 4 neighbouring lanes): the scale is the smallest power
-    // of two s = 2^e >= 2^-126 with max|x| <= 6 s, found from the exponent and mantissa bits of the maximum
-    // (max|x| = 1.m * 2^(E - 127) <= 1.5 * 2^(e + 2)  <=>  e = E - 129, one more if 1.m > 1.5), stored as the
-    // byte e + 127 (0 for an all-zero block); the codes come from the hardware conversion, which divides by
-    // the scale's power of two and rounds to the nearest E2M1 element, ties to even, saturating.
-    auto encode_fp4 = [&](const float (&xh)[QUANT ? 8 : 1], uint32_t &word, uint32_t &sbyte) {
-        float amax = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(xh[e]));
-        amax = max_over_4_lanes(amax);
-        const uint32_t bits = __float_as_uint(amax);
-        int byte = (int)(bits >> 23) - 2 + ((bits & 0x7fffffu) > 0x400000u ? 1 : 0);
-        byte = byte < 1 ? 1 : (byte > 254 ? 254 : byte);
-        const bool zero = !(amax > 0.f);
-        sbyte = zero ? 0u : (uint32_t)byte;
-        const float scale = __uint_as_float((zero ? 127u : (uint32_t)byte) << 23);
-        uint32_t w = 0u;
-        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[0], xh[QUANT ? 1 : 0], scale, 0);
-        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[QUANT ? 2 : 0], xh[QUANT ? 3 : 0], scale, 1);
-        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[QUANT ? 4 : 0], xh[QUANT ? 5 : 0], scale, 2);
-        w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[QUANT ? 6 : 0], xh[QUANT ? 7 : 0], scale, 3);
-        word = w;
-    };
     auto quantize = [&](int g, const Smoothed &sm) {
-        if (QUANT && FMT == 1) {
+        if constexpr (QUANT && FMT == 1) {
             uint32_t wa, wb, ba, bb;
-            encode_fp4(sm.a, wa, ba);
-            encode_fp4(sm.b, wb, bb);
+            fp4_encode(sm.a, wa, ba);
+            fp4_encode(sm.b, wb, bb);
             // unconditional stores, as below; the four lanes of a block write the same scale byte (lanes with an
             // even c8 that of token r8, odd ones that of token r8 + 8)
             const int sc = g * p.Mpad * kFp4RowBytes;
@@ -409,24 +367,8 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
     // INT4: the codes of a lane's runs of 8 channels (two tokens of one group, or of two groups) come out of one pack
     // conversion (act_common.h); the words of a group then go through one of the wavefront's staging blocks and leave
     // with one 16-byte store per lane.
-    auto stage_w4 = [&](uint32_t alo, uint32_t ahi, uint32_t sa, uint32_t blo, uint32_t bhi, uint32_t sb, unsigned char *stage) {
-        // Two neighbouring lanes hold the 16 codes of one triple = 96 bits: dword 0 is the even lane's low word,
-        // dword 1 the even lane's high 16 bits and the odd lane's low 16, dword 2 the rest of the odd lane.
-        const uint32_t na = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)alo, 0xB1, 0xf, 0xf, true);      // the pair's other lane
-        const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)blo, 0xB1, 0xf, 0xf, true);
-        const bool odd = c8 & 1;
-        const uint32_t a1 = odd ? ((alo >> 16) | (ahi << 16)) : alo;                // first store: dword 2 (odd) or dword 0 (even)
-        const uint32_t b1 = odd ? ((blo >> 16) | (bhi << 16)) : blo;
-        const uint32_t a2 = odd ? (c8 == 1 ? sa : a1) : (ahi | (na << 16));         // second: the scale, dword 2 again, or dword 1
-        const uint32_t b2 = odd ? (c8 == 1 ? sb : b1) : (bhi | (nb << 16));
-        // The words meet in the wavefront's staging block (only this wavefront touches it: the LDS queue of a
-        // wavefront is in order) and leave as 832 contiguous bytes in three runs; rows past M land in the padding
-        // rows of the workspace (it is sized for Mpad rows).
-        *reinterpret_cast<uint32_t *>(stage + lca) = a1;
-        *reinterpret_cast<uint32_t *>(stage + lcb) = b1;
-        *reinterpret_cast<uint32_t *>(stage + lca2) = a2;
-        *reinterpret_cast<uint32_t *>(stage + lcb2) = b2;
-    };
+    // (only this wavefront touches its staging block: the LDS queue of a wavefront is in order; rows past M land in the
+    // padding rows of the workspace, which is sized for Mpad rows)
     // one group: tokens r8 and r8 + 8 are runs 0 and 1 of one conversion
     auto quantize_w4 = [&](const Smoothed &sm, unsigned char *stage) {
         if constexpr (QUANT && FMT == 0) {
@@ -436,7 +378,7 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
             const act_u32x6 r = w4_codes<2>(runs, rcp);
             w4_run48(r, 0, alo, ahi);
             w4_run48(r, 1, blo, bhi);
-            stage_w4(alo, ahi, sa, blo, bhi, sb, stage);
+            w4.put(stage, alo, ahi, sa, blo, bhi, sb);
         }
     };
     // two groups: four runs, one conversion
@@ -448,8 +390,8 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
             const act_u32x6 r = w4_codes<4>(runs, rcp);
 #pragma unroll
             for (int j = 0; j < 4; ++j) w4_run48(r, j, lo[j], hi[j]);
-            stage_w4(lo[0], hi[0], sc[0], lo[1], hi[1], sc[1], stage);
-            stage_w4(lo[2], hi[2], sc[2], lo[3], hi[3], sc[3], stage + kActOutStage);
+            w4.put(stage, lo[0], hi[0], sc[0], lo[1], hi[1], sc[1]);
+            w4.put(stage + kActOutStage, lo[2], hi[2], sc[2], lo[3], hi[3], sc[3]);
         }
     };
     auto store_w4 = [&](int g, const unsigned char *stage) {

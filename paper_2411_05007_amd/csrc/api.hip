@@ -142,8 +142,9 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
 
     hipError_t e;
     if (!unfused) {
+        const bool one_pass = !w.act.deposit && act_force == 0 && act_override() == 0 && svdq::act_one_pass(0, M, s.K, s.rank);
         a.deposit = w.act.deposit;
-        e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
+        e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
         if (e != hipSuccess) return hip_fail(e);
         if (void *ev = g_profile_event) {
             e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);
@@ -356,7 +357,8 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
     a.arrived = reinterpret_cast<unsigned long long *>(ws + w.aflags_off);
     a.deposit = w.act.deposit;
-    hipError_t e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
+    const bool one_pass = act_override() == 0 && !w.act.deposit && svdq::act_one_pass(1, M, s.K, s.rank);
+    hipError_t e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (void *ev = g_profile_event) {
         e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);
@@ -511,7 +513,7 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     const bool lowrank = s.rank > 0 && !(g_options & SVDQ_OPT_SKIP_LOWRANK);
 
     // one kernel: per-token maxima, smoothing + INT8 codes + the down projection H = X L1s, in one pass over X that a
-    // workgroup holds in registers (act_w8_one_pass) or in two walks over it;
+    // workgroup holds in registers (act_one_pass) or in two walks over it;
     // small launches with a longer K: the walking kernel twice over K cut into runs (the maxima of the runs, then everything else)
     svdq::ActParams a{};
     a.X = static_cast<const uint16_t *>(X);
@@ -527,7 +529,7 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     const int kpar = svdq::plan_kpar_blocks(true, M, s.N, s.K / svdq::kGroup, ksplit_override());
     a.n_zero = kpar ? 0 : w.n_counters;
     hipError_t e;
-    const bool one_pass = act_override() == 0 && svdq::act_w8_one_pass(M, s.K, s.rank);
+    const bool one_pass = act_override() == 0 && svdq::act_one_pass(2, M, s.K, s.rank);
     if (!one_pass && w.act_cut) {
         a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
         a.pmax = reinterpret_cast<float *>(ws + w.pmax_off);
@@ -538,7 +540,7 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
         if (e != hipSuccess) return hip_fail(e);
         a.maxmode = 2;
     }
-    e = one_pass ? svdq::launch_act_w8(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
+    e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (void *ev = g_profile_event) {
         e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);

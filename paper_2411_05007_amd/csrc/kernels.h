@@ -36,9 +36,9 @@ struct ActParams {
 
 // flags: bit 0 = quantize (codes + scales), bit 1 = down projection (H)
 hipError_t launch_act(const ActParams &p, int flags, hipStream_t stream);
-// the 8-bit format in one pass over X, for the sizes that act_w8_one_pass names (act_w8_kernel.hip)
-hipError_t launch_act_w8(const ActParams &p, int flags, hipStream_t stream);
-bool act_w8_one_pass(int M, int K, int rank);
+// the same in one pass over X, for the sizes that act_one_pass names (act_onepass_kernel.hip): K is not cut, H is made whole
+hipError_t launch_act_one_pass(const ActParams &p, int flags, hipStream_t stream);
+bool act_one_pass(int fmt, int M, int K, int rank);
 
 // W4A4 GEMM on the block-scaled matrix instruction: INT4 codes as 6-bit float operands, exact fp32 group sums,
 // scale tiles from an f16 MFMA, one FMA per partial sum (gemm_w4a4_kernel.hip; layouts in layout.h)

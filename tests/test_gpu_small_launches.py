@@ -77,6 +77,22 @@ def test_block_formats_on_smaller_tiles(torch, fmt, M, K, N, r, tile):  # noqa: 
     _block_format(torch, fmt, M, K, N, r, tile)
 
 
+# one activation workgroup per 16 tokens with K in its wavefronts' registers (64 to 256 slices): fewer groups than
+# wavefronts, group counts off sixteen in every variant, no projection, the last slice of a launch ragged
+@pytest.mark.parametrize("M,K,N,r", [(1009, 704, 272, 16), (1009, 1088, 9232, 32), (1500, 3136, 9232, 16), (2050, 6080, 272, 32), (4095, 128, 144, 0)])
+@pytest.mark.parametrize("fmt", ["int4", "fp4"])
+def test_activation_in_one_pass(torch, fmt, M, K, N, r):  # noqa: F811
+    if fmt == "fp4":
+        return _block_format(torch, fmt, M, K, N, r, None)
+    rng = np.random.default_rng(5500 + M + K + N)
+    prep = _layer(rng, K, N, r)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x[:, rng.choice(K, max(1, K // 100), replace=False)] *= 50
+    sample = np.unique(np.concatenate([np.arange(40), np.arange(M - 40, M), rng.integers(0, M, 60)]))
+    print(f"one pass: M={M} K={K} N={N} r={r}", flush=True)
+    _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"one pass {M}x{K}x{N}", window=False)
+
+
 def _block_format(torch, fmt, M, K, N, r, tile):  # noqa: F811
     from tests import test_gpu_fp4, test_gpu_w8a8
     rng = np.random.default_rng(5400 + M + K + N)
@@ -92,7 +108,7 @@ def _block_format(torch, fmt, M, K, N, r, tile):  # noqa: F811
     if fmt == "fp4":
         prep = S.svdq_fp4_pack(rinv, l1, l2, rng.integers(0, 16, size=(K, N)).astype(np.uint8), rng.integers(110, 118, size=(K // 32, N)).astype(np.uint8), bias)
         plan = S.svdq_debug_launch_plan(M, prep.shape)
-        assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // tile[0]) * -(-N // tile[1]), 1)
+        assert tile is None or (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // tile[0]) * -(-N // tile[1]), 1)
         test_gpu_fp4._run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"fp4 small {M}x{K}x{N}")
     else:
         prep = S.svdq_w8a8_pack(rinv, l1, l2, rng.integers(-127, 128, size=(K, N)).astype(np.int8), rng.uniform(5e-5, 4e-4, N).astype(np.float16), bias)
