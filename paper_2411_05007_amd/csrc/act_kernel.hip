@@ -100,8 +100,8 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
     // wavefront w owns a contiguous run of groups, walked in steps of two; from rank 33 on a run of odd length repeats its
     // last group once more (it recomputes and rewrites the same codes and is kept out of the projection), so
     // the loop body has no divergent or data-dependent control flow around its memory operations and the
-    // load/store counters can be waited on precisely.  (Up to rank 32 the second step of such a run is left out: no slower
-    // on long runs, 1 us faster on runs of three groups.)
+    // load/store counters can be waited on precisely.  (Up to rank 32 such a run ends with a step of its own behind the loop:
+    // 1 us faster on runs of three groups.)
     const int gbeg = nchunks > 1 ? chunk * gchunk : 0;                      // this workgroup's run of groups
     const int gend = nchunks > 1 && gbeg + gchunk < p.G ? gbeg + gchunk : p.G;
     const int per = (gend - gbeg + WAVES - 1) / WAVES;
@@ -455,14 +455,17 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
         __builtin_amdgcn_sched_barrier(0);
     };
     constexpr bool kPairStep = RBMAX > 2;
-    for (int ip = 0; ip < npairs; ++ip) {
-        const int g = g0 + 2 * ip;
-        if (kPairStep) {
+    if constexpr (kPairStep) {
+        for (int ip = 0; ip < npairs; ++ip) {
+            const int g = g0 + 2 * ip;
             step2(g, g + 1 < g1);
-        } else {
-            step1(g, true, xs0, bs0);
-            if (g + 1 < g1) step1(g + 1, true, xs1, bs1);
         }
+    } else {
+        for (int g = g0; g + 1 < g1; g += 2) {
+            step1(g, true, xs0, bs0);
+            step1(g + 1, true, xs1, bs1);
+        }
+        if (g0 < g1 && ((g1 - g0) & 1)) step1(g1 - 1, true, xs0, bs0);
     }
 
     // housekeeping for the kernel that follows on the stream: its tile arrival counters start at zero

@@ -43,7 +43,8 @@ struct KparParams {
 };
 
 // I8: INT8 (32 channels per step), else MXFP4 (64).  RB row blocks of 32, KS wavefronts that share K, DEPTH steps ahead.
-template <bool I8, int RB, int KS, int DEPTH>
+// RUNS (MXFP4): H comes as the partial sums of the activation kernel's runs (else ready-made).
+template <bool I8, int RB, int KS, int DEPTH, bool RUNS>
 __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_kernel(KparParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int CB = 2;
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
                 gemm_lowrank_multiply<RB, CB>(acc, o);
             }
         };
-        if (p.runs > 0) {
+        if constexpr (RUNS) {
             kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.Mpad, p.rank, gm0, tile_n == 0 ? p.H : nullptr, threadIdx.x);
             low_rank(lds);
         } else {
@@ -225,23 +226,30 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
             for (int c = 0; c < CB; ++c)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) f[r][c][v] = acc[r][c][v];
-        if (p.runs > 0) __syncthreads();      // nobody reads H any more
+        if constexpr (RUNS) __syncthreads();      // nobody reads H any more
         kpar_reduce_store<RB, CB, KS>(f, lds, p.Y, p.M, p.N, gm0, gn0, wave, lane);
     }
 }
 
-template <bool I8, int RB, int KS, int DEPTH>
-hipError_t launch_one(const KparParams &p, hipStream_t stream) {
+template <bool I8, int RB, int KS, int DEPTH, bool RUNS>
+hipError_t launch_tile(const KparParams &p, hipStream_t stream) {
     const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 63) / 64;
     // H, L2, the scales and the bias are read with plain loads: every tile must lie inside the padded rows and columns
     if (tiles_m * 32 * RB > p.Mpad || tiles_n * 64 > p.Npad) return hipErrorInvalidValue;
-    auto k = gemm_kpar_blocks_kernel<I8, RB, KS, DEPTH>;
+    auto k = gemm_kpar_blocks_kernel<I8, RB, KS, DEPTH, RUNS>;
     constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
-    if (p.runs > 0 && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
+    if (RUNS && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);
     return hipGetLastError();
+}
+
+template <bool I8, int RB, int KS, int DEPTH>
+hipError_t launch_one(const KparParams &p, hipStream_t stream) {
+    if constexpr (!I8)
+        if (p.runs > 0) return launch_tile<false, RB, KS, DEPTH, true>(p, stream);
+    return launch_tile<I8, RB, KS, DEPTH, false>(p, stream);
 }
 
 template <bool I8>

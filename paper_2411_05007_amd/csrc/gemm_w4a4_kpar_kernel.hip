@@ -35,8 +35,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr int kFmtE2M3 = 2;                 // operand format selector of the instruction
 constexpr int kScaleBytes = 0x8082;         // block scales 2^3 and 2^1, as in gemm_w4a4_kernel.hip
 
-// RB row blocks of 32, KS wavefronts that share K, DEPTH groups requested ahead
-template <int RB, int KS, int DEPTH>
+// RB row blocks of 32, KS wavefronts that share K, DEPTH groups requested ahead; RUNS: H comes as the partial sums of the
+// activation kernel's runs (else ready-made)
+template <int RB, int KS, int DEPTH, bool RUNS>
 __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kernel(GemmW4Params p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     constexpr int CB = 2;
@@ -122,7 +123,6 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kerne
 #pragma unroll
             for (int r = 0; r < RB; ++r) lr[r][c] = floatx16{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
         }
-        // H comes ready-made, or as the partial sums of the activation kernel's runs
         auto low_rank = [&](const unsigned char *hf) {
             for (int ks = wave; ks < p.rank / 16; ks += KS) {
                 GemmLowRankStep<RB, CB> o;
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kerne
                 gemm_lowrank_multiply<RB, CB>(lr, o);
             }
         };
-        if (p.runs > 0) {
+        if constexpr (RUNS) {
             kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.Mpad, p.rank, gm0, tile_n == 0 ? p.H : nullptr, threadIdx.x);
             low_rank(lds);
         } else {
@@ -213,22 +213,27 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kerne
             }
         }
     }
-    if (p.runs > 0) __syncthreads();      // nobody reads H any more
+    if constexpr (RUNS) __syncthreads();      // nobody reads H any more
     kpar_reduce_store<RB, CB, KS>(acc, lds, p.Y, p.M, p.N, gm0, gn0, wave, lane);
 }
 
-template <int RB, int KS, int DEPTH>
-hipError_t launch_kpar(const GemmW4Params &p, hipStream_t stream) {
+template <int RB, int KS, int DEPTH, bool RUNS>
+hipError_t launch_variant(const GemmW4Params &p, hipStream_t stream) {
     const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 63) / 64;
     // H, L2 and the bias are read with plain loads: every tile must lie inside the padded rows and columns
     if (tiles_m * 32 * RB > p.Mpad || tiles_n * 64 > p.Npad) return hipErrorInvalidValue;
-    auto k = gemm_w4a4_kpar_kernel<RB, KS, DEPTH>;
+    auto k = gemm_w4a4_kpar_kernel<RB, KS, DEPTH, RUNS>;
     constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
-    if (p.runs > 0 && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
+    if (RUNS && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);
     return hipGetLastError();
+}
+
+template <int RB, int KS, int DEPTH>
+hipError_t launch_kpar(const GemmW4Params &p, hipStream_t stream) {
+    return p.runs > 0 ? launch_variant<RB, KS, DEPTH, true>(p, stream) : launch_variant<RB, KS, DEPTH, false>(p, stream);
 }
 
 }  // namespace

@@ -337,6 +337,10 @@ hipError_t launch_mfma_shape(const W4A16Params &p, hipStream_t stream) {
     }
     // sixteen wavefronts where a long K meets few columns (K = 12288, N = 3072: 24.6 -> 21.7 us; at K = 3072 eight are as fast)
     if (cb == 1 && p.K >= 6144 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU) return launch_mfma<STACK, 1, RK, 16>(p, stream);
+    // and two column blocks up to rank 32, whose registers allow it (rank 32, K = N = 12288: 4 rows 30.7 -> 29.1 us, 16 rows 38.5 ->
+    // 35.4; K = 6144: 17.8 -> 17.6, 21.8 -> 20.6; rank 64 and three column blocks spill)
+    if constexpr (RK <= 2)
+        if (cb == 2 && p.K >= 6144 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU) return launch_mfma<STACK, 2, RK, 16>(p, stream);
     return cb == 1 ? launch_mfma<STACK, 1, RK, 8>(p, stream) : cb == 2 ? launch_mfma<STACK, 2, RK, 8>(p, stream) : launch_mfma<STACK, 3, RK, 8>(p, stream);
 }
 template <bool STACK>
