@@ -123,11 +123,12 @@ inline __host__ __device__ size_t fp4_scale_offset(int g, int rows_pad, int row,
 }
 inline __host__ __device__ size_t fp4_scale_bytes(int G, int rows_pad) { return (size_t)((G + 3) / 4) * rows_pad * 8; }
 
-// Launch plan of the MXFP4 GEMM (one tile shape, 128 x 256).  A launch with fewer workgroups than the chip has
+// Launch plan of the MXFP4 GEMM.  A launch with fewer workgroups than the chip has
 // places for (two per CU) splits a long K loop over up to four workgroups per tile, each a multiple of four steps
 // and at least 32 steps long (measured: at 48 steps per tile the parked partial tiles cost what the shorter loop
 // saves; at 192 steps four splits halve the time, eight are slower again); the partial tiles meet in the
-// workspace as in the INT4 kernel.
+// workspace as in the INT4 kernel.  Left to themselves such launches run the kernel whose wavefronts share K
+// (plan_kpar_blocks) and split nothing; the workspace keeps room for the split, which a caller can ask for.
 struct GemmPlanFp4 {
     int tile;        // 0: 128 x 256, 1: 192 x 192, 2: 192 x 128, 3: 128 x 128
     int tiles, ksplit;
