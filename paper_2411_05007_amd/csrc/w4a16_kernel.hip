@@ -26,6 +26,7 @@
 // N = 9216: 16 rows 44 -> 11.8; N = 3072: 1 row 11.5 -> 7.9.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "buffer.h"
 #include "kernels.h"
@@ -55,12 +56,14 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
     const int part = STACK ? l16 / kStackRows : 0;      // (operand row 15 carries nothing: part 3, dropped twice, never added)
     const uint32_t drop1 = part >= 1 ? 0xffff0000u : 0u, drop2 = part >= 2 ? 0xffff0000u : 0u;
     const int m_lane = m0 + (STACK ? l16 % kStackRows : l16), row = m_lane < p.M ? m_lane : p.M - 1;      // rows past M repeat the last row; never stored
-    // eight fp32 values of a row as the operand registers of the SETS MFMAs
-    auto split8 = [&](const float (&x)[8], u32x4 (&a)[SETS]) {
+    // eight fp32 values of a row as the operand registers of the SETS MFMAs; with `careful`, the parts below an infinite value's
+    // first are zero (without, they are Inf - Inf)
+    auto split8 = [&](const float (&x)[8], u32x4 (&a)[SETS], auto careful) {
         float t[8], u[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             t[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & (STACK ? drop1 : 0xffff0000u));
+            if (decltype(careful)::value && (!STACK || drop1 != 0u) && __builtin_isinf(x[e])) t[e] = 0.f;
             u[e] = t[e] - __uint_as_float(__float_as_uint(t[e]) & (STACK ? drop2 : 0xffff0000u));
         }
         auto top = [](float lo, float hi) { return (uint32_t)__builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302); };
@@ -143,7 +146,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
         u32x4 a[SETS];
         const float4 ha = low.h[0], hb = low.h[1];
         const float x[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
-        split8(x, a);
+        split8(x, a, std::true_type{});
         if (!live)
 #pragma unroll
             for (int st = 0; st < SETS; ++st) a[st] = u32x4{0u, 0u, 0u, 0u};
@@ -163,33 +166,29 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
     floatx4 hacc[RK > 0 ? RK : 1];
 #pragma unroll
     for (int c = 0; c < RK; ++c) hacc[RK > 0 ? c : 0] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int g = wave; g < G; g += WAVES) {
-        const Batch nxt = load(g + WAVES < G ? g + WAVES : g);      // past the end: this group again, loaded and ignored
-#pragma unroll
-        for (int i = 0; i < 2 * RK; ++i) hacc[RK > 0 ? i / 2 : 0] = mfma(cur.x[i % 2], cur.l[RK > 0 ? i : 0], hacc[RK > 0 ? i / 2 : 0]);
+    // one group: X^'s parts, then every column block
+    auto multiply = [&](const Batch &t, int g, auto careful) {
         u32x4 a[2][SETS];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const float4 *rp = reinterpret_cast<const float4 *>(lrinv + 64 * g + 16 * q4 + 8 * j);
             const float4 r0 = rp[0], r1 = rp[1];
-            {
-                const u32x4 w = cur.x[j];
-                const float x[8] = {__uint_as_float(w.x << 16) * r0.x, __uint_as_float(w.x & 0xffff0000u) * r0.y, __uint_as_float(w.y << 16) * r0.z, __uint_as_float(w.y & 0xffff0000u) * r0.w,
-                                    __uint_as_float(w.z << 16) * r1.x, __uint_as_float(w.z & 0xffff0000u) * r1.y, __uint_as_float(w.w << 16) * r1.z, __uint_as_float(w.w & 0xffff0000u) * r1.w};
-                split8(x, a[j]);
-            }
+            const u32x4 w = t.x[j];
+            const float x[8] = {__uint_as_float(w.x << 16) * r0.x, __uint_as_float(w.x & 0xffff0000u) * r0.y, __uint_as_float(w.y << 16) * r0.z, __uint_as_float(w.y & 0xffff0000u) * r0.w,
+                                __uint_as_float(w.z << 16) * r1.x, __uint_as_float(w.z & 0xffff0000u) * r1.y, __uint_as_float(w.w << 16) * r1.z, __uint_as_float(w.w & 0xffff0000u) * r1.w};
+            split8(x, a[j], careful);
         }
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-            const u32x4 q = cur.w[cb];
-            u32x6 t;
-            t[0] = q.x & ~kW4Z0;
-            t[1] = q.y & ~kW4Z1;
-            t[2] = (q.x & kW4Z0) | (q.y & kW4Z1);
-            t[3] = q.z & ~kW4Z0;
-            t[4] = q.w & ~kW4Z1;
-            t[5] = (q.z & kW4Z0) | (q.w & kW4Z1);
-            const u32x16 c = __builtin_bit_cast(u32x16, __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(t, 8.0f));
+            const u32x4 q = t.w[cb];
+            u32x6 d;
+            d[0] = q.x & ~kW4Z0;
+            d[1] = q.y & ~kW4Z1;
+            d[2] = (q.x & kW4Z0) | (q.y & kW4Z1);
+            d[3] = q.z & ~kW4Z0;
+            d[4] = q.w & ~kW4Z1;
+            d[5] = (q.z & kW4Z0) | (q.w & kW4Z1);
+            const u32x16 c = __builtin_bit_cast(u32x16, __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(d, 8.0f));
             u32x4 op[2][2];      // [k step][columns 0-15, 16-31]
 #pragma unroll
             for (int j = 0; j < 2; ++j)
@@ -201,7 +200,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
                 }
 #pragma unroll
             for (int cc = 0; cc < 2; ++cc) {
-                const float sc = (float)__builtin_bit_cast(_Float16, cur.s[cb][cc]);
+                const float sc = (float)__builtin_bit_cast(_Float16, t.s[cb][cc]);
                 floatx4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
@@ -211,17 +210,41 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
                 for (int v = 0; v < 4; ++v) acc[cb][cc][v] = __builtin_fmaf(sc, sum[v], acc[cb][cc][v]);
             }
         }
+    };
+    for (int g = wave; g < G; g += WAVES) {
+        const Batch nxt = load(g + WAVES < G ? g + WAVES : g);      // past the end: this group again, loaded and ignored
+#pragma unroll
+        for (int i = 0; i < 2 * RK; ++i) hacc[RK > 0 ? i / 2 : 0] = mfma(cur.x[i % 2], cur.l[RK > 0 ? i : 0], hacc[RK > 0 ? i / 2 : 0]);
+        multiply(cur, g, std::false_type{});
         cur = nxt;
     }
+    // An infinite X^ (an infinite input, or one that 1 / lambda carries past fp32) has made NaN of every sum of its row: such a
+    // wavefront walks its groups once more, with parts that keep the infinity to the products it belongs to.  A walk of its own,
+    // because the test in the loop costs registers (two column blocks, 16 wavefronts: spills) and up to 2 % of a forward; here
+    // K = 3072, N = 18432, rank 32 pays, with the low-rank steps' careful parts, 12.68 -> 12.77 us (1 row), 16.08 -> 16.25 (16).
+    floatx4 all = acc[0][0] + acc[0][1];
+#pragma unroll
+    for (int cb = 1; cb < CB; ++cb) all += acc[cb][0] + acc[cb][1];
+    const float any = (all[0] + all[1]) + (all[2] + all[3]);
+    if (__builtin_expect(__any(any != any), 0)) {
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) acc[cb][0] = acc[cb][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (RK == 0)
+            for (int s = wave; s < steps; s += WAVES) {
+                low = load_lowrank(s);
+                add_lowrank(s);
+            }
+        for (int g = wave; g < G; g += WAVES) multiply(load(g), g, std::true_type{});
+    }
+    // H: the wavefronts' shares meet in LDS behind 1 / lambda; the wavefront of a low-rank step adds up the 32 columns it
+    // needs, in wavefront order, as it reads its operand
+    constexpr int kHRow = 16 * (RK > 0 ? RK : 1) + 4;
+    float *hs = lrinv + p.K;      // [wave][16 rows][kHRow]
+#pragma unroll
+    for (int c = 0; c < RK; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) hs[(wave * 16 + 4 * q4 + v) * kHRow + 16 * c + l16] = hacc[RK > 0 ? c : 0][v];
     if (RK > 0) {
-        // H: the wavefronts' shares meet in LDS behind 1 / lambda; the wavefront of a low-rank step adds up the 32 columns it
-        // needs, in wavefront order, as it reads its operand
-        constexpr int kHRow = 16 * (RK > 0 ? RK : 1) + 4;
-        float *hs = lrinv + p.K;      // [wave][16 rows][kHRow]
-#pragma unroll
-        for (int c = 0; c < RK; ++c)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) hs[(wave * 16 + 4 * q4 + v) * kHRow + 16 * c + l16] = hacc[RK > 0 ? c : 0][v];
         __syncthreads();
         if (wave < steps) {      // (RK <= 4: at most two steps)
             const int j = 32 * wave + 8 * q4, jc = j < p.rank ? j : 0;

@@ -145,3 +145,48 @@ def test_graph_replay_matches_eager(torch):
         torch.cuda.synchronize()
         assert np.array_equal(replayed, S.bits_from_bf16_tensor(eager)), it
         _compare(replayed, O.forward_w4a16(xb, S.svdq_unpack(prep)), f"w4a16 replay {it}")
+
+
+@pytest.mark.parametrize("M,K,N,r", [(1, 320, 80, 0), (5, 1152, 272, 32), (4, 1152, 272, 128), (18, 1152, 272, 48), (70, 704, 144, 96),
+                                     (2, 6208, 80, 0), (19, 6208, 80, 32), (9, 6208, 8240, 32)])
+def test_infinite_activations_reach_only_the_outputs_they_meet(torch, M, K, N, r):
+    """An infinite X^ (an infinite input, or a finite one that 1 / lambda carries past fp32) gives a column the signed
+    infinity of its code, NaN where the code is zero or infinities of both signs meet - as in any fp32 sum of the products -
+    and touches no other row.  Every launch variant, H made in the loop and by a launch of its own."""
+    rng = np.random.default_rng(9000 + M + K + N)
+    prep = _random_packed_layer(rng, K, N, r)
+    U = S.svdq_unpack(prep)
+    rinv = U["rinv"].copy()
+    over = np.flatnonzero(rinv > 1.1)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    hit = {}
+    for m in range(0, M, 3):                       # every third row holds one or two such channels
+        ks = rng.choice(over, 1 + (m // 3) % 2, replace=False)
+        for i, k in enumerate(ks):
+            # with a 16-bit branch the input itself stays finite, so that H does
+            x[m, k] = (np.inf if r == 0 else 3.3e38) * (-1) ** i
+        hit[m] = ks
+    xb = O.bf16_round(x)
+    xf = O.bf16_to_f32(xb)
+    with np.errstate(over="ignore", invalid="ignore"):
+        dq = np.repeat(U["sw"].astype(np.float64), 64, axis=0) * U["qw"].astype(np.float64)
+        calm = xf.copy()
+        for m, ks in hit.items():
+            calm[m, ks] = 0.0
+        want = O.forward_w4a16(O.bf16_round(calm), U)["Y64"]
+        for m, ks in hit.items():
+            for k in ks:
+                xh = np.float32(xf[m, k] * rinv[k])
+                assert np.isinf(xh)
+                want[m] += np.float64(xh) * dq[k]
+    layer = S.DeviceLayer(prep)
+    y = torch.full((M, N), 0.5, dtype=torch.bfloat16, device="cuda:0")
+    _say(f"w4a16 infinities: M={M} K={K} N={N} r={r}")
+    layer.forward_w4a16(S.bf16_tensor_from_bits(xb), out=y)
+    torch.cuda.synchronize()
+    got = O.bf16_to_f32(S.bits_from_bf16_tensor(y)).astype(np.float64)
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want))
+    quiet = [m for m in range(M) if m not in hit]
+    if quiet:
+        assert np.all(np.abs(got[quiet] - want[quiet]) <= 2.0 ** -7 * np.abs(want[quiet]) + 1e-4 * np.max(np.abs(want[quiet])))
