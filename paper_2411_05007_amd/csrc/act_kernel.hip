@@ -27,6 +27,7 @@
 #include "buffer.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -606,21 +607,21 @@ hipError_t launch_rb(const ActParams &p, int flags, hipStream_t stream) {
     size_t lds = (q ? L::rinv_bytes(glds) : 0) + L::wave_bytes();
     if (lds < 16) lds = 16;
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    // the limit on dynamic LDS is raised once per instantiation, to all a CU has (the size of a launch varies with K and the rank)
+    // the limit on dynamic LDS is raised once per instantiation and device, to all a CU has (the size of a launch varies with K and the rank)
     if (q && pr) {
         auto k = act_kernel<RBMAX, WAVES, true, true, STAGE, FMT>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesPerCU);
-        if (attr != hipSuccess) return attr;
+        static LdsLimit limit;
+        if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), kLdsBytesPerCU); e != hipSuccess) return e;
         hipLaunchKernelGGL(k, grid, block, lds, stream, p);
     } else if (q) {
         auto k = act_kernel<1, WAVES, true, false, false, FMT>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesPerCU);
-        if (attr != hipSuccess) return attr;
+        static LdsLimit limit;
+        if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), kLdsBytesPerCU); e != hipSuccess) return e;
         hipLaunchKernelGGL(k, grid, block, lds, stream, p);
     } else if (pr) {
         auto k = act_kernel<RBMAX, WAVES, false, true, STAGE, 0>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesPerCU);
-        if (attr != hipSuccess) return attr;
+        static LdsLimit limit;
+        if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), kLdsBytesPerCU); e != hipSuccess) return e;
         hipLaunchKernelGGL(k, grid, block, lds, stream, p);
     }
     return hipGetLastError();

@@ -14,6 +14,7 @@
 #include "buffer.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -277,8 +278,8 @@ template <int FMT, int RB, int NG>
 hipError_t launch_one(const ActParams &p, hipStream_t stream) {
     auto k = act_onepass_kernel<FMT, RB, NG>;
     constexpr int bytes = OnePassLds<RB>::kBytes;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (attr != hipSuccess) return attr;
+    static LdsLimit limit;
+    if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), bytes); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3((unsigned)((p.M + 15) / 16)), dim3(kWaves * 64), bytes, stream, p);
     return hipGetLastError();
 }

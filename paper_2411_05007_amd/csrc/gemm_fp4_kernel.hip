@@ -27,6 +27,7 @@
 #include "gemm_common.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -299,8 +300,8 @@ hipError_t launch_fp4_tile(const GemmFp4Params &p, hipStream_t stream) {
     const dim3 grid(tiles_m * tiles_n * p.ksplit), block(256);
     auto k = gemm_fp4_kernel<RB, CB>;
     // the limit on dynamic LDS is raised once per instantiation, not per launch
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    static LdsLimit limit;
+    if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, grid, block, T::kLdsBytes, stream, p);
     return hipGetLastError();
 }

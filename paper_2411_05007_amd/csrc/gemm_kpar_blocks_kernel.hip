@@ -15,6 +15,7 @@
 #include "gemm_kpar.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -239,8 +240,8 @@ hipError_t launch_tile(const KparParams &p, hipStream_t stream) {
     auto k = gemm_kpar_blocks_kernel<I8, RB, KS, DEPTH, RUNS>;
     constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
     if (RUNS && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (attr != hipSuccess) return attr;
+    static LdsLimit limit;
+    if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), bytes); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);
     return hipGetLastError();
 }

@@ -36,6 +36,7 @@
 #include "gemm_common.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -588,20 +589,20 @@ hipError_t launch_w4_tile(const GemmW4Params &p, hipStream_t stream) {
     const int last_round = (tiles_m * tiles_n) % kGemmPlaces;
     if (!p.dbg && p.ksplit == 1 && tiles_m * tiles_n > kGemmPlaces && last_round >= 1 && last_round <= kGemmPlaces / 2) {
         auto k = gemm_w4a4_kernel<RB, 0, true>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLdsBytesPersistent);
-        if (attr != hipSuccess) return attr;
+        static LdsLimit limit;
+        if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytesPersistent); e != hipSuccess) return e;
         hipLaunchKernelGGL(k, dim3(kGemmPlaces), block, T::kLdsBytesPersistent, stream, p);
         return hipGetLastError();
     }
     if (p.dbg) {
         auto k = gemm_w4a4_kernel<RB, 1, false>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLdsBytes);
-        if (attr != hipSuccess) return attr;
+        static LdsLimit limit;
+        if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;
         hipLaunchKernelGGL(k, grid, block, T::kLdsBytes, stream, p);
     } else {
         auto k = gemm_w4a4_kernel<RB, 0, false>;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLdsBytes);
-        if (attr != hipSuccess) return attr;
+        static LdsLimit limit;
+        if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;
         hipLaunchKernelGGL(k, grid, block, T::kLdsBytes, stream, p);
     }
     return hipGetLastError();

@@ -31,6 +31,7 @@
 #include "buffer.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -336,8 +337,8 @@ __global__ __launch_bounds__(1024) void w4a16_proj_kernel(const uint16_t *X, con
 template <bool STACK, int CB, int RK, int WAVES>
 hipError_t launch_mfma(const W4A16Params &p, hipStream_t stream) {
     auto k = w4a16_mfma_kernel<STACK, CB, RK, WAVES>;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytesPerCU);
-    if (attr != hipSuccess) return attr;
+    static LdsLimit limit;
+    if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), kLdsBytesPerCU); e != hipSuccess) return e;
     const int rows = STACK ? kStackRows : 16;
     const int loop = mfma_loop_bytes(p.K, RK, WAVES), sums = mfma_sums_bytes(CB, WAVES), bytes = loop > sums ? loop : sums;
     if (bytes > kLdsBytesPerCU) return hipErrorInvalidValue;

@@ -17,6 +17,7 @@
 #include "gemm_common.h"
 #include "kernels.h"
 #include "layout.h"
+#include "lds_limit.h"
 
 namespace svdq {
 namespace {
@@ -289,8 +290,8 @@ static hipError_t launch_w8_tile(const GemmW8Params &p, hipStream_t stream) {
     if (tiles_m * T::kBM > p.Mpad || tiles_n * T::kBN > p.Npad) return hipErrorInvalidValue;
     auto k = gemm_w8a8_kernel<RB, CB>;
     // the limit on dynamic LDS is raised once per instantiation, not per launch
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, T::kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    static LdsLimit limit;
+    if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n * p.ksplit), dim3(256), T::kLdsBytes, stream, p);
     return hipGetLastError();
 }

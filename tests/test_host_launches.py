@@ -1,0 +1,68 @@
+"""What the forwards ask of the HIP runtime, recorded on the CPU (host_launch_recorder.cpp): the host half of every launch
+runs as it is, nothing reaches a GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2411_05007_amd import svdq as S
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+INT4, FP4, W8A8, W4A16 = 64, 32, 0, 16
+
+
+@pytest.fixture(scope="module")
+def record(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    if not os.path.exists(S.LIB_PATH):
+        import __graft_entry__ as g
+        g.build()
+    exe = str(tmp_path_factory.mktemp("rec") / "recorder")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-rdynamic", os.path.join(HERE, "host_launch_recorder.cpp"), "-o", exe, "-ldl"], check=True)
+
+    def run(calls):
+        """One list of records per call (device, format, M, K, N, rank[, options]); all calls in one process."""
+        text = "".join(" ".join(str(v) for v in (c if len(c) == 7 else (*c, 0))) + "\n" for c in calls)
+        r = subprocess.run([exe, S.LIB_PATH], input=text, capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stderr
+        out, cur = [], []
+        for line in r.stdout.splitlines():
+            w = line.split()
+            if w[0] == "status":
+                assert w[1] == "0", (calls[len(out)], w)
+                out.append(cur)
+                cur = []
+            else:
+                cur.append((w[0], int(w[1]), w[2], *(int(v) for v in w[3:])))
+        assert len(out) == len(calls)
+        return out
+    return run
+
+
+# one call for every kernel family: K-sharing and large tiles, one-pass and walking activation kernels, forced splits
+SHAPES = [(INT4, 256, 1152, 1152, 32), (INT4, 512, 12288, 3072, 128), (INT4, 4608, 3072, 12288, 32), (INT4, 4096, 4608, 1152, 32), (INT4, 512, 3072, 3072, 32, 3 << 8),
+          (FP4, 512, 3072, 3072, 32), (FP4, 4608, 3072, 12288, 32), (FP4, 1337, 3072, 9216, 32), (FP4, 100, 6144, 272, 32, 3 << 8),
+          (W8A8, 1337, 3072, 9216, 16), (W8A8, 512, 12288, 3072, 16), (W8A8, 4608, 12288, 3072, 16),
+          (W4A16, 1, 3072, 18432, 32), (W4A16, 16, 12288, 12288, 32), (W4A16, 16, 3072, 18432, 128), (W4A16, 70, 3072, 9216, 96)]
+
+
+def test_the_lds_limit_is_raised_on_every_device(record):
+    """A kernel that takes more than 64 KB of dynamic LDS needs the limit raised on the device it runs on: on the first
+    device's word alone, a second GPU of the same process would have to launch without."""
+    calls = [(dev, *s) for dev in (0, 1, 0, 5) for s in SHAPES]
+    raised = {}
+    big = set()
+    for call, rec in zip(calls, record(calls)):
+        assert any(r[0] == "launch" for r in rec), call
+        for r in rec:
+            if r[0] == "attr":
+                raised[r[1], r[2]] = max(raised.get((r[1], r[2]), 0), r[3])
+            else:
+                assert r[1] == call[0]
+                if r[6] > 65536:
+                    big.add(r[2])
+                    assert raised.get((r[1], r[2]), 0) >= r[6], (call, r)
+    assert len(big) >= 8      # (the shapes do reach such kernels)
