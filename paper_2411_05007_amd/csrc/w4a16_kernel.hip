@@ -359,12 +359,15 @@ hipError_t launch_mfma_shape(const W4A16Params &p, hipStream_t stream) {
         const double cost = (wgs > 512 && c < 3 ? wgs / 256.0 : (double)((wgs + 255) / 256)) * (1.2 + c);
         if (c == 1 || cost < best) { best = cost; cb = c; }
     }
-    // sixteen wavefronts where a long K meets few columns (K = 12288, N = 3072: 24.6 -> 21.7 us; at K = 3072 eight are as fast)
-    if (cb == 1 && p.K >= 6144 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU) return launch_mfma<STACK, 1, RK, 16>(p, stream);
-    // and two column blocks up to rank 32, whose registers allow it (rank 32, K = N = 12288: 4 rows 30.7 -> 29.1 us, 16 rows 38.5 ->
-    // 35.4; K = 6144: 17.8 -> 17.6, 21.8 -> 20.6; rank 64 and three column blocks spill)
+    // Sixteen wavefronts where a long K meets few columns (K = 12288, N = 3072: 24.6 -> 21.7 us; at K = 3072 eight are as fast),
+    // and on two column blocks up to rank 32, whose registers allow it (rank 32, K = N = 12288: 4 rows 30.7 -> 29.1 us, 16 rows
+    // 38.5 -> 35.4; K = 6144: 17.8 -> 17.6, 21.8 -> 20.6; rank 64 and three column blocks spill).  Only in one round: two workgroups of
+    // eight wavefronts share a CU, where the second one of sixteen waits (eight | sixteen, us: 64 rows, K = N = 8192 46.2 | 51.3; 40 rows,
+    // K = 6144, N = 10240 35.0 | 39.6; 4 rows, K = 6144, N = 30720 29.8 | 34.7; 16 rows, K = 12288, N = 30720 66.1 | 72.8)
+    const bool sixteen = p.K >= 6144 && (long)((blocks + cb - 1) / cb) * passes <= 256 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU;
+    if (sixteen && cb == 1) return launch_mfma<STACK, 1, RK, 16>(p, stream);
     if constexpr (RK <= 2)
-        if (cb == 2 && p.K >= 6144 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU) return launch_mfma<STACK, 2, RK, 16>(p, stream);
+        if (sixteen && cb == 2) return launch_mfma<STACK, 2, RK, 16>(p, stream);
     return cb == 1 ? launch_mfma<STACK, 1, RK, 8>(p, stream) : cb == 2 ? launch_mfma<STACK, 2, RK, 8>(p, stream) : launch_mfma<STACK, 3, RK, 8>(p, stream);
 }
 template <bool STACK>

@@ -45,6 +45,7 @@ def test_every_variant_at_its_edges(torch, M, K, N, r, rows):  # noqa: F811
 @pytest.mark.parametrize("M,K,N,r", [(5, 64, 16, 16), (6, 64, 48, 48), (17, 576, 1008, 64), (33, 1088, 9232, 32), (4, 704, 18448, 48),     # one, two, three column blocks
                                      (2, 6208, 80, 80), (19, 6144, 1040, 32), (3, 6208, 272, 0),                                        # sixteen wavefronts
                                      (5, 6208, 8240, 32), (9, 6208, 8240, 16),                                                         # sixteen wavefronts, two column blocks
+                                     (4500, 6208, 32, 32),                                                                             # the same K in more than one round: eight
                                      (16, 320, 400, 256), (70, 256, 144, 96),                                                            # H from a launch of its own
                                      (2, 32768, 16, 16), (7, 32768, 32, 32)])                                                            # 1 / lambda fills the LDS
 def test_w4a16_at_its_edges(torch, M, K, N, r):  # noqa: F811

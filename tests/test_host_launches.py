@@ -66,3 +66,15 @@ def test_the_lds_limit_is_raised_on_every_device(record):
                     big.add(r[2])
                     assert raised.get((r[1], r[2]), 0) >= r[6], (call, r)
     assert len(big) >= 8      # (the shapes do reach such kernels)
+
+
+def test_w4a16_takes_sixteen_wavefronts_only_in_one_round(record):
+    """A workgroup of sixteen wavefronts leaves no room for a second one on its CU, so a launch of more workgroups than CUs
+    runs them one after the other where two of eight wavefronts would overlap."""
+    #         M, K, N, rank, threads per workgroup: long K on one and two column blocks in one round, then beyond, then short K
+    shapes = [(16, 12288, 3072, 32, 1024), (16, 12288, 12288, 32, 1024), (4, 6144, 12288, 16, 1024), (32, 6144, 8192, 32, 1024),
+              (64, 8192, 8192, 32, 512), (40, 6144, 10240, 32, 512), (4, 6144, 30720, 32, 512), (4800, 6144, 32, 32, 512), (16, 3072, 12288, 32, 512)]
+    for (M, K, N, r, threads), rec in zip(shapes, record([(0, W4A16, *s[:4]) for s in shapes])):
+        launches = [x for x in rec if x[0] == "launch"]
+        assert len(launches) == 1 and launches[0][5] == threads, (M, K, N, r, launches)
+        assert threads == 512 or launches[0][3] * launches[0][4] <= 256, (M, K, N, r, launches)
