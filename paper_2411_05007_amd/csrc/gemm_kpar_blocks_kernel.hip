@@ -69,7 +69,7 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
     auto load = [&](Set &s, int i) {
         // past the end of the wavefront's steps: a lane offset beyond every buffer, which loads zeros and asks the memory for nothing
         const int past = i < n ? 0 : (int)0x80000000u;      // (every buffer is smaller than 2^31 bytes)
-        const int st = wave + KS * (i < n ? i : 0);
+        const int st = kpar_step(wave, KS, i, n);
         const int va = lane * 16 + past, vs = lane * 4 + past;
         const int oa = (st * p.Mpad + gm0) * kRowBytes, ob = (st * p.Npad + gn0) * kRowBytes;
 #pragma unroll

@@ -113,6 +113,15 @@ inline __host__ __device__ size_t i8_code_offset(int k, int rows_pad, int row) {
 //             four consecutive steps, picked by the instruction's byte selector
 // so one 32-row block of one step is one contiguous kilobyte of codes, loaded with one 16-byte load per lane.
 constexpr int kFp4Block = 32;
+// Loads of the MXFP4 and INT8 GEMMs that ask for nothing (a step past the wavefront's last, a place of the ring that a tile
+// has no block for) get their zeros from a lane offset of 2^31, beyond every buffer.  Their uniform offset stays inside the
+// buffer all the same: what a range check makes of one beyond it depends on whether it is part of the check.
+//   the step a wavefront's i-th load belongs to (wavefront w of KS has steps w, w + KS, ..., n of them):
+inline __host__ __device__ int kpar_step(int wave, int KS, int i, int n) { return i < n ? wave + KS * i : 0; }
+//   byte offset of ring place j in a step of its operand (activation blocks, weight blocks, none), for a tile at (gm0, gn0):
+inline __host__ __device__ int ring_offset(int j, int frags_a, int frags_b, int gm0, int gn0) {
+    return j < frags_a ? gm0 * 32 + j * 1024 : j < frags_a + frags_b ? gn0 * 32 + (j - frags_a) * 1024 : 0;
+}
 constexpr int kFp4RowBytes = 32;     // packed bytes of one row of one 64-channel step
 constexpr int kMaxKSplitFp4 = 8;
 inline __host__ __device__ size_t fp4_code_offset(int g, int rows_pad, int row, int kb) {

@@ -110,7 +110,7 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_w8a8_kernel(Ge
         d_lane[i] = j < kFragsA + T::kFragsB ? lane * 16 : (int)0x80000000u;      // no such block: beyond the buffer (smaller than 2^31 bytes)
         const bool is_a = j < kFragsA;
         rs_d[i] = is_a ? make_rsrc(p.xcodes, (size_t)p.K * p.Mpad) : make_rsrc(p.wcodes, (size_t)p.K * p.Npad);
-        d_base[i] = is_a ? gm0 * kI8RowBytes + j * 1024 : gn0 * kI8RowBytes + (j - kFragsA) * 1024;
+        d_base[i] = ring_offset(j, kFragsA, T::kFragsB, gm0, gn0);
         d_stride[i] = is_a ? a_stride : b_stride;
     }
     auto dma = [&](int g, int stage) {

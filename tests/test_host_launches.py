@@ -78,3 +78,51 @@ def test_w4a16_takes_sixteen_wavefronts_only_in_one_round(record):
         launches = [x for x in rec if x[0] == "launch"]
         assert len(launches) == 1 and launches[0][5] == threads, (M, K, N, r, launches)
         assert threads == 512 or launches[0][3] * launches[0][4] <= 256, (M, K, N, r, launches)
+
+
+OFFSETS = r"""
+#include <stdio.h>
+#include <initializer_list>
+#include "layout.h"
+using namespace svdq;
+int main() {
+    long checked = 0;
+    // K-sharing kernels: every wavefront's loads up to the ring's depth past its last step; a block is a kilobyte
+    for (int steps = 1; steps <= 40; ++steps)
+        for (int KS : {4, 8})
+            for (int wave = 0; wave < KS; ++wave) {
+                const int n = wave < steps ? (steps - wave + KS - 1) / KS : 0;
+                for (int i = 0; i <= n + 6; ++i) {
+                    const int st = kpar_step(wave, KS, i, n);
+                    if (st < 0 || st >= steps || (i < n && st != wave + KS * i)) return printf("step %d of %d\n", st, steps), 1;
+                    ++checked;
+                }
+            }
+    // ring kernels: the four tiles, the last tile of the padded rows and columns, every place of the ring, the last step
+    const int tiles[4][2] = {{4, 8}, {6, 6}, {6, 4}, {4, 4}};
+    for (auto &t : tiles)
+        for (int rows = 1; rows <= 9; ++rows)
+            for (int cols = 1; cols <= 9; ++cols) {
+                const int Mpad = rows * kRowPad, Npad = cols * kRowPad, steps = 3;
+                for (int gm0 = 0; gm0 + t[0] * 32 <= Mpad; gm0 += t[0] * 32)
+                    for (int gn0 = 0; gn0 + t[1] * 32 <= Npad; gn0 += t[1] * 32)
+                        for (int j = 0; j < (t[0] + t[1] + 3) / 4 * 4; ++j) {
+                            const long pad = j < t[0] ? Mpad : Npad, end = ring_offset(j, t[0], t[1], gm0, gn0) + (steps - 1) * pad * 32 + 1024;
+                            if (end > steps * pad * 32) return printf("tile %d x %d place %d: %ld\n", t[0], t[1], j, end), 1;
+                            ++checked;
+                        }
+            }
+    return printf("ok %ld\n", checked), 0;
+}
+"""
+
+
+def test_loads_that_ask_for_nothing_keep_their_offsets_inside_the_buffers(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "offsets.cpp", tmp_path / "offsets"
+    src.write_text(OFFSETS)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", os.path.join(os.path.dirname(HERE), "paper_2411_05007_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout
