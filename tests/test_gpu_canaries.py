@@ -52,7 +52,8 @@ def _check(torch, big_ws, ws_bytes, big_y, M, what):
 
 
 @pytest.mark.parametrize("M,K,N,r,opts", [(300, 1152, 656, 32, 0),                       # ragged in M and N
-                                          (77, 3072, 272, 48, 0),                        # split K loop, activation runs cut
+                                          (77, 3072, 272, 48, 0),                        # partial H of the activation runs left to the GEMM
+                                          (77, 3072, 272, 48, 4 << 8),                   # split K loop, activation runs cut
                                           (130, 1152, 144, 128, (3 << 8) | (4 << 12)),   # forced splits, uneven runs
                                           (1, 12288, 256, 16, 0)])
 def test_int4_forward_stays_inside_its_buffers(torch, M, K, N, r, opts):
@@ -81,25 +82,29 @@ def test_int4_forward_stays_inside_its_buffers(torch, M, K, N, r, opts):
     S.svdq_forward_options(0)
 
 
-@pytest.mark.parametrize("M,K,N,r", [(300, 1152, 656, 32), (77, 3072, 272, 48), (1, 12288, 256, 16)])
-def test_fp4_forward_stays_inside_its_buffers(torch, M, K, N, r):
+@pytest.mark.parametrize("M,K,N,r,opts", [(300, 1152, 656, 32, 0), (77, 3072, 272, 48, 0), (1, 12288, 256, 16, 0), (77, 6208, 272, 48, 3 << 8)])
+def test_fp4_forward_stays_inside_its_buffers(torch, M, K, N, r, opts):
     xb, w, ax, b = _layer_inputs(M, K, N, 7100 + M + N)
+    S.svdq_forward_options(opts)
     layer = S.DeviceLayer(S.svdq_fp4_prepare(w, ax, r, bias=b))
     n = layer.workspace(M).numel()
     big_ws, ws, big_y, y = _guarded(torch, layer, M, N, n)
     x = S.bf16_tensor_from_bits(xb)
     for _ in range(2):
         layer.forward(x, out=y, workspace=ws)
+    S.svdq_forward_options(0)
     _check(torch, big_ws, n, big_y, M, f"fp4 {M}x{K}x{N} r{r}")
 
 
-@pytest.mark.parametrize("M,K,N,r", [(300, 1152, 656, 16), (77, 3072, 272, 16), (1, 12288, 256, 16)])
-def test_w8a8_forward_stays_inside_its_buffers(torch, M, K, N, r):
+@pytest.mark.parametrize("M,K,N,r,opts", [(300, 1152, 656, 16, 0), (77, 3072, 272, 16, 0), (1, 12288, 256, 16, 0), (77, 6208, 272, 48, 3 << 8)])
+def test_w8a8_forward_stays_inside_its_buffers(torch, M, K, N, r, opts):
     xb, w, ax, b = _layer_inputs(M, K, N, 7200 + M + N)
+    S.svdq_forward_options(opts)
     layer = S.DeviceLayer(S.svdq_w8a8_prepare(w, ax, r, bias=b))
     n = layer.workspace(M).numel()
     big_ws, ws, big_y, y = _guarded(torch, layer, M, N, n)
     x = S.bf16_tensor_from_bits(xb)
     for _ in range(2):
         layer.forward(x, out=y, workspace=ws)
+    S.svdq_forward_options(0)
     _check(torch, big_ws, n, big_y, M, f"w8a8 {M}x{K}x{N} r{r}")

@@ -117,16 +117,28 @@ def test_activation_launch_with_whole_and_cut_slices(torch, M, K, N, r):
     _run_and_compare(torch, xb, prep, what=f"fp4 whole+cut {M}x{K}x{N} r{r}")
 
 
-@pytest.mark.parametrize("M,K,N,r", [(100, 6144, 272, 32), (70, 6208, 144, 16), (200, 12288, 400, 48), (130, 4160, 528, 0)])
-def test_small_launches_with_split_k_loop(torch, M, K, N, r):
-    """Few tiles and a long K: the K loop is split over several workgroups per tile (each a multiple of four steps),
-    which park fp32 partial tiles in the workspace; the last one to arrive adds them in split order.  Run twice on
-    the same workspace: the arrival counters must be left ready, and the result must not depend on arrival order.
-    (K = 6144: 3 splits of 32 steps; 6208: 97 steps as 36 + 36 + 25; 12288: 4 splits; 4160: 65 steps as 36 + 29.)"""
+@pytest.mark.parametrize("ksplit", ["asked for", "by shape"])
+@pytest.mark.parametrize("M,K,N,r,s", [(100, 6144, 272, 32, 3), (70, 6208, 144, 16, 3), (200, 12288, 400, 48, 4), (130, 4160, 528, 0, 2)])
+def test_small_launches_with_split_k_loop(torch, M, K, N, r, s, ksplit):
+    """Few tiles and a long K.  Asked for (option bits 8-11), the K loop is split over s workgroups per tile (each a multiple
+    of four steps), which park fp32 partial tiles in the workspace; the last one to arrive adds them in split order.
+    Run again on the same workspace: the arrival counters must be left ready, and the result must not depend on arrival order.
+    (K = 6144: 3 splits of 32 steps; 6208: 97 steps as 36 + 36 + 25; 12288: 4 splits; 4160: 65 steps as 36 + 29.)
+    By shape, such launches run the kernel whose wavefronts share K, and nothing is split."""
+    S.svdq_forward_options(s << S.OPT_KSPLIT_SHIFT if ksplit == "asked for" else 0)
+    try:
+        _split_k_loop(torch, M, K, N, r, s if ksplit == "asked for" else 1)
+    finally:
+        S.svdq_forward_options(0)
+
+
+def _split_k_loop(torch, M, K, N, r, s):
     rng = np.random.default_rng(2600 + M + K)
     xb, w, ax, b = _random_layer(rng, M, K, N)
     prep = S.svdq_fp4_prepare(w, ax, r, bias=b)
-    _say(f"fp4 split-K: M={M} K={K} N={N} r={r}")
+    plan = S.svdq_debug_launch_plan(M, prep.shape)
+    assert (plan["gemm_ksplit"], plan["gemm_split_tiles"]) == (s, plan["gemm_tiles"] if s > 1 else 0)
+    _say(f"fp4 split-K: M={M} K={K} N={N} r={r}, {s} splits")
     _run_and_compare(torch, xb, prep, what=f"fp4 split {M}x{K}x{N} r{r}")
     layer = S.DeviceLayer(prep)
     x = S.bf16_tensor_from_bits(xb)
@@ -207,12 +219,21 @@ def test_lora_appended_to_an_fp4_layer(torch):
     _run_and_compare(torch, xb, tuned, what="fp4 + lora")
 
 
-@pytest.mark.parametrize("M,K,N", [(200, 704, 528), (90, 6144, 272)])
-def test_forward_replayed_from_a_hip_graph(torch, M, K, N):
+@pytest.mark.parametrize("M,K,N,ksplit", [(200, 704, 528, 0), (90, 6144, 272, 0), (90, 6144, 272, 3), (400, 704, 9232, 0)])
+def test_forward_replayed_from_a_hip_graph(torch, M, K, N, ksplit):
     """Both kernels captured once and replayed with eager work and synchronisations in between: every replay
-    must reproduce the eager result bit for bit (the direct-to-LDS ring and the barriers hold no state across launches)."""
+    must reproduce the eager result bit for bit (the direct-to-LDS ring and the barriers hold no state across launches).
+    Small tiles, the K loop split on request (its arrival counters cleared and left ready by every replay), large tiles."""
+    S.svdq_forward_options(ksplit << S.OPT_KSPLIT_SHIFT)
+    try:
+        _replayed(torch, M, K, N)
+    finally:
+        S.svdq_forward_options(0)
+
+
+def _replayed(torch, M, K, N):
     rng = np.random.default_rng(2500)
-    xb, w, ax, b = _random_layer(rng, M, K, N)      # the second shape runs with the K loop split
+    xb, w, ax, b = _random_layer(rng, M, K, N)
     layer = S.DeviceLayer(S.svdq_fp4_prepare(w, ax, 32, bias=b))
     x = S.bf16_tensor_from_bits(xb)
     ws = layer.workspace(M)

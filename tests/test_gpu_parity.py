@@ -243,11 +243,21 @@ def test_large_launches_with_persistent_workgroups(torch, M, K, N, r):
     assert np.array_equal(S.bits_from_bf16_tensor(layer.forward(xt, workspace=ws)), y0)
 
 
-@pytest.mark.parametrize("M,K,N,r", [(100, 3072, 272, 32), (70, 3136, 144, 16), (200, 6144, 400, 48)])
-def test_small_launches_with_split_k_loop(torch, M, K, N, r):
-    """Few tiles and a long K: the library splits the K loop over several workgroups per tile, which park fp32
+@pytest.mark.parametrize("ksplit", ["asked for", "by shape"])
+@pytest.mark.parametrize("M,K,N,r,s", [(100, 3072, 272, 32, 4), (70, 3136, 144, 16, 4), (200, 6144, 400, 48, 8)])
+def test_small_launches_with_split_k_loop(torch, M, K, N, r, s, ksplit):
+    """Few tiles and a long K.  Asked for (option bits 8-11), the K loop is split over s workgroups per tile, which park fp32
     partial tiles in the workspace; the last one to arrive adds them in split order.  K = 3136 gives splits of
-    unequal length.  The result must match the oracle and must not depend on arrival order."""
+    unequal length.  By shape, such launches run the kernel whose wavefronts share K, and nothing is split.
+    The result must match the oracle and must not depend on arrival order."""
+    s = s if ksplit == "asked for" else 0
+    try:
+        _split_k_loop(torch, M, K, N, r, s)
+    finally:
+        S.svdq_forward_options(0)
+
+
+def _split_k_loop(torch, M, K, N, r, s):
     rng = np.random.default_rng(7000 + M + K + N)
     x = rng.standard_normal((M, K)).astype(np.float32)
     x[:, rng.choice(K, K // 100, replace=False)] *= 50
@@ -257,8 +267,11 @@ def test_small_launches_with_split_k_loop(torch, M, K, N, r):
     ax = np.abs(O.bf16_to_f32(xb)).max(axis=0)
     b = (rng.standard_normal(N) * 0.1).astype(np.float32)
     prep = S.svdq_prepare(w, ax, r, bias=b)
-    _say(f"split-K: M={M} K={K} N={N} r={r}")
-    _run_and_compare(torch, xb, prep, what=f"split-K {M}x{K}x{N} r{r}")
+    _say(f"split-K: M={M} K={K} N={N} r={r}, {s or 1} splits")
+    _run_and_compare(torch, xb, prep, what=f"split-K {M}x{K}x{N} r{r}", ksplit=s)
+    S.svdq_forward_options(s << S.OPT_KSPLIT_SHIFT)
+    plan = S.svdq_debug_launch_plan(M, prep.shape)
+    assert (plan["gemm_ksplit"], plan["gemm_split_tiles"]) == (s or 1, plan["gemm_tiles"] if s else 0)
     layer = S.DeviceLayer(prep)
     xt = S.bf16_tensor_from_bits(xb)
     ws = layer.workspace(M)
@@ -403,11 +416,18 @@ def test_deterministic_and_stream_ordered(torch):
         layer.forward(x, workspace=small)
 
 
-@pytest.mark.parametrize("M,K,N,r", [(300, 1152, 656, 32), (100, 3072, 272, 32)])
-def test_forward_replayed_from_a_hip_graph(torch, M, K, N, r):
+@pytest.mark.parametrize("M,K,N,r,ksplit", [(300, 1152, 656, 32, 0), (100, 3072, 272, 32, 0), (100, 3072, 272, 32, 4), (1100, 704, 9232, 32, 0)])
+def test_forward_replayed_from_a_hip_graph(torch, M, K, N, r, ksplit):
     """The forward only enqueues kernels, so a caller may capture it.  Every replay, with eager work and
-    synchronisations in between, must reproduce the eager result bit for bit; the second shape runs with the
-    K loop split, whose arrival counters have to be left ready by each replay."""
+    synchronisations in between, must reproduce the eager result bit for bit: small tiles, the K loop split on request
+    (its arrival counters have to be left ready by each replay), large tiles behind the one-pass activation kernel."""
+    try:
+        _replayed(torch, M, K, N, r, ksplit)
+    finally:
+        S.svdq_forward_options(0)
+
+
+def _replayed(torch, M, K, N, r, ksplit):
     rng = np.random.default_rng(99 + M)
     xb = O.bf16_round(rng.standard_normal((M, K)).astype(np.float32))
     qw = rng.integers(-7, 8, size=(K, N)).astype(np.int8)
@@ -415,7 +435,7 @@ def test_forward_replayed_from_a_hip_graph(torch, M, K, N, r):
     l1 = O.bf16_round((rng.standard_normal((K, r)) * 0.02).astype(np.float32))
     l2 = O.bf16_round((rng.standard_normal((r, N)) * 0.05).astype(np.float32))
     prep = S.svdq_pack(np.ones(K, np.float32), l1, l2, qw, sw, rng.standard_normal(N).astype(np.float32))
-    S.svdq_forward_options(0)
+    S.svdq_forward_options(ksplit << S.OPT_KSPLIT_SHIFT)
     layer = S.DeviceLayer(prep)
     x = S.bf16_tensor_from_bits(xb)
     ws = layer.workspace(M)

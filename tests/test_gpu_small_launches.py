@@ -115,3 +115,31 @@ def _block_format(torch, fmt, M, K, N, r, tile):  # noqa: F811
     else:
         prep = S.svdq_w8a8_pack(rinv, l1, l2, rng.integers(-127, 128, size=(K, N)).astype(np.int8), rng.uniform(5e-5, 4e-4, N).astype(np.float16), bias)
         test_gpu_w8a8._run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"w8a8 small {M}x{K}x{N}")
+
+
+@pytest.mark.parametrize("M,K,N,rows", [(64, 1088, 272, 32), (290, 704, 2064, 64), (577, 832, 2320, 64), (520, 8256, 1984, 128), (897, 320, 3056, 128)])
+def test_int4_group_sums_are_exact(torch, M, K, N, rows):  # noqa: F811
+    """Every integer group sum of the K-sharing INT4 kernel, bit for bit, through its output: column n has the scale 1 in
+    group n % G and 0 in the others, a token's scale is 1 (its largest value is 7), and twelve non-zero channels per
+    token and group keep a sum within 49 + 11 * 14 = 203, a whole number that bf16 holds."""
+    G = K // 64
+    rng = np.random.default_rng(5600 + M)
+    x = np.zeros((M, G, 64), np.int64)
+    at = np.argsort(rng.random((M, G, 64)), axis=2)[:, :, :12]
+    v = rng.integers(-2, 3, size=(M, G, 12))
+    v[:, :, 0] = rng.choice([-7, 7], (M, G))
+    np.put_along_axis(x, at, v, axis=2)
+    qw = rng.integers(-7, 8, size=(K, N)).astype(np.int8)
+    sw = (np.arange(G)[:, None] == np.arange(N)[None, :] % G).astype(np.float16)
+    prep = S.svdq_pack(np.ones(K, np.float32), np.zeros((K, 0), np.uint16), np.zeros((0, N), np.uint16), qw, sw, np.zeros(N, np.float32))
+    plan = S.svdq_debug_launch_plan(M, prep.shape)
+    assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // rows) * -(-N // 64), 1)
+    print(f"group sums: M={M} K={K} N={N}, {rows}-row tiles", flush=True)
+    layer = S.DeviceLayer(prep)
+    y = layer.forward(S.bf16_tensor_from_bits(O.bf16_round(x.reshape(M, K).astype(np.float32))))
+    torch.cuda.synchronize()
+    want = np.empty((M, N), np.int64)
+    for g in range(G):
+        want[:, g::G] = x[:, g] @ qw.reshape(G, 64, N)[g][:, g::G].astype(np.int64)
+    assert np.abs(want).max() > 100
+    assert np.array_equal(O.bf16_to_f32(S.bits_from_bf16_tensor(y)), want.astype(np.float32))

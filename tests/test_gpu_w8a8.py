@@ -102,10 +102,10 @@ def test_ragged_shapes(torch, M, K, N, r):
 
 @pytest.mark.parametrize("M,K,N,r", [(100, 6144, 272, 32), (70, 6208, 144, 16), (200, 12288, 400, 48), (130, 4160, 528, 0)])
 def test_small_launches_with_split_k_loop(torch, M, K, N, r):
-    """Few tiles and a long K: the K loop is split over several workgroups per tile (the MXFP4 GEMM's plan: multiples of
-    four steps of 64 channels; K = 6144: three splits, 6208: 36 + 36 + 25 steps, 12288: four, 4160: 36 + 29), which park
-    int32 partial tiles; the last to arrive adds the others' to its own.  Integer sums: the split result must equal the
-    unsplit one BIT FOR BIT; and twice on the same workspace (the arrival counters must be left ready)."""
+    """Few tiles and a long K.  By shape: the kernel whose wavefronts share K.  Asked for (option bits 8-11): the large-tile
+    kernel, its K loop whole or split over several workgroups per tile (multiples of four steps of 64 channels), which park
+    int32 partial tiles; the last to arrive adds the others' to its own.  Integer sums: all of them must be the same BIT FOR
+    BIT; and again on the same workspace (the arrival counters must be left ready)."""
     rng = np.random.default_rng(3600 + M + K)
     xb, w, ax, b = _random_layer(rng, M, K, N)
     prep = S.svdq_w8a8_prepare(w, ax, r, bias=b)
@@ -119,10 +119,11 @@ def test_small_launches_with_split_k_loop(torch, M, K, N, r):
     for _ in range(3):
         assert np.array_equal(S.bits_from_bf16_tensor(layer.forward(x, workspace=ws)), y0)
     try:
-        for ks in (1, 2, 5):
+        for ks in (1, 2, 3, 4, 5):
             S.svdq_forward_options(ks << S.OPT_KSPLIT_SHIFT)
             ws_k = layer.workspace(M)      # sized under the same option word
-            assert np.array_equal(S.bits_from_bf16_tensor(layer.forward(x, workspace=ws_k)), y0), f"forced split {ks}"
+            for _ in range(2):
+                assert np.array_equal(S.bits_from_bf16_tensor(layer.forward(x, workspace=ws_k)), y0), f"forced split {ks}"
     finally:
         S.svdq_forward_options(0)
 
@@ -174,7 +175,7 @@ def test_full_size_layers_on_sampled_rows(torch, name):
 
 
 def test_lora_and_graph_replay(torch):
-    """An adapter appended to a W8A8 layer (the 16-bit branch is format-independent), and the three kernels of the
+    """An adapter appended to a W8A8 layer (the 16-bit branch is format-independent), and the kernels of the
     forward captured in a HIP graph and replayed with eager work in between: bit-equal to the eager result."""
     rng = np.random.default_rng(3300)
     M, K, N, r = 150, 512, 400, 16

@@ -176,9 +176,9 @@ def test_shape_errors_and_workspace_size(lib):
     lib.svdq_forward_options(2 << 8)
     assert S.svdq_workspace_bytes(4608, sh) == 48 * (4608 // 32) * 1792 + 2 * 4 * 4608 * 32 + 192 * 4 + 2 * 192 * 128 * 256 * 4 + act_cut
     lib.svdq_forward_options(0)
-    # a one-token forward runs one row of 48 tiles of 128 x 256 with the K loop split four ways: one arrival counter
-    # per tile (padded to 256 bytes) and four fp32 partial tiles per tile come on top; and its activation kernel cuts K
-    # into six runs of eight groups, whose partial H (fp32, 256 padded rows) and 8-byte arrival words are parked too
+    # a one-token forward keeps room for one row of 48 tiles of 128 x 256 with the K loop split four ways: one arrival counter
+    # per tile (padded to 256 bytes) and four fp32 partial tiles per tile; and for an activation kernel that cuts K
+    # into six runs of eight groups and parks their partial H (fp32, 256 padded rows) and 8-byte arrival words
     act_parked = 6 * 256 * 32 * 4 + align256(16 * 6 * 8)
     assert S.svdq_workspace_bytes(1, sh) == 48 * 8 * 1792 + 2 * 4 * 256 * 32 + 256 + 4 * 48 * 128 * 256 * 4 + act_parked
     # the K split can be forced per thread through the option word (bits 8-11), which the size query follows
@@ -312,8 +312,8 @@ def test_fp4_prepare_matches_the_oracle_given_the_same_factors(lib):
         S.svdq_fp4_pack(U["rinv"], U["l1s"], U["l2"], U["qw"], bad, U["bias"])
     # workspace: codes G * Mpad * 32, scale dwords ceil(G/4) * Mpad * 8, H and its bf16 split (rank 0: one column each)
     assert S.svdq_workspace_bytes(300, prep.shape) == 4 * 512 * 32 + 1 * 512 * 8 + 2 * (512 * 1 * 4)
-    # a long K and few tiles: arrival counters (one per tile, padded to 256 bytes) and ksplit fp32 partial tiles of 128 x 256 per
-    # tile; and the activation kernel's parked partial H (K cut into 8 runs of 24 groups for these 32 slices) with its
+    # a long K and few tiles: room for arrival counters (one per tile, padded to 256 bytes) and four fp32 partial tiles of 128 x 256
+    # per tile; and the activation kernel's parked partial H (K cut into 8 runs of 24 groups for these 32 slices) with its
     # 8-byte arrival words
     long_k = S.make_shape(12288, 3072, 32, group=32)
     assert S.svdq_workspace_bytes(512, long_k) == (192 * 512 * 32 + 48 * 512 * 8 + 2 * (512 * 32 * 4) + 256 + 4 * 48 * 128 * 256 * 4
@@ -508,12 +508,15 @@ def test_launch_plans_keep_what_the_kernels_index_by(lib):
     cases = [(M, K, N, r, g) for M in Ms for K in Ks for (N, r) in ((3072, 32), (256, 128)) for g in (64, 32)]
     for _ in range(1500):
         cases.append((int(rng.integers(1, 20000)), 64 * int(rng.integers(1, 300)), 16 * int(rng.integers(1, 800)), 16 * int(rng.integers(0, 17)), int(rng.choice([64, 32]))))
-    seen_cut = seen_two = 0
-    for (M, K, N, r, g) in cases:
+    # and every third case once more with a K split asked for, which no launch chooses by itself
+    cases = [(*c, 0) for c in cases] + [(*c, (2 + i % 7) << 8) for i, c in enumerate(cases[::3])]
+    seen_cut = seen_two = seen_split = 0
+    for (M, K, N, r, g, opts) in cases:
         if r > min(K, N) or M * K >= 2 ** 31:
             continue
+        lib.svdq_forward_options(opts)
         p = S.svdq_debug_launch_plan(M, S.make_shape(K, N, r, group=g))
-        G, slices, what = K // 64, (M + 15) // 16, (M, K, N, r, g)
+        G, slices, what = K // 64, (M + 15) // 16, (M, K, N, r, g, opts)
         for runs, per in ((p["act_runs"], p["act_groups_per_run"]), (p["act_leading_runs"], p["act_leading_groups_per_run"])):
             assert 1 <= runs <= 64, what
             if runs > 1:
@@ -541,8 +544,11 @@ def test_launch_plans_keep_what_the_kernels_index_by(lib):
         if g == 32 and p["gemm_ksplit"] > 1:
             per = (per + 3) // 4 * 4
         assert (p["gemm_ksplit"] - 1) * per < G, what
+        assert p["gemm_ksplit"] == 1 or opts, what
+        seen_split += p["gemm_ksplit"] > 1
         assert p["gemm_workgroups"] == p["gemm_tiles"] - p["gemm_split_tiles"] + p["gemm_split_tiles"] * p["gemm_ksplit"], what
-    assert seen_cut > 50 and seen_two > 5
+    lib.svdq_forward_options(0)
+    assert seen_cut > 50 and seen_two > 5 and seen_split > 200
     # the metric shape: 256 slices whole, the last 32 in six runs of eight groups, four wavefronts; 1728 whole tiles
     p = S.svdq_debug_launch_plan(4608, S.make_shape(3072, 12288, 32))
     assert (p["act_leading_slices"], p["act_leading_runs"], p["act_runs"], p["act_groups_per_run"], p["act_waves"], p["act_workgroups"]) == (256, 1, 6, 8, 4, 448)

@@ -1,6 +1,6 @@
 """The allocation-free entry point (svdq_linear_forward_static: the workspace is a device array inside the library)
-against svdq_linear_forward, through the C ABI: two calls in a row, the second with a smaller input, on shapes with
-and without a split K loop, and the refusal of a batch that does not fit."""
+against svdq_linear_forward, through the C ABI: two calls in a row, the second with a smaller input, with and without a
+K loop split on request, and the refusal of a batch that does not fit."""
 import ctypes as C
 
 import numpy as np
@@ -38,11 +38,19 @@ def _x(M, K, seed):
     return O.bf16_round(x)
 
 
-@pytest.mark.parametrize("K,N,r,M1,M2", [(1152, 656, 32, 300, 77),       # no K split at either size
-                                         (3072, 272, 32, 200, 100),      # both sizes run with the K loop split (arrival counters in the array)
-                                         (3072, 12288, 32, 1500, 130)])  # the second call's split plan asks for more than the array: no split there
-def test_static_workspace_forward_matches_the_ordinary_one(torch, K, N, r, M1, M2):
-    S.svdq_forward_options(0)
+@pytest.mark.parametrize("K,N,r,M1,M2,opts", [(1152, 656, 32, 300, 77, 0), (3072, 272, 32, 200, 100, 0),      # no K split at either size
+                                              (3072, 272, 32, 200, 100, 4 << 8),      # both sizes run with the K loop split (arrival counters in the array)
+                                              (3072, 12288, 32, 1500, 130, 0),        # the second call's ordinary workspace is larger than the array
+                                              (3072, 12288, 32, 130, 100, 8 << 8)])   # the split asked for does not fit: no split there
+def test_static_workspace_forward_matches_the_ordinary_one(torch, K, N, r, M1, M2, opts):
+    S.svdq_forward_options(opts)
+    try:
+        _static_matches(torch, K, N, r, M1, M2)
+    finally:
+        S.svdq_forward_options(0)
+
+
+def _static_matches(torch, K, N, r, M1, M2):
     prep = _layer(K, N, r, 5 + K + N)
     layer = S.DeviceLayer(prep)
     for M in (M1, M2):                                               # two calls in a row on the same array, the second smaller
@@ -56,7 +64,7 @@ def test_static_workspace_forward_matches_the_ordinary_one(torch, K, N, r, M1, M
         fits = S.svdq_workspace_bytes(M, prep.shape) <= 64 << 20
         if fits:      # same plan, same kernels: the same bits
             assert torch.equal(got.view(torch.int16), want.view(torch.int16))
-        else:         # no K split on the static path: equal up to fp32 summation order, i.e. one bf16 rounding
+        else:         # no room for parked results on the static path: equal up to fp32 summation order, i.e. one bf16 rounding
             g = O.bf16_to_f32(S.bits_from_bf16_tensor(got)).astype(np.float64)
             w = O.bf16_to_f32(S.bits_from_bf16_tensor(want)).astype(np.float64)
             assert np.all(np.isfinite(g))
