@@ -257,7 +257,9 @@ template <bool I8>
 hipError_t launch_variant(const KparParams &p, int variant, hipStream_t stream) {
     switch (variant) {
         case kKpar1x8: return launch_one<I8, 1, 8, 6>(p, stream);
-        case kKpar2x8: return launch_one<I8, 2, 8, 4>(p, stream);
+        case kKpar2x8:      // (MXFP4 takes four wavefronts for 64-row tiles: plan_kpar_blocks)
+            if constexpr (I8) return launch_one<true, 2, 8, 4>(p, stream);
+            return hipErrorInvalidValue;
         case kKpar2x4: return launch_one<I8, 2, 4, 4>(p, stream);
         case kKpar4x8: return launch_one<I8, 4, 8, 2>(p, stream);
         case kKpar4x4: return launch_one<I8, 4, 4, 2>(p, stream);
