@@ -121,7 +121,7 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
 
     // small launches: the kernel whose wavefronts share K, unless the caller's options force a K split.  All others: tile
     // count and K split follow the plan the workspace was sized for
-    const int kpar = svdq::plan_kpar_int4(M, s.N, s.K / svdq::kGroup, ksplit_override());
+    const int kpar = svdq::plan_kpar_int4(M, s.N, s.K / svdq::kGroup, s.rank, ksplit_override());
     const svdq::GemmPlan plan = svdq::plan_gemm(M, s.N, s.K / svdq::kGroup, ksplit_force > 0 ? ksplit_force : ksplit_override());
 
     svdq::ActParams a{};
@@ -237,7 +237,7 @@ int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
         const svdq::GemmPlan pl = svdq::plan_gemm(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.tail; out[10] = pl.ksplit; out[11] = pl.tiles - pl.tail + pl.tail * pl.ksplit;
-        kpar = svdq::plan_kpar_int4(M, s->N, G, ksplit_override());
+        kpar = svdq::plan_kpar_int4(M, s->N, G, s->rank, ksplit_override());
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else {
         return SVDQ_EUNSUPPORTED;

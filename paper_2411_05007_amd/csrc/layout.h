@@ -219,13 +219,20 @@ enum KparVariant { kKparNone = 0, kKpar1x8, kKpar2x8, kKpar2x4, kKpar4x8, kKpar4
 //   M = 2048, K = N = 3072 (1536): 47.6; 2x4 42.9, 4x4 39.6.                            M = 1024, K = 3072, N = 9216 (2304): 59.1; 2x4 53.1, 4x4 52.7
 //   M = 4608, K = N = 3072 (3456): 69.5; 2x4 84.9, 4x4 77.0.                            M = 4096, K = 1152, N = 4608 (4608): 47.5; 2x4 55.8, 4x4 51.0
 inline int kpar_rows(int variant) { return variant == kKpar1x8 ? 32 : variant == kKpar2x8 || variant == kKpar2x4 ? 64 : 128; }
-inline int plan_kpar_int4(int M, int N, int G, int ksplit_override = 0) {
+inline int plan_kpar_int4(int M, int N, int G, int rank, int ksplit_override = 0) {
     if (ksplit_override > 0) return kKparNone;
     const long tn = (N + 63) / 64, t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
     if (t32 <= 256) return kKpar1x8;
     if (t64 <= 256) return kKpar2x8;
     if (t128 <= 256 && G >= 128) return kKpar4x8;
-    if (t64 > 2304) return kKparNone;
+    // Many tiles of few groups: a round's fixed parts are not earned back, and the 128 x 256 tiles, of which the launch has one or
+    // barely two per CU, are faster while the branch is narrow (a wide one makes their activation kernel dear).  Forwards of both
+    // kernels over 2300 shapes, us this kernel | 128 x 256 tiles: M = 1024, N = 9216, rank 32: K = 1152 37.6 | 31.2, K = 640 28.6 | 23.5;
+    // M = 2048, K = 1536, N = 4608 43.6 | 37.5; M = 1800, K = 1152, N = 4608 36.5 | 32.2; M = 900, K = 320, N = 9216 25.0 | 18.0.  The calls
+    // that the last two conditions move gain 13 % in the geometric mean.  Left here: launches that are not wide (M = 4096, K = 1536,
+    // N = 2064 36.5 | 40.0; M = N = 3000 37.7 | 42.0), wide branches (M = 1000, K = 1536, N = 9216, rank 128 50.0 | 56.7), and some that
+    // lose (M = 1800, K = 2048, N = 4608 49.3 | 43.4).
+    if (t64 > 2304 || (t64 > 2048 && G <= 24 && rank <= 32 && N >= 2 * M) || (t64 > 1280 && G <= 5 && rank <= 64)) return kKparNone;
     const long rest = t128 % 512;      // 128-row tiles where their last round of 512 places is at least half full
     return t128 > 256 && (rest == 0 || rest >= 256) ? kKpar4x4 : kKpar2x4;
 }
@@ -502,7 +509,7 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     const bool parked = w.act.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
-    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_int4(M > 0 ? M : 1, N, G, ksplit_override)), rank);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_int4(M > 0 ? M : 1, N, G, rank, ksplit_override)), rank);
     return w;
 }
 

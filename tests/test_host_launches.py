@@ -126,3 +126,17 @@ def test_loads_that_ask_for_nothing_keep_their_offsets_inside_the_buffers(tmp_pa
     subprocess.run([cxx, "-std=c++17", "-O1", "-I", os.path.join(os.path.dirname(HERE), "paper_2411_05007_amd", "csrc"), str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout
+
+
+def _gemm_grid(rec):
+    return [x for x in rec if x[0] == "launch"][-1][3]
+
+
+@pytest.mark.parametrize("M,K,N,r,tiles", [(1800, 1152, 4608, 16, 15 * 18), (2048, 1536, 4608, 32, 16 * 18), (900, 320, 9216, 16, 8 * 36), (700, 320, 9216, 32, 6 * 36),
+                                           (2048, 1600, 4608, 32, 32 * 72), (2048, 1536, 4608, 48, 32 * 72), (3000, 1536, 3072, 32, 47 * 48),      # more groups, a wider branch, square
+                                           (2048, 384, 3072, 32, 16 * 48), (512, 320, 9216, 32, 8 * 144), (512, 320, 6144, 32, 4 * 96)])          # fewer tiles
+def test_int4_few_groups_on_many_tiles_take_the_large_tiles(record, M, K, N, r, tiles):
+    """The K-sharing kernel pays its fixed parts once per round of 512 workgroups, which few groups do not earn back: wide
+    launches beyond four rounds up to 24 groups, any beyond two and a half up to five, take 128 x 256 tiles if the branch is
+    narrow."""
+    assert _gemm_grid(record([(0, INT4, M, K, N, r)])[0]) == tiles
