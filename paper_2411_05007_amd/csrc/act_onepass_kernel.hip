@@ -305,7 +305,9 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 
 // Which calls take this kernel.  us per forward, act_kernel.hip -> this one:
 // INT8: everything whose K fits the registers (six groups per wavefront up to rank 32, three up to rank 64), except short rows in
-// more than one round of workgroups (M = 4608, K = 1152, rank 64: 42.0 -> 42.8).  M = 1, K = 3072, N = 9216 15.7 -> 14.2; M = 300,
+// more than one round of workgroups (M = 4608, K = 1152, rank 64: 42.0 -> 42.8) and rows of at most eight groups, which leave half of
+// the wavefronts without one (1 to 4000 tokens: 1 to 13 % slower than the walking kernel at up to eight groups, 1 to 6 % faster from
+// nine on).  M = 1, K = 3072, N = 9216 15.7 -> 14.2; M = 300,
 // K = 3072, N = 2064 22.4 -> 17.9; M = 2048, K = N = 3072 40.4 -> 34.6; M = 4608, K = N = 3072 69.7 -> 64.1.
 // INT4 and MXFP4, whose groups do not wait for each other: one round of workgroups that fills a quarter of the CUs at
 // least; fewer slices do better with K cut into runs, a second round undoes the gain.  INT4: M = 1337, K = 3072, N = 9216
@@ -314,7 +316,7 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 bool act_one_pass(int fmt, int M, int K, int rank) {
     const int G = K / kGroup, slices = (M + 15) / 16;
     if (fmt != 2) return slices >= 64 && slices <= 256 && G <= 6 * kWaves && rank <= 32;
-    if (slices > 256 && G <= 24) return false;
+    if (G <= 8 || (slices > 256 && G <= 24)) return false;
     return (G <= 3 * kWaves && rank <= 64) || (G <= 6 * kWaves && rank <= 32);
 }
 

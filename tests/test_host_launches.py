@@ -140,3 +140,9 @@ def test_int4_few_groups_on_many_tiles_take_the_large_tiles(record, M, K, N, r, 
     launches beyond four rounds up to 24 groups, any beyond two and a half up to five, take 128 x 256 tiles if the branch is
     narrow."""
     assert _gemm_grid(record([(0, INT4, M, K, N, r)])[0]) == tiles
+
+
+@pytest.mark.parametrize("M,K,N,r,threads", [(900, 192, 4608, 64, 256), (256, 512, 12288, 16, 256), (2300, 320, 4608, 0, 256), (900, 576, 4608, 64, 1024), (16, 3072, 3072, 16, 1024)])
+def test_w8a8_short_rows_take_the_walking_activation_kernel(record, M, K, N, r, threads):
+    """The one-pass activation kernel deals a token's groups to sixteen wavefronts: at most eight groups leave half of them idle."""
+    assert [x for x in record([(0, W8A8, M, K, N, r)])[0] if x[0] == "launch"][0][5] == threads
