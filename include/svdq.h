@@ -193,9 +193,11 @@ int svdq_linear_forward(const svdq_layer_dev *layer, const void *X, int M, void 
  * SVDQ_STATIC_SCRATCH_BYTES bytes inside the library (every GPU the library runs on holds its copy until the process
  * ends); the call allocates and frees nothing.  Same arithmetic, kernels, arguments and errors as
  * svdq_linear_forward, except:
- *   - a forward whose workspace (svdq_workspace_bytes) exceeds the array runs without the K split of small launches
- *     (no fp32 partial tiles: same result up to fp32 summation order); if even that does not fit - the activation
- *     blocks of M tokens alone are about 0.6 * M * K bytes - the call returns SVDQ_ENOSPACE and launches nothing;
+ *   - a forward whose workspace (svdq_workspace_bytes) exceeds the array runs without room for the partial tiles of a
+ *     split K loop: no split that the options ask for, and the partial sums of the down projection meet in the
+ *     activation kernel instead of the GEMM; if even that does not fit, without parked sums either (same results up to
+ *     fp32 summation order); if the activation blocks of M tokens alone - about 0.9 * M * K bytes, M padded to 256 - do
+ *     not fit, the call returns SVDQ_ENOSPACE and launches nothing;
  *   - all calls on one GPU share that GPU's array: two calls that overlap in time on one GPU (different streams or
  *     threads) race; calls on one stream are ordered like any other work;
  *   - svdq_debug_act / svdq_debug_group_acc do not see this workspace.
@@ -229,7 +231,8 @@ int svdq_debug_group_acc(const svdq_layer_dev *layer, const void *workspace, int
  *   [6] workgroups of the activation kernel, [7] its LDS bytes per workgroup,
  *   [8] output tiles of the GEMM, [9] how many of them have their K loop split, [10] into how many workgroups,
  *   [11] workgroups of the GEMM,
- *   [12] bytes / 256 of the workspace behind the GEMM's partial tiles (parked partial H and arrival words),
+ *   [12] bytes / 256 of the workspace from the parked partial H on (which lies in the place of the partial tiles of a split
+ *        where the GEMM adds it),
  *   [13] bytes / 256 (rounded up) of the parked partial H, [14] arrival words, [15] bytes / 256 of the whole workspace.
  * SVDQ_EINVAL for a null pointer or M <= 0, SVDQ_EUNSUPPORTED for a shape the forwards refuse outright.
  */

@@ -66,7 +66,7 @@ constexpr int act_min_workgroups(int rbmax, int waves, bool stage) {
 // FMT 2: INT8 codes with one fp16 scale per token (the 8-bit setting of App. "Implementation Details": per-token dynamic
 // activation quantization).  A token's scale needs its maximum over all of K before the first code can be written, so
 // that format walks its groups twice: once for the maxima (exchanged between the wavefronts through LDS), then the
-// ordinary loop, whose loads find the slice in the L2.  It does not take a cut K (chunks <= 1).
+// ordinary loop, whose loads find the slice in the L2.  With a cut K the two walks are two launches (ActParams::maxmode).
 template <int RBMAX, int WAVES, bool QUANT, bool PROJ, bool STAGE, int FMT>
 __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)) void act_kernel(ActParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char act_lds[];

@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
     const __amdgpu_buffer_rsrc_t rs_l = make_rsrc(p.l1s, (size_t)p.K * p.rank * 2);
     const __amdgpu_buffer_rsrc_t rs_c = make_rsrc(p.codes, FMT == 2 ? (size_t)p.K * p.Mpad : FMT == 1 ? (size_t)p.G * p.Mpad * kFp4RowBytes : w4_a_bytes(p.G, p.Mpad));
     const __amdgpu_buffer_rsrc_t rs_s = make_rsrc(p.sx, FMT == 1 ? fp4_scale_bytes(p.G, p.Mpad) : 0);
-    // (byte offsets below 2^32: the entry point refuses batches of 2^30 elements or more; unsigned on purpose)
+    // (byte offsets below 2^32: the entry point refuses batches of 2^31 elements or more; unsigned on purpose)
     const int vxa = (int)(((uint32_t)(ma < p.M ? ma : p.M - 1) * (uint32_t)p.K + 8u * (uint32_t)c8) * 2u);
     const int vxb = (int)(((uint32_t)(mb < p.M ? mb : p.M - 1) * (uint32_t)p.K + 8u * (uint32_t)c8) * 2u);
     const int vca = FMT == 2 ? (int)i8_code_offset(8 * c8, p.Mpad, ma) : (int)fp4_code_offset(0, p.Mpad, ma, c8 >> 2) + 4 * (c8 & 3);

@@ -4,9 +4,9 @@
 // wavefront w taking steps w, w + KS, ...  Both formats store a 32-row block of one step (64 channels of MXFP4, 32 of
 // INT8) as one contiguous kilobyte in operand order, so a step is RB + 2 loads of 16 bytes per lane straight into the
 // registers that the 2 RB MFMAs read, DEPTH steps ahead; nobody waits for anybody in the loop, and the partial tiles meet
-// once, in LDS.  Bound: one image row by the weights' way from memory (M = 16, K = N = 12288: 75 MB of MXFP4 codes in 16 us),
-// larger launches by the CUs' load units.  us of the GEMM alone, before -> after, MXFP4: M = 512, K = N = 3072 18.8 -> 11.0;
-// the rule that picks a variant, with more shapes: layout.h, plan_kpar_blocks.
+// once, in LDS.  Bound: one image row by the weights' way from memory (M = 16, K = N = 12288: 75 MB of MXFP4 codes in a forward
+// of 24 us), larger launches by the operands' way from the L2.  us of the GEMM in a kernel trace, before -> after, MXFP4:
+// M = 512, K = N = 3072 18.7 -> 12.6; the rule that picks a variant, with more shapes: layout.h, plan_kpar_blocks.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

@@ -3,16 +3,15 @@
 // Eq. 5), another division of the work.
 //
 // Such a launch is bound by one tile's chain of K steps - the 128 x 256 tiles of gemm_w4a4_kernel.hip leave most CUs
-// idle, walk K behind a barrier per group, and a K loop split over workgroups parks its partial tiles past the L2 (at
-// M = 512, K = 3072, N = 9216: 16 of 33 us in the loop, 10 in parking and adding).  Here a workgroup owns a small
+// idle, walk K behind a barrier per group, and a K loop split over workgroups parks its partial tiles past the L2.  Here a workgroup owns a small
 // tile, (32 RB) x 64, and its four or eight wavefronts share the tile's K, each taking every KS-th group: operands go
 // from the L2 straight into the registers the MFMAs read (one weight block and RB activation blocks per group and
 // wavefront, requested one or two groups ahead, each as soon as its registers are free), nobody waits for anybody in
 // the loop, and the partial tiles meet once, in LDS.  Bound: a lone launch by its fixed parts (start, first
-// operands, low-rank product, the meeting: 5 to 6 us together), larger ones by what the CUs' load units deliver (17 of
-// 24 TB/s measured for this mix of requests).  us of the GEMM alone, before -> after: M = 256, K = N = 1152 20.6 -> 4.5;
-// M = 300, K = 3072, N = 2064 26.7 -> 7; M = 512, K = N = 3072 25 -> 11.4; M = 512, K = 3072, N = 9216 32.9 -> 26;
-// M = 512, K = 12288, N = 3072 48 -> 26; M = 4096, K = 4608, N = 1152 44.5 -> 34.  The variants' limits: layout.h, plan_kpar_int4.
+// operands, low-rank product, the meeting: 5 to 6 us together), larger ones by the operands' way from the L2 (by counters 375
+// MB at M = 512, K = 3072, N = 9216, 13 TB/s; 511 MB at M = 4096, K = 4608, N = 1152, 15 TB/s).  us of the GEMM in a kernel trace,
+// before -> after: M = 256, K = N = 1152 20.5 -> 5.8; M = 300, K = 3072, N = 2064 26.4 -> 8.6; M = 512, K = 3072, N = 9216 31.7 -> 28.3;
+// M = 512, K = 12288, N = 3072 45.0 -> 27.1; M = 4096, K = 4608, N = 1152 41.1 -> 34.8.  The variants' limits: layout.h, plan_kpar_int4.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>

@@ -67,7 +67,7 @@ inline __host__ __device__ size_t l1s_index(int K, int rank, int k, int j) {
 //       bytes 1536 + 4 (m % 32) = the row's fp16 group scale in the low half of a dword whose high half is zero;
 //       the last 128 bytes are padding that is never read (a block is seven times 256 bytes so that one LDS
 //       address register reaches the scales of every block).  The activation kernel writes this form directly.
-//   weight blocks (prepared layer) wb[g][n / 64][2176 bytes], one block per 64 columns (what one wavefront of the
+//   weight blocks (prepared layer) wb[g][n / 64][2304 bytes], one block per 64 columns (what one wavefront of the
 //       GEMM multiplies): bytes 1024 (n % 64 / 32) + 16 l .. + 15 = lane l's 32 codes at FOUR bits each, bytes
 //       2048 + 4 (n % 64) = the column's fp16 group scale, again as the low half of a dword.  A scale dword read into
 //       both registers of an f16 MFMA operand makes that operand without a vector instruction.
@@ -170,13 +170,18 @@ inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, i
     // What a launch takes follows the CU with the most tiles: tiles per CU times MFMAs per step of a tile, weighted with what the
     // tile loads per MFMA, and a fifth more where no CU has a second tile to fill the first one's waits.  192 x 128 (six
     // MFMAs) and 128 x 128 (four) are taken where that comes out 5 % below the 128 x 256 tile (eight).
-    // us per forward, 128 x 256 | 192 x 128 | 128 x 128, the rule's choice in brackets; MXFP4 rank 32, INT8 rank 16:
+    // us per forward, 128 x 256 | 192 x 128 | 128 x 128, the rule's choice in brackets, its losses below the line; MXFP4 rank 32, INT8 rank 16:
     //   M = 1337, K = 3072, N = 9216 (396 | 504 | 792 tiles)   43.2 [40.4] 47.4     70.4 [59.2] 65.9
     //   M = 2048, K = N = 3072 (192 | - | 384)                 31.8   -   [29.0]    44.4   -   [41.5]
     //   M = 4096, K = 4608, N = 1152 (160 | - | 288)           46.0   -   [38.2]    61.0   -   [53.6]
     //   M = 1800, K = 3072, N = 12288 (720 | 960 | 1440)       60.7  61.8 [59.2]    [89.8] 94.0  90.8
     //   M = 4608, K = N = 3072 (432 | 576 | 864)               [43.8] 51.3  49.9    [71.0] 82.3  74.4
     //   M = 3000, K = 3072, N = 9216 (864 | 1152 | 1728)       [70.5] 74.9  71.7    [110] 115  107
+    //   ------
+    //   M = 4608, K = 3072, N = 9216 (1296 | 1728 | 2592)      96.9 [95.7] 99.6     157.6 [152.4] 156.0 (192 x 192, 1152 tiles: 92.4, 147.9)
+    //   M = 900, K = 3072, N = 4608 (144 | 180 | 288)          29.3 [27.2] 25.4     40.2 [39.0] 35.9
+    //   M = 2304, K = 3072, N = 9216 (648 | 864 | 1296)        [59.1] 56.3  58.2    [87.1] 86.7  87.5
+    // The 192 x 192 tile has its own condition above and no place in this comparison.
     if (pl.ksplit == 1 && pl.tile == 0) {
         auto cost = [](long tiles, int products, double traffic) { return (double)((tiles + 255) / 256 * products) * traffic * (tiles <= 256 ? 1.2 : 1.0); };
         const double c0 = cost(pl.tiles, 8, 1.0);
