@@ -20,10 +20,11 @@
 // its next group requested while it works on this one; a group's scale is one FMA per output; behind the loop the
 // wavefronts' shares of H meet in LDS, H L2 is one or two more steps of the same MFMA, and the wavefronts' sums meet in
 // LDS, both in wavefront order (deterministic).
-// Bound: the vector ALU (about 250 instructions per wavefront, group and 96 columns, half of them X^'s parts) and the fixed
-// parts around the loop; us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
-// launch of its own) -> now: N = 18432: 1 row 13.7 -> 12.6, 2 rows 24 -> 12.7, 16 rows 63.5 -> 15.9, 64 rows 175 -> 43;
-// N = 9216: 16 rows 44 -> 11.8; N = 3072: 1 row 11.5 -> 7.9.
+// Bound: a wavefront's chain of groups (about 250 vector instructions each, half of them X^'s parts, between the waits for the
+// next) and the fixed parts around the loop; by counters the vector ALU is busy 38 % of the time, the matrix core 7 to 15 %, and
+// the wavefronts wait for 60 %.  us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
+// launch of its own) -> now: N = 18432: 1 row 13.5 -> 12.8, 2 rows 24 -> 12.9, 16 rows 61.7 -> 16.3, 64 rows 175 -> 43;
+// N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
