@@ -193,10 +193,10 @@ int svdq_linear_forward(const svdq_layer_dev *layer, const void *X, int M, void 
  * SVDQ_STATIC_SCRATCH_BYTES bytes inside the library (every GPU the library runs on holds its copy until the process
  * ends); the call allocates and frees nothing.  Same arithmetic, kernels, arguments and errors as
  * svdq_linear_forward, except:
- *   - a forward whose workspace (svdq_workspace_bytes) exceeds the array runs without room for the partial tiles of a
- *     split K loop: no split that the options ask for, and the partial sums of the down projection meet in the
- *     activation kernel instead of the GEMM; if even that does not fit, without parked sums either (same results up to
- *     fp32 summation order); if the activation blocks of M tokens alone - about 0.9 * M * K bytes, M padded to 256 - do
+ *   - a forward whose workspace (svdq_workspace_bytes) exceeds the array does without the room for partial tiles of a
+ *     split K loop (the same launches if it makes no split); if that is not enough, without a split that the
+ *     options ask for, then without parked sums of the down projection (same results up to fp32 summation order); if the
+ *     activation blocks of M tokens alone - about 0.9 * M * K bytes, M padded to 256 - do
  *     not fit, the call returns SVDQ_ENOSPACE and launches nothing;
  *   - all calls on one GPU share that GPU's array: two calls that overlap in time on one GPU (different streams or
  *     threads) race; calls on one stream are ordered like any other work;

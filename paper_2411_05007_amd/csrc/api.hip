@@ -96,9 +96,9 @@ int static_scratch(unsigned char **out) {
 }
 
 // The INT4 forward behind both entry points.  ksplit_force / act_force > 0 replace the K split of the GEMM / the groups
-// per activation-kernel workgroup of the calling thread's option word.
+// per activation-kernel workgroup of the calling thread's option word; lean: layout.h, workspace_layout.
 int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *workspace, size_t workspace_bytes, void *hip_stream,
-                 int ksplit_force, int act_force) {
+                 int ksplit_force, int act_force, bool lean) {
     const int st = check_layer(L);
     if (st != SVDQ_OK) return st;
     if (M < 0) return SVDQ_EINVAL;
@@ -107,7 +107,7 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     if (((uintptr_t)X & 15) || ((uintptr_t)Y & 1) || ((uintptr_t)workspace & 255)) return SVDQ_EINVAL;
     const svdq_shape &s = L->shape;
     const svdq::Workspace w = svdq::workspace_layout(M, s.K, s.N, s.rank, ksplit_force > 0 ? ksplit_force : ksplit_override(),
-                                                     act_force > 0 ? act_force : act_override());
+                                                     act_force > 0 ? act_force : act_override(), lean);
     if (workspace_bytes < w.total) return SVDQ_ENOSPACE;
     // the activation kernel keeps 1 / lambda of its workgroups' channels in LDS beside its per-wavefront blocks
     if (s.K > 32768 || svdq::act_lds_bytes(w.act.whole > 0 && w.act.gchunk0 > w.act.gchunk ? w.act.gchunk0 : w.act.gchunk, s.rank, w.act.waves) > (size_t)svdq::kLdsBytesPerCU) return SVDQ_EUNSUPPORTED;
@@ -215,7 +215,7 @@ size_t svdq_workspace_bytes(int M, const svdq_shape *s) {
 
 int svdq_linear_forward(const svdq_layer_dev *L, const void *X, int M, void *Y, void *workspace,
                         size_t workspace_bytes, void *hip_stream) {
-    return forward_int4(L, X, M, Y, workspace, workspace_bytes, hip_stream, 0, 0);
+    return forward_int4(L, X, M, Y, workspace, workspace_bytes, hip_stream, 0, 0, false);
 }
 
 int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
@@ -268,17 +268,20 @@ int svdq_linear_forward_static(const svdq_layer_dev *L, const void *X, int M, vo
     const int got = static_scratch(&ws);
     if (got != SVDQ_OK) return got;
     const svdq_shape &s = L->shape;
-    // the plan the caller's options ask for if its workspace fits the array, else the same forward without parked partial
-    // tiles (no K split in the GEMM), else without any parked results (one activation-kernel workgroup per 16 tokens
-    // too); a batch whose activation blocks alone do not fit is refused
+    // the plan the caller's options ask for if its workspace fits the array, else the same launches without the room of a
+    // split that they do not make, else the same forward without parked partial tiles (no K split in the GEMM), else without
+    // any parked results (one activation-kernel workgroup per 16 tokens too); a batch whose activation blocks alone do not
+    // fit is refused
     int kforce = 0, aforce = 0;
+    bool lean = false;
     auto bytes = [&]() {
-        return svdq::workspace_layout(M, s.K, s.N, s.rank, kforce > 0 ? kforce : ksplit_override(), aforce > 0 ? aforce : act_override()).total;
+        return svdq::workspace_layout(M, s.K, s.N, s.rank, kforce > 0 ? kforce : ksplit_override(), aforce > 0 ? aforce : act_override(), lean).total;
     };
+    if (bytes() > kStaticScratchBytes) lean = true;
     if (bytes() > kStaticScratchBytes) kforce = 1;
     if (bytes() > kStaticScratchBytes) aforce = svdq::kActChunkWhole;
     if (bytes() > kStaticScratchBytes) return SVDQ_ENOSPACE;
-    return forward_int4(L, X, M, Y, ws, kStaticScratchBytes, hip_stream, kforce, aforce);
+    return forward_int4(L, X, M, Y, ws, kStaticScratchBytes, hip_stream, kforce, aforce, lean);
 }
 
 int svdq_debug_act(const svdq_layer_dev *L, const void *workspace, int M, int8_t *out_codes, uint16_t *out_sx,

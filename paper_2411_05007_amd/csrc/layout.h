@@ -497,7 +497,9 @@ struct Workspace {
     int n_counters;      // one arrival counter per tile whose K loop is split
     ActPlan act;
 };
-inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_override = 0, int act_override = 0) {
+// lean: a launch that runs the kernel whose wavefronts share K gets no room for a split K loop, which it does not make, and all
+// the room it needs for the partial H that its GEMM adds (the static workspace, whose size is given; the public size stays as it was).
+inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_override = 0, int act_override = 0, bool lean = false) {
     Workspace w;
     w.Mpad = round_up(M > 0 ? M : 1, kRowPad);
     const int G = K / kGroup;
@@ -506,15 +508,22 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     w.hfrag_off = w.h_off + align256((size_t)w.Mpad * (rank > 0 ? rank : 1) * 4);
     w.counters_off = w.hfrag_off + align256((size_t)w.Mpad * (rank > 0 ? rank : 1) * 4);
     const GemmPlan pl = plan_gemm(M > 0 ? M : 1, N, G, ksplit_override);
-    w.n_counters = pl.tail;                                               // one arrival counter per split tile
+    const int kpar = plan_kpar_int4(M > 0 ? M : 1, N, G, rank, ksplit_override);
+    const bool no_split = lean && kpar != kKparNone;
+    w.n_counters = no_split ? 0 : pl.tail;                                // one arrival counter per split tile
     w.partial_off = w.counters_off + align256((size_t)w.n_counters * 4);
-    w.hpart_off = w.partial_off + align256((size_t)pl.ksplit * pl.tail * pl.bm * pl.bn * 4);
+    w.hpart_off = w.partial_off + (no_split ? 0 : align256((size_t)pl.ksplit * pl.tail * pl.bm * pl.bn * 4));
     // the activation kernel's partial H [chunks][rows of the cut slices][rank] fp32 and one arrival word per workgroup
     w.act = plan_act(M > 0 ? M : 1, G, rank, act_override);
     const bool parked = w.act.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
-    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_int4(M > 0 ? M : 1, N, G, rank, ksplit_override)), rank);
+    const ActPlan small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, kpar);
+    if (no_split && small.deposit) {
+        const size_t need = w.partial_off + align256(act_parked_floats(small, w.Mpad, rank) * 4) + align256(act_arrival_words(small, w.Mpad) * 8);
+        if (w.total < need) w.total = need;
+    }
+    act_use_small_plan(w, small, rank);
     return w;
 }
 

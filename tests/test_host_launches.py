@@ -9,7 +9,7 @@ import pytest
 from paper_2411_05007_amd import svdq as S
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-INT4, FP4, W8A8, W4A16 = 64, 32, 0, 16
+INT4, STATIC, FP4, W8A8, W4A16 = 64, 65, 32, 0, 16
 
 
 @pytest.fixture(scope="module")
@@ -146,3 +146,11 @@ def test_int4_few_groups_on_many_tiles_take_the_large_tiles(record, M, K, N, r, 
 def test_w8a8_short_rows_take_the_walking_activation_kernel(record, M, K, N, r, threads):
     """The one-pass activation kernel deals a token's groups to sixteen wavefronts: at most eight groups leave half of them idle."""
     assert [x for x in record([(0, W8A8, M, K, N, r)])[0] if x[0] == "launch"][0][5] == threads
+
+
+@pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
+def test_the_static_workspace_runs_the_ordinary_launches(record, M, K, N, r):
+    """Ordinary workspaces of small launches are larger than the static array for the room of a K split that such launches do
+    not make: the static call does without that room, not without its launches."""
+    mine, ordinary = record([(0, STATIC, M, K, N, r), (0, INT4, M, K, N, r)])
+    assert [x[2:] for x in mine if x[0] == "launch"] == [x[2:] for x in ordinary if x[0] == "launch"]
