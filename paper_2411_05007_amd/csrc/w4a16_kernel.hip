@@ -23,8 +23,8 @@
 // Bound: a wavefront's chain of groups (about 250 vector instructions each, half of them X^'s parts, between the waits for the
 // next) and the fixed parts around the loop; by counters the vector ALU is busy 38 % of the time, the matrix core 7 to 15 %, and
 // the wavefronts wait for 60 %.  us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
-// launch of its own) -> now: N = 18432: 1 row 13.5 -> 12.8, 2 rows 24 -> 12.9, 16 rows 61.7 -> 16.3, 64 rows 175 -> 43;
-// N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9.
+// launch of its own) -> now: N = 18432: 1 row 13.5 -> 12.3, 16 rows 61.7 -> 15.4;
+// N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9 (the last two without the barrier in split8).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -68,6 +68,10 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
             if (decltype(careful)::value && (!STACK || drop1 != 0u) && __builtin_isinf(x[e])) t[e] = 0.f;
             u[e] = t[e] - __uint_as_float(__float_as_uint(t[e]) & (STACK ? drop2 : 0xffff0000u));
         }
+        // (All parts are made before the first is packed: interleaved, the packing's reads waited for the subtractions right in front
+        // of them, and K = 3072, N = 18432, rank 32 took 13.4 us instead of 12.3 (1 row), 16.9 instead of 15.4 (16).  Sixteen
+        // wavefronts have no registers for it: two column blocks spill.)
+        if constexpr (WAVES == 8) __builtin_amdgcn_sched_barrier(0);
         auto top = [](float lo, float hi) { return (uint32_t)__builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302); };
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
