@@ -119,9 +119,10 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     const bool lowrank = s.rank > 0 && !(opts & SVDQ_OPT_SKIP_LOWRANK);
     const bool unfused = opts & SVDQ_OPT_UNFUSED;
 
-    // small launches: the kernel whose wavefronts share K, unless the caller's options force a K split.  All others: tile
-    // count and K split follow the plan the workspace was sized for
-    const int kpar = svdq::plan_kpar_int4(M, s.N, s.K / svdq::kGroup, s.rank, ksplit_override());
+    // small launches: a kernel of their own, unless the caller's options force a K split.  All others: tile count and K split
+    // follow the plan the workspace was sized for
+    const svdq::SmallInt4 small = svdq::plan_small_int4(M, s.N, s.K / svdq::kGroup, s.rank, ksplit_override());
+    const bool whole = small.rows() > 0;      // no tile's K loop is split
     const svdq::GemmPlan plan = svdq::plan_gemm(M, s.N, s.K / svdq::kGroup, ksplit_force > 0 ? ksplit_force : ksplit_override());
 
     svdq::ActParams a{};
@@ -134,7 +135,7 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     a.hfrag = ws + w.hfrag_off;
     a.M = M; a.K = s.K; a.G = s.K / svdq::kGroup; a.Mpad = w.Mpad; a.rank = s.rank;
     a.zero_words = reinterpret_cast<uint32_t *>(ws + w.counters_off);
-    a.n_zero = kpar ? 0 : w.n_counters;
+    a.n_zero = whole ? 0 : w.n_counters;
     a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
     a.whole = w.act.whole; a.chunks0 = w.act.chunks0; a.gchunk0 = w.act.gchunk0;
     a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
@@ -151,9 +152,9 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
             if (e != hipSuccess) return hip_fail(e);
         }
         svdq::GemmW4Params g = gemm_params(L, ws, w, M, Y, lowrank ? s.rank : 0);
-        g.ksplit = kpar ? 1 : plan.ksplit;
-        g.tail = kpar ? 0 : plan.tail;
-        g.kpar = kpar;
+        g.ksplit = whole ? 1 : plan.ksplit;
+        g.tail = whole ? 0 : plan.tail;
+        g.kpar = small.kpar; g.mid_blocks = small.blocks;
         g.runs = lowrank && w.act.deposit ? w.act.chunks : 0;
         e = svdq::launch_gemm_w4a4(g, stream);
         if (e != hipSuccess) return hip_fail(e);
@@ -170,9 +171,9 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
             if (e != hipSuccess) return hip_fail(e);
         }
         svdq::GemmW4Params g = gemm_params(L, ws, w, M, Y, 0);
-        g.ksplit = kpar ? 1 : plan.ksplit;
-        g.tail = kpar ? 0 : plan.tail;
-        g.kpar = kpar;
+        g.ksplit = whole ? 1 : plan.ksplit;
+        g.tail = whole ? 0 : plan.tail;
+        g.kpar = small.kpar; g.mid_blocks = small.blocks;
         e = svdq::launch_gemm_w4a4(g, stream);
         if (e != hipSuccess) return hip_fail(e);
         if (lowrank) {
@@ -224,26 +225,28 @@ int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
     const int G = s->K / svdq::kGroup;
     svdq::ActPlan a;
     size_t parked_bytes = 0, total = 0;
-    int kpar = 0;
+    int tile_rows = 0, tile_cols = 0;
     if (s->group == svdq::kFp4Block) {
         const svdq::WorkspaceFp4 w = svdq::workspace_layout_fp4(M, s->K, s->N, s->rank, ksplit_override(), act_override());
         const svdq::GemmPlanFp4 pl = svdq::plan_gemm_fp4(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.ksplit > 1 ? pl.tiles : 0; out[10] = pl.ksplit; out[11] = pl.tiles * pl.ksplit;
-        kpar = svdq::plan_kpar_blocks(false, M, s->N, G, ksplit_override());
+        const int kpar = svdq::plan_kpar_blocks(false, M, s->N, G, ksplit_override());
+        if (kpar) { tile_rows = svdq::kpar_rows(kpar); tile_cols = 64; }
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else if (s->group == svdq::kGroup) {
         const svdq::Workspace w = svdq::workspace_layout(M, s->K, s->N, s->rank, ksplit_override(), act_override());
         const svdq::GemmPlan pl = svdq::plan_gemm(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.tail; out[10] = pl.ksplit; out[11] = pl.tiles - pl.tail + pl.tail * pl.ksplit;
-        kpar = svdq::plan_kpar_int4(M, s->N, G, s->rank, ksplit_override());
+        const svdq::SmallInt4 small = svdq::plan_small_int4(M, s->N, G, s->rank, ksplit_override());
+        tile_rows = small.rows(); tile_cols = small.cols();
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else {
         return SVDQ_EUNSUPPORTED;
     }
-    if (kpar) {
-        out[8] = out[11] = ((M + svdq::kpar_rows(kpar) - 1) / svdq::kpar_rows(kpar)) * ((s->N + 63) / 64);
+    if (tile_rows) {
+        out[8] = out[11] = ((M + tile_rows - 1) / tile_rows) * ((s->N + tile_cols - 1) / tile_cols);
         out[9] = 0; out[10] = 1;
     }
     const int slices = (M + 15) / 16;

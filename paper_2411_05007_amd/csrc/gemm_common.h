@@ -32,7 +32,7 @@ __device__ __forceinline__ void gemm_tile_of(int bid, int tiles_m, int tiles_n, 
 // hardware pair conversion, then one row of blocks at a time through a wavefront-private LDS block `ob` (32 rows of
 // 64 CB + 16 bytes) so that every store instruction writes whole 128-byte lines.
 //   acc_at(r, c, v): the accumulator;  bias[c]: the lane's bias of column block c;  (row0, col0): the wavefront's first
-//   output element;  full: the whole tile lies inside M x N and N % 8 == 0 (16-byte stores), else element-wise.
+//   output element;  full: the whole tile lies inside M x N, else every 16-byte chunk is looked at.
 //   between(r): called behind the stores of row block r (whose accumulators are dead from there on).
 struct GemmNothingBetween { __device__ __forceinline__ void operator()(int) const {} };
 template <int RB, int CB, bool ADD_BIAS = true, typename AccAt, typename Between = GemmNothingBetween>
@@ -64,12 +64,8 @@ __device__ __forceinline__ void gemm_store_wave_tile(AccAt acc_at, const float (
             uint16_t *dst = Y + (size_t)grow * N + gcol;
             if (full) {
                 *reinterpret_cast<uint4 *>(dst) = v;
-            } else if (grow < M) {
-                const uint16_t e[8] = {(uint16_t)v.x, (uint16_t)(v.x >> 16), (uint16_t)v.y, (uint16_t)(v.y >> 16),
-                                       (uint16_t)v.z, (uint16_t)(v.z >> 16), (uint16_t)v.w, (uint16_t)(v.w >> 16)};
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    if (gcol + k < N) dst[k] = e[k];
+            } else if (grow < M && gcol < N) {      // (N is a multiple of 16: a chunk is whole or absent)
+                *reinterpret_cast<uint4 *>(dst) = v;
             }
         }
         between(r);

@@ -658,6 +658,7 @@ hipError_t launch_gemm_w4a4(const GemmW4Params &p, hipStream_t stream) {
     if (p.ksplit < 1 || p.ksplit > p.G || (p.ksplit > 1 && (p.dbg || !p.partial || !p.counters))) return hipErrorInvalidValue;
     if (p.ksplit > 1 && (size_t)(p.ksplit - 1) * ((p.G + p.ksplit - 1) / p.ksplit) >= (size_t)p.G) return hipErrorInvalidValue;      // no empty split
     if (p.kpar > 0 && !p.dbg) return launch_gemm_w4a4_kpar(p, stream);
+    if (p.mid_blocks > 0 && !p.dbg) return launch_gemm_w4a4_mid(p, stream);
     return launch_w4_tile<4>(p, stream);
 }
 

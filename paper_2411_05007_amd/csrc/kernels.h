@@ -57,7 +57,8 @@ struct GemmW4Params {
     float *partial;          // ksplit > 1: fp32 [split tile][split][BM * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per split tile, zero when the kernel starts
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
-    const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
+    int mid_blocks;          // > 0: the kernel of 128 x (32 mid_blocks) tiles (layout.h, plan_small_int4)
+    const float *hpart;      // kpar or mid, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
     int runs;
     float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
@@ -65,6 +66,9 @@ hipError_t launch_gemm_w4a4(const GemmW4Params &p, hipStream_t stream);
 // small launches (p.kpar > 0): the same product by workgroups whose wavefronts share the K of one small tile
 // (gemm_w4a4_kpar_kernel.hip); p.ksplit must be 1
 hipError_t launch_gemm_w4a4_kpar(const GemmW4Params &p, hipStream_t stream);
+
+// launches in between (p.mid_blocks > 0): gemm_w4a4_mid_kernel.hip; p.ksplit must be 1
+hipError_t launch_gemm_w4a4_mid(const GemmW4Params &p, hipStream_t stream);
 
 // Y[m][n] += sum_j H[m][j] L2[j][n]  as a separate read-modify-write pass (unfused baseline only)
 hipError_t launch_upproj(const uint8_t *hfrag, const uint16_t *l2t, uint16_t *Y, int M, int N, int rank, hipStream_t stream);

@@ -122,6 +122,7 @@ inline __host__ __device__ int kpar_step(int wave, int KS, int i, int n) { retur
 inline __host__ __device__ int ring_offset(int j, int frags_a, int frags_b, int gm0, int gn0) {
     return j < frags_a ? gm0 * 32 + j * 1024 : j < frags_a + frags_b ? gn0 * 32 + (j - frags_a) * 1024 : 0;
 }
+constexpr int kGemmPlaces = 512;     // places for workgroups of the 128 x 256 tiles: two per CU
 constexpr int kFp4RowBytes = 32;     // packed bytes of one row of one 64-channel step
 constexpr int kMaxKSplitFp4 = 8;
 inline __host__ __device__ size_t fp4_code_offset(int g, int rows_pad, int row, int kb) {
@@ -242,6 +243,42 @@ inline int plan_kpar_int4(int M, int N, int G, int rank, int ksplit_override = 0
     return t128 > 256 && (rest == 0 || rest >= 256) ? kKpar4x4 : kKpar2x4;
 }
 
+// The INT4 GEMM of a launch that the 128 x 256 tiles do not suit: small tiles whose wavefronts share K, or tiles of 128 x (32 blocks)
+// of which a CU holds one (gemm_w4a4_mid_kernel.hip), or neither.
+struct SmallInt4 {
+    int kpar, blocks;
+    int rows() const { return kpar ? kpar_rows(kpar) : blocks ? 128 : 0; }
+    int cols() const { return kpar ? 64 : 32 * blocks; }
+};
+// Costs of a launch in units of what one 32 x 32 block costs a CU per group of 64: the tiles of 128 x (32 blocks) by rounds of one
+// per CU, the small tiles by their number, the 128 x 256 tiles by rounds of two per CU, of which a last one that gives every CU at most
+// one runs at the lone speed.  Fitted to forwards of all three kernels over 85 shapes of more than 480 tiles of 64 x 64, rank 64
+// at most (wider branches make partial H dear); the kernel is taken where it comes out 3 % below the others.  us per
+// forward, others -> this kernel (blocks):
+//   M = 512, K = 3072, N = 9216 36.3 -> 32.4 (5); M = 4096, K = 4608, N = 1152 53.8 -> 46.9 (5); M = 2048, K = N = 3072 43.7 -> 37.4 (6)
+//   M = 609, K = 3712, N = 9360 47.8 -> 41.8 (6); M = 978, K = 4992, N = 9712 87.6 -> 77.0 (5); M = 1774, K = 9536, N = 10256 264 -> 220 (6)
+//   M = 2474, K = 1280, N = 1888 24.1 -> 19.7 (5); M = 645, K = 640, N = 6416 19.5 -> 15.3 (5)
+// No measured shape lost.  Without the 3 %: M = 1715, K = 1792, N = 2368 loses 10 %, M = 439, K = 9536, N = 9552 3 %.
+inline SmallInt4 plan_small_int4(int M, int N, int G, int rank, int ksplit_override = 0) {
+    SmallInt4 s{plan_kpar_int4(M, N, G, rank, ksplit_override), 0};
+    const long tm = (M + 127) / 128, t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
+    // (not taken, besides: K below 448, which was not measured, and few groups on more tiles than one round of 160 columns, whose second round's
+    // fixed parts they do not earn back: M = 4096, K = 1152, N = 4608 47.1 | 48.0)
+    if (ksplit_override > 0 || rank > 64 || t64 <= 1024 || G <= 6 || (t64 > 2048 && G <= 25)) return s;
+    const long large = tm * ((N + 255) / 256), rest = large % kGemmPlaces;
+    double best = s.kpar ? 130 + 1.25 * G * t64 / 256.0
+                         : (large / kGemmPlaces + (rest > 256)) * (85 + 2.05 * 8 * G) + (rest > 0 && rest <= 256 ? 85 + 1.1 * 8 * G : 0.0);
+    best *= 0.97;
+    for (int blocks = 5; blocks <= 6; ++blocks) {
+        const double cost = (tm * ((N + 32 * blocks - 1) / (32 * blocks)) + 255) / 256 * (125.0 + blocks * G);
+        if (cost < best) {
+            best = cost;
+            s = SmallInt4{kKparNone, blocks};
+        }
+    }
+    return s;
+}
+
 // MXFP4 and INT8 (gemm_kpar_blocks_kernel.hip): one MFMA per block and step and nothing behind it, so these variants are bound
 // by what a CU's load unit delivers, (RB + 2) KB for 2 RB MFMAs, and give way to the 128 x 256 tiles, which share their
 // operands through LDS, as soon as those fill the CUs.  us per forward, rank 32 / 16, with the large-tile kernels first:
@@ -278,7 +315,6 @@ struct GemmPlan {
     int ksplit;      // workgroups per split tile, >= 1; workgroups in all = tiles - tail + tail * ksplit
 };
 constexpr int kMaxKSplit = 8;
-constexpr int kGemmPlaces = 512;
 inline GemmPlan plan_gemm(int M, int N, int G, int ksplit_override = 0) {
     GemmPlan pl;
     pl.bm = 128; pl.bn = 256;
@@ -379,7 +415,7 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
     }
     return pl;
 }
-// The same where the GEMM is one whose wavefronts share K (`kpar`, the variant).  Such a GEMM can add the
+// The same where the GEMM is a small-launch kernel (its tile; 0 x 0: it is not).  Such a GEMM can add the
 // runs' partial H itself when it loads them, which takes the meeting of a slice's runs - four round trips past the L2 - out of
 // the activation kernel; runs then cost next to nothing and are cut so that a wavefront walks three groups.  What they do
 // cost is that every tile reads its rows of all partial H: up to 64 MB of that per launch (measured: 50 MB gains 2-3 us,
@@ -387,9 +423,9 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
 //   K = N = 3072, rank 32: M = 512 20.6 -> 18.4 (4, 12), 18.6 (8, 16), 19.1 (8, 24); M = 1024 29.5 -> 27.4 (4, 12); M = 2048 43.5 -> 40.2 (4, 12)
 //   M = 64, K = 12288, N = 3072: 22.1 -> 20.0 (4, 12), 19.8 (8, 24); M = 512 41.7 -> 39.7 (4, 12), 37.6 (8, 24); M = 256, K = N = 1152 12.2 -> 10.3 (4, 12)
 //   rank 128, K = N = 3072: M = 64 17.8 -> 14.1 (4, 12), M = 512 26.3 -> 24.3;  M = 512, K = 12288: 48.4 -> 54.1 (201 MB: not taken)
-inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, int kpar) {
+inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, int tile_rows, int tile_cols) {
     const ActPlan old = plan_act(M, G, rank, act_override);
-    if (act_override > 0 || kpar == kKparNone || rank <= 0 || rank > 128) return old;
+    if (act_override > 0 || tile_rows == 0 || rank <= 0 || rank > 128) return old;
     const long slices = (M + 15) / 16;
     ActPlan pl = old;
     pl.waves = G > 96 ? 8 : 4;
@@ -397,8 +433,8 @@ inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, i
     pl.chunks = (G + pl.gchunk - 1) / pl.gchunk;
     pl.whole = 0; pl.chunks0 = 1; pl.gchunk0 = G;
     pl.deposit = pl.chunks > 1;
-    const long tiles = (long)((M + kpar_rows(kpar) - 1) / kpar_rows(kpar)) * ((N + 63) / 64);
-    if (slices * pl.chunks > 512 || pl.chunks > 64 || tiles * kpar_rows(kpar) * rank * 4 * pl.chunks > 64l << 20) return old;
+    const long tiles = (long)((M + tile_rows - 1) / tile_rows) * ((N + tile_cols - 1) / tile_cols);
+    if (slices * pl.chunks > 512 || pl.chunks > 64 || tiles * tile_rows * rank * 4 * pl.chunks > 64l << 20) return old;
     return pl;
 }
 // the value a workgroup leaves in its arrival word; the word is cleared again before the kernel ends, so whatever a
@@ -486,7 +522,8 @@ inline WorkspaceFp4 workspace_layout_fp4(int M, int K, int N, int rank, int kspl
     const bool parked = ap.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(ap, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(ap, w.Mpad) * 8) : 0);
-    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override)), rank);
+    const int kpar = plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, kpar ? kpar_rows(kpar) : 0, kpar ? 64 : 0), rank);
     return w;
 }
 
@@ -508,8 +545,8 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     w.hfrag_off = w.h_off + align256((size_t)w.Mpad * (rank > 0 ? rank : 1) * 4);
     w.counters_off = w.hfrag_off + align256((size_t)w.Mpad * (rank > 0 ? rank : 1) * 4);
     const GemmPlan pl = plan_gemm(M > 0 ? M : 1, N, G, ksplit_override);
-    const int kpar = plan_kpar_int4(M > 0 ? M : 1, N, G, rank, ksplit_override);
-    const bool no_split = lean && kpar != kKparNone;
+    const SmallInt4 sm = plan_small_int4(M > 0 ? M : 1, N, G, rank, ksplit_override);
+    const bool no_split = lean && sm.rows() > 0;
     w.n_counters = no_split ? 0 : pl.tail;                                // one arrival counter per split tile
     w.partial_off = w.counters_off + align256((size_t)w.n_counters * 4);
     w.hpart_off = w.partial_off + (no_split ? 0 : align256((size_t)pl.ksplit * pl.tail * pl.bm * pl.bn * 4));
@@ -518,7 +555,7 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     const bool parked = w.act.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
-    const ActPlan small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, kpar);
+    const ActPlan small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols());
     if (no_split && small.deposit) {
         const size_t need = w.partial_off + align256(act_parked_floats(small, w.Mpad, rank) * 4) + align256(act_arrival_words(small, w.Mpad) * 8);
         if (w.total < need) w.total = need;

@@ -42,6 +42,23 @@ def test_every_variant_at_its_edges(torch, M, K, N, r, rows):  # noqa: F811
     _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"small {M}x{K}x{N}", window=False)
 
 
+# 128 x 160 and 128 x 192 tiles whose two shares of wavefronts take the even and the odd groups (csrc/gemm_w4a4_mid_kernel.hip): odd
+# and even counts of either share's groups, rank steps that the shares divide unevenly, H ready-made and added from runs, columns
+# past the padded ones, ragged M and N
+@pytest.mark.parametrize("M,K,N,r,cols", [(454, 448, 8272, 48, 160), (579, 576, 6576, 32, 160), (452, 832, 8272, 64, 160), (457, 512, 8336, 0, 160),
+                                          (514, 448, 8976, 48, 192), (516, 832, 8912, 32, 192), (577, 640, 8176, 16, 192)])
+def test_two_shares_of_a_wide_tile(torch, M, K, N, r, cols):  # noqa: F811
+    rng = np.random.default_rng(5700 + M + K + N)
+    prep = _layer(rng, K, N, r)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x[:, rng.choice(K, max(1, K // 100), replace=False)] *= 50
+    plan = S.svdq_debug_launch_plan(M, prep.shape)
+    assert (plan["gemm_tiles"], plan["gemm_ksplit"]) == (-(-M // 128) * -(-N // cols), 1)
+    print(f"wide tile: M={M} K={K} N={N} r={r}, {cols} columns", flush=True)
+    sample = np.unique(np.concatenate([np.arange(40), np.arange(M - 70, M), rng.integers(0, M, 60)]))
+    _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"wide {M}x{K}x{N}", window=False)
+
+
 @pytest.mark.parametrize("M,K,N,r", [(5, 64, 16, 16), (6, 64, 48, 48), (17, 576, 1008, 64), (33, 1088, 9232, 32), (4, 704, 18448, 48),     # one, two, three column blocks
                                      (2, 6208, 80, 80), (19, 6144, 1040, 32), (3, 6208, 272, 0),                                        # sixteen wavefronts
                                      (5, 6208, 8240, 32), (9, 6208, 8240, 16),                                                         # sixteen wavefronts, two column blocks
