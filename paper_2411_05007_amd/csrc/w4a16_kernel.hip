@@ -24,7 +24,7 @@
 // next) and the fixed parts around the loop; by counters the vector ALU is busy 38 % of the time, the matrix core 7 to 15 %, and
 // the wavefronts wait for 60 %.  us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
 // launch of its own) -> now: N = 18432: 1 row 13.5 -> 12.3, 16 rows 61.7 -> 15.4;
-// N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9 (the last two without the barrier in split8).
+// N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -48,7 +48,8 @@ constexpr int kStackRows = 5;
 constexpr int mfma_loop_bytes(int K, int rk, int waves) { return K * 4 + (rk > 0 ? waves * 16 * (16 * rk + 4) * 4 : 0); }
 constexpr int mfma_sums_bytes(int cb, int waves) { return waves * cb * 2 * 16 * 17 * 4; }
 
-template <bool STACK, int CB, int RK, int WAVES>
+// APART: all parts of X^ are made before the first is packed (split8)
+template <bool STACK, int CB, int RK, int WAVES, bool APART>
 __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // 1 / lambda of all channels, later the wavefronts' sums
     constexpr int SETS = STACK ? 1 : 3, RM = STACK ? kStackRows : 16;
@@ -68,10 +69,9 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
             if (decltype(careful)::value && (!STACK || drop1 != 0u) && __builtin_isinf(x[e])) t[e] = 0.f;
             u[e] = t[e] - __uint_as_float(__float_as_uint(t[e]) & (STACK ? drop2 : 0xffff0000u));
         }
-        // (All parts are made before the first is packed: interleaved, the packing's reads waited for the subtractions right in front
-        // of them, and K = 3072, N = 18432, rank 32 took 13.4 us instead of 12.3 (1 row), 16.9 instead of 15.4 (16).  Sixteen
-        // wavefronts have no registers for it: two column blocks spill.)
-        if constexpr (WAVES == 8) __builtin_amdgcn_sched_barrier(0);
+        // (Interleaved with the subtractions, the packing waits for the ones right in front of it: K = 3072, N = 18432, rank 32 took 13.4 us
+        // instead of 12.3 (1 row), 16.9 instead of 15.4 (16).)
+        if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
         auto top = [](float lo, float hi) { return (uint32_t)__builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302); };
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -339,9 +339,9 @@ __global__ __launch_bounds__(1024) void w4a16_proj_kernel(const uint16_t *X, con
 }
 
 // ---- host side ----------------------------------------------------------------------------------------------------
-template <bool STACK, int CB, int RK, int WAVES>
-hipError_t launch_mfma(const W4A16Params &p, hipStream_t stream) {
-    auto k = w4a16_mfma_kernel<STACK, CB, RK, WAVES>;
+template <bool STACK, int CB, int RK, int WAVES, bool APART>
+hipError_t launch_mfma_apart(const W4A16Params &p, hipStream_t stream) {
+    auto k = w4a16_mfma_kernel<STACK, CB, RK, WAVES, APART>;
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), kLdsBytesPerCU); e != hipSuccess) return e;
     const int rows = STACK ? kStackRows : 16;
@@ -349,6 +349,18 @@ hipError_t launch_mfma(const W4A16Params &p, hipStream_t stream) {
     if (bytes > kLdsBytesPerCU) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, dim3((p.N + 32 * CB - 1) / (32 * CB), (p.M + rows - 1) / rows), dim3(WAVES * 64), bytes, stream, p);
     return hipGetLastError();
+}
+// Parts of X^ apart from their packing costs registers.  Sixteen wavefronts have none for it.  Some variants of eight have two
+// workgroups on a CU without and one with it, and do it only while one is all there is (M = 54, K = 3840, N = 8960, rank 32, 560
+// workgroups: 32.3 us without, 37.9 with; M = 40, K = 3200, N = 12976 29.5 | 33.8).
+template <bool STACK, int CB, int RK, int WAVES>
+hipError_t launch_mfma(const W4A16Params &p, hipStream_t stream) {
+    constexpr bool kTwoFit = (CB == 2 && RK == 2) || (CB == 1 && RK == 4) || (STACK && CB == 3 && RK == 0);
+    const long wgs = (long)((p.N + 32 * CB - 1) / (32 * CB)) * ((p.M + (STACK ? kStackRows : 16) - 1) / (STACK ? kStackRows : 16));
+    if constexpr (WAVES != 8) return launch_mfma_apart<STACK, CB, RK, WAVES, false>(p, stream);
+    if constexpr (kTwoFit)
+        if (wgs > 256) return launch_mfma_apart<STACK, CB, RK, WAVES, false>(p, stream);
+    return launch_mfma_apart<STACK, CB, RK, WAVES, WAVES == 8>(p, stream);
 }
 template <bool STACK, int RK>
 hipError_t launch_mfma_shape(const W4A16Params &p, hipStream_t stream) {
