@@ -159,4 +159,17 @@ __device__ __forceinline__ void fp4_encode(const float (&xh)[8], uint32_t &word,
     word = w;
 }
 
+// Partial H [runs][Mpad][rank] in place of H: how a launch says so in H's first 16 bytes, and how a reader of H follows it.
+__device__ __forceinline__ void h_in_parts(float *H, const float *hpart, int runs) {
+    *reinterpret_cast<uint4 *>(H) = make_uint4(kHInParts0, kHInParts1, (uint32_t)runs, (uint32_t)((hpart - H) / 64));
+}
+__device__ __forceinline__ float h_element(const float *H, size_t idx, int Mpad, int rank) {
+    const uint4 w = *reinterpret_cast<const uint4 *>(H);
+    if (w.x != kHInParts0 || w.y != kHInParts1) return H[idx];
+    const float *part = H + (size_t)w.w * 64 + idx;
+    float h = 0.f;
+    for (uint32_t r = 0; r < w.z; ++r) h += part[(size_t)r * Mpad * rank];
+    return h;
+}
+
 }  // namespace svdq

@@ -491,6 +491,7 @@ __global__ __launch_bounds__(WAVES * 64, act_min_workgroups(RBMAX, WAVES, STAGE)
         // Small launches whose GEMM adds the runs itself: the run's sum goes out with plain stores, and that is all (the
         // meeting below costs four round trips past the L2, 3 us of a launch that takes 5 without it).
         if (p.deposit) {
+            if (blockIdx.x == 0 && threadIdx.x == 0) h_in_parts(p.H, p.hpart, nchunks);
             float *mine = p.hpart + ((size_t)chunk * p.Mpad + m0) * p.rank;
             for (int idx = threadIdx.x; idx < 4 * p.rank; idx += WAVES * 64) {
                 const int r = idx / (p.rank / 4), col = 4 * (idx - r * (p.rank / 4));
@@ -644,7 +645,7 @@ __global__ void debug_act_kernel(DebugActParams p) {
         const int m = (int)(idx / p.G), g = (int)(idx % p.G);
         p.out_sx[idx] = *reinterpret_cast<const uint16_t *>(p.codes + w4_a_block(g, p.Mpad, m) + kW4ACodes + 4 * (m % 32));
     }
-    if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = p.H[idx];
+    if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = h_element(p.H, idx, p.Mpad, p.rank);
 }
 
 // the same for the MXFP4 workspace: codes one per byte [M][K], scale bytes [M][K / 32]
@@ -660,7 +661,7 @@ __global__ void debug_act_fp4_kernel(DebugActFp4Params p) {
         const int m = (int)(idx / (p.G * 2)), blk = (int)(idx % (p.G * 2));
         p.out_bx[idx] = p.bx[fp4_scale_offset(blk / 2, p.Mpad, m, blk & 1)];
     }
-    if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = p.H[idx];
+    if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = h_element(p.H, idx, p.Mpad, p.rank);
 }
 
 }  // namespace

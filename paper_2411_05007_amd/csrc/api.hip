@@ -58,7 +58,6 @@ svdq::GemmW4Params gemm_params(const svdq_layer_dev *L, unsigned char *ws, const
     g.partial = reinterpret_cast<float *>(ws + w.partial_off);
     g.counters = reinterpret_cast<uint32_t *>(ws + w.counters_off);
     g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
-    g.H = reinterpret_cast<float *>(ws + w.h_off);
     g.runs = 0;
     return g;
 }
@@ -232,7 +231,7 @@ int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.ksplit > 1 ? pl.tiles : 0; out[10] = pl.ksplit; out[11] = pl.tiles * pl.ksplit;
         const int kpar = svdq::plan_kpar_blocks(false, M, s->N, G, ksplit_override());
-        if (kpar) { tile_rows = svdq::kpar_rows(kpar); tile_cols = 64; }
+        if (kpar) { tile_rows = svdq::kpar_rows(kpar); tile_cols = svdq::kpar_cols(kpar); }
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else if (s->group == svdq::kGroup) {
         const svdq::Workspace w = svdq::workspace_layout(M, s->K, s->N, s->rank, ksplit_override(), act_override());
@@ -372,7 +371,6 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     }
     svdq::GemmFp4Params g{};
     g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
-    g.H = reinterpret_cast<float *>(ws + w.h_off);
     g.runs = lowrank && w.act.deposit ? w.act.chunks : 0;
     g.xcodes = ws + w.codes_off;
     g.bx = ws + w.bx_off;
@@ -518,9 +516,9 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const bool lowrank = s.rank > 0 && !(g_options & SVDQ_OPT_SKIP_LOWRANK);
 
-    // one kernel: per-token maxima, smoothing + INT8 codes + the down projection H = X L1s, in one pass over X that a
-    // workgroup holds in registers (act_one_pass) or in two walks over it;
-    // small launches with a longer K: the walking kernel twice over K cut into runs (the maxima of the runs, then everything else)
+    // per-token maxima, smoothing + INT8 codes + the down projection H = X L1s: in one launch of quantizing and projecting
+    // workgroups (act_w8_small); in one pass over X that a workgroup holds in registers (act_one_pass); in two walks over it;
+    // small launches of neither kind: the walking kernel twice over K cut into runs (the maxima of the runs, then everything else)
     svdq::ActParams a{};
     a.X = static_cast<const uint16_t *>(X);
     a.rinv = static_cast<const float *>(L->rinv);
@@ -535,18 +533,29 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     const int kpar = svdq::plan_kpar_blocks(true, M, s.N, s.K / svdq::kGroup, ksplit_override());
     a.n_zero = kpar ? 0 : w.n_counters;
     hipError_t e;
-    const bool one_pass = act_override() == 0 && svdq::act_one_pass(2, M, s.K, s.rank);
+    // small batches: tokens quantized four to a workgroup beside workgroups that project runs of K (w.act_cut: the plan has such runs)
+    const bool small = w.act_cut && act_override() == 0 && svdq::act_w8_small(M, s.K, s.rank, kpar);
+    const bool one_pass = !small && act_override() == 0 && svdq::act_one_pass(2, M, s.K, s.rank);
     if (!one_pass && w.act_cut) {
         a.chunks = w.act.chunks; a.gchunk = w.act.gchunk; a.waves = w.act.waves;
         a.pmax = reinterpret_cast<float *>(ws + w.pmax_off);
         a.hpart = reinterpret_cast<float *>(ws + w.hpart_off);
         a.arrived = reinterpret_cast<unsigned long long *>(ws + w.aflags_off);
-        a.maxmode = 1;
-        e = svdq::launch_act(a, 1, stream);
-        if (e != hipSuccess) return hip_fail(e);
-        a.maxmode = 2;
     }
-    e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
+    if (small) {
+        e = svdq::launch_act_w8_small(a, lowrank ? 3 : 1, stream);
+        if (e == hipSuccess && lowrank && !kpar) e = svdq::launch_act_sum_h(a, stream);
+    } else if (one_pass) {
+        e = svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream);
+    } else {
+        if (w.act_cut) {
+            a.maxmode = 1;
+            e = svdq::launch_act(a, 1, stream);
+            if (e != hipSuccess) return hip_fail(e);
+            a.maxmode = 2;
+        }
+        e = svdq::launch_act(a, lowrank ? 3 : 1, stream);
+    }
     if (e != hipSuccess) return hip_fail(e);
     if (void *ev = g_profile_event) {
         e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);
@@ -567,6 +576,8 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     g.ksplit = kpar ? 1 : w.ksplit;
     g.partial = reinterpret_cast<int32_t *>(ws + w.partial_off);
     g.counters = reinterpret_cast<uint32_t *>(ws + w.counters_off);
+    g.hpart = reinterpret_cast<const float *>(ws + w.hpart_off);
+    g.runs = small && lowrank && kpar ? w.act.chunks : 0;
     e = svdq::launch_gemm_w8a8(g, stream);
     return e == hipSuccess ? SVDQ_OK : hip_fail(e);
 }

@@ -84,9 +84,7 @@ typedef float gemm_floatx16 __attribute__((ext_vector_type(16)));
 template <int RB, int CB>
 struct GemmLowRankStep { uint4 hhi[RB], hlo[RB], braw[CB]; };
 template <int RB, int CB>
-__device__ __forceinline__ void gemm_lowrank_load(GemmLowRankStep<RB, CB> &o, const unsigned char *hf, const uint16_t *l2t, int rank, int col0,
-                                                  int lane, int ks) {
-    const int li = lane & 31, lh = lane >> 5;
+__device__ __forceinline__ void gemm_lowrank_load_h(GemmLowRankStep<RB, CB> &o, const unsigned char *hf, int rank, int ks) {
     const int ksteps = rank / 16;
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
@@ -94,6 +92,10 @@ __device__ __forceinline__ void gemm_lowrank_load(GemmLowRankStep<RB, CB> &o, co
         o.hhi[r] = *reinterpret_cast<const uint4 *>(hp);
         o.hlo[r] = *reinterpret_cast<const uint4 *>(hp + 1024);
     }
+}
+template <int RB, int CB>
+__device__ __forceinline__ void gemm_lowrank_load_l2(GemmLowRankStep<RB, CB> &o, const uint16_t *l2t, int rank, int col0, int lane, int ks) {
+    const int li = lane & 31, lh = lane >> 5;
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
         // element (col0 + 32 c + li) rank + ... of L2^T, as an unsigned 32-bit index: every launch checks that
@@ -101,6 +103,12 @@ __device__ __forceinline__ void gemm_lowrank_load(GemmLowRankStep<RB, CB> &o, co
         const uint32_t col = (uint32_t)(col0 + c * 32 + li);        // < Npad
         o.braw[c] = *reinterpret_cast<const uint4 *>(l2t + (col * (uint32_t)rank + (uint32_t)(ks * 16 + 8 * lh)));
     }
+}
+template <int RB, int CB>
+__device__ __forceinline__ void gemm_lowrank_load(GemmLowRankStep<RB, CB> &o, const unsigned char *hf, const uint16_t *l2t, int rank, int col0,
+                                                  int lane, int ks) {
+    gemm_lowrank_load_h<RB, CB>(o, hf, rank, ks);
+    gemm_lowrank_load_l2<RB, CB>(o, l2t, rank, col0, lane, ks);
 }
 template <int RB, int CB>
 __device__ __forceinline__ void gemm_lowrank_multiply(gemm_floatx16 (&acc)[RB][CB], const GemmLowRankStep<RB, CB> &o) {

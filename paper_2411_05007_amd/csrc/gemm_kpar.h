@@ -32,12 +32,12 @@ struct KparLds {
     static constexpr int kPart = KS * kPR * CB * 4 * 1024;            // fp32 partial blocks of one phase
     static constexpr int kOctets = kPR * 4;                           // groups of eight rows in a phase
     static constexpr int kOPW = kOctets >= KS ? kOctets / KS : 1;     // octets one wavefront adds up per phase,
-    static constexpr int kWPO = kOctets >= KS ? 1 : KS / kOctets;     // or wavefronts that share an octet
+    static constexpr int kWPO = kOctets >= KS ? 1 : KS / kOctets < CB ? KS / kOctets : CB;      // or wavefronts that share an octet
     static constexpr int kCPW = CB / kWPO;                            // column blocks per wavefront
+    static constexpr int kActive = kOctets / kOPW * kWPO;             // wavefronts that add up a share (all, unless there are more than octets of column blocks)
     static constexpr int kOutRow = kCPW * 64 + 16;
-    static constexpr int kBytes = kPart + KS * kOPW * 8 * kOutRow;
-    static_assert(kOPW * KS == kOctets || kWPO * kOctets == KS, "");
-    static_assert(kCPW * kWPO == CB, "");
+    static constexpr int kBytes = kPart + kActive * kOPW * 8 * kOutRow;
+    static_assert(kActive <= KS && kCPW * kWPO == CB, "");
     static_assert(RB % kPR == 0 && kBytes <= 160 * 1024, "");
 };
 
@@ -71,6 +71,7 @@ __device__ __forceinline__ void kpar_meet(const E (&acc)[RB][CB][16], unsigned c
                     *reinterpret_cast<e4 *>(lds + (((wave * T::kPR + pr) * 4 + q) * CB + c) * 1024 + lane * 16) =
                         e4{acc[p0 + pr][c][4 * q], acc[p0 + pr][c][4 * q + 1], acc[p0 + pr][c][4 * q + 2], acc[p0 + pr][c][4 * q + 3]};
         __syncthreads();
+        if (T::kActive < KS && wave >= T::kActive) continue;
 #pragma unroll
         for (int k = 0; k < T::kOPW; ++k) {
             int oct, c0;
@@ -130,49 +131,56 @@ __device__ __forceinline__ void kpar_reduce_store(const float (&acc)[RB][CB][16]
     kpar_meet<RB, CB, KS>(acc, lds, wave, lane, [&](int, int k, int c, Kpar4<float> s) { out.put(k, c, s); }, [&](int p0) { out.store(p0, Y, M, N, gm0, gn0); });
 }
 
-// Columns col .. + 7 of H's row m from the partial H that the runs of the activation kernel left (fp32 [runs][Mpad][rank]):
-// added in run order, split into bf16 hi + lo.  Hout: where the sums also go, or null.
-__device__ __forceinline__ void kpar_sum_h(const float *hpart, int runs, int Mpad, int rank, int m, int col, float *Hout, uint4 &vhi, uint4 &vlo) {
+// Columns col .. + 7 of H's row m from the partial H that the runs of the activation kernel left (fp32 [runs][Mpad][rank]), added
+// in run order, BATCH runs requested before the first addition waits.
+struct KparH { float h[8]; };
+template <int BATCH = 4>
+__device__ __forceinline__ KparH kpar_sum_h(const float *hpart, int runs, int Mpad, int rank, int m, int col) {
     const size_t at = (size_t)m * rank + col, stride = (size_t)Mpad * rank;
-    float h[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c0 = 0; c0 < runs; c0 += 4) {      // four runs are requested before the first addition waits
-        float4 t[4][2];
+    KparH o{};
+    for (int c0 = 0; c0 < runs; c0 += BATCH) {
+        float4 t[BATCH][2];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < BATCH; ++c) {
             const float4 *q = reinterpret_cast<const float4 *>(hpart + (c0 + c < runs ? c0 + c : c0) * stride + at);
             t[c][0] = q[0];
             t[c][1] = q[1];
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
+        for (int c = 0; c < BATCH; ++c)
             if (c0 + c < runs) {
-                h[0] += t[c][0].x; h[1] += t[c][0].y; h[2] += t[c][0].z; h[3] += t[c][0].w;
-                h[4] += t[c][1].x; h[5] += t[c][1].y; h[6] += t[c][1].z; h[7] += t[c][1].w;
+                o.h[0] += t[c][0].x; o.h[1] += t[c][0].y; o.h[2] += t[c][0].z; o.h[3] += t[c][0].w;
+                o.h[4] += t[c][1].x; o.h[5] += t[c][1].y; o.h[6] += t[c][1].z; o.h[7] += t[c][1].w;
             }
     }
+    return o;
+}
+// such values as the bf16 hi and lo parts that the matrix core is fed
+__device__ __forceinline__ void kpar_split_h(const KparH &v, uint4 &vhi, uint4 &vlo) {
     uint32_t hi[4], lo[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        hi[e] = bf16_rne_pair(h[2 * e], h[2 * e + 1]);
-        lo[e] = bf16_rne_pair(h[2 * e] - bf16lo(hi[e]), h[2 * e + 1] - bf16hi(hi[e]));
+        hi[e] = bf16_rne_pair(v.h[2 * e], v.h[2 * e + 1]);
+        lo[e] = bf16_rne_pair(v.h[2 * e] - bf16lo(hi[e]), v.h[2 * e + 1] - bf16hi(hi[e]));
     }
     vhi = make_uint4(hi[0], hi[1], hi[2], hi[3]);
     vlo = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-    if (Hout) {
-        float4 *o = reinterpret_cast<float4 *>(Hout + at);
-        o[0] = make_float4(h[0], h[1], h[2], h[3]);
-        o[1] = make_float4(h[4], h[5], h[6], h[7]);
-    }
 }
-// The same for all of a tile's 32 RB rows, left in LDS in the operand order of hfrag (rows counted from the tile's first).
-// All threads take part; ends with a barrier.
+// H of the tile's rows below M (the others' places are left as they are: they only meet outputs that are not stored), left in LDS in
+// the operand order of hfrag (rows counted from the tile's first).  All threads take part; ends with a barrier.
+// (H is not written to memory here: a store in front of the K loop holds up every later load of its wavefront until memory has
+// acknowledged it, 2.5 us per store and wait in the workgroups that wrote it, and so in the launch.)
 template <int RB, int KS>
-__device__ __forceinline__ void kpar_sum_h_tile(unsigned char *lds, const float *hpart, int runs, int Mpad, int rank, int gm0, float *Hout, int tid) {
-    const int octets = rank / 8;
-    for (int idx = tid; idx < 32 * RB * octets; idx += KS * 64) {
+__device__ __forceinline__ void kpar_sum_h_tile(unsigned char *lds, const float *hpart, int runs, int M, int Mpad, int rank, int gm0, int tid) {
+    const int octets = rank / 8, rows = M - gm0 < 32 * RB ? M - gm0 : 32 * RB;
+    for (int idx = tid; idx < rows * octets; idx += KS * 64) {
         const int m = idx / octets, col = 8 * (idx - m * octets);
+        KparH h;      // (a batch beyond the runs asks for the first of them again)
+        if (runs <= 2) h = kpar_sum_h<2>(hpart, runs, Mpad, rank, gm0 + m, col);
+        else if (KS != 8 || runs <= 4) h = kpar_sum_h<4>(hpart, runs, Mpad, rank, gm0 + m, col);
+        else h = kpar_sum_h<8>(hpart, runs, Mpad, rank, gm0 + m, col);
         uint4 hi, lo;
-        kpar_sum_h(hpart, runs, Mpad, rank, gm0 + m, col, Hout, hi, lo);
+        kpar_split_h(h, hi, lo);
         *reinterpret_cast<uint4 *>(lds + hfrag_offset(rank, m, col, 0)) = hi;
         *reinterpret_cast<uint4 *>(lds + hfrag_offset(rank, m, col, 1)) = lo;
     }

@@ -38,25 +38,23 @@ struct KparParams {
     const float *bias;
     uint16_t *Y;
     int M, N, steps, Mpad, Npad, rank;
-    const float *hpart;      // MXFP4, runs > 0: partial H of the activation kernel's runs, else hfrag holds the whole H
-    float *H;
+    const float *hpart;      // runs > 0: partial H of the activation kernel's runs, else hfrag holds the whole H
     int runs;
 };
 
-// I8: INT8 (32 channels per step), else MXFP4 (64).  RB row blocks of 32, KS wavefronts that share K, DEPTH steps ahead.
-// RUNS (MXFP4): H comes as the partial sums of the activation kernel's runs (else ready-made).
-template <bool I8, int RB, int KS, int DEPTH, bool RUNS>
-__global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_kernel(KparParams p) {
+// I8: INT8 (32 channels per step), else MXFP4 (64).  RB row blocks and CB column blocks of 32, KS wavefronts that share K, DEPTH steps ahead.
+// RUNS: H comes as the partial sums of the activation kernel's runs (else ready-made).
+template <bool I8, int RB, int CB, int KS, int DEPTH, bool RUNS>
+__global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_kernel(KparParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-    constexpr int CB = 2;
     using T = KparLds<RB, CB, KS>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 31, lh = lane >> 5;
-    const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 63) / 64;
+    const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 32 * CB - 1) / (32 * CB);
     int tile_m, tile_n;
     kpar_tile_of((int)blockIdx.x, tiles_m, tiles_n, RB * 1024, CB * 1024, tile_m, tile_n);
-    const int gm0 = tile_m * 32 * RB, gn0 = tile_n * 64;      // the launch checks that every tile lies inside the padded rows and columns
+    const int gm0 = tile_m * 32 * RB, gn0 = tile_n * 32 * CB;      // the launch checks that every tile lies inside the padded rows and columns
 
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.xcodes, (size_t)p.steps * p.Mpad * kRowBytes);
     const __amdgpu_buffer_rsrc_t rs_b = make_rsrc(p.wcodes, (size_t)p.steps * p.Npad * kRowBytes);
@@ -97,31 +95,49 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
         constexpr int kPhases = RB / T::kPR;
         const int ksteps = p.rank / 16;
         int oct0, c0;
-        kpar_share<RB, CB, KS>(wave, 0, oct0, c0);
+        kpar_share<RB, CB, KS>(wave % T::kActive, 0, oct0, c0);
         uint2 sx[kPhases][T::kOPW];
         float sw[T::kCPW], bias[T::kCPW];
-        struct RankStep { uint4 hi, lo, b[T::kCPW]; };
-        auto load_rank = [&](RankStep &o, int ph, int ks) {
-            const int m = gm0 + (ph * T::kPR + oct0 / 4) * 32 + 8 * (oct0 % 4 + li / 8 % T::kOPW) + li % 8;      // < Mpad
-#pragma unroll
-            for (int c = 0; c < T::kCPW; ++c) o.b[c] = *reinterpret_cast<const uint4 *>(p.l2t + (size_t)(gn0 + (c0 + c) * 32 + li) * p.rank + 16 * ks + 8 * lh);
-            const unsigned char *h = p.hfrag + hfrag_offset(p.rank, m, 16 * ks + 8 * lh, 0);
+        struct RankH { uint4 hi, lo; };
+        struct RankL2 { uint4 b[T::kCPW]; };
+        auto share_row = [&](int ph) { return (ph * T::kPR + oct0 / 4) * 32 + 8 * (oct0 % 4 + li / 8 % T::kOPW) + li % 8; };      // of the tile
+        auto load_h = [&](RankH &o, int ph, int ks) {
+            const unsigned char *h = p.hfrag + hfrag_offset(p.rank, gm0 + share_row(ph), 16 * ks + 8 * lh, 0);      // row < Mpad
             o.hi = *reinterpret_cast<const uint4 *>(h);
             o.lo = *reinterpret_cast<const uint4 *>(h + 1024);
         };
-        RankStep first[kPhases];
+        auto load_l2 = [&](RankL2 &o, int ks) {
+#pragma unroll
+            for (int c = 0; c < T::kCPW; ++c) o.b[c] = *reinterpret_cast<const uint4 *>(p.l2t + (size_t)(gn0 + (c0 + c) * 32 + li) * p.rank + 16 * ks + 8 * lh);
+        };
+        // (H from runs: all of it is taken into registers here, its place in LDS is the partial tiles' later; at most two rank steps)
+        constexpr int kEarly = RUNS ? 2 : 1;
+        RankH first_h[kPhases][kEarly];
+        RankL2 first_l2;
 #pragma unroll
         for (int c = 0; c < T::kCPW; ++c) {
             sw[c] = (float)__builtin_bit_cast(_Float16, p.sw[gn0 + (c0 + c) * 32 + li]);      // padded to Npad
             bias[c] = p.bias[gn0 + (c0 + c) * 32 + li];
         }
 #pragma unroll
-        for (int ph = 0; ph < kPhases; ++ph) {
+        for (int ph = 0; ph < kPhases; ++ph)
 #pragma unroll
             for (int k = 0; k < T::kOPW; ++k)
                 sx[ph][k] = *reinterpret_cast<const uint2 *>(p.sx + gm0 + (ph * T::kPR + oct0 / 4) * 32 + 8 * (oct0 % 4 + k) + 4 * lh);      // < Mpad
-            if (ksteps > 0) load_rank(first[ph], ph, 0);
-        }
+        if (ksteps > 0) load_l2(first_l2, 0);
+        if constexpr (RUNS) kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.M, p.Mpad, p.rank, gm0, threadIdx.x);
+#pragma unroll
+        for (int ph = 0; ph < kPhases; ++ph)
+#pragma unroll
+            for (int ks = 0; ks < kEarly; ++ks)
+                if (ks < ksteps) {
+                    if constexpr (RUNS) {
+                        const unsigned char *h = lds + hfrag_offset(p.rank, share_row(ph), 16 * ks + 8 * lh, 0);
+                        first_h[ph][ks].hi = *reinterpret_cast<const uint4 *>(h);
+                        first_h[ph][ks].lo = *reinterpret_cast<const uint4 *>(h + 1024);
+                    }
+                    else load_h(first_h[ph][ks], ph, ks);
+                }
         intx16 acc[RB][CB];
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -147,6 +163,7 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
             for (int c = 0; c < CB; ++c)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) f[r][c][v] = acc[r][c][v];
+        if constexpr (RUNS) __syncthreads();      // nobody reads H any more
         KparStore<RB, CB, KS> out(lds, wave, lane);
         floatx16 y[T::kCPW];
 #pragma unroll
@@ -164,17 +181,23 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
                 }
             },
             [&](int p0) {
-                RankStep o = first[p0 / T::kPR];
+                RankH h = first_h[p0 / T::kPR][0];
+                RankL2 l2 = first_l2;
                 for (int ks = 0; ks < ksteps; ++ks) {
-                    RankStep next = o;
-                    if (ks + 1 < ksteps) load_rank(next, p0 / T::kPR, ks + 1);
+                    RankH next_h = first_h[p0 / T::kPR][kEarly - 1];
+                    RankL2 next_l2 = l2;
+                    if (ks + 1 < ksteps) {
+                        load_l2(next_l2, ks + 1);
+                        if (!RUNS) load_h(next_h, p0 / T::kPR, ks + 1);
+                    }
 #pragma unroll
                     for (int c = 0; c < T::kCPW; ++c) {
-                        const bf16x8_t b = __builtin_bit_cast(bf16x8_t, o.b[c]);
-                        y[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, o.hi), b, y[c], 0, 0, 0);
-                        y[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, o.lo), b, y[c], 0, 0, 0);
+                        const bf16x8_t b = __builtin_bit_cast(bf16x8_t, l2.b[c]);
+                        y[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, h.hi), b, y[c], 0, 0, 0);
+                        y[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, h.lo), b, y[c], 0, 0, 0);
                     }
-                    o = next;
+                    h = next_h;
+                    l2 = next_l2;
                 }
 #pragma unroll
                 for (int k = 0; k < T::kOPW; ++k)
@@ -192,18 +215,22 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
 #pragma unroll
             for (int r = 0; r < RB; ++r) acc[r][c] = floatx16{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
         }
-        auto low_rank = [&](const unsigned char *hf) {
+        if constexpr (RUNS) {
+            // L2's operands of the wavefront's first rank step are requested before H is added up
+            GemmLowRankStep<RB, CB> o;
+            if (wave < p.rank / 16) gemm_lowrank_load_l2<RB, CB>(o, p.l2t, p.rank, gn0, lane, wave);
+            kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.M, p.Mpad, p.rank, gm0, threadIdx.x);
             for (int ks = wave; ks < p.rank / 16; ks += KS) {
-                GemmLowRankStep<RB, CB> o;
-                gemm_lowrank_load<RB, CB>(o, hf + lane * 16, p.l2t, p.rank, gn0, lane, ks);
+                if (ks != wave) gemm_lowrank_load_l2<RB, CB>(o, p.l2t, p.rank, gn0, lane, ks);
+                gemm_lowrank_load_h<RB, CB>(o, lds + lane * 16, p.rank, ks);
                 gemm_lowrank_multiply<RB, CB>(acc, o);
             }
-        };
-        if constexpr (RUNS) {
-            kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.Mpad, p.rank, gm0, tile_n == 0 ? p.H : nullptr, threadIdx.x);
-            low_rank(lds);
         } else {
-            low_rank(p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048);
+            for (int ks = wave; ks < p.rank / 16; ks += KS) {
+                GemmLowRankStep<RB, CB> o;
+                gemm_lowrank_load<RB, CB>(o, p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048 + lane * 16, p.l2t, p.rank, gn0, lane, ks);
+                gemm_lowrank_multiply<RB, CB>(acc, o);
+            }
         }
         for (int i = 0; i < n; i += DEPTH) {
 #pragma unroll
@@ -232,37 +259,36 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_kpar_blocks_ker
     }
 }
 
-template <bool I8, int RB, int KS, int DEPTH, bool RUNS>
+template <bool I8, int RB, int CB, int KS, int DEPTH, bool RUNS>
 hipError_t launch_tile(const KparParams &p, hipStream_t stream) {
-    const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 63) / 64;
+    const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 32 * CB - 1) / (32 * CB);
     // H, L2, the scales and the bias are read with plain loads: every tile must lie inside the padded rows and columns
-    if (tiles_m * 32 * RB > p.Mpad || tiles_n * 64 > p.Npad) return hipErrorInvalidValue;
-    auto k = gemm_kpar_blocks_kernel<I8, RB, KS, DEPTH, RUNS>;
-    constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
-    if (RUNS && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
+    if (tiles_m * 32 * RB > p.Mpad || tiles_n * 32 * CB > p.Npad) return hipErrorInvalidValue;
+    auto k = gemm_kpar_blocks_kernel<I8, RB, CB, KS, DEPTH, RUNS>;
+    constexpr int bytes = KparLds<RB, CB, KS>::kBytes;
+    if (RUNS && (!p.hpart || p.rank <= 0 || (I8 && p.rank > 32) || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), bytes); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);
     return hipGetLastError();
 }
 
-template <bool I8, int RB, int KS, int DEPTH>
+template <bool I8, int RB, int CB, int KS, int DEPTH>
 hipError_t launch_one(const KparParams &p, hipStream_t stream) {
-    if constexpr (!I8)
-        if (p.runs > 0) return launch_tile<false, RB, KS, DEPTH, true>(p, stream);
-    return launch_tile<I8, RB, KS, DEPTH, false>(p, stream);
+    return p.runs > 0 ? launch_tile<I8, RB, CB, KS, DEPTH, true>(p, stream) : launch_tile<I8, RB, CB, KS, DEPTH, false>(p, stream);
 }
 
 template <bool I8>
 hipError_t launch_variant(const KparParams &p, int variant, hipStream_t stream) {
     switch (variant) {
-        case kKpar1x8: return launch_one<I8, 1, 8, 6>(p, stream);
+        case kKparNarrow: return launch_one<I8, 1, 1, 16, 6>(p, stream);
+        case kKpar1x8: return launch_one<I8, 1, 2, 8, 6>(p, stream);
         case kKpar2x8:      // (MXFP4 takes four wavefronts for 64-row tiles: plan_kpar_blocks)
-            if constexpr (I8) return launch_one<true, 2, 8, 4>(p, stream);
+            if constexpr (I8) return launch_one<true, 2, 2, 8, 4>(p, stream);
             return hipErrorInvalidValue;
-        case kKpar2x4: return launch_one<I8, 2, 4, 4>(p, stream);
-        case kKpar4x8: return launch_one<I8, 4, 8, 2>(p, stream);
-        case kKpar4x4: return launch_one<I8, 4, 4, 2>(p, stream);
+        case kKpar2x4: return launch_one<I8, 2, 2, 4, 4>(p, stream);
+        case kKpar4x8: return launch_one<I8, 4, 2, 8, 2>(p, stream);
+        case kKpar4x4: return launch_one<I8, 4, 2, 4, 2>(p, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -275,7 +301,7 @@ hipError_t launch_gemm_fp4_kpar(const GemmFp4Params &q, hipStream_t stream) {
     p.xcodes = q.xcodes; p.wcodes = q.wcodes; p.bx = q.bx; p.bw = q.bw;
     p.hfrag = q.hfrag; p.l2t = q.l2t; p.bias = q.bias; p.Y = q.Y;
     p.M = q.M; p.N = q.N; p.steps = q.G; p.Mpad = q.Mpad; p.Npad = q.Npad; p.rank = q.rank;
-    p.hpart = q.hpart; p.H = q.H; p.runs = q.runs;
+    p.hpart = q.hpart; p.runs = q.runs;
     return launch_variant<false>(p, q.kpar, stream);
 }
 
@@ -285,6 +311,7 @@ hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &q, hipStream_t stream) {
     p.xcodes = q.xcodes; p.wcodes = q.wcodes; p.sx = q.sx; p.sw = q.sw;
     p.hfrag = q.hfrag; p.l2t = q.l2t; p.bias = q.bias; p.Y = q.Y;
     p.M = q.M; p.N = q.N; p.steps = q.K / 32; p.Mpad = q.Mpad; p.Npad = q.Npad; p.rank = q.rank;
+    p.hpart = q.hpart; p.runs = q.runs;
     return launch_variant<true>(p, q.kpar, stream);
 }
 

@@ -123,18 +123,22 @@ __global__ __launch_bounds__(KS * 64, KS == 8 ? 1 : 2) void gemm_w4a4_kpar_kerne
 #pragma unroll
             for (int r = 0; r < RB; ++r) lr[r][c] = floatx16{b, b, b, b, b, b, b, b, b, b, b, b, b, b, b, b};
         }
-        auto low_rank = [&](const unsigned char *hf) {
+        if constexpr (RUNS) {
+            // L2's operands of the wavefront's first rank step are requested before H is added up
+            GemmLowRankStep<RB, CB> o;
+            if (wave < p.rank / 16) gemm_lowrank_load_l2<RB, CB>(o, p.l2t, p.rank, gn0, lane, wave);
+            kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.M, p.Mpad, p.rank, gm0, threadIdx.x);
             for (int ks = wave; ks < p.rank / 16; ks += KS) {
-                GemmLowRankStep<RB, CB> o;
-                gemm_lowrank_load<RB, CB>(o, hf + lane * 16, p.l2t, p.rank, gn0, lane, ks);
+                if (ks != wave) gemm_lowrank_load_l2<RB, CB>(o, p.l2t, p.rank, gn0, lane, ks);
+                gemm_lowrank_load_h<RB, CB>(o, lds + lane * 16, p.rank, ks);
                 gemm_lowrank_multiply<RB, CB>(lr, o);
             }
-        };
-        if constexpr (RUNS) {
-            kpar_sum_h_tile<RB, KS>(lds, p.hpart, p.runs, p.Mpad, p.rank, gm0, tile_n == 0 ? p.H : nullptr, threadIdx.x);
-            low_rank(lds);
         } else {
-            low_rank(p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048);
+            for (int ks = wave; ks < p.rank / 16; ks += KS) {
+                GemmLowRankStep<RB, CB> o;
+                gemm_lowrank_load<RB, CB>(o, p.hfrag + (size_t)(gm0 / 32) * (p.rank / 16) * 2048 + lane * 16, p.l2t, p.rank, gn0, lane, ks);
+                gemm_lowrank_multiply<RB, CB>(lr, o);
+            }
         }
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -224,7 +228,7 @@ hipError_t launch_variant(const GemmW4Params &p, hipStream_t stream) {
     if (tiles_m * 32 * RB > p.Mpad || tiles_n * 64 > p.Npad) return hipErrorInvalidValue;
     auto k = gemm_w4a4_kpar_kernel<RB, KS, DEPTH, RUNS>;
     constexpr int bytes = KparLds<RB, 2, KS>::kBytes;
-    if (RUNS && (!p.hpart || !p.H || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
+    if (RUNS && (!p.hpart || p.rank <= 0 || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), bytes); e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3(tiles_m * tiles_n), dim3(KS * 64), bytes, stream, p);

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(512, 1) void gemm_w4a4_mid_kernel(GemmW4Params p) {
             for (int r = 0; r < 2; ++r) {
                 const int m = gm0 + 32 * row_block(r) + li;
                 if constexpr (RUNS) {
-                    kpar_sum_h(p.hpart, p.runs, p.Mpad, p.rank, m, 16 * ks + 8 * lh, tile_n == 0 && cw == 0 ? p.H : nullptr, o.hi[r], o.lo[r]);
+                    kpar_split_h(kpar_sum_h<4>(p.hpart, p.runs, p.Mpad, p.rank, m, 16 * ks + 8 * lh), o.hi[r], o.lo[r]);
                 } else {
                     const unsigned char *h = p.hfrag + hfrag_offset(p.rank, m, 16 * ks + 8 * lh, 0);
                     o.hi[r] = *reinterpret_cast<const uint4 *>(h);
@@ -367,7 +367,7 @@ hipError_t launch_mid(const GemmW4Params &p, hipStream_t stream) {
     using T = MidTile<C>;
     const int tiles_m = (p.M + T::kBM - 1) / T::kBM, tiles_n = (p.N + T::kBN - 1) / T::kBN;
     if (tiles_m * T::kBM > p.Mpad) return hipErrorInvalidValue;      // H is read with plain loads
-    if (RUNS && (!p.hpart || !p.H || p.rank <= 0)) return hipErrorInvalidValue;
+    if (RUNS && (!p.hpart || p.rank <= 0)) return hipErrorInvalidValue;
     auto k = gemm_w4a4_mid_kernel<C, RUNS>;
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;

@@ -24,7 +24,7 @@ struct ActParams {
     int whole, chunks0, gchunk0;     // the first `whole` 16-token slices are cut differently: chunks0 runs of gchunk0 groups (chunks0 <= 1: not cut)
     // partial H of every run of the cut slices, fp32: [chunks0][16 whole][rank] (if chunks0 > 1), then [chunks][Mpad - 16 whole][rank] (if chunks > 1)
     float *hpart;
-    // deposit: H is not made here; the runs' partial H stay in hpart and the GEMM (a variant whose wavefronts share K) adds them
+    // deposit: H is not made here; the runs' partial H stay in hpart and the GEMM (of small launches) adds them; H says where they are (layout.h)
     int deposit;
     // arrival words: [whole][chunks0] (if chunks0 > 1), then [Mpad / 16 - whole][chunks] (if chunks > 1)
     unsigned long long *arrived;
@@ -39,6 +39,12 @@ hipError_t launch_act(const ActParams &p, int flags, hipStream_t stream);
 // the same in one pass over X, for the sizes that act_one_pass names (act_onepass_kernel.hip): K is not cut, H is made whole
 hipError_t launch_act_one_pass(const ActParams &p, int flags, hipStream_t stream);
 bool act_one_pass(int fmt, int M, int K, int rank);
+
+// INT8, small batches (act_w8_small_kernel.hip): quantizes as above and leaves the partial H of p.chunks runs of p.gchunk groups in p.hpart
+hipError_t launch_act_w8_small(const ActParams &p, int flags, hipStream_t stream);
+constexpr int kActW8SmallGroups = 192;      // K up to 12288: what sixteen wavefronts hold of four tokens
+// H (and its bf16 parts) from those runs, for a GEMM that does not add them itself
+hipError_t launch_act_sum_h(const ActParams &p, hipStream_t stream);
 
 // W4A4 GEMM on the block-scaled matrix instruction: INT4 codes as 6-bit float operands, exact fp32 group sums,
 // scale tiles from an f16 MFMA, one FMA per partial sum (gemm_w4a4_kernel.hip; layouts in layout.h)
@@ -60,7 +66,6 @@ struct GemmW4Params {
     int mid_blocks;          // > 0: the kernel of 128 x (32 mid_blocks) tiles (layout.h, plan_small_int4)
     const float *hpart;      // kpar or mid, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
     int runs;
-    float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
 hipError_t launch_gemm_w4a4(const GemmW4Params &p, hipStream_t stream);
 // small launches (p.kpar > 0): the same product by workgroups whose wavefronts share the K of one small tile
@@ -112,7 +117,6 @@ struct GemmFp4Params {
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
     const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
     int runs;
-    float *H;                // runs > 0: fp32 [Mpad][rank], written by the first tile of every row of tiles
 };
 hipError_t launch_gemm_fp4(const GemmFp4Params &p, hipStream_t stream);
 // small launches (p.kpar > 0): the same product by workgroups whose wavefronts share the K of one small tile
@@ -158,6 +162,8 @@ struct GemmW8Params {
     int32_t *partial;        // ksplit > 1: int32 [tile][split][128 * 256] partial tiles, register order
     uint32_t *counters;      // ksplit > 1: one arrival counter per tile, zero when the kernel starts
     int kpar;                // > 0: the small-launch kernel, in this variant (layout.h, KparVariant)
+    const float *hpart;      // kpar, runs > 0: fp32 partial H [runs][Mpad][rank], to be added in order; else hfrag holds the whole H
+    int runs;
 };
 hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream);
 hipError_t launch_gemm_w8a8_kpar(const GemmW8Params &p, hipStream_t stream);      // small launches, as launch_gemm_fp4_kpar

@@ -213,8 +213,9 @@ struct WorkspaceFp4 {
 };
 
 
-// Variants of the GEMM for launches of few tiles: (32 RB) x 64 tiles, KS wavefronts per workgroup that share K.
-enum KparVariant { kKparNone = 0, kKpar1x8, kKpar2x8, kKpar2x4, kKpar4x8, kKpar4x4, kKparVariants };
+// Variants of the GEMM for launches of few tiles: (32 RB) x 64 tiles, KS wavefronts per workgroup that share K; kKparNarrow: 32 x 32 tiles,
+// sixteen wavefronts.
+enum KparVariant { kKparNone = 0, kKpar1x8, kKpar2x8, kKpar2x4, kKpar4x8, kKpar4x4, kKparNarrow, kKparVariants };
 // INT4.  Small tiles where the launch is short of workgroups, larger ones where it is not (fewer bytes from the L2 per
 // product); eight wavefronts while one such workgroup per CU is all there is, four (two workgroups per CU) beyond.
 // Measured, us per forward at rank 32 with the kernel of 128 x 256 tiles (K loops split over workgroups) first:
@@ -224,7 +225,8 @@ enum KparVariant { kKparNone = 0, kKpar1x8, kKpar2x8, kKpar2x4, kKpar4x8, kKpar4
 //   M = 512, K = 3072, N = 9216 (1152): 40.5; 2x4 34.0, 4x4 36.9.                       M = 4096, K = 4608, N = 1152 (1152): 59.6; 2x4 51.5, 4x4 54.2
 //   M = 2048, K = N = 3072 (1536): 47.6; 2x4 42.9, 4x4 39.6.                            M = 1024, K = 3072, N = 9216 (2304): 59.1; 2x4 53.1, 4x4 52.7
 //   M = 4608, K = N = 3072 (3456): 69.5; 2x4 84.9, 4x4 77.0.                            M = 4096, K = 1152, N = 4608 (4608): 47.5; 2x4 55.8, 4x4 51.0
-inline int kpar_rows(int variant) { return variant == kKpar1x8 ? 32 : variant == kKpar2x8 || variant == kKpar2x4 ? 64 : 128; }
+inline int kpar_cols(int variant) { return variant == kKparNarrow ? 32 : 64; }
+inline int kpar_rows(int variant) { return variant == kKpar1x8 || variant == kKparNarrow ? 32 : variant == kKpar2x8 || variant == kKpar2x4 ? 64 : 128; }
 inline int plan_kpar_int4(int M, int N, int G, int rank, int ksplit_override = 0) {
     if (ksplit_override > 0) return kKparNone;
     const long tn = (N + 63) / 64, t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
@@ -248,7 +250,7 @@ inline int plan_kpar_int4(int M, int N, int G, int rank, int ksplit_override = 0
 struct SmallInt4 {
     int kpar, blocks;
     int rows() const { return kpar ? kpar_rows(kpar) : blocks ? 128 : 0; }
-    int cols() const { return kpar ? 64 : 32 * blocks; }
+    int cols() const { return kpar ? kpar_cols(kpar) : 32 * blocks; }
 };
 // Costs of a launch in units of what one 32 x 32 block costs a CU per group of 64: the tiles of 128 x (32 blocks) by rounds of one
 // per CU, the small tiles by their number, the 128 x 256 tiles by rounds of two per CU, of which a last one that gives every CU at most
@@ -289,9 +291,15 @@ inline SmallInt4 plan_small_int4(int M, int N, int G, int rank, int ksplit_overr
 //   M = 512, K = 12288, N = 3072 (192): 38.6; 2x4 38.6, 4x8 34.9, 4x4 38.1.                  52.4; 2x4 50.4, 4x8 47.5, 4x4 52.4
 //   M = 1024, K = N = 3072 (384): 28.6; 2x4 24.6, 4x8 28.0, 4x4 24.4.                        42.8; 2x4 37.1, 4x8 39.8, 4x4 33.5
 //   M = 512, K = 3072, N = 9216 (576): 27.9; 2x4 31.0, 4x4 29.8.                             39.6; 2x4 41.6, 4x4 43.3
+//   32 x 32 tiles with sixteen wavefronts, 1x8 -> narrow, ranks 16 to 128 (a launch of few tiles pulls its weights through few CUs):
+//   INT8: M = 4, K = 10048, N = 1232 (20 tiles of 32 x 64) 18.7 -> 15.8, M = 82, K = 6208, N = 1888 (90) 15.8 -> 14.1, M = 7, K = 1984, N = 4176 (66) 9.4 -> 8.8,
+//   M = 3, K = 1408, N = 1584 8.05 -> 8.05; MXFP4: M = 1, K = 5056, N = 1344 13.1 -> 12.3, M = 5, K = 8640, N = 4592 (72) 17.0 -> 15.8, M = 9, K = 2176,
+//   N = 4000 10.30 -> 10.32, M = 28, K = 1152, N = 2752 9.8 -> 10.3; beyond 128 tiles of 32 x 64 it loses (INT8, M = 99, K = 9024, N = 2864 19.8 -> 25.9);
+//   fewer than 16 were not measured
 inline int plan_kpar_blocks(bool i8, int M, int N, int G, int ksplit_override = 0) {
     if (ksplit_override > 0) return kKparNone;
     const long tn = (N + 63) / 64, t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
+    if (t32 <= 128 && t32 >= 16 && G >= (i8 ? 20 : 52)) return kKparNarrow;
     if (t32 <= 256) return kKpar1x8;
     if (t64 <= 256) return i8 ? kKpar2x8 : kKpar2x4;
     if (t128 <= 256) return i8 && G < 128 ? kKpar2x4 : kKpar4x8;
@@ -428,8 +436,17 @@ inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, i
     if (act_override > 0 || tile_rows == 0 || rank <= 0 || rank > 128) return old;
     const long slices = (M + 15) / 16;
     ActPlan pl = old;
-    pl.waves = G > 96 ? 8 : 4;
-    pl.gchunk = G > 96 ? 24 : G > 12 ? 12 : G;
+    // Two groups to a wavefront while that fills the CUs once (three for a narrow branch with a long K, and where wide tiles add the
+    // runs for fewer columns): us per forward, 12 or 24 groups per run -> 8: M = 2, K = 1600, N = 7968, rank 128 12.0 -> 10.7; M = 10, K = 10944, N = 9680,
+    // rank 128 27.8 -> 21.3; M = 13, K = 1664, N = 6448, rank 64 10.5 -> 9.6; M = 5, K = 6976, N = 10400, rank 32 16.1 -> 15.3; rank 32, M = 16, K = 10240, N = 1728
+    // 15.9 -> 16.3 (12: 15.7); M = 390, K = 7424, N = 1184 (375 workgroups) 19.0 -> 20.0
+    pl.waves = 4;
+    pl.gchunk = tile_cols > 64 || (rank <= 32 && G > 144) ? 12 : 8;
+    if (slices * ((G + 7) / 8) > 256) {
+        pl.waves = G > 96 ? 8 : 4;
+        pl.gchunk = G > 96 ? 24 : 12;
+    }
+    if (pl.gchunk > G) pl.gchunk = G;
     pl.chunks = (G + pl.gchunk - 1) / pl.gchunk;
     pl.whole = 0; pl.chunks0 = 1; pl.gchunk0 = G;
     pl.deposit = pl.chunks > 1;
@@ -437,6 +454,10 @@ inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, i
     if (slices * pl.chunks > 512 || pl.chunks > 64 || tiles * tile_rows * rank * 4 * pl.chunks > 64l << 20) return old;
     return pl;
 }
+// Where partial H is left for the GEMM, H itself is never made in memory; its first 16 bytes name the place of the parts instead, for
+// svdq_debug_act: two words that no sum of products gives (a NaN with this payload), the number of runs, and how many 256-byte
+// units behind H the parts [runs][Mpad][rank] start.
+constexpr uint32_t kHInParts0 = 0x7fc5eed1u, kHInParts1 = 0x7fd0e571u;
 // the value a workgroup leaves in its arrival word; the word is cleared again before the kernel ends, so whatever a
 // fresh workspace holds is taken for "not arrived" (anything but this one 64-bit value)
 constexpr unsigned long long kActArrived = 0x5356445141525256ull;
@@ -461,6 +482,16 @@ inline bool act_use_small_plan(W &w, const ActPlan &a, int rank) {
     w.hpart_off = w.partial_off;
     w.aflags_off = w.hpart_off + h;
     return true;
+}
+
+// INT8 batches that act_w8_small_kernel.hip takes, of those whose plan cuts K (at most 128 slices): where the GEMM adds the runs'
+// partial H itself (kpar); where a launch of its own has to, from K = 3136 on or with few slices.  us per forward, walking or one-pass
+// kernel -> this one: M = 1, K = 3648, N = 5200 17.5 -> 11.3; M = 14, K = 5760, N = 1568 22.5 -> 13.8; M = 4, K = 10048, N = 1232 24.7 -> 18.7;
+// M = 3, K = 1408, N = 1584 10.6 -> 8.1; M = 664, K = 6976, N = 1824 39.7 -> 30.7; M = 1293, K = 6016, N = 1616 45.7 -> 39.5; with the launch: M = 1104, K = 7424, N = 9408
+// 108 -> 97; M = 600, K = 3072, N = 12288 40.6 -> 38.3; M = 1337, K = 3072, N = 9216 51.0 -> 51.3 and M = 1412, K = 1664, N = 10816 42.0 -> 43.9 (not taken).
+inline bool act_w8_small(int M, int K, int rank, int kpar) {
+    const int G = K / kGroup;
+    return G <= 192 && rank <= 32 && (kpar || G > 48 || (M + 15) / 16 <= 48);
 }
 
 // The int8 MFMA takes twice the time of the 4-bit one per step of 64 channels, so a split of the 8-bit GEMM's K loop pays
@@ -523,7 +554,7 @@ inline WorkspaceFp4 workspace_layout_fp4(int M, int K, int N, int rank, int kspl
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(ap, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(ap, w.Mpad) * 8) : 0);
     const int kpar = plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override);
-    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, kpar ? kpar_rows(kpar) : 0, kpar ? 64 : 0), rank);
+    act_use_small_plan(w, plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, kpar ? kpar_rows(kpar) : 0, kpar ? kpar_cols(kpar) : 0), rank);
     return w;
 }
 

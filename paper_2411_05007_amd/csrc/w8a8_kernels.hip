@@ -54,7 +54,7 @@ __global__ void debug_act_w8_kernel(DebugActW8Params p) {
         p.out_codes[idx] = (int8_t)p.codes[i8_code_offset(k, p.Mpad, m)];
     }
     if (p.out_sx && idx < (size_t)p.M) p.out_sx[idx] = p.sx[idx];
-    if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = p.H[idx];
+    if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = h_element(p.H, idx, p.Mpad, p.rank);
 }
 
 template <int RB, int CB>

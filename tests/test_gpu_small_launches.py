@@ -112,6 +112,22 @@ def test_activation_in_one_pass(torch, fmt, M, K, N, r):  # noqa: F811
     _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"one pass {M}x{K}x{N}", window=False)
 
 
+# INT8: four tokens to a quantizing workgroup beside workgroups that project runs of K (csrc/act_w8_small_kernel.hip): tokens off four and
+# sixteen, half a unit of 128 channels at the end, every number of units per wavefront, one and two rank steps and none, a GEMM that adds
+# the runs on every kind of its tiles (32 x 32 ones among them) and one that needs H whole
+@pytest.mark.parametrize("M,K,N,r", [(1, 1472, 528, 16), (5, 1408, 1040, 32), (18, 2112, 4176, 0), (67, 4160, 1552, 32), (130, 6208, 2064, 16), (3, 12288, 784, 32),
+                                     (290, 3136, 2064, 32), (600, 640, 1552, 16), (1030, 1216, 2064, 32), (700, 576, 6160, 32), (1100, 3200, 4112, 16)])
+def test_w8a8_small_batches(torch, M, K, N, r):  # noqa: F811
+    _block_format(torch, "w8a8", M, K, N, r, None)
+
+
+# MXFP4 on 32 x 32 tiles with sixteen wavefronts: K off four steps, fewer steps than the wavefronts ask ahead, ragged M and N, ranks with
+# more steps than a wavefront has, H ready-made and added from runs
+@pytest.mark.parametrize("M,K,N,r", [(1, 3328, 1040, 32), (33, 3520, 1552, 128), (64, 6144, 2064, 0), (17, 8256, 4112, 48)])
+def test_mxfp4_on_narrow_tiles(torch, M, K, N, r):  # noqa: F811
+    _block_format(torch, "fp4", M, K, N, r, (32, 32))
+
+
 def _block_format(torch, fmt, M, K, N, r, tile):  # noqa: F811
     from tests import test_gpu_fp4, test_gpu_w8a8
     rng = np.random.default_rng(5400 + M + K + N)
