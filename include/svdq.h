@@ -168,13 +168,15 @@ typedef struct {
 size_t svdq_workspace_bytes(int M, const svdq_shape *shape);
 
 /*
- * The hot path (Eq. 5; kernel split after Sec. 4.3 / Fig. 6b): two kernels on `hip_stream`
+ * The hot path (Eq. 5; kernel split after Sec. 4.3 / Fig. 6b): two kernels on `hip_stream` (three for many tokens at ranks
+ * above 64, where runs' partial H are added up between them)
  *   1. activation kernel: reads X once; smoothing, per-group INT4 quantization with fp16 scales,
  *      and the down projection H = X^ L1
  *   2. W4A4 GEMM: the INT4 codes go through the matrix core as exact 6-bit floats, one instruction per group of
  *      64 with the exact integer group sum as its fp32 result; fp32 rescale by s_x s_w (the scale products of a
  *      32 x 32 block come from an f16 MFMA), accumulated on top of H L2 in the same registers; bias, bf16 store.
- *   X  device bf16 [M x K] row-major, 16-byte aligned;  Y device bf16 [M x N] row-major.
+ *   X  device bf16 [M x K] row-major, 16-byte aligned;  Y device bf16 [M x N] row-major: may hold partial H before it holds the
+ *   output (it does not if it shares memory with X).
  *   workspace: device, 256-byte aligned, >= svdq_workspace_bytes(M, shape); contents are
  *   overwritten; two forwards that share a workspace must be ordered on one stream.
  *   M = 0 is a no-op.  hip_stream is a hipStream_t (NULL = the default stream).
@@ -229,7 +231,7 @@ int svdq_debug_group_acc(const svdq_layer_dev *layer, const void *workspace, int
  *   [0] runs per 16-token slice of the activation kernel, [1] groups of 64 channels per run, [2] wavefronts per
  *   workgroup, [3] how many leading slices are cut differently, into [4] runs of [5] groups (runs <= 1: walked whole),
  *   [6] workgroups of the activation kernel, [7] its LDS bytes per workgroup (launches that take the one-pass activation
- *   kernel, one workgroup per slice, use none of [0] to [7]),
+ *   kernel, one workgroup per slice, or the one of 64-token workgroups use none of [0] to [7]),
  *   [8] output tiles of the GEMM, [9] how many of them have their K loop split, [10] into how many workgroups,
  *   [11] workgroups of the GEMM,
  *   [12] bytes / 256 of the workspace from the parked partial H on (which lies in the place of the partial tiles of a split
@@ -338,7 +340,8 @@ int svdq_w4a16_forward(const svdq_layer_dev *layer, const void *X, int M, void *
  * behaviour are those of their INT4 namesakes; wcodes holds one int8 per weight (K * Npad bytes, operand order
  * of the int8 matrix-core instruction), wscales fp16 [Npad].  The forward enqueues two kernels (quantization with
  * the down projection, GEMM); three for batches of at most 2048 tokens whose K is above 6144 (3072 for ranks above 32, any
- * K for ranks above 64) and cut into runs, where the first kernel runs twice (the tokens' maxima, then everything else).  The K / rank limits of svdq_linear_forward apply; K * Npad and K * Mpad below 2^31.
+ * K for ranks above 64) and cut into runs, where the first kernel runs twice (the tokens' maxima, then everything else), or of small launches whose GEMM does not
+ * add up the runs' partial H.  The K / rank limits of svdq_linear_forward apply; K * Npad and K * Mpad below 2^31.
  * The workspace also holds, for launches of few tiles with a long K, the int32 partial tiles and arrival counters of a
  * split K loop (integer sums: the same bits as the unsplit loop); svdq_w8a8_workspace_bytes follows the calling
  * thread's SVDQ_OPT_KSPLIT bits like its INT4 namesake.

@@ -110,19 +110,24 @@ struct W4Stage {
         a2 = (c8 & 1) ? (c8 == 1 ? 768 + 4 * r8 : a) : a + 4;
         b2 = (c8 & 1) ? (c8 == 1 ? 768 + 4 * (r8 + 8) : b) : b + 4;
     }
-    // the 48 bits of codes and the scale of token r8 (alo, ahi, sa) and of token r8 + 8
-    __device__ __forceinline__ void put(unsigned char *stage, uint32_t alo, uint32_t ahi, uint32_t sa, uint32_t blo, uint32_t bhi, uint32_t sb) const {
+    // the 48 bits of codes and the scale of token r8 (alo, ahi, sa) and of token r8 + 8 as the words that go to a, b, a2, b2
+    __device__ __forceinline__ void words(uint32_t alo, uint32_t ahi, uint32_t sa, uint32_t blo, uint32_t bhi, uint32_t sb, uint32_t &a1, uint32_t &b1, uint32_t &a2v,
+                                          uint32_t &b2v) const {
         // Two neighbouring lanes hold the 16 codes of one triple = 96 bits: dword 0 is the even lane's low word,
         // dword 1 the even lane's high 16 bits and the odd lane's low 16, dword 2 the rest of the odd lane.
         const uint32_t na = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)alo, 0xB1, 0xf, 0xf, true);      // the pair's other lane
         const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)blo, 0xB1, 0xf, 0xf, true);
         const bool odd = c8 & 1;
-        const uint32_t a1 = odd ? ((alo >> 16) | (ahi << 16)) : alo;                // first store: dword 2 (odd) or dword 0 (even)
-        const uint32_t b1 = odd ? ((blo >> 16) | (bhi << 16)) : blo;
+        a1 = odd ? ((alo >> 16) | (ahi << 16)) : alo;                // first store: dword 2 (odd) or dword 0 (even)
+        b1 = odd ? ((blo >> 16) | (bhi << 16)) : blo;
+        a2v = odd ? (c8 == 1 ? sa : a1) : (ahi | (na << 16));        // second: the scale, dword 2 again, or dword 1
+        b2v = odd ? (c8 == 1 ? sb : b1) : (bhi | (nb << 16));
+    }
+    __device__ __forceinline__ void put(unsigned char *stage, uint32_t alo, uint32_t ahi, uint32_t sa, uint32_t blo, uint32_t bhi, uint32_t sb) const {
         // (all four words are made before the first is stored: made in between the stores, the second two cost the ranks
         // above 64 four registers and, with a long K, 1 us of a launch: M = 4608, K = 12288, rank 128 71.2 against 69.9)
-        const uint32_t a2v = odd ? (c8 == 1 ? sa : a1) : (ahi | (na << 16));        // second: the scale, dword 2 again, or dword 1
-        const uint32_t b2v = odd ? (c8 == 1 ? sb : b1) : (bhi | (nb << 16));
+        uint32_t a1, b1, a2v, b2v;
+        words(alo, ahi, sa, blo, bhi, sb, a1, b1, a2v, b2v);
         *reinterpret_cast<uint32_t *>(stage + a) = a1;
         *reinterpret_cast<uint32_t *>(stage + b) = b1;
         *reinterpret_cast<uint32_t *>(stage + a2) = a2v;

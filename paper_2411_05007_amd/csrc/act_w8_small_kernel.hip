@@ -14,7 +14,6 @@
 
 #include "act_common.h"
 #include "buffer.h"
-#include "gemm_kpar.h"
 #include "kernels.h"
 #include "layout.h"
 #include "lds_limit.h"
@@ -160,21 +159,6 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_w8_small_kernel(ActParams 
     }
 }
 
-// H from the runs' partial sums, for a GEMM that does not add them itself
-__global__ __launch_bounds__(256) void act_sum_h_kernel(const float *hpart, int runs, int M, int Mpad, int rank, float *H, uint8_t *hfrag) {
-    const int octets = rank / 8, idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * octets) return;
-    const int m = idx / octets, col = 8 * (idx - m * octets);
-    const KparH h = kpar_sum_h(hpart, runs, Mpad, rank, m, col);
-    uint4 hi, lo;
-    kpar_split_h(h, hi, lo);
-    float4 *o = reinterpret_cast<float4 *>(H + (size_t)m * rank + col);
-    o[0] = make_float4(h.h[0], h.h[1], h.h[2], h.h[3]);
-    o[1] = make_float4(h.h[4], h.h[5], h.h[6], h.h[7]);
-    *reinterpret_cast<uint4 *>(hfrag + hfrag_offset(rank, m, col, 0)) = hi;
-    *reinterpret_cast<uint4 *>(hfrag + hfrag_offset(rank, m, col, 1)) = lo;
-}
-
 template <int RB, int UN>
 hipError_t launch_small(const ActParams &p, hipStream_t stream) {
     auto k = act_w8_small_kernel<RB, UN>;
@@ -206,12 +190,6 @@ hipError_t launch_act_w8_small(const ActParams &p, int flags, hipStream_t stream
     if (rank > 0 && (!p.hpart || p.chunks < 1 || (size_t)p.gchunk * p.chunks < (size_t)p.G || (p.chunks - 1) * p.gchunk >= p.G)) return hipErrorInvalidValue;      // runs that cover K, none empty
     if (rank == 0) return launch_units<0>(p, stream);
     return rank <= 16 ? launch_units<1>(p, stream) : launch_units<2>(p, stream);
-}
-
-hipError_t launch_act_sum_h(const ActParams &p, hipStream_t stream) {
-    if (p.M <= 0 || p.rank <= 0) return hipSuccess;
-    hipLaunchKernelGGL(act_sum_h_kernel, dim3((unsigned)((p.M * (p.rank / 8) + 255) / 256)), dim3(256), 0, stream, p.hpart, p.chunks, p.M, p.Mpad, p.rank, p.H, p.hfrag);
-    return hipGetLastError();
 }
 
 }  // namespace svdq

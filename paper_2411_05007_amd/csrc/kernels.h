@@ -43,8 +43,11 @@ bool act_one_pass(int fmt, int M, int K, int rank);
 // INT8, small batches (act_w8_small_kernel.hip): quantizes as above and leaves the partial H of p.chunks runs of p.gchunk groups in p.hpart
 hipError_t launch_act_w8_small(const ActParams &p, int flags, hipStream_t stream);
 constexpr int kActW8SmallGroups = 192;      // K up to 12288: what sixteen wavefronts hold of four tokens
-// H (and its bf16 parts) from those runs, for a GEMM that does not add them itself
-hipError_t launch_act_sum_h(const ActParams &p, hipStream_t stream);
+// INT4 and MXFP4, ranks up to 128, 64 tokens to a workgroup (act_wide_kernel.hip): quantizes and leaves the partial H of p.chunks runs of p.gchunk
+// groups in p.hpart, fp32 [p.chunks][M][rank]
+hipError_t launch_act_wide(const ActParams &p, hipStream_t stream);
+// H (and its bf16 parts) from such parts, [p.chunks][rows][rank], where the GEMM does not add them itself
+hipError_t launch_act_sum_h(const ActParams &p, int rows, hipStream_t stream);
 
 // W4A4 GEMM on the block-scaled matrix instruction: INT4 codes as 6-bit float operands, exact fp32 group sums,
 // scale tiles from an f16 MFMA, one FMA per partial sum (gemm_w4a4_kernel.hip; layouts in layout.h)

@@ -454,6 +454,25 @@ inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, i
     if (slices * pl.chunks > 512 || pl.chunks > 64 || tiles * tile_rows * rank * 4 * pl.chunks > 64l << 20) return old;
     return pl;
 }
+// INT4 and MXFP4 launches of wide branches that take the kernel of 64-token workgroups (act_wide_kernel.hip): the number of runs that K
+// is cut into (0: they do not), for `room` runs' partial H: up to two workgroups per CU, at least six groups to a run.
+// us per forward at rank 128, act_kernel.hip -> this: INT4 M = 4608, K = 12288, N = 3072 247 -> 230, M = 1096, K = 9728, N = 1184 63.4 -> 45.8, M = 780, K = 11520,
+// N = 8240 127 -> 117, M = 2595, K = 5632, N = 5136 121.5 -> 114.4; MXFP4 M = 1432, K = 9856, N = 2720 84.9 -> 61.6, M = 1415, K = 6144, N = 2256 59.8 -> 46.3,
+// M = 1386, K = 2752, N = 5376 41.0 -> 36.2.  Not taken: few tokens (M = 512, K = 12288, N = 3072 43.9 | 45.1; M = 482, K = 6784, N = 7920 49.3 | 49.9), which 16-token
+// workgroups spread further; many tokens with a short K (M = 4608, K = 3072, N = 12288 215 | 218; M = 4539, K = 3520, N = 9408 210 | 215), whose sum launch
+// is not earned back.  At rank 64 (half the fragments) M = 4608, K = N = 3072 72.8 | 74.6.
+constexpr int kActWideTokens = 64;
+inline int plan_act_wide(int M, int G, int rank, size_t room) {
+    if (rank <= 64 || rank > 128 || M < 576 || G < 40 || (M > 3000 && G < 72)) return 0;
+    const int tiles = (M + kActWideTokens - 1) / kActWideTokens;
+    size_t runs = tiles < 512 ? 512 / tiles : 1;
+    if (runs > (size_t)((G + 5) / 6)) runs = (G + 5) / 6;
+    if (runs > room) runs = room;
+    if (runs < 1) return 0;
+    const int gc = (G + (int)runs - 1) / (int)runs;
+    return (G + gc - 1) / gc;
+}
+
 // Where partial H is left for the GEMM, H itself is never made in memory; its first 16 bytes name the place of the parts instead, for
 // svdq_debug_act: two words that no sum of products gives (a NaN with this payload), the number of runs, and how many 256-byte
 // units behind H the parts [runs][Mpad][rank] start.

@@ -112,6 +112,36 @@ def test_activation_in_one_pass(torch, fmt, M, K, N, r):  # noqa: F811
     _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"one pass {M}x{K}x{N}", window=False)
 
 
+# wide branches, 64 tokens to an activation workgroup, partial H in the output's memory or in the workspace (csrc/act_wide_kernel.hip): tokens
+# off 64, groups off the runs, runs shorter than the ring has stages, ranks off 128, room for one run only
+@pytest.mark.parametrize("M,K,N,r", [(577, 2560, 1040, 128), (1100, 2624, 528, 80), (700, 5632, 144, 112), (3010, 4672, 272, 128)])
+@pytest.mark.parametrize("fmt", ["int4", "fp4"])
+def test_wide_branches(torch, fmt, M, K, N, r):  # noqa: F811
+    if fmt == "fp4":
+        return _block_format(torch, fmt, M, K, N, r, None)
+    rng = np.random.default_rng(5800 + M + K + N)
+    prep = _layer(rng, K, N, r)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    x[:, rng.choice(K, max(1, K // 100), replace=False)] *= 50
+    sample = np.unique(np.concatenate([np.arange(40), np.arange(M - 70, M), rng.integers(0, M, 60)]))
+    print(f"wide branch: M={M} K={K} N={N} r={r}", flush=True)
+    _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"wide branch {M}x{K}x{N}", window=False)
+
+
+def test_wide_branch_into_any_output(torch):  # noqa: F811
+    """The output's memory holds partial sums only where it can: not where it is the input's, and not at an odd address.  Bound:
+    sums in another order, 2e-5 in the 2-norm (see perf/cases.py)."""
+    M, K = 640, 2560
+    rng = np.random.default_rng(5900)
+    layer = S.DeviceLayer(_layer(rng, K, K, 128))
+    x = S.bf16_tensor_from_bits(O.bf16_round(rng.standard_normal((M, K)).astype(np.float32)))
+    y = layer.forward(x).float()
+    odd = torch.empty(M * K + 8, dtype=torch.bfloat16, device=x.device)[1:1 + M * K].view(M, K)
+    for out in (odd, x.clone()):
+        got = layer.forward(x if out is odd else out, out=out).float()
+        assert ((got - y).norm() / y.norm()).item() < 1.5e-4
+
+
 # INT8: four tokens to a quantizing workgroup beside workgroups that project runs of K (csrc/act_w8_small_kernel.hip): tokens off four and
 # sixteen, half a unit of 128 channels at the end, every number of units per wavefront, one and two rank steps and none, a GEMM that adds
 # the runs on every kind of its tiles (32 x 32 ones among them) and one that needs H whole
