@@ -42,7 +42,7 @@ struct W8Tile {
     static constexpr int kRingBytes = 4 * kStageBytes;               // four stages
     static constexpr int kOutBytes = 4 * 32 * kOutRow;
     static constexpr int kLdsBytes = kRingBytes > kOutBytes ? kRingBytes : kOutBytes;
-    static_assert(RB + CB >= 4 && RB + CB <= 6, "four to six operand blocks per wavefront");
+    static_assert(RB + CB >= 4 && RB + CB <= 8, "four to eight operand blocks per wavefront");
 };
 typedef __attribute__((address_space(3))) void *lds_ptr;
 constexpr int kI8RowBytes = 32;      // bytes of one row of one 32-channel step
@@ -57,8 +57,9 @@ __global__ void debug_act_w8_kernel(DebugActW8Params p) {
     if (p.out_H && idx < (size_t)p.M * p.rank) p.out_H[idx] = h_element(p.H, idx, p.Mpad, p.rank);
 }
 
-template <int RB, int CB>
-__global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_w8a8_kernel(GemmW8Params p) {
+// SPREAD: requests and LDS reads of a step stand between its products, not in front of them
+template <int RB, int CB, bool SPREAD>
+__global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : RB * CB <= 9 ? 2 : 1) void gemm_w8a8_kernel(GemmW8Params p) {
     using T = W8Tile<RB, CB>;
     constexpr int kRB = RB, kCB = CB, kWM = T::kWM, kWN = T::kWN, kBM = T::kBM, kBN = T::kBN;
     constexpr int kFragsA = T::kFragsA, kStageBytes = T::kStageBytes, kOutRowW8 = T::kOutRow;
@@ -102,8 +103,8 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_w8a8_kernel(Ge
     // dealt to the four wavefronts, blocks w, w + 4 and w + 8 to wavefront w (one kilobyte each; lane l's 16 bytes
     // land at l * 16 of the block, which is the operand order).  Which operand a block belongs to is uniform per wavefront.
     const int glast = g_end - 1;
-    __amdgpu_buffer_rsrc_t rs_d[3];      // (of which the first T::kReq)
-    int d_base[3], d_stride[3], d_lane[3];
+    __amdgpu_buffer_rsrc_t rs_d[4];      // (of which the first T::kReq)
+    int d_base[4], d_stride[4], d_lane[4];
 #pragma unroll
     for (int i = 0; i < T::kReq; ++i) {
         const int j = wave + 4 * i;
@@ -126,13 +127,14 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_w8a8_kernel(Ge
     const uint32_t rd_a = lds_base + lane * 16 + (wm0 / 32) * 1024;
     const uint32_t rd_b = lds_base + lane * 16 + (kFragsA + wn0 / 32) * 1024;
 #define SVDQ_LDS_READ(F, I, STAGE) \
-    if ((I) < RB + CB) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[I]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) - kRB) * 1024))
+    if ((I) < RB + CB) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[(I) % (RB + CB)]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) % (RB + CB) - kRB) * 1024))
 #define SVDQ_READ_STAGE(F, STAGE) \
     SVDQ_LDS_READ(F, 0, STAGE); SVDQ_LDS_READ(F, 1, STAGE); SVDQ_LDS_READ(F, 2, STAGE); \
-    SVDQ_LDS_READ(F, 3, STAGE); SVDQ_LDS_READ(F, 4, STAGE); SVDQ_LDS_READ(F, 5, STAGE);
+    SVDQ_LDS_READ(F, 3, STAGE); SVDQ_LDS_READ(F, 4, STAGE); SVDQ_LDS_READ(F, 5, STAGE); SVDQ_LDS_READ(F, 6, STAGE); SVDQ_LDS_READ(F, 7, STAGE);
     // all LDS reads of this wavefront have returned; tied to the registers they fill, so that nothing that uses them moves above
 #define SVDQ_READS_DONE(F)                                                                                                                    \
-    if (RB + CB == 6) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 2]), "+v"(F.f[kRB + kCB - 1])); \
+    if (RB + CB == 8) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 4]), "+v"(F.f[kRB + kCB - 3]), "+v"(F.f[kRB + kCB - 2]), "+v"(F.f[kRB + kCB - 1])); \
+    else if (RB + CB == 6) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 2]), "+v"(F.f[kRB + kCB - 1])); \
     else if (RB + CB == 5) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]), "+v"(F.f[kRB + kCB - 1])); \
     else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(F.f[0]), "+v"(F.f[1]), "+v"(F.f[2]), "+v"(F.f[3]))
 
@@ -149,21 +151,47 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_w8a8_kernel(Ge
     // its own requests for step g + 1 have landed (all but the newest six, which are those for steps g + 2 and g + 3),
     // one barrier (now every wavefront's share of step g + 1 is in LDS, and everybody has read step g out of its stage,
     // during step g - 1), read step g + 1 into the other register set, request step g + 4 into the stage that step g
-    // has just left, 8 or 9 MFMAs.
+    // has just left, 4 to 16 MFMAs.
+    // Bound: half power (zero activations run 12 to 20 % faster), half L2 reads (15 TB/s inside the loop of the 192 x 128 tile).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     SVDQ_READ_STAGE(f0, 0)
     SVDQ_READS_DONE(f0);
+    // one product and the one or two requests behind it
+#define SVDQ_W8_ITEM(I, SEL, nxt)                                                                                     \
+    SVDQ_LDS_READ(nxt, I, (SEL + 1) & 3);                                                                             \
+    if ((I) >= RB + CB && (I) < RB + CB + T::kReq) {                                                                  \
+        constexpr int i = (I) >= RB + CB && (I) < RB + CB + T::kReq ? (I) - RB - CB : 0;                              \
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_d[i], (lds_ptr)(st + i * 4096), 16, d_lane[i], d_base[i] + gd * d_stride[i], 0, 0); \
+    }
+#define SVDQ_W8_SLOT(J, SEL, cur, nxt)                                                                                \
+    if ((J) < RB * CB) {                                                                                              \
+        constexpr int r = (J) / CB % RB, c = (J) % CB;                                                                \
+        iacc[r][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(intx4, cur.f[r]), __builtin_bit_cast(intx4, cur.f[kRB + c]), iacc[r][c], 0, 0, 0); \
+        if (!SPREAD) {                                                                                                \
+        } else if (RB + CB + T::kReq <= RB * CB) {                                                                    \
+            SVDQ_W8_ITEM(J, SEL, nxt)                                                                                 \
+        } else {                                                                                                      \
+            SVDQ_W8_ITEM(2 * J, SEL, nxt)                                                                             \
+            SVDQ_W8_ITEM(2 * J + 1, SEL, nxt)                                                                         \
+        }                                                                                                             \
+        if (SPREAD) __builtin_amdgcn_sched_barrier(0);                                                                \
+    }
 #define SVDQ_W8_STEP(SEL, cur, nxt)                                                                                  \
     if (g0 + SEL < g_end) {                                                                                           \
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq) : "memory");                                                              \
         __builtin_amdgcn_s_barrier();                                                                                 \
-        SVDQ_READ_STAGE(nxt, (SEL + 1) & 3)                                                                           \
-        dma(g0 + SEL + 4, SEL);                                                                             \
+        const int gd = g0 + SEL + 4 < glast ? g0 + SEL + 4 : glast;                                                   \
+        unsigned char *st = lds + SEL * kStageBytes + wave * 1024;                                                    \
+        if (!SPREAD) {                                                                                                \
+            SVDQ_READ_STAGE(nxt, (SEL + 1) & 3)                                                                       \
+            dma(g0 + SEL + 4, SEL);                                                                                   \
+        }                                                                                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                            \
-        _Pragma("unroll") for (int r = 0; r < kRB; ++r)                                                               \
-            _Pragma("unroll") for (int c = 0; c < kCB; ++c)                                                           \
-                iacc[r][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(intx4, cur.f[r]), __builtin_bit_cast(intx4, cur.f[kRB + c]), iacc[r][c], 0, 0, 0); \
+        SVDQ_W8_SLOT(0, SEL, cur, nxt) SVDQ_W8_SLOT(1, SEL, cur, nxt) SVDQ_W8_SLOT(2, SEL, cur, nxt) SVDQ_W8_SLOT(3, SEL, cur, nxt) \
+        SVDQ_W8_SLOT(4, SEL, cur, nxt) SVDQ_W8_SLOT(5, SEL, cur, nxt) SVDQ_W8_SLOT(6, SEL, cur, nxt) SVDQ_W8_SLOT(7, SEL, cur, nxt) \
+        SVDQ_W8_SLOT(8, SEL, cur, nxt) SVDQ_W8_SLOT(9, SEL, cur, nxt) SVDQ_W8_SLOT(10, SEL, cur, nxt) SVDQ_W8_SLOT(11, SEL, cur, nxt) \
+        SVDQ_W8_SLOT(12, SEL, cur, nxt) SVDQ_W8_SLOT(13, SEL, cur, nxt) SVDQ_W8_SLOT(14, SEL, cur, nxt) SVDQ_W8_SLOT(15, SEL, cur, nxt) \
         __builtin_amdgcn_sched_barrier(0);                                                                            \
         SVDQ_READS_DONE(nxt);                                                                                         \
     }
@@ -282,13 +310,13 @@ hipError_t launch_debug_act_w8(const DebugActW8Params &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int RB, int CB>
+template <int RB, int CB, bool SPREAD>
 static hipError_t launch_w8_tile(const GemmW8Params &p, hipStream_t stream) {
     using T = W8Tile<RB, CB>;
     const int tiles_m = (p.M + T::kBM - 1) / T::kBM, tiles_n = (p.N + T::kBN - 1) / T::kBN;
     // H, L2, the scales and the bias are read with plain loads: every tile must lie inside the padded rows and columns
     if (tiles_m * T::kBM > p.Mpad || tiles_n * T::kBN > p.Npad) return hipErrorInvalidValue;
-    auto k = gemm_w8a8_kernel<RB, CB>;
+    auto k = gemm_w8a8_kernel<RB, CB, SPREAD>;
     // the limit on dynamic LDS is raised once per instantiation, not per launch
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;
@@ -308,14 +336,25 @@ hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream) {
     if (p.ksplit < 1 || (p.ksplit > 1 && (!p.partial || !p.counters))) return hipErrorInvalidValue;
     const int G = p.K / kGroup;
     if (p.ksplit > 1 && (size_t)(p.ksplit - 1) * (((G + p.ksplit - 1) / p.ksplit + 3) / 4 * 4) >= (size_t)G) return hipErrorInvalidValue;
-    if (p.ksplit > 1) return launch_w8_tile<2, 4>(p, stream);
+    if (p.ksplit > 1) return launch_w8_tile<2, 4, false>(p, stream);
     // the tile shape follows the MXFP4 GEMM's rule
     const GemmPlanFp4 plan = plan_gemm_fp4(p.M, p.N, G, 1);
+    // 256 x 256 tiles, one per CU, where a CU has two of 128 x 256: two thirds of the bytes from the L2 per product and three quarters of the LDS
+    // reads, but nobody to work while a workgroup fills its ring or stores its tile, which a long K loop has to earn back.  us per forward,
+    // 128 x 256 | 256 x 256: M = 4608, K = 12288, N = 3072 241 | 226, M = 2048, K = 9216, N = 8192 152 | 145, M = 1500, K = 8192, N = 9008 122.2 | 114.9,
+    // M = 3000, K = N = 4608 83.7 | 79.6; K = 4096 (M = 1024, N = 16000) 70.4 | 70.6, K = 3072 (M = 1664, N = 8192) 56.4 | 57.8; in a second round of
+    // the CUs (M = 2048, K = 3072, N = 9216, 288 tiles) 78.1 | 99.8.
+    if (plan.tile == 0 && plan.tiles > 256 && G >= 72 && (long)((p.M + 255) / 256) * ((p.N + 255) / 256) <= 256) return launch_w8_tile<4, 4, true>(p, stream);
+    // What a step asks of memory holds its products back where it stands in front of them and no other workgroup of the CU has products
+    // meanwhile; with several workgroups it is better asked for early.  us per forward, in front | between: 192 x 192 M = 4608, K = 3072,
+    // N = 12288 175 | 168; 192 x 128 up to one tile per CU M = 3129, K = 11456, N = 1648 4 % faster, beyond M = 1311, K = 8576, N = 6464 (357 tiles)
+    // 114.5 | 118.1, M = 3758, K = 1216, N = 2688 (420) 30.9 | 31.7; 128 x 128 up to 768 tiles (three per CU) -1 to +6 % (M = 823, K = 3776, N = 8128
+    // 1.6 % faster), M = 3837, K = 4992, N = 4944 (1170) 131.8 | 133.7; 128 x 256 M = 4119, K = 1408, N = 5392 62.5 | 63.7.
     switch (plan.tile) {
-        case 0: return launch_w8_tile<2, 4>(p, stream);
-        case 1: return launch_w8_tile<3, 3>(p, stream);
-        case 2: return launch_w8_tile<3, 2>(p, stream);
-        case 3: return launch_w8_tile<2, 2>(p, stream);
+        case 0: return launch_w8_tile<2, 4, false>(p, stream);
+        case 1: return launch_w8_tile<3, 3, true>(p, stream);
+        case 2: return plan.tiles <= 256 ? launch_w8_tile<3, 2, true>(p, stream) : launch_w8_tile<3, 2, false>(p, stream);
+        case 3: return plan.tiles <= 768 ? launch_w8_tile<2, 2, true>(p, stream) : launch_w8_tile<2, 2, false>(p, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -112,6 +112,12 @@ def test_activation_in_one_pass(torch, fmt, M, K, N, r):  # noqa: F811
     _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"one pass {M}x{K}x{N}", window=False)
 
 
+# INT8 on 256 x 256 tiles (csrc/w8a8_kernels.hip): last rows and columns of a tile, steps off the ring, the shortest K, all 256 CUs, three ranks
+@pytest.mark.parametrize("M,K,N,r", [(2561, 4672, 5136, 48), (3841, 4608, 3856, 16), (2310, 4864, 6160, 0)])
+def test_w8a8_on_large_tiles(torch, M, K, N, r):  # noqa: F811
+    _block_format(torch, "w8a8", M, K, N, r, None)
+
+
 # wide branches, 64 tokens to an activation workgroup, partial H in the output's memory or in the workspace (csrc/act_wide_kernel.hip): tokens
 # off 64, groups off the runs, runs shorter than the ring has stages, ranks off 128, room for one run only
 @pytest.mark.parametrize("M,K,N,r", [(577, 2560, 1040, 128), (1100, 2624, 528, 80), (700, 5632, 144, 112), (3010, 4672, 272, 128)])
