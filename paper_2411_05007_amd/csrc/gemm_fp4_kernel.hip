@@ -57,6 +57,7 @@ struct Fp4Tile {
     static constexpr int kOutBytes = 4 * 32 * kOutRow;
     static constexpr int kLdsBytes = kRingBytes > kOutBytes ? kRingBytes : kOutBytes;
     static_assert(RB + CB >= 4 && RB + CB <= 6, "four to six operand blocks per wavefront");
+    static constexpr bool kSpreads = RB + CB + kReq <= RB * CB;      // a step's reads and requests are no more than its products
 };
 typedef __attribute__((address_space(3))) void *lds_ptr;
 constexpr int kFmtE2M1 = 4;                  // operand format selector of the instruction
@@ -66,7 +67,8 @@ __device__ __forceinline__ intx8 as_operand(u32x4 v) {
     return intx8{(int)v.x, (int)v.y, (int)v.z, (int)v.w, 0, 0, 0, 0};
 }
 
-template <int RB, int CB>
+// SPREAD: requests and LDS reads of a step stand between its products, not in front of them
+template <int RB, int CB, bool SPREAD>
 __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(GemmFp4Params p) {
     using T = Fp4Tile<RB, CB>;
     constexpr int kRB = RB, kCB = CB, kWM = T::kWM, kWN = T::kWN, kBM = T::kBM, kBN = T::kBN;
@@ -118,11 +120,13 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(Gem
 
     struct Frags { u32x4 f[kRB + kCB]; };      // the wavefront's activation blocks, then its weight blocks
     struct Scales { uint32_t a[kRB], b[kCB]; };
+    auto load_scale = [&](Scales &s, int q, int i) {
+        if (i < kRB) s.a[i] = __builtin_amdgcn_raw_buffer_load_b32(rs_sa, lane * 4, sa_base + q * sa_stride + i * 256, 0);
+        else s.b[i - kRB] = __builtin_amdgcn_raw_buffer_load_b32(rs_sb, lane * 4, sb_base + q * sb_stride + (i - kRB) * 256, 0);
+    };
     auto load_scales = [&](Scales &s, int q) {
 #pragma unroll
-        for (int r = 0; r < kRB; ++r) s.a[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_sa, lane * 4, sa_base + q * sa_stride + r * 256, 0);
-#pragma unroll
-        for (int c = 0; c < kCB; ++c) s.b[c] = __builtin_amdgcn_raw_buffer_load_b32(rs_sb, lane * 4, sb_base + q * sb_stride + c * 256, 0);
+        for (int i = 0; i < kRB + kCB; ++i) load_scale(s, q, i);
     };
     // Memory -> LDS without a stop in registers: the twelve operand blocks of a step (activation blocks first) are
     // dealt to the four wavefronts, blocks w, w + 4 and w + 8 to wavefront w (one kilobyte each; lane l's 16 bytes
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(Gem
     const uint32_t rd_a = lds_base + lane * 16 + (wm0 / 32) * 1024;
     const uint32_t rd_b = lds_base + lane * 16 + (kFragsA + wn0 / 32) * 1024;
 #define SVDQ_LDS_READ(F, I, STAGE) \
-    if ((I) < RB + CB) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[I]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) - kRB) * 1024))
+    if ((I) < RB + CB) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(F.f[(I) % (RB + CB)]) : "v"((I) < kRB ? rd_a : rd_b), "n"((STAGE) * kStageBytes + ((I) < kRB ? (I) : (I) % (RB + CB) - kRB) * 1024))
 #define SVDQ_READ_STAGE(F, STAGE) \
     SVDQ_LDS_READ(F, 0, STAGE); SVDQ_LDS_READ(F, 1, STAGE); SVDQ_LDS_READ(F, 2, STAGE); \
     SVDQ_LDS_READ(F, 3, STAGE); SVDQ_LDS_READ(F, 4, STAGE); SVDQ_LDS_READ(F, 5, STAGE);
@@ -185,41 +189,78 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(Gem
     // everybody has read step g out of its stage, during step g - 1), read step g + 1 into the other register set,
     // request step g + 4 into the stage that step g has just left, 8 or 9 MFMAs.  A step's operands are thus requested
     // three steps before they are read (one step later, as the first version did, runs at the same speed on large
-    // launches and 3 % slower on small ones: the loop does not wait for memory).  Timing-only variants at the headline
-    // shape: the MFMAs alone 70 us, the data movement alone 60 us (LDS busy nine tenths of that: 36 KB per workgroup and
-    // step through a 128-byte port), both 99 us - the two overlap only in part.
+    // launches and 3 % slower on small ones).  192 x 192 tiles issue a step's reads and requests between its products.
     // The wait names how many newer requests may still be in flight: the three each of steps g + 2 and g + 3, and in
     // the two steps behind selector 0 the six scale loads of the next four steps, which were issued between them.
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (as a builtin, which the compiler takes into account: what it believed to be outstanding here, it waited for in the loop)
+    __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     SVDQ_READ_STAGE(f0, 0)
     SVDQ_READS_DONE(f0);
-#define SVDQ_FP4_STEP(SEL, cur, nxt)                                                                                  \
-    if (g0 + SEL < g_end) {                                                                                           \
-        if (SEL == 1 || SEL == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq + kRB + kCB) : "memory");                \
-        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq) : "memory");                                                         \
+    // one product and the read or request behind it; behind the first six of selector 0 also the scale bytes of the next four steps
+    // (the counts above do not depend on the order within a step)
+#define SVDQ_FP4_SLOT(J, SEL, cur, nxt, MORE)                                                                          \
+    if ((J) < RB * CB) {                                                                                              \
+        constexpr int r = (J) / CB % RB, c = (J) % CB;                                                                \
+        acc[r][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_operand(cur.f[r]), as_operand(cur.f[kRB + c]), acc[r][c], \
+                                                                    kFmtE2M1, kFmtE2M1, SEL, (int)sc.a[r], SEL, (int)sc.b[c]); \
+        if (SPREAD) {                                                                                                 \
+            SVDQ_LDS_READ(nxt, J, (SEL + 1) & 3);                                                                     \
+            if (MORE && SEL == 0 && (J) < RB + CB) load_scale(sn, qn, (J) % (RB + CB));                               \
+            if ((J) >= RB + CB && (J) < RB + CB + T::kReq) {                                                          \
+                constexpr int i = (J) >= RB + CB && (J) < RB + CB + T::kReq ? (J) - RB - CB : 0;                      \
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_d[i], (lds_ptr)(st + i * 4096), 16, d_lane[i], d_base[i] + gd * d_stride[i], 0, 0); \
+            }                                                                                                         \
+            __builtin_amdgcn_sched_barrier(0);                                                                        \
+        }                                                                                                             \
+    }
+    // MORE: with the scale bytes of the next four steps
+#define SVDQ_FP4_STEP(SEL, cur, nxt, MORE)                                                                            \
+    {                                                                                                                 \
+        if (MORE && (SEL == 1 || SEL == 2)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq + kRB + kCB) : "memory"); \
+        else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * T::kReq) : "memory");                                       \
         __builtin_amdgcn_s_barrier();                                                                                 \
-        SVDQ_READ_STAGE(nxt, (SEL + 1) & 3)                                                                           \
-        if (SEL == 0) load_scales(sn, q + 1 < q_end ? q + 1 : q);                                                     \
-        dma(g0 + SEL + 4, SEL);                                                                             \
+        const int gd = g0 + SEL + 4 < glast ? g0 + SEL + 4 : glast;                                                   \
+        unsigned char *st = lds + SEL * kStageBytes + wave * 1024;                                                    \
+        if (!SPREAD) {                                                                                                \
+            SVDQ_READ_STAGE(nxt, (SEL + 1) & 3)                                                                       \
+            if (MORE && SEL == 0) load_scales(sn, qn);                                                                \
+            dma(g0 + SEL + 4, SEL);                                                                                   \
+        }                                                                                                             \
         __builtin_amdgcn_sched_barrier(0);                                                                            \
-        _Pragma("unroll") for (int r = 0; r < kRB; ++r)                                                               \
-            _Pragma("unroll") for (int c = 0; c < kCB; ++c)                                                           \
-                acc[r][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_operand(cur.f[r]), as_operand(cur.f[kRB + c]), acc[r][c], \
-                                                                            kFmtE2M1, kFmtE2M1, SEL, (int)sc.a[r], SEL, (int)sc.b[c]); \
+        SVDQ_FP4_SLOT(0, SEL, cur, nxt, MORE) SVDQ_FP4_SLOT(1, SEL, cur, nxt, MORE) SVDQ_FP4_SLOT(2, SEL, cur, nxt, MORE) \
+        SVDQ_FP4_SLOT(3, SEL, cur, nxt, MORE) SVDQ_FP4_SLOT(4, SEL, cur, nxt, MORE) SVDQ_FP4_SLOT(5, SEL, cur, nxt, MORE) \
+        SVDQ_FP4_SLOT(6, SEL, cur, nxt, MORE) SVDQ_FP4_SLOT(7, SEL, cur, nxt, MORE) SVDQ_FP4_SLOT(8, SEL, cur, nxt, MORE) \
         __builtin_amdgcn_sched_barrier(0);                                                                            \
         SVDQ_READS_DONE(nxt);                                                                                         \
     }
-    for (int q = q_begin; q < q_end; ++q) {
-        const int g0 = 4 * q;
+    // Four steps at a time without a condition between them: the compiler counts the requests on the shortest way to the use of
+    // the scale bytes, and its wait let all but one of the ring's requests land once every four steps.  us per forward with such a
+    // wait and without: M = 4608, K = 3072, N = 12288 115.0 | 109.3, M = 1337, K = 3072, N = 9216 39.3 | 35.1, M = 1000, K = 8000, N = 5120
+    // 49.0 | 42.4, M = 1500, K = 1152, N = 4608 20.5 | 17.0; M = 4608, K = 1216, N = 12288 66.1 | 66.4.
+    const int q_full = g_end / 4;
+    for (int q = q_begin; q < q_full; ++q) {
+        const int g0 = 4 * q, qn = q + 1 < q_end ? q + 1 : q;
         Scales sn;
-        SVDQ_FP4_STEP(0, f0, f1)
-        SVDQ_FP4_STEP(1, f1, f0)
-        SVDQ_FP4_STEP(2, f0, f1)
-        SVDQ_FP4_STEP(3, f1, f0)
+        SVDQ_FP4_STEP(0, f0, f1, true)
+        SVDQ_FP4_STEP(1, f1, f0, true)
+        SVDQ_FP4_STEP(2, f0, f1, true)
+        SVDQ_FP4_STEP(3, f1, f0, true)
         sc = sn;
     }
+    if (q_full < q_end) {      // the last one to three steps
+        const int g0 = 4 * q_full, qn = q_full;
+        Scales sn;
+        (void)qn; (void)sn;
+        SVDQ_FP4_STEP(0, f0, f1, false)
+        if (g0 + 1 < g_end) {
+            SVDQ_FP4_STEP(1, f1, f0, false)
+            if (g0 + 2 < g_end) SVDQ_FP4_STEP(2, f0, f1, false)
+        }
+    }
 #undef SVDQ_FP4_STEP
+#undef SVDQ_FP4_SLOT
     // the ring becomes the epilogue's staging area: every request of every wavefront must have landed first
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -298,7 +339,7 @@ hipError_t launch_fp4_tile(const GemmFp4Params &p, hipStream_t stream) {
     // H, L2 and the bias are read with plain loads: every tile must lie inside the padded rows and columns
     if (tiles_m * T::kBM > p.Mpad || tiles_n * T::kBN > p.Npad) return hipErrorInvalidValue;
     const dim3 grid(tiles_m * tiles_n * p.ksplit), block(256);
-    auto k = gemm_fp4_kernel<RB, CB>;
+    auto k = gemm_fp4_kernel<RB, CB, Fp4Tile<RB, CB>::kSpreads>;
     // the limit on dynamic LDS is raised once per instantiation, not per launch
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), T::kLdsBytes); e != hipSuccess) return e;
