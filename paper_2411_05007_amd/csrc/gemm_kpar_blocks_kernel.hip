@@ -62,6 +62,7 @@ __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_ker
     const __amdgpu_buffer_rsrc_t rs_sb = make_rsrc(p.bw, I8 ? 0 : fp4_scale_bytes(p.steps, p.Npad));
     const int n = wave < p.steps ? (p.steps - wave + KS - 1) / KS : 0;      // this wavefront's steps
 
+    static_assert(KS % 4 == 0, "");
     struct Set { u32x4 a[RB], b[CB]; uint32_t sa[I8 ? 1 : RB], sb[I8 ? 1 : CB]; };
     Set S[DEPTH];
     auto load = [&](Set &s, int i) {
@@ -75,16 +76,22 @@ __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_ker
 #pragma unroll
         for (int r = 0; r < RB; ++r) s.a[r] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_a, va, oa + r * 1024, 0));
         if constexpr (!I8) {
-            const int osa = (st >> 2) * p.Mpad * 8 + gm0 * 8 + (st & 3), osb = (st >> 2) * p.Npad * 8 + gn0 * 8 + (st & 3);
+            // (whole dwords, which hold the bytes of four steps: of a byte's load the compiler masks the result, at the top of the K loop
+            // for all sets at once)
+            const int osa = (st >> 2) * p.Mpad * 8 + gm0 * 8, osb = (st >> 2) * p.Npad * 8 + gn0 * 8;
 #pragma unroll
-            for (int c = 0; c < CB; ++c) s.sb[c] = __builtin_amdgcn_raw_buffer_load_b8(rs_sb, vs, osb + c * 256, 0);
+            for (int c = 0; c < CB; ++c) s.sb[c] = __builtin_amdgcn_raw_buffer_load_b32(rs_sb, vs, osb + c * 256, 0);
 #pragma unroll
-            for (int r = 0; r < RB; ++r) s.sa[r] = __builtin_amdgcn_raw_buffer_load_b8(rs_sa, vs, osa + r * 256, 0);
+            for (int r = 0; r < RB; ++r) s.sa[r] = __builtin_amdgcn_raw_buffer_load_b32(rs_sa, vs, osa + r * 256, 0);
         }
     };
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) load(S[d], d);
-    __builtin_amdgcn_sched_barrier(0);      // the first operands are requested before H and L2
+    for (int d = 0; d < DEPTH; ++d) {
+        load(S[d], d);
+        // the first operands are requested before H and L2, and one step's before the next one's: mixed here, the wait at the top of the
+        // K loop, which is the same for its first and every later round, is one for all of them
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
     if constexpr (I8) {
         // What Eq. 2 and the 16-bit branch need of this wavefront's share of the outputs, requested while the first
@@ -143,19 +150,27 @@ __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_ker
         for (int r = 0; r < RB; ++r)
 #pragma unroll
             for (int c = 0; c < CB; ++c) acc[r][c] = intx16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        for (int i = 0; i < n; i += DEPTH) {
+        auto multiply = [&](int d) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    acc[r][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(intx4, S[d].a[r]), __builtin_bit_cast(intx4, S[d].b[c]), acc[r][c], 0, 0, 0);
+        };
+        // whole rounds of DEPTH steps without a way out between them (the compiler counts the requests on the shortest way to a set's use:
+        // with one, every round began with a wait for all of them), then what is left, already requested.  us per forward before and
+        // after: MXFP4, rank 32, M = 512, K = N = 3072 16.9 | 15.3, M = 1024 21.9 | 19.6, rank 64, M = 300, K = 6144, N = 4096 25.4 | 22.3
+        int i = 0;
+        for (; i + DEPTH <= n; i += DEPTH)
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {
-                if (d > 0 && i + d >= n) break;
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int r = 0; r < RB; ++r)
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        acc[r][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(intx4, S[d].a[r]), __builtin_bit_cast(intx4, S[d].b[c]), acc[r][c], 0, 0, 0);
+                multiply(d);
                 load(S[d], i + d + DEPTH);
             }
-        }
+#pragma unroll
+        for (int d = 0; d + 1 < DEPTH; ++d)
+            if (i + d < n) multiply(d);
         int f[RB][CB][16];
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -232,21 +247,29 @@ __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_ker
                 gemm_lowrank_multiply<RB, CB>(acc, o);
             }
         }
-        for (int i = 0; i < n; i += DEPTH) {
+        auto multiply = [&](int d) {
+            __builtin_amdgcn_sched_barrier(0);
+            int shift = (wave & 3) * 8;      // the wavefront's place in every chunk of four steps
+            asm volatile("" : "+s"(shift));  // shifted here, not where the loads return
+            auto op = [](u32x4 v) { return intx8{(int)v.x, (int)v.y, (int)v.z, (int)v.w, 0, 0, 0, 0}; };      // 4-bit formats: the first four registers
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    acc[r][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(op(S[d].a[r]), op(S[d].b[c]), acc[r][c], kFmtE2M1, kFmtE2M1,
+                                                                               0, (int)(S[d].sa[I8 ? 0 : r] >> shift), 0, (int)(S[d].sb[I8 ? 0 : c] >> shift));
+        };
+        // (rounds as above; of two steps the second may be past the end and multiply zeros: a remainder's own copy of the registers spills)
+        int i = 0;
+        for (; DEPTH == 2 ? i < n : i + DEPTH <= n; i += DEPTH)
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {
-                if (d > 0 && i + d >= n) break;
-                __builtin_amdgcn_sched_barrier(0);
-                auto op = [](u32x4 v) { return intx8{(int)v.x, (int)v.y, (int)v.z, (int)v.w, 0, 0, 0, 0}; };      // 4-bit formats: the first four registers
-#pragma unroll
-                for (int r = 0; r < RB; ++r)
-#pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        acc[r][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(op(S[d].a[r]), op(S[d].b[c]), acc[r][c], kFmtE2M1, kFmtE2M1,
-                                                                                   0, (int)S[d].sa[I8 ? 0 : r], 0, (int)S[d].sb[I8 ? 0 : c]);
+                multiply(d);
                 load(S[d], i + d + DEPTH);
             }
-        }
+#pragma unroll
+        for (int d = 0; d + 1 < DEPTH; ++d)
+            if (DEPTH > 2 && i + d < n) multiply(d);
         float f[RB][CB][16];
 #pragma unroll
         for (int r = 0; r < RB; ++r)
