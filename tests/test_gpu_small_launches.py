@@ -212,3 +212,11 @@ def test_int4_group_sums_are_exact(torch, M, K, N, rows):  # noqa: F811
         want[:, g::G] = x[:, g] @ qw.reshape(G, 64, N)[g][:, g::G].astype(np.int64)
     assert np.abs(want).max() > 100
     assert np.array_equal(O.bf16_to_f32(S.bits_from_bf16_tensor(y)), want.astype(np.float32))
+
+
+# MXFP4 in large tiles of every shape: K loops of one, two and three steps more than whole rounds of four, of fewer than four, a rank that
+# is no power of two; launches whose wavefronts share K: steps off the rounds of two, four and six
+@pytest.mark.parametrize("M,K,N,r", [(1530, 320, 12272, 32), (1530, 704, 12272, 48), (4100, 192, 3088, 16), (1337, 1472, 9200, 32), (2040, 1728, 3072, 0),
+                                     (1000, 2240, 5136, 32), (257, 1984, 2064, 32), (100, 2368, 3088, 64), (1024, 1856, 3072, 16)])
+def test_mxfp4_steps_off_the_rounds(torch, M, K, N, r):  # noqa: F811
+    _block_format(torch, "fp4", M, K, N, r, None)
