@@ -46,8 +46,7 @@ struct MidTile {
     static constexpr int KS = 2;                                                // shares of K
     static constexpr int kBM = 128, kBN = 32 * C;
     static constexpr int kABytes = 4 * kW4ABlock;                               // 7168
-    static constexpr int kBlocksB = (C + 1) / 2;                                // weight blocks of 64 columns that cover the tile wherever it starts
-    static constexpr int kPieces = (kABytes + kBlocksB * kW4BBlock + 1023) / 1024;
+    static constexpr int kPieces = mid_pieces(C);                               // a kilobyte each: activation blocks, then weight blocks
     static constexpr int kReq = (kPieces + 3) / 4;                              // direct-to-LDS requests per wavefront and group
     static constexpr int kStage = kReq * 4096;
     static constexpr int kStages = 4;
@@ -82,8 +81,8 @@ __global__ __launch_bounds__(512, 1) void gemm_w4a4_mid_kernel(GemmW4Params p) {
     kpar_tile_of((int)blockIdx.x, tiles_m, tiles_n, 4 * kW4ABlock, C * kW4BBlock / 2, tile_m, tile_n);
     const int gm0 = tile_m * T::kBM, gn0 = tile_n * T::kBN;      // rows: inside the padded rows; columns: the last tile may reach past the padded ones
 
-    // ---- memory -> LDS: the tile's four activation blocks and kBlocksB weight blocks are contiguous in memory, one kilobyte piece
-    // after the other dealt to the share's four wavefronts; what lies past a buffer's end arrives as zeros
+    // ---- memory -> LDS: the tile's four activation blocks and its weight blocks are contiguous in memory, one kilobyte piece after the
+    // other dealt to the share's four wavefronts; weight blocks past the padded columns are not asked for (layout.h, mid_piece)
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.xa, w4_a_bytes(p.G, p.Mpad));
     const __amdgpu_buffer_rsrc_t rs_b = make_rsrc(p.wb, w4_b_bytes(p.G, p.Npad));
     const int a_stride = (p.Mpad / 32) * kW4ABlock, b_stride = (p.Npad / 64) * kW4BBlock;
@@ -93,10 +92,11 @@ __global__ __launch_bounds__(512, 1) void gemm_w4a4_mid_kernel(GemmW4Params p) {
     for (int k = 0; k < T::kReq; ++k) {
         const int j = w4 + 4 * k;
         const bool is_a = j < 7;
-        piece_off[k] = is_a ? (gm0 / 32) * kW4ABlock + j * 1024 : j < T::kPieces ? (gn0 / 64) * kW4BBlock + (j - 7) * 1024 : 0;
+        const MidPiece piece = mid_piece(j, lane, T::kPieces, gm0, gn0, p.Npad);
+        piece_off[k] = piece.base;
         piece_stride[k] = is_a ? a_stride : b_stride;
         piece_rs[k] = is_a ? rs_a : rs_b;
-        piece_lane[k] = j < T::kPieces ? lane * 16 : (int)0x80000000u;      // no such piece: beyond the buffer (smaller than 2^31 bytes)
+        piece_lane[k] = piece.lane;      // (or beyond the buffer, which is smaller than 2^31 bytes)
     }
     const int steps = (p.G + KS - 1) / KS, own = (p.G - share + KS - 1) / KS;      // the workgroup's steps, and those in which this share has a group
     unsigned char *ring = lds + share * (T::kStages * T::kStage);

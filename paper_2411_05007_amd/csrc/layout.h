@@ -113,7 +113,7 @@ inline __host__ __device__ size_t i8_code_offset(int k, int rows_pad, int row) {
 //             four consecutive steps, picked by the instruction's byte selector
 // so one 32-row block of one step is one contiguous kilobyte of codes, loaded with one 16-byte load per lane.
 constexpr int kFp4Block = 32;
-// Loads of the MXFP4 and INT8 GEMMs that ask for nothing (a step past the wavefront's last, a place of the ring that a tile
+// Loads of the GEMMs that ask for nothing (a step past the wavefront's last, a place of the ring that a tile
 // has no block for) get their zeros from a lane offset of 2^31, beyond every buffer.  Their uniform offset stays inside the
 // buffer all the same: what a range check makes of one beyond it depends on whether it is part of the check.
 //   the step a wavefront's i-th load belongs to (wavefront w of KS has steps w, w + KS, ..., n of them):
@@ -279,6 +279,19 @@ inline SmallInt4 plan_small_int4(int M, int N, int G, int rank, int ksplit_overr
         }
     }
     return s;
+}
+
+// What gemm_w4a4_mid_kernel.hip brings from memory per group for a tile of 128 x (32 blocks) at (gm0, gn0): one-kilobyte pieces, 0 to 6 from
+// the tile's four activation blocks, the rest from the weight blocks of 64 columns that cover it wherever it starts.  A piece's uniform
+// byte offset counts from the start of the group's blocks.  The last tile of a row may reach past the padded columns: what lies past the
+// group's weight blocks (behind the last group: past the buffer) is not asked for, by the rule above (kpar_step).
+constexpr int mid_weight_blocks(int blocks) { return (blocks + 1) / 2; }
+constexpr int mid_pieces(int blocks) { return (4 * kW4ABlock + mid_weight_blocks(blocks) * kW4BBlock + 1023) / 1024; }
+struct MidPiece { int base, lane; };      // uniform offset, lane offset
+inline __host__ __device__ MidPiece mid_piece(int j, int lane, int pieces, int gm0, int gn0, int Npad) {
+    if (j < 7) return MidPiece{(gm0 / 32) * kW4ABlock + j * 1024, lane * 16};
+    const int at = (gn0 / 64) * kW4BBlock + (j - 7) * 1024, end = (Npad / 64) * kW4BBlock;
+    return MidPiece{j < pieces && at < end ? at : 0, j < pieces && at + lane * 16 < end ? lane * 16 : (int)0x80000000u};
 }
 
 // MXFP4 and INT8 (gemm_kpar_blocks_kernel.hip): one MFMA per block and step and nothing behind it, so these variants are bound

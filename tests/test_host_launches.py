@@ -89,7 +89,7 @@ int main() {
     long checked = 0;
     // K-sharing kernels: every wavefront's loads up to the ring's depth past its last step; a block is a kilobyte
     for (int steps = 1; steps <= 40; ++steps)
-        for (int KS : {4, 8})
+        for (int KS : {4, 8, 16})
             for (int wave = 0; wave < KS; ++wave) {
                 const int n = wave < steps ? (steps - wave + KS - 1) / KS : 0;
                 for (int i = 0; i <= n + 6; ++i) {
@@ -98,8 +98,8 @@ int main() {
                     ++checked;
                 }
             }
-    // ring kernels: the four tiles, the last tile of the padded rows and columns, every place of the ring, the last step
-    const int tiles[4][2] = {{4, 8}, {6, 6}, {6, 4}, {4, 4}};
+    // ring kernels: their tiles, the last tile of the padded rows and columns, every place of the ring, the last step
+    const int tiles[5][2] = {{4, 8}, {6, 6}, {6, 4}, {4, 4}, {8, 8}};
     for (auto &t : tiles)
         for (int rows = 1; rows <= 9; ++rows)
             for (int cols = 1; cols <= 9; ++cols) {
@@ -112,6 +112,28 @@ int main() {
                             ++checked;
                         }
             }
+    // 128 x (32 blocks) tiles of the INT4 kernel: every tile of a launch (the last one of a row may reach past the padded columns), the last group.
+    // A lane asks for nothing or for 16 bytes of its group's weight blocks, and what the tile has of them is asked for
+    for (int blocks : {5, 6})
+        for (int N = 16; N <= 12 * kRowPad; N += 16) {
+            const int Npad = round_up(N, kRowPad), G = 3, pieces = mid_pieces(blocks);
+            const long slab = (long)(Npad / 64) * kW4BBlock, whole = (long)w4_b_bytes(G, Npad);
+            for (int gn0 = 0; gn0 < N; gn0 += 32 * blocks)
+                for (int j = 7; j < (pieces + 3) / 4 * 4; ++j)
+                    for (int lane = 0; lane < 64; ++lane) {
+                        const MidPiece p = mid_piece(j, lane, pieces, 0, gn0, Npad);
+                        const long want = gn0 / 64 * (long)kW4BBlock + (j - 7) * 1024 + lane * 16, first = p.base + (G - 1) * slab;
+                        const bool asks = p.lane >= 0, wanted = j < pieces && want < slab;
+                        if (p.base < 0 || first >= whole || (asks && first + p.lane + 16 > whole) || (!asks && p.lane != (int)0x80000000u) || asks != wanted || (asks && p.base + p.lane != want))
+                            return printf("%d blocks, N %d, column %d, piece %d, lane %d: %ld of %ld\n", blocks, N, gn0, j, lane, first + p.lane, whole), 1;
+                        ++checked;
+                    }
+        }
+    for (int gm0 = 0; gm0 < 4 * kRowPad; gm0 += 128)
+        for (int j = 0; j < 7; ++j)
+            for (int lane = 0; lane < 64; ++lane)
+                if (const MidPiece p = mid_piece(j, lane, mid_pieces(5), gm0, 0, kRowPad); p.base + p.lane != (long)w4_a_block(0, 4 * kRowPad, gm0) + j * 1024 + lane * 16 || p.base + p.lane + 16 > (long)w4_a_bytes(1, 4 * kRowPad))
+                    return printf("row %d, piece %d\n", gm0, j), 1;
     return printf("ok %ld\n", checked), 0;
 }
 """
