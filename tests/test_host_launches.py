@@ -24,8 +24,8 @@ def record(tmp_path_factory):
     subprocess.run([cxx, "-std=c++17", "-O1", "-rdynamic", os.path.join(HERE, "host_launch_recorder.cpp"), "-o", exe, "-ldl"], check=True)
 
     def run(calls):
-        """One list of records per call (device, format, M, K, N, rank[, options]); all calls in one process."""
-        text = "".join(" ".join(str(v) for v in (c if len(c) == 7 else (*c, 0))) + "\n" for c in calls)
+        """One list of records per call (device, format, M, K, N, rank[, options[, output]]); all calls in one process."""
+        text = "".join(" ".join(str(v) for v in (*c, 0, 0)[:8]) + "\n" for c in calls)
         r = subprocess.run([exe, S.LIB_PATH], input=text, capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stderr
         out, cur = [], []
