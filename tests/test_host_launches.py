@@ -170,6 +170,19 @@ def test_w8a8_short_rows_take_the_walking_activation_kernel(record, M, K, N, r, 
     assert [x for x in record([(0, W8A8, M, K, N, r)])[0] if x[0] == "launch"][0][5] == threads
 
 
+def _kernels(rec):
+    return [x[2] for x in rec if x[0] == "launch"]
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r", [(FP4, 2, 4352, 240, 128), (FP4, 48, 4736, 160, 128), (FP4, 9, 4864, 160, 112), (INT4, 131, 5056, 5104, 112),
+                                         (INT4, 72, 3008, 11840, 128), (INT4, 4, 12160, 144, 112), (STATIC, 119, 5184, 7712, 128)])
+def test_runs_too_many_for_the_gemm_give_way_to_longer_ones(record, fmt, M, K, N, r):
+    """The short runs of a small launch may leave more partial H than the workspace holds or than the tiles should read: then
+    the longer runs, whose partial H the GEMM adds too, and not the meeting of a slice's runs in the activation kernel."""
+    gemm = _kernels(record([(0, fmt, M, K, N, r)])[0])[-1]
+    assert "kpar" in gemm and gemm.endswith(",true>"), gemm
+
+
 @pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
 def test_the_static_workspace_runs_the_ordinary_launches(record, M, K, N, r):
     """Ordinary workspaces of small launches are larger than the static array for the room of a K split that such launches do
