@@ -444,7 +444,8 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
 //   K = N = 3072, rank 32: M = 512 20.6 -> 18.4 (4, 12), 18.6 (8, 16), 19.1 (8, 24); M = 1024 29.5 -> 27.4 (4, 12); M = 2048 43.5 -> 40.2 (4, 12)
 //   M = 64, K = 12288, N = 3072: 22.1 -> 20.0 (4, 12), 19.8 (8, 24); M = 512 41.7 -> 39.7 (4, 12), 37.6 (8, 24); M = 256, K = N = 1152 12.2 -> 10.3 (4, 12)
 //   rank 128, K = N = 3072: M = 64 17.8 -> 14.1 (4, 12), M = 512 26.3 -> 24.3;  M = 512, K = 12288: 48.4 -> 54.1 (201 MB: not taken)
-// fine: shorter runs where the launch does not fill the CUs; there are more of them, and act_use_small_plan may have to take the longer ones.
+// fine: shorter runs where the launch does not fill the CUs (act_short_runs); there are more of them, and act_use_small_plan may have to
+// take the longer ones.
 inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, int tile_rows, int tile_cols, bool fine) {
     const ActPlan old = plan_act(M, G, rank, act_override);
     if (act_override > 0 || tile_rows == 0 || rank <= 0 || rank > 128) return old;
@@ -502,6 +503,11 @@ inline size_t act_arrival_words(const ActPlan &a, int Mpad) {
     return (a.whole > 0 && a.chunks0 > 1 ? (size_t)a.chunks0 * a.whole : 0) + (a.chunks > 1 ? (size_t)a.chunks * (Mpad / 16 - a.whole) : 0);
 }
 
+// A K of 9 to 12 groups is one long run, whose H the activation kernel makes by itself, or two short ones that every tile adds.  us per forward,
+// one run | two: MXFP4 32-row tiles 4 to 12 % faster in two (M = 136, K = 640, N = 9248, rank 96 on 128-row tiles 15.1 | 17.3, M = 713, K = 576,
+// N = 1408, rank 32 11.5 | 12.3); INT4 32-row tiles at ranks from 48 on 3 to 5 % faster, narrower ones 9.4 | 9.6 (M = 6, K = 576, N = 7136), taller tiles
+// M = 365, K = 640, N = 6016, rank 96 16.5 | 19.3, M = 986, K = 704, N = 6544, rank 32 21.9 | 23.6.
+inline bool act_short_runs(bool int4, int G, int rank, int tile_rows) { return G > 12 || (int4 ? tile_rows <= 32 && rank >= 48 : tile_rows <= 64); }
 // Gives a workspace a plan of plan_act_small where what that plan parks fits into what the workspace holds from
 // partial_off on: the launches it is made for leave the room of the GEMM's partial tiles unused, and
 // a workspace's size stays what callers may have kept from the plan above.
@@ -522,9 +528,10 @@ inline bool act_plan_fits(W &w, const ActPlan &a, int rank) {
 // slice (MXFP4 M = 69, K = 7296, N = 6304, rank 112 22.9 | 28.0), more tokens or 128-row tiles (INT4 M = 323, K = 3904, N = 5824, rank 64 28.8 | 32.2).
 inline bool act_longer_runs(int M, int G, int tile_rows) { return tile_rows > 0 && tile_rows <= 64 && M <= (G <= 96 ? 256 : 16); }
 template <typename W>
-inline void act_use_small_plan(W &w, int M, int N, int G, int rank, int act_override, int tile_rows, int tile_cols) {
-    if (act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, true), rank)) return;
-    if (act_longer_runs(M, G, tile_rows)) act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, false), rank);
+inline void act_use_small_plan(W &w, bool int4, int M, int N, int G, int rank, int act_override, int tile_rows, int tile_cols) {
+    const bool fine = act_short_runs(int4, G, rank, tile_rows);
+    if (act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, fine), rank)) return;
+    if (fine && act_longer_runs(M, G, tile_rows)) act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, false), rank);
 }
 
 // INT8 batches that act_w8_small_kernel.hip takes, of those whose plan cuts K (at most 128 slices): where the GEMM adds the runs'
@@ -597,7 +604,7 @@ inline WorkspaceFp4 workspace_layout_fp4(int M, int K, int N, int rank, int kspl
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(ap, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(ap, w.Mpad) * 8) : 0);
     const int kpar = plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override);
-    act_use_small_plan(w, M > 0 ? M : 1, N, G, rank, act_override, kpar ? kpar_rows(kpar) : 0, kpar ? kpar_cols(kpar) : 0);
+    act_use_small_plan(w, false, M > 0 ? M : 1, N, G, rank, act_override, kpar ? kpar_rows(kpar) : 0, kpar ? kpar_cols(kpar) : 0);
     return w;
 }
 
@@ -629,13 +636,14 @@ inline Workspace workspace_layout(int M, int K, int N, int rank, int ksplit_over
     const bool parked = w.act.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(w.act, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(w.act, w.Mpad) * 8) : 0);
-    ActPlan small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols(), true);
-    if (!small.deposit && small.chunks > 1 && act_longer_runs(M > 0 ? M : 1, G, sm.rows())) small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols(), false);
+    const bool fine = act_short_runs(true, G, rank, sm.rows());
+    ActPlan small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols(), fine);
+    if (fine && !small.deposit && small.chunks > 1 && act_longer_runs(M > 0 ? M : 1, G, sm.rows())) small = plan_act_small(M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols(), false);
     if (no_split && small.deposit) {
         const size_t need = w.partial_off + align256(act_parked_floats(small, w.Mpad, rank) * 4) + align256(act_arrival_words(small, w.Mpad) * 8);
         if (w.total < need) w.total = need;
     }
-    act_use_small_plan(w, M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols());
+    act_use_small_plan(w, true, M > 0 ? M : 1, N, G, rank, act_override, sm.rows(), sm.cols());
     return w;
 }
 

@@ -183,6 +183,15 @@ def test_runs_too_many_for_the_gemm_give_way_to_longer_ones(record, fmt, M, K, N
     assert "kpar" in gemm and gemm.endswith(",true>"), gemm
 
 
+@pytest.mark.parametrize("fmt,M,K,N,r,runs", [(FP4, 136, 640, 9248, 96, 1), (FP4, 713, 576, 1408, 32, 1), (INT4, 6, 576, 7136, 16, 1), (INT4, 365, 640, 6016, 96, 1),
+                                              (INT4, 986, 704, 6544, 32, 1), (INT4, 217, 576, 2320, 32, 1), (FP4, 33, 640, 1040, 96, 2), (INT4, 33, 640, 1040, 96, 2), (INT4, 33, 832, 1040, 16, 2)])
+def test_nine_to_twelve_groups_are_cut_for_small_tiles_only(record, fmt, M, K, N, r, runs):
+    """Two runs' partial H are read by every tile: of a K this short only 32-row tiles (INT4: of a branch of 48 columns or more), and
+    MXFP4's 64-row tiles, earn that back."""
+    act = [x for x in record([(0, fmt, M, K, N, r)])[0] if x[0] == "launch"][0]
+    assert act[2].startswith("act_kernel<") and act[3] == -(-M // 16) * runs, act
+
+
 @pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
 def test_the_static_workspace_runs_the_ordinary_launches(record, M, K, N, r):
     """Ordinary workspaces of small launches are larger than the static array for the room of a K split that such launches do
