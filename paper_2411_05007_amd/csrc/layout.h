@@ -481,16 +481,29 @@ inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, i
 // M = 1386, K = 2752, N = 5376 41.0 -> 36.2.  Not taken: few tokens (M = 512, K = 12288, N = 3072 43.9 | 45.1; M = 482, K = 6784, N = 7920 49.3 | 49.9), which 16-token
 // workgroups spread further; many tokens with a short K (M = 4608, K = 3072, N = 12288 215 | 218; M = 4539, K = 3520, N = 9408 210 | 215), whose sum launch
 // is not earned back.  At rank 64 (half the fragments) M = 4608, K = N = 3072 72.8 | 74.6.
+// Few workgroups with long runs, where a layer of few columns or the static workspace has room for few runs only, leave CUs idle: a run of n
+// groups takes its workgroup n x 1.1 us (MXFP4 M = 2595, K = 2560, N = 272 26.6 | 44.3; INT4, static, M = 3019, K = 7488, N = 304, rank 112 51.6 | 134.7).
+// INT4's other kernel is the faster one of the two formats', and how good it is depends on its own plan (`other`).  Runs on eight wavefronts are slow
+// (M = 1445, K = 5440, N = 416, rank 112 39.7 | 30.1), and so are seven or more groups to a wavefront on more than one round of workgroups (M = 2419, K = 4160,
+// N = 304, rank 96 34.2 | 29.4, M = 1579, K = 5312, N = 448 35.7 | 31.0); fewer lose to an even load only (M = 2790, K = 2624, N = 400, rank 96, 308 workgroups, a
+// second one on a few of the CUs 28.7 | 30.8; M = 577, K = 2752, N = 2576, 80 workgroups 24.1 | 25.9; M = 622, K = 6144, N = 4576, rank 80 42.0 | 44.1).
+// The lines are those between faster and slower of 3100 forwards: of those taken 1 in 150 is slower, by 2 to 6 %.
 constexpr int kActWideTokens = 64;
-inline int plan_act_wide(int M, int G, int rank, size_t room) {
+inline int plan_act_wide(bool int4, const ActPlan &other, int M, int G, int rank, size_t room) {
     if (rank <= 64 || rank > 128 || M < 576 || G < 40 || (M > 3000 && G < 72)) return 0;
     const int tiles = (M + kActWideTokens - 1) / kActWideTokens;
     size_t runs = tiles < 512 ? 512 / tiles : 1;
     if (runs > (size_t)((G + 5) / 6)) runs = (G + 5) / 6;
     if (runs > room) runs = room;
     if (runs < 1) return 0;
-    const int gc = (G + (int)runs - 1) / (int)runs;
-    return (G + gc - 1) / gc;
+    const int gc = (G + (int)runs - 1) / (int)runs, cut = (G + gc - 1) / gc, workgroups = tiles * cut;
+    if (!int4) return gc <= 12 || workgroups >= 144 ? cut : 0;
+    const int slices = (M + 15) / 16, other_runs = other.whole > 0 ? other.chunks0 : other.chunks, other_groups = other.whole > 0 ? other.gchunk0 : other.gchunk;
+    bool take;
+    if (other_runs > 1 && other.waves == 8) take = workgroups >= (gc > 24 ? 176 : 128);
+    else if (other_groups > 6 * other.waves && (other_runs == 1 || slices * other_runs > 256)) take = workgroups >= (gc > 12 ? 352 : 128);
+    else take = other_runs > 1 && gc <= 12 && M >= 768 && workgroups >= 128 && workgroups <= 256;
+    return take ? cut : 0;
 }
 
 // Where partial H is left for the GEMM, H itself is never made in memory; its first 16 bytes name the place of the parts instead, for

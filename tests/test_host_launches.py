@@ -199,6 +199,16 @@ def test_wide_tiles_add_few_columns_of_partial_h(record, M, K, N, r, runs):
     assert gemm.startswith("gemm_w4a4_mid_kernel<") and gemm.endswith(",true>") == runs, gemm
 
 
+@pytest.mark.parametrize("fmt,M,K,N,r,wide", [(FP4, 2595, 2560, 272, 128, False), (FP4, 2233, 3392, 512, 96, False), (STATIC, 3019, 7488, 304, 112, False), (STATIC, 4352, 11136, 416, 96, False),
+                                              (INT4, 577, 2752, 2576, 128, False), (INT4, 2790, 2624, 400, 96, False), (INT4, 1905, 3648, 112, 96, False), (INT4, 622, 6144, 4576, 80, False),
+                                              (FP4, 700, 2560, 2560, 128, True), (FP4, 1432, 9856, 2720, 128, True), (INT4, 4608, 12288, 3072, 128, True), (INT4, 1096, 9728, 1184, 128, True),
+                                              (INT4, 1445, 5440, 416, 112, True), (INT4, 2419, 4160, 304, 96, True), (INT4, 1579, 5312, 448, 128, True), (INT4, 741, 12352, 2608, 80, True), (STATIC, 3875, 12352, 144, 128, True)])
+def test_wide_branches_keep_their_kernel_off_launches_it_would_leave_cus_idle_in(record, fmt, M, K, N, r, wide):
+    """Workgroups of 64 tokens with room for few runs' partial H are few, with long chains of groups: such launches take the
+    kernel of 16-token workgroups."""
+    assert _kernels(record([(0, fmt, M, K, N, r)])[0])[0].startswith("act_wide_kernel<") == wide
+
+
 @pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
 def test_the_static_workspace_runs_the_ordinary_launches(record, M, K, N, r):
     """Ordinary workspaces of small launches are larger than the static array for the room of a K split that such launches do
