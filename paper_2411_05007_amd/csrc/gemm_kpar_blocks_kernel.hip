@@ -43,8 +43,8 @@ struct KparParams {
 };
 
 // I8: INT8 (32 channels per step), else MXFP4 (64).  RB row blocks and CB column blocks of 32, KS wavefronts that share K, DEPTH steps ahead.
-// RUNS: H comes as the partial sums of the activation kernel's runs (else ready-made).
-template <bool I8, int RB, int CB, int KS, int DEPTH, bool RUNS>
+// RUNS: H comes as the partial sums of the activation kernel's runs (else ready-made).  WALK (INT8): a way out behind every step of the K loop.
+template <bool I8, int RB, int CB, int KS, int DEPTH, bool WALK, bool RUNS>
 __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_kernel(KparParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     using T = KparLds<RB, CB, KS>;
@@ -161,16 +161,27 @@ __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_ker
         // whole rounds of DEPTH steps without a way out between them (the compiler counts the requests on the shortest way to a set's use:
         // with one, every round began with a wait for all of them), then what is left, already requested.  us per forward before and
         // after: MXFP4, rank 32, M = 512, K = N = 3072 16.9 | 15.3, M = 1024 21.9 | 19.6, rank 64, M = 300, K = 6144, N = 4096 25.4 | 22.3
-        int i = 0;
-        for (; i + DEPTH <= n; i += DEPTH)
+        if constexpr (WALK) {
+            for (int i = 0; i < n; i += DEPTH) {
 #pragma unroll
-            for (int d = 0; d < DEPTH; ++d) {
-                multiply(d);
-                load(S[d], i + d + DEPTH);
+                for (int d = 0; d < DEPTH; ++d) {
+                    if (d > 0 && i + d >= n) break;
+                    multiply(d);
+                    load(S[d], i + d + DEPTH);
+                }
             }
+        } else {
+            int i = 0;
+            for (; i + DEPTH <= n; i += DEPTH)
 #pragma unroll
-        for (int d = 0; d + 1 < DEPTH; ++d)
-            if (i + d < n) multiply(d);
+                for (int d = 0; d < DEPTH; ++d) {
+                    multiply(d);
+                    load(S[d], i + d + DEPTH);
+                }
+#pragma unroll
+            for (int d = 0; d + 1 < DEPTH; ++d)
+                if (i + d < n) multiply(d);
+        }
         int f[RB][CB][16];
 #pragma unroll
         for (int r = 0; r < RB; ++r)
@@ -282,12 +293,12 @@ __global__ __launch_bounds__(KS * 64, KS >= 8 ? 1 : 2) void gemm_kpar_blocks_ker
     }
 }
 
-template <bool I8, int RB, int CB, int KS, int DEPTH, bool RUNS>
+template <bool I8, int RB, int CB, int KS, int DEPTH, bool WALK, bool RUNS>
 hipError_t launch_tile(const KparParams &p, hipStream_t stream) {
     const int tiles_m = (p.M + 32 * RB - 1) / (32 * RB), tiles_n = (p.N + 32 * CB - 1) / (32 * CB);
     // H, L2, the scales and the bias are read with plain loads: every tile must lie inside the padded rows and columns
     if (tiles_m * 32 * RB > p.Mpad || tiles_n * 32 * CB > p.Npad) return hipErrorInvalidValue;
-    auto k = gemm_kpar_blocks_kernel<I8, RB, CB, KS, DEPTH, RUNS>;
+    auto k = gemm_kpar_blocks_kernel<I8, RB, CB, KS, DEPTH, WALK, RUNS>;
     constexpr int bytes = KparLds<RB, CB, KS>::kBytes;
     if (RUNS && (!p.hpart || p.rank <= 0 || (I8 && p.rank > 32) || kpar_h_bytes<RB>(p.rank) > bytes)) return hipErrorInvalidValue;
     static LdsLimit limit;
@@ -298,7 +309,16 @@ hipError_t launch_tile(const KparParams &p, hipStream_t stream) {
 
 template <bool I8, int RB, int CB, int KS, int DEPTH>
 hipError_t launch_one(const KparParams &p, hipStream_t stream) {
-    return p.runs > 0 ? launch_tile<I8, RB, CB, KS, DEPTH, true>(p, stream) : launch_tile<I8, RB, CB, KS, DEPTH, false>(p, stream);
+    // INT8 on four wavefronts with a long K: us of the GEMM, rounds without a way out | a way out behind every step, rank 48: M = 700, N = 1824 (64-row
+    // tiles): K = 640 5.8 | 6.2, 2048 9.7 | 9.6, 4608 16.4 | 15.4, 6080 21.0 | 19.0; M = 1464, N = 1520 (128-row): K = 2048 14.0 | 14.6, 3072 17.4 | 17.6,
+    // 4608 23.2 | 21.7, 9600 43.9 | 39.8; 64-row tiles that add runs' H gain nothing (rank 16: K = 4608 16.2 | 17.0, 6080 20.2 | 19.7).  With eight wavefronts no
+    // K was found where the rounds lose.
+    if constexpr (I8 && KS == 4)
+        if (p.steps > 128) {
+            if (p.runs == 0) return launch_tile<I8, RB, CB, KS, DEPTH, true, false>(p, stream);
+            if constexpr (RB == 4) return launch_tile<I8, RB, CB, KS, DEPTH, true, true>(p, stream);
+        }
+    return p.runs > 0 ? launch_tile<I8, RB, CB, KS, DEPTH, false, true>(p, stream) : launch_tile<I8, RB, CB, KS, DEPTH, false, false>(p, stream);
 }
 
 template <bool I8>

@@ -157,6 +157,12 @@ def test_w8a8_small_batches(torch, M, K, N, r):  # noqa: F811
     _block_format(torch, "w8a8", M, K, N, r, None)
 
 
+# INT8, four wavefronts that share a long K: steps off the wavefronts and the sets requested ahead, 64- and 128-row tiles, H ready-made and from runs
+@pytest.mark.parametrize("M,K,N,r", [(690, 4160, 1840, 48), (700, 6208, 1808, 16), (1450, 4224, 1520, 96), (1463, 4352, 1488, 32)])
+def test_w8a8_long_k_on_four_wavefronts(torch, M, K, N, r):  # noqa: F811
+    _block_format(torch, "w8a8", M, K, N, r, None)
+
+
 # MXFP4 on 32 x 32 tiles with sixteen wavefronts: K off four steps, fewer steps than the wavefronts ask ahead, ragged M and N, ranks with
 # more steps than a wavefront has, H ready-made and added from runs
 @pytest.mark.parametrize("M,K,N,r", [(1, 3328, 1040, 32), (33, 3520, 1552, 128), (64, 6144, 2064, 0), (17, 8256, 4112, 48)])

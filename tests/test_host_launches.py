@@ -209,6 +209,12 @@ def test_wide_branches_keep_their_kernel_off_launches_it_would_leave_cus_idle_in
     assert _kernels(record([(0, fmt, M, K, N, r)])[0])[0].startswith("act_wide_kernel<") == wide
 
 
+@pytest.mark.parametrize("M,K,N,r,walk", [(700, 4608, 1824, 48, True), (1464, 6080, 1520, 96, True), (700, 6208, 1824, 16, False), (1464, 4160, 1520, 16, True), (700, 4096, 1824, 48, False), (1464, 3072, 1520, 96, False)])
+def test_int8_on_four_wavefronts_walks_a_long_k(record, M, K, N, r, walk):
+    gemm = _kernels(record([(0, W8A8, M, K, N, r)])[0])[-1].split("<")[1].split(",")
+    assert gemm[0] == "true" and gemm[3] == "4" and (gemm[5] == "true") == walk, gemm
+
+
 @pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
 def test_the_static_workspace_runs_the_ordinary_launches(record, M, K, N, r):
     """Ordinary workspaces of small launches are larger than the static array for the room of a K split that such launches do
