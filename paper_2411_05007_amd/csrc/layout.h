@@ -260,7 +260,8 @@ struct SmallInt4 {
 //   M = 512, K = 3072, N = 9216 36.3 -> 32.4 (5); M = 4096, K = 4608, N = 1152 53.8 -> 46.9 (5); M = 2048, K = N = 3072 43.7 -> 37.4 (6)
 //   M = 609, K = 3712, N = 9360 47.8 -> 41.8 (6); M = 978, K = 4992, N = 9712 87.6 -> 77.0 (5); M = 1774, K = 9536, N = 10256 264 -> 220 (6)
 //   M = 2474, K = 1280, N = 1888 24.1 -> 19.7 (5); M = 645, K = 640, N = 6416 19.5 -> 15.3 (5)
-// No measured shape lost.  Without the 3 %: M = 1715, K = 1792, N = 2368 loses 10 %, M = 439, K = 9536, N = 9552 3 %.
+// Not beyond four rounds: 35 such launches were 5 % slower (median; M = 1719, K = 4928, N = 14448 163 | 178), 136 of four rounds 2 % faster.
+// Without the 3 %: M = 1715, K = 1792, N = 2368 loses 10 %, M = 439, K = 9536, N = 9552 3 %.
 inline SmallInt4 plan_small_int4(int M, int N, int G, int rank, int ksplit_override = 0) {
     SmallInt4 s{plan_kpar_int4(M, N, G, rank, ksplit_override), 0};
     const long tm = (M + 127) / 128, t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
@@ -272,8 +273,9 @@ inline SmallInt4 plan_small_int4(int M, int N, int G, int rank, int ksplit_overr
                          : (large / kGemmPlaces + (rest > 256)) * (85 + 2.05 * 8 * G) + (rest > 0 && rest <= 256 ? 85 + 1.1 * 8 * G : 0.0);
     best *= 0.97;
     for (int blocks = 5; blocks <= 6; ++blocks) {
-        const double cost = (tm * ((N + 32 * blocks - 1) / (32 * blocks)) + 255) / 256 * (125.0 + blocks * G);
-        if (cost < best) {
+        const long rounds = (tm * ((N + 32 * blocks - 1) / (32 * blocks)) + 255) / 256;
+        const double cost = rounds * (125.0 + blocks * G);
+        if (rounds <= 4 && cost < best) {
             best = cost;
             s = SmallInt4{kKparNone, blocks};
         }

@@ -215,6 +215,12 @@ def test_int8_on_four_wavefronts_walks_a_long_k(record, M, K, N, r, walk):
     assert gemm[0] == "true" and gemm[3] == "4" and (gemm[5] == "true") == walk, gemm
 
 
+@pytest.mark.parametrize("M,K,N,r,kernel", [(1719, 4928, 14448, 0, "gemm_w4a4_kernel<"), (3404, 5056, 7360, 16, "gemm_w4a4_kernel<"), (2191, 5056, 10816, 32, "gemm_w4a4_kernel<"),
+                                            (4096, 4608, 1152, 32, "gemm_w4a4_mid_kernel<5,"), (2048, 3072, 3072, 32, "gemm_w4a4_mid_kernel<6,"), (1774, 9536, 10256, 16, "gemm_w4a4_mid_kernel<6,")])
+def test_wide_tiles_take_four_rounds_at_most(record, M, K, N, r, kernel):
+    assert _kernels(record([(0, INT4, M, K, N, r)])[0])[-1].startswith(kernel)
+
+
 @pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
 def test_the_static_workspace_runs_the_ordinary_launches(record, M, K, N, r):
     """Ordinary workspaces of small launches are larger than the static array for the room of a K split that such launches do
