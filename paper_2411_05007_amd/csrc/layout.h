@@ -448,7 +448,8 @@ inline ActPlan plan_act(int M, int G, int rank, int gchunk_override = 0) {
 //   rank 128, K = N = 3072: M = 64 17.8 -> 14.1 (4, 12), M = 512 26.3 -> 24.3;  M = 512, K = 12288: 48.4 -> 54.1 (201 MB: not taken)
 // The 128-row tiles of more than 64 columns make every lane add up its rows' parts between the loads of L2: up to 128 columns of them in all
 // runs, beyond that H comes ready-made.  us per forward, added | ready-made: M = 562, K = 3136, N = 9024, rank 64 (5 runs) 47.5 | 39.0, M = 832, K = 3904,
-// N = 5408, rank 64 (6) 53.4 | 40.7, M = 396, K = 9792, N = 11584, rank 64 (7) 94.0 | 82.5; 467 launches beyond the line: median 8 % faster, none slower.
+// N = 5408, rank 64 (6) 53.4 | 40.7, M = 396, K = 9792, N = 11584, rank 64 (7) 94.0 | 82.5; 467 launches beyond the line: median 8 % faster, none slower.  In a second and third round the same rows are added up again:
+// 96 and 64 columns there.
 constexpr int kMidPartColumns = 128;
 // fine: shorter runs where the launch does not fill the CUs (act_short_runs); there are more of them, and act_use_small_plan may have to
 // take the longer ones.
@@ -472,7 +473,7 @@ inline ActPlan plan_act_small(int M, int N, int G, int rank, int act_override, i
     pl.whole = 0; pl.chunks0 = 1; pl.gchunk0 = G;
     pl.deposit = pl.chunks > 1;
     const long tiles = (long)((M + tile_rows - 1) / tile_rows) * ((N + tile_cols - 1) / tile_cols);
-    if (tile_cols > 64 && pl.chunks * rank > kMidPartColumns) return old;
+    if (tile_cols > 64 && pl.chunks * rank > (tiles <= 256 ? kMidPartColumns : kMidPartColumns * 3 / 2 / ((tiles + 255) / 256))) return old;
     if (slices * pl.chunks > 512 || pl.chunks > 64 || tiles * tile_rows * rank * 4 * pl.chunks > 64l << 20) return old;
     return pl;
 }

@@ -192,7 +192,7 @@ def test_nine_to_twelve_groups_are_cut_for_small_tiles_only(record, fmt, M, K, N
     assert act[2].startswith("act_kernel<") and act[3] == -(-M // 16) * runs, act
 
 
-@pytest.mark.parametrize("M,K,N,r,runs", [(562, 3136, 9024, 64, False), (832, 3904, 5408, 64, False), (396, 9792, 11584, 64, False), (598, 4288, 9024, 32, False),
+@pytest.mark.parametrize("M,K,N,r,runs", [(562, 3136, 9024, 64, False), (832, 3904, 5408, 64, False), (396, 9792, 11584, 64, False), (598, 4288, 9024, 32, False), (1810, 2112, 9584, 32, False),
                                           (452, 832, 8272, 64, True), (516, 832, 8912, 32, True), (512, 3072, 9216, 32, True)])
 def test_wide_tiles_add_few_columns_of_partial_h(record, M, K, N, r, runs):
     gemm = _kernels(record([(0, INT4, M, K, N, r)])[0])[-1]
