@@ -108,3 +108,25 @@ def test_w8a8_forward_stays_inside_its_buffers(torch, M, K, N, r, opts):
         layer.forward(x, out=y, workspace=ws)
     S.svdq_forward_options(0)
     _check(torch, big_ws, n, big_y, M, f"w8a8 {M}x{K}x{N} r{r}")
+
+
+# one ragged shape for every kernel that writes in a way of its own: partial H in the output's memory and in the workspace, masked stores of wide
+# tiles, tokens four at a time, tiles of 32 x 32 and of 256 x 256
+KERNELS = [("int4", (2001, 2752, 4672, 112), "act_wide_kernel<0>"), ("fp4", (577, 2752, 2576, 112), "act_wide_kernel<1>"), ("int4", (1500, 5632, 528, 80), "act_wide_kernel<0>"),
+           ("int4", (579, 576, 6576, 32), "gemm_w4a4_mid_kernel<5,false>"), ("int4", (516, 832, 8912, 32), "gemm_w4a4_mid_kernel<6,true>"), ("w8a8", (67, 4160, 1552, 32), "act_w8_small_kernel<2,3>"),
+           ("fp4", (33, 3520, 1552, 128), "gemm_kpar_blocks_kernel<false,1,1,16,6,"), ("w8a8", (2561, 4672, 5136, 48), "gemm_w8a8_kernel<4,4,true>"), ("w8a8", (1463, 4352, 1488, 32), "gemm_kpar_blocks_kernel<true,4,2,4,2,true,true>")]
+
+
+@pytest.mark.parametrize("fmt,shape", [k[:2] for k in KERNELS])
+def test_forwards_of_every_kernel_stay_inside_their_buffers(torch, fmt, shape):
+    from tests.test_gpu_small_launches import _block_layer, _layer
+    M, K, N, r = shape
+    rng = np.random.default_rng(7300 + M + N)
+    layer = S.DeviceLayer(_layer(rng, K, N, r) if fmt == "int4" else _block_layer(rng, fmt, K, N, r))
+    x = S.bf16_tensor_from_bits((rng.standard_normal((M, K)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16))
+    n = layer.workspace(M).numel()
+    big_ws, ws, big_y, y = _guarded(torch, layer, M, N, n)
+    print(f"canaries: {fmt} {shape}", flush=True)
+    for _ in range(2):
+        layer.forward(x, out=y, workspace=ws)
+    _check(torch, big_ws, n, big_y, M, f"{fmt} {shape}")

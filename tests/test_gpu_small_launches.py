@@ -45,8 +45,12 @@ def test_every_variant_at_its_edges(torch, M, K, N, r, rows):  # noqa: F811
 # 128 x 160 and 128 x 192 tiles whose two shares of wavefronts take the even and the odd groups (csrc/gemm_w4a4_mid_kernel.hip): odd
 # and even counts of either share's groups, rank steps that the shares divide unevenly, H ready-made and added from runs, columns
 # past the padded ones, ragged M and N
-@pytest.mark.parametrize("M,K,N,r,cols", [(454, 448, 8272, 48, 160), (579, 576, 6576, 32, 160), (452, 832, 8272, 64, 160), (457, 512, 8336, 0, 160),
-                                          (514, 448, 8976, 48, 192), (516, 832, 8912, 32, 192), (577, 640, 8176, 16, 192)])
+TWO_SHARES = [(454, 448, 8272, 48, 160, "gemm_w4a4_mid_kernel<5,false>"), (579, 576, 6576, 32, 160, "gemm_w4a4_mid_kernel<5,false>"), (452, 832, 8272, 64, 160, "gemm_w4a4_mid_kernel<5,true>"),
+              (457, 512, 8336, 0, 160, "gemm_w4a4_mid_kernel<5,false>"), (514, 448, 8976, 48, 192, "gemm_w4a4_mid_kernel<6,false>"), (516, 832, 8912, 32, 192, "gemm_w4a4_mid_kernel<6,true>"),
+              (577, 640, 8176, 16, 192, "gemm_w4a4_mid_kernel<6,false>")]
+
+
+@pytest.mark.parametrize("M,K,N,r,cols", [s[:5] for s in TWO_SHARES])
 def test_two_shares_of_a_wide_tile(torch, M, K, N, r, cols):  # noqa: F811
     rng = np.random.default_rng(5700 + M + K + N)
     prep = _layer(rng, K, N, r)
@@ -98,7 +102,12 @@ def test_block_formats_on_smaller_tiles(torch, fmt, M, K, N, r, tile):  # noqa: 
 
 # one activation workgroup per 16 tokens with K in its wavefronts' registers (64 to 256 slices): fewer groups than
 # wavefronts, group counts off sixteen in every variant, no projection, the last slice of a launch ragged
-@pytest.mark.parametrize("M,K,N,r", [(1009, 704, 272, 16), (1009, 1088, 9232, 32), (1500, 3136, 9232, 16), (2050, 6080, 272, 32), (4095, 128, 144, 0)])
+# (the first shape: INT4 only; MXFP4's small tiles add the walking kernel's runs)
+ONE_PASS = [(1009, 704, 272, 16, "act_"), (1009, 704, 9232, 16, "act_onepass_kernel<"), (1009, 1088, 9232, 32, "act_onepass_kernel<"), (1500, 3136, 9232, 16, "act_onepass_kernel<"),
+            (2050, 6080, 272, 32, "act_onepass_kernel<"), (4095, 128, 144, 0, "act_onepass_kernel<")]
+
+
+@pytest.mark.parametrize("M,K,N,r", [s[:4] for s in ONE_PASS])
 @pytest.mark.parametrize("fmt", ["int4", "fp4"])
 def test_activation_in_one_pass(torch, fmt, M, K, N, r):  # noqa: F811
     if fmt == "fp4":
@@ -113,16 +122,34 @@ def test_activation_in_one_pass(torch, fmt, M, K, N, r):  # noqa: F811
 
 
 # INT8 on 256 x 256 tiles (csrc/w8a8_kernels.hip): last rows and columns of a tile, steps off the ring, the shortest K, all 256 CUs, three ranks
-@pytest.mark.parametrize("M,K,N,r", [(2561, 4672, 5136, 48), (3841, 4608, 3856, 16), (2310, 4864, 6160, 0)])
+W8A8_LARGE = [(2561, 4672, 5136, 48, "gemm_w8a8_kernel<4,4,true>"), (3841, 4608, 3856, 16, "gemm_w8a8_kernel<4,4,true>"), (2310, 4864, 6160, 0, "gemm_w8a8_kernel<4,4,true>")]
+
+
+@pytest.mark.parametrize("M,K,N,r", [s[:4] for s in W8A8_LARGE])
 def test_w8a8_on_large_tiles(torch, M, K, N, r):  # noqa: F811
     _block_format(torch, "w8a8", M, K, N, r, None)
 
 
-# wide branches, 64 tokens to an activation workgroup, partial H in the output's memory or in the workspace (csrc/act_wide_kernel.hip): tokens
-# off 64, groups off the runs, runs shorter than the ring has stages, ranks off 128, room for one run only
+# wide branches, 64 tokens to an activation workgroup (csrc/act_wide_kernel.hip): tokens off 64, groups off the runs, last runs of one and two
+# groups (fewer than the ring has stages), ranks off 128; the runs' partial H in the output's memory or in the workspace.  The last number: how
+# many runs there are where the output cannot hold them
+WIDE = [("int4", 2001, 2752, 4672, 112, 8, 0), ("int4", 1500, 2816, 6160, 80, 8, 0), ("int4", 1001, 5632, 3088, 128, 15, 15), ("int4", 1500, 5632, 528, 80, 15, 15), ("int4", 3010, 4672, 272, 128, 10, 10),
+        ("fp4", 577, 2752, 2576, 112, 8, 7), ("fp4", 1001, 4672, 4672, 80, 13, 0), ("fp4", 2001, 4672, 528, 128, 13, 13), ("fp4", 577, 2624, 4112, 112, 7, 7), ("fp4", 3010, 4672, 272, 128, 8, 8)]
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r", [s[:5] for s in WIDE])
+def test_wide_branches_in_64_token_workgroups(torch, fmt, M, K, N, r):  # noqa: F811
+    _wide_branch(torch, fmt, M, K, N, r)
+
+
+# the same ranks in 16-token workgroups, whose partial H the GEMM adds
 @pytest.mark.parametrize("M,K,N,r", [(577, 2560, 1040, 128), (1100, 2624, 528, 80), (700, 5632, 144, 112), (3010, 4672, 272, 128)])
 @pytest.mark.parametrize("fmt", ["int4", "fp4"])
 def test_wide_branches(torch, fmt, M, K, N, r):  # noqa: F811
+    _wide_branch(torch, fmt, M, K, N, r)
+
+
+def _wide_branch(torch, fmt, M, K, N, r):  # noqa: F811
     if fmt == "fp4":
         return _block_format(torch, fmt, M, K, N, r, None)
     rng = np.random.default_rng(5800 + M + K + N)
@@ -134,12 +161,17 @@ def test_wide_branches(torch, fmt, M, K, N, r):  # noqa: F811
     _run_and_compare(torch, O.bf16_round(x), prep, rows=sample, what=f"wide branch {M}x{K}x{N}", window=False)
 
 
-def test_wide_branch_into_any_output(torch):  # noqa: F811
+# square layers, so that the output can be the input; runs in the output's memory, and where it cannot hold them (in the workspace, or none:
+# another kernel).  The third takes that other kernel anyhow
+ANY_OUTPUT = [("int4", 2001, 4672, 128, 13, 0), ("fp4", 700, 2560, 128, 7, 5), ("int4", 640, 2560, 128, 0, 0)]
+
+
+@pytest.mark.parametrize("fmt,M,K,r", [s[:4] for s in ANY_OUTPUT])
+def test_wide_branch_into_any_output(torch, fmt, M, K, r):  # noqa: F811
     """The output's memory holds partial sums only where it can: not where it is the input's, and not at an odd address.  Bound:
     sums in another order, 2e-5 in the 2-norm (see perf/cases.py)."""
-    M, K = 640, 2560
     rng = np.random.default_rng(5900)
-    layer = S.DeviceLayer(_layer(rng, K, K, 128))
+    layer = S.DeviceLayer(_block_layer(rng, fmt, K, K, r) if fmt == "fp4" else _layer(rng, K, K, r))
     x = S.bf16_tensor_from_bits(O.bf16_round(rng.standard_normal((M, K)).astype(np.float32)))
     y = layer.forward(x).float()
     odd = torch.empty(M * K + 8, dtype=torch.bfloat16, device=x.device)[1:1 + M * K].view(M, K)
@@ -148,26 +180,77 @@ def test_wide_branch_into_any_output(torch):  # noqa: F811
         assert ((got - y).norm() / y.norm()).item() < 1.5e-4
 
 
+# one shape for every kernel that adds up runs, shares K or stages its operands: the kernel it is for follows
+SPECIAL = [("int4", 1500, 5632, 528, 80, "act_wide_kernel<0>"), ("fp4", 577, 2752, 2576, 112, "act_wide_kernel<1>"), ("int4", 452, 832, 8272, 64, "gemm_w4a4_mid_kernel<5,true>"),
+           ("int4", 579, 576, 6576, 32, "gemm_w4a4_mid_kernel<5,false>"), ("w8a8", 290, 3136, 2064, 32, "act_w8_small_kernel<2,2>"), ("w8a8", 67, 4160, 1552, 32, "gemm_kpar_blocks_kernel<true,1,1,16,6,false,true>"),
+           ("fp4", 33, 3520, 1552, 128, "gemm_kpar_blocks_kernel<false,1,1,16,6,false,true>"), ("w8a8", 2561, 4672, 5136, 48, "gemm_w8a8_kernel<4,4,true>")]
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r", [s[:5] for s in SPECIAL])
+def test_infinities_and_nan_stay_in_their_rows(torch, fmt, M, K, N, r):  # noqa: F811
+    """A row of X with an infinity or a NaN gives a row of NaN (its H is infinite or NaN, and infinity less its own bf16 part is
+    NaN); every other row is what it is without them, bit for bit."""
+    rng = np.random.default_rng(5950 + M + K + N)
+    layer = S.DeviceLayer(_layer(rng, K, N, r) if fmt == "int4" else _block_layer(rng, fmt, K, N, r))
+    x = S.bf16_tensor_from_bits(O.bf16_round(rng.standard_normal((M, K)).astype(np.float32)))
+    print(f"infinities and NaN: {fmt} M={M} K={K} N={N} r={r}", flush=True)
+    want = layer.forward(x).clone()
+    rows = sorted({0, 5, M // 2, M - 2, M - 1})
+    bad = x.clone()
+    for i, m in enumerate(rows):
+        bad[m, int(rng.integers(0, K))] = (float("inf"), float("nan"), float("-inf"))[i % 3]
+    got = layer.forward(bad)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(want.float()).all())
+    assert bool(torch.isnan(got[rows].float()).all())
+    rest = [m for m in range(M) if m not in rows]
+    assert torch.equal(got[rest].view(torch.int16), want[rest].view(torch.int16))
+
+
 # INT8: four tokens to a quantizing workgroup beside workgroups that project runs of K (csrc/act_w8_small_kernel.hip): tokens off four and
 # sixteen, half a unit of 128 channels at the end, every number of units per wavefront, one and two rank steps and none, a GEMM that adds
 # the runs on every kind of its tiles (32 x 32 ones among them) and one that needs H whole
-@pytest.mark.parametrize("M,K,N,r", [(1, 1472, 528, 16), (5, 1408, 1040, 32), (18, 2112, 4176, 0), (67, 4160, 1552, 32), (130, 6208, 2064, 16), (3, 12288, 784, 32),
-                                     (290, 3136, 2064, 32), (600, 640, 1552, 16), (1030, 1216, 2064, 32), (700, 576, 6160, 32), (1100, 3200, 4112, 16)])
+W8A8_SMALL = [(1, 1472, 528, 16, "gemm_kpar_blocks_kernel<true,1,2,8,6,false,true>"), (5, 1408, 1040, 32, "gemm_kpar_blocks_kernel<true,1,1,16,6,false,true>"),
+              (18, 2112, 4176, 0, "gemm_kpar_blocks_kernel<true,1,1,16,6,false,false>"), (67, 4160, 1552, 32, "gemm_kpar_blocks_kernel<true,1,1,16,6,false,true>"),
+              (130, 6208, 2064, 16, "gemm_kpar_blocks_kernel<true,1,2,8,6,false,true>"), (3, 12288, 784, 32, "gemm_kpar_blocks_kernel<true,1,2,8,6,false,true>"),
+              (290, 3136, 2064, 32, "gemm_kpar_blocks_kernel<true,2,2,8,4,false,true>"), (600, 640, 1552, 16, "gemm_kpar_blocks_kernel<true,2,2,8,4,false,true>"),
+              (700, 3136, 1840, 16, "gemm_kpar_blocks_kernel<true,2,2,4,4,false,true>"), (1030, 1216, 2064, 32, "gemm_kpar_blocks_kernel<true,4,2,4,2,false,true>"),
+              (520, 8256, 3056, 32, "gemm_kpar_blocks_kernel<true,4,2,8,2,false,true>"), (700, 576, 6160, 32, "act_sum_h_kernel"), (1100, 3200, 4112, 16, "act_sum_h_kernel")]
+
+
+@pytest.mark.parametrize("M,K,N,r", [s[:4] for s in W8A8_SMALL])
 def test_w8a8_small_batches(torch, M, K, N, r):  # noqa: F811
     _block_format(torch, "w8a8", M, K, N, r, None)
 
 
 # INT8, four wavefronts that share a long K: steps off the wavefronts and the sets requested ahead, 64- and 128-row tiles, H ready-made and from runs
-@pytest.mark.parametrize("M,K,N,r", [(690, 4160, 1840, 48), (700, 6208, 1808, 16), (1450, 4224, 1520, 96), (1463, 4352, 1488, 32)])
+W8A8_LONG = [(690, 4160, 1840, 48, "gemm_kpar_blocks_kernel<true,2,2,4,4,true,false>"), (700, 6208, 1808, 16, "gemm_kpar_blocks_kernel<true,2,2,4,4,false,true>"),
+             (1450, 4224, 1520, 96, "gemm_kpar_blocks_kernel<true,4,2,4,2,true,false>"), (1463, 4352, 1488, 32, "gemm_kpar_blocks_kernel<true,4,2,4,2,true,true>")]
+
+
+@pytest.mark.parametrize("M,K,N,r", [s[:4] for s in W8A8_LONG])
 def test_w8a8_long_k_on_four_wavefronts(torch, M, K, N, r):  # noqa: F811
     _block_format(torch, "w8a8", M, K, N, r, None)
 
 
 # MXFP4 on 32 x 32 tiles with sixteen wavefronts: K off four steps, fewer steps than the wavefronts ask ahead, ragged M and N, ranks with
 # more steps than a wavefront has, H ready-made and added from runs
-@pytest.mark.parametrize("M,K,N,r", [(1, 3328, 1040, 32), (33, 3520, 1552, 128), (64, 6144, 2064, 0), (17, 8256, 4112, 48)])
+NARROW = [(1, 3328, 1040, 32), (33, 3520, 1552, 128), (64, 6144, 2064, 0), (17, 8256, 4112, 48)]
+
+
+@pytest.mark.parametrize("M,K,N,r", NARROW)
 def test_mxfp4_on_narrow_tiles(torch, M, K, N, r):  # noqa: F811
     _block_format(torch, "fp4", M, K, N, r, (32, 32))
+
+
+def _block_layer(rng, fmt, K, N, r):
+    rinv = np.exp2(rng.uniform(-1, 1, K)).astype(np.float32)
+    l1 = O.bf16_round((rng.standard_normal((K, r)) * 0.02).astype(np.float32))
+    l2 = O.bf16_round((rng.standard_normal((r, N)) * 0.05).astype(np.float32))
+    bias = rng.standard_normal(N).astype(np.float32)
+    if fmt == "fp4":
+        return S.svdq_fp4_pack(rinv, l1, l2, rng.integers(0, 16, size=(K, N)).astype(np.uint8), rng.integers(110, 118, size=(K // 32, N)).astype(np.uint8), bias)
+    return S.svdq_w8a8_pack(rinv, l1, l2, rng.integers(-127, 128, size=(K, N)).astype(np.int8), rng.uniform(5e-5, 4e-4, N).astype(np.float16), bias)
 
 
 def _block_format(torch, fmt, M, K, N, r, tile):  # noqa: F811
@@ -222,7 +305,12 @@ def test_int4_group_sums_are_exact(torch, M, K, N, rows):  # noqa: F811
 
 # MXFP4 in large tiles of every shape: K loops of one, two and three steps more than whole rounds of four, of fewer than four, a rank that
 # is no power of two; launches whose wavefronts share K: steps off the rounds of two, four and six
-@pytest.mark.parametrize("M,K,N,r", [(1530, 320, 12272, 32), (1530, 704, 12272, 48), (4100, 192, 3088, 16), (1337, 1472, 9200, 32), (2040, 1728, 3072, 0),
-                                     (1000, 2240, 5136, 32), (257, 1984, 2064, 32), (100, 2368, 3088, 64), (1024, 1856, 3072, 16)])
+MXFP4_ROUNDS = [(1530, 320, 12272, 32, "gemm_fp4_kernel<3,3,true>"), (1530, 704, 12272, 48, "gemm_fp4_kernel<3,3,true>"), (4100, 192, 3088, 16, "gemm_fp4_kernel<2,4,false>"),
+                (1337, 1472, 9200, 32, "gemm_fp4_kernel<3,2,false>"), (2040, 1728, 3072, 0, "gemm_fp4_kernel<2,2,false>"), (1000, 2240, 5136, 32, "gemm_fp4_kernel<2,2,false>"),
+                (257, 1984, 2064, 32, "gemm_kpar_blocks_kernel<false,2,2,4,4,false,true>"), (100, 2368, 3088, 64, "gemm_kpar_blocks_kernel<false,1,2,8,6,false,true>"),
+                (1024, 1856, 3072, 16, "gemm_kpar_blocks_kernel<false,4,2,4,2,false,true>")]
+
+
+@pytest.mark.parametrize("M,K,N,r", [s[:4] for s in MXFP4_ROUNDS])
 def test_mxfp4_steps_off_the_rounds(torch, M, K, N, r):  # noqa: F811
     _block_format(torch, "fp4", M, K, N, r, None)

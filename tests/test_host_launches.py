@@ -7,6 +7,8 @@ import subprocess
 import pytest
 
 from paper_2411_05007_amd import svdq as S
+from tests import test_gpu_small_launches as G
+from tests.test_gpu_canaries import KERNELS as G_CANARIES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 INT4, STATIC, FP4, W8A8, W4A16 = 64, 65, 32, 0, 16
@@ -219,6 +221,33 @@ def test_int8_on_four_wavefronts_walks_a_long_k(record, M, K, N, r, walk):
                                             (4096, 4608, 1152, 32, "gemm_w4a4_mid_kernel<5,"), (2048, 3072, 3072, 32, "gemm_w4a4_mid_kernel<6,"), (1774, 9536, 10256, 16, "gemm_w4a4_mid_kernel<6,")])
 def test_wide_tiles_take_four_rounds_at_most(record, M, K, N, r, kernel):
     assert _kernels(record([(0, INT4, M, K, N, r)])[0])[-1].startswith(kernel)
+
+
+FORMATS = {"int4": INT4, "fp4": FP4, "w8a8": W8A8}
+GPU_SHAPES = ([("int4", *s[:4], s[-1]) for s in G.TWO_SHARES] + [("w8a8", *s) for s in G.W8A8_LARGE + G.W8A8_LONG] + [("w8a8", *s[:4], k) for s in G.W8A8_SMALL for k in ("act_w8_small_kernel<", s[4])]
+              + [("fp4", *s) for s in G.MXFP4_ROUNDS] + [(f, *s) for s in G.ONE_PASS for f in ("int4", "fp4")] + [("fp4", *s, "gemm_kpar_blocks_kernel<false,1,1,16,6,") for s in G.NARROW] + G.SPECIAL
+              + [(f, *s, k) for f, s, k in G_CANARIES])
+
+
+def test_the_gpu_tests_run_the_kernels_they_are_for(record):
+    """A change of a rule must not turn a kernel's tests into tests of another kernel without a word."""
+    calls = [(0, FORMATS[f], M, K, N, r) for f, M, K, N, r, _ in GPU_SHAPES]
+    for call, rec in zip(GPU_SHAPES, record(calls)):
+        assert any(k.startswith(call[-1]) for k in _kernels(rec)), (call, _kernels(rec))
+
+
+def _wide_runs(rec, M):
+    act = [x for x in rec if x[0] == "launch"][0]
+    return act[3] // -(-M // 64) if act[2].startswith("act_wide_kernel<") else 0
+
+
+def test_partial_h_lies_where_the_gpu_tests_of_wide_branches_expect_it(record):
+    """Runs of the 64-token workgroups with an output of its own memory, at an odd address and in the input's: where the number does
+    not change, the workspace holds them."""
+    shapes = [(f, M, K, N, r, runs, other) for f, M, K, N, r, runs, other in G.WIDE] + [(f, M, K, K, r, runs, other) for f, M, K, r, runs, other in G.ANY_OUTPUT]
+    recs = record([(0, FORMATS[f], M, K, N, r, 0, output) for f, M, K, N, r, *_ in shapes for output in (0, 1, 2)])
+    for i, (f, M, K, N, r, runs, other) in enumerate(shapes):
+        assert [_wide_runs(x, M) for x in recs[3 * i:3 * i + 3]] == [runs, other, other], shapes[i]
 
 
 @pytest.mark.parametrize("M,K,N,r", [(512, 3072, 8192, 32), (1024, 3072, 4096, 32), (512, 3072, 9216, 32), (300, 3072, 2064, 48), (64, 12288, 12288, 16), (4608, 3072, 3072, 32)])
