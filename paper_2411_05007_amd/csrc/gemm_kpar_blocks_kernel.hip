@@ -1,9 +1,9 @@
 // MXFP4 and INT8 GEMMs for launches of few output tiles (small batches, narrow layers): the arithmetic of
 // gemm_fp4_kernel.hip and w8a8_kernels.hip (arXiv 2411.05007 Eq. 5), the division of the work of
-// gemm_w4a4_kpar_kernel.hip.  A workgroup owns a small tile, (32 RB) x 64; its four or eight wavefronts share the tile's K,
-// wavefront w taking steps w, w + KS, ...  Both formats store a 32-row block of one step (64 channels of MXFP4, 32 of
-// INT8) as one contiguous kilobyte in operand order, so a step is RB + 2 loads of 16 bytes per lane straight into the
-// registers that the 2 RB MFMAs read, DEPTH steps ahead; nobody waits for anybody in the loop, and the partial tiles meet
+// gemm_w4a4_kpar_kernel.hip.  A workgroup owns a small tile, (32 RB) x 64 or 32 x 32 (CB = 1); its four, eight or (32 x 32 tiles) sixteen
+// wavefronts share the tile's K, wavefront w taking steps w, w + KS, ...  Both formats store a 32-row block of one step (64 channels
+// of MXFP4, 32 of INT8) as one contiguous kilobyte in operand order, so a step is RB + CB loads of 16 bytes per lane straight into the
+// registers that the RB CB MFMAs read, DEPTH steps ahead; nobody waits for anybody in the loop, and the partial tiles meet
 // once, in LDS.  Bound: one image row by the weights' way from memory (M = 16, K = N = 12288: 75 MB of MXFP4 codes in a forward
 // of 24 us), larger launches by the operands' way from the L2.  us of the GEMM in a kernel trace, before -> after, MXFP4:
 // M = 512, K = N = 3072 18.7 -> 12.6; the rule that picks a variant, with more shapes: layout.h, plan_kpar_blocks.
