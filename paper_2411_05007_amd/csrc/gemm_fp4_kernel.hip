@@ -238,7 +238,7 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(Gem
     // Four steps at a time without a condition between them: the compiler counts the requests on the shortest way to the use of
     // the scale bytes, and its wait let all but one of the ring's requests land once every four steps.  us per forward with such a
     // wait and without: M = 1337, K = 3072, N = 9216 39.3 | 35.1, M = 1000, K = 8000, N = 5120 49.0 | 42.4, M = 1500, K = 1152, N = 4608 20.5 | 17.0.
-    // 192 x 192 tiles gain from SPREAD, on top of it: M = 4608, K = 3072, N = 12288 114.5 | 107.9, M = 1536, K = 8192, N = 12288 97.3 | 95.0.
+    // 192 x 192 tiles gain from SPREAD, on top of it: M = 4608, K = 3072, N = 12288 112.2 | 105.9, M = 1536, K = 8192, N = 12288 97.3 | 95.0.
     const int q_full = g_end / 4;
     for (int q = q_begin; q < q_full; ++q) {
         const int g0 = 4 * q, qn = q + 1 < q_end ? q + 1 : q;

@@ -11,12 +11,15 @@
 // stream everything from the L2 by themselves, the wavefronts of a share read the same blocks.
 // A wavefront's instruction stream is a chain of slots, one per 32 x 32 block, column by column, as in gemm_w4a4_kernel.hip:
 //     MFMA A_g(next block) | 16 FMAs of this block | MFMA S_g(next block)
-// with the weight block two columns ahead on its way from LDS and the next column's spread to six bits.  Bound: like the large
-// tiles, by the energy of a slot's two MFMAs and FMAs (in copies of the kernel without the requests, the LDS reads, the scale tiles
-// or the barrier none was more than 10 % faster, without the spreading none at all; with one row block of C columns to a
-// wavefront, twice the spreading, it ran at the same speed) and 7 us of start, low-rank product, meeting and stores.  Five stages of
-// the ring instead of four, and requests that always hit the L2, change nothing.  us per forward, where the rule takes it: layout.h,
-// plan_small_int4.
+// with the weight block two columns ahead on its way from LDS and the next column's spread to six bits.  Bound: by no unit.  At M =
+// 512, K = 3072, N = 9216 (27.0 us) and M = 4096, K = 4608, N = 1152 (32.8 us) the matrix cores are busy 23 and 30 % of the launch and the
+// vector ALU 43 and 53 % (the 128 x 256 tiles: 40 and 57 %), the L2 delivers 8 TB/s, and the wavefronts wait for 59 and 53 % of their
+// time.  About 7 us are start, low-rank product, meeting and stores; in what is left a SIMD's slot takes about 83 and 72 ns, where a full
+// round of the large tiles takes about 55.  One barrier per group spans both shares, so that the two wavefronts of a SIMD enter
+// every step together, which is the likely cause, not shown.  No part alone is: copies of the kernel without the requests, the LDS
+// reads, the scale tiles or the barrier were at most 10 % faster each, without the spreading none; one row block of C columns to a
+// wavefront (twice the spreading), five stages of the ring instead of four, and requests that always hit the L2 change nothing.
+// us per forward, where the rule takes it: layout.h, plan_small_int4.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <utility>

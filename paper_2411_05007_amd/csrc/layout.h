@@ -256,8 +256,8 @@ struct SmallInt4 {
 // per CU, the small tiles by their number, the 128 x 256 tiles by rounds of two per CU, of which a last one that gives every CU at most
 // one runs at the lone speed.  Fitted to forwards of all three kernels over 85 shapes of more than 480 tiles of 64 x 64, rank 64
 // at most (wider branches make partial H dear); the kernel is taken where it comes out 3 % below the others.  us per
-// forward, others -> this kernel (blocks):
-//   M = 512, K = 3072, N = 9216 36.3 -> 32.4 (5); M = 4096, K = 4608, N = 1152 53.8 -> 46.9 (5); M = 2048, K = N = 3072 43.7 -> 37.4 (6)
+// forward, others -> this kernel (blocks; the first two are whole forwards of commit 57cc197 and of 1891fc7 in turn on one box):
+//   M = 512, K = 3072, N = 9216 32.6 -> 30.3 (5); M = 4096, K = 4608, N = 1152 49.3 -> 45.4 (5); M = 2048, K = N = 3072 43.7 -> 37.4 (6)
 //   M = 609, K = 3712, N = 9360 47.8 -> 41.8 (6); M = 978, K = 4992, N = 9712 87.6 -> 77.0 (5); M = 1774, K = 9536, N = 10256 264 -> 220 (6)
 //   M = 2474, K = 1280, N = 1888 24.1 -> 19.7 (5); M = 645, K = 640, N = 6416 19.5 -> 15.3 (5)
 // Not beyond four rounds: 35 such launches were 5 % slower (median; M = 1719, K = 4928, N = 14448 163 | 178), 136 of four rounds 2 % faster.

@@ -23,7 +23,7 @@
 // Bound: a wavefront's chain of groups (about 250 vector instructions each, half of them X^'s parts, between the waits for the
 // next) and the fixed parts around the loop; by counters the vector ALU is busy 38 % of the time, the matrix core 7 to 15 %, and
 // the wavefronts wait for 60 %.  us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
-// launch of its own) -> now: N = 18432: 1 row 13.5 -> 12.3, 16 rows 61.7 -> 15.4;
+// launch of its own) -> now: N = 18432: 1 row 13.5 -> 11.9, 16 rows 61.7 -> 14.6;
 // N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -69,8 +69,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
             if (decltype(careful)::value && (!STACK || drop1 != 0u) && __builtin_isinf(x[e])) t[e] = 0.f;
             u[e] = t[e] - __uint_as_float(__float_as_uint(t[e]) & (STACK ? drop2 : 0xffff0000u));
         }
-        // (Interleaved with the subtractions, the packing waits for the ones right in front of it: K = 3072, N = 18432, rank 32 took 13.4 us
-        // instead of 12.3 (1 row), 16.9 instead of 15.4 (16).)
+        // (Interleaved with the subtractions, the packing waits for the ones right in front of it: K = 3072, N = 18432, rank 32 took 12.8 us
+        // instead of 11.9 (1 row), 16.3 instead of 14.6 (16).)
         if constexpr (APART) __builtin_amdgcn_sched_barrier(0);
         auto top = [](float lo, float hi) { return (uint32_t)__builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302); };
 #pragma unroll
