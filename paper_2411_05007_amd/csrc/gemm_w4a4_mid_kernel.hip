@@ -61,7 +61,7 @@ struct MidTile {
     static constexpr int kOut = 4 * KS * kOutWave;
     static constexpr int kMax = kMeet > kOut ? kMeet : kOut;
     static constexpr int kLdsBytes = kRing > kMax ? kRing : kMax;
-    static_assert(C >= 3 && C <= 8 && kReq <= C && kLdsBytes <= kLdsBytesPerCU, "");
+    static_assert((C == 5 || C == 6) && kReq <= C && kLdsBytes <= kLdsBytesPerCU, "");
 };
 
 template <typename F, int... t>
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(512, 1) void gemm_w4a4_mid_kernel(GemmW4Params p) {
     // LDS reads of a slot, in issue order: a column's first slot asks for the weight block two columns on, its last slot for the
     // scales two columns on, slot kTA for both activation blocks of the next group and their scales (eight reads).  The waits name
     // how many newer reads may still be in flight (at most 15 can be named).
-    constexpr int kTA = C > 3 ? 1 : 0, NC = T::kCols;
+    constexpr int kTA = 1, NC = T::kCols;
     constexpr auto wrap = [](int t) { return (t + 2 * C) % C; };
     constexpr auto col_first = [](int q) { return q >= 0 ? 2 * q : 2 * (q + NC) - C; };                                  // (q < 0: of the step before)
     constexpr auto col_last = [](int q) { return q >= 0 ? (q < T::kCW ? 2 * q + 1 : 2 * q) : (q + NC < T::kCW ? 2 * (q + NC) + 1 : 2 * (q + NC)) - C; };
