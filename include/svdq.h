@@ -175,6 +175,8 @@ size_t svdq_workspace_bytes(int M, const svdq_shape *shape);
  *   2. W4A4 GEMM: the INT4 codes go through the matrix core as exact 6-bit floats, one instruction per group of
  *      64 with the exact integer group sum as its fp32 result; fp32 rescale by s_x s_w (the scale products of a
  *      32 x 32 block come from an f16 MFMA), accumulated on top of H L2 in the same registers; bias, bf16 store.
+ *   Small batches with a short K run both as one kernel (csrc/layout.h, fused_small), if no option is set and Y does not share
+ *   memory with X; what they leave in the workspace is the same.
  *   X  device bf16 [M x K] row-major, 16-byte aligned;  Y device bf16 [M x N] row-major: may hold partial H before it holds the
  *   output (it does not if it shares memory with X).
  *   workspace: device, 256-byte aligned, >= svdq_workspace_bytes(M, shape); contents are
@@ -264,7 +266,7 @@ int svdq_forward_options(int flags);
  * Measurement only, for the calling thread: if `hip_event` (a hipEvent_t) is non-NULL, every following
  * svdq_linear_forward of this thread records it on its stream between the activation kernel and the GEMM, so a
  * caller that brackets the call with its own events gets the two kernels' durations separately
- * (the per-kernel split behind Fig. 6a).  Pass NULL to switch it off.  Returns SVDQ_OK.
+ * (the per-kernel split behind Fig. 6a; in front of the one kernel of a small batch).  Pass NULL to switch it off.  Returns SVDQ_OK.
  */
 int svdq_profile_event(void *hip_event);
 

@@ -33,14 +33,10 @@ __device__ __forceinline__ float max_over_8_lanes(float a) {
     return a;
 }
 
-// Eq. 1 for the 8 channels one lane holds of a token's group of 64 (the group's other 56 channels sit in the 7 lanes
-// beside it): s = max|x| / q_max over the whole group, stored as fp16 (`sbits`); returns 1 / s, the factor that turns
-// x^ into its code (0 for a group of zeros).
-__device__ __forceinline__ float w4_group_rcp(const float (&xh)[8], uint32_t &sbits) {
-    float amax = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(xh[e]));
-    amax = max_over_8_lanes(amax);
+// Eq. 1 for a token's group of 64 with the maximum `amax`: s = max|x| / q_max, stored as fp16 (`sbits`); returns 1 / s, the factor
+// that turns x^ into its code (0 for a group of zeros).  w4_group_rcp: a lane holds 8 channels of the group, the other 56 sit in the
+// 7 lanes beside it.
+__device__ __forceinline__ float w4_rcp_of(float amax, uint32_t &sbits) {
     // amax / 7.0f and 1.0f / s, both correctly rounded like the IEEE divisions they stand for, in three instructions
     // each: a product with the rounded reciprocal (1/7 as a constant, v_rcp_f32 for s, good to one ulp), the exact
     // remainder by FMA, one correction by FMA.  For the division by 7 this equals the IEEE quotient for every finite
@@ -57,6 +53,12 @@ __device__ __forceinline__ float w4_group_rcp(const float (&xh)[8], uint32_t &sb
     const float rcp_any = __builtin_fmaf(__builtin_fmaf(-den, y0, 1.0f), y0, y0);
     sbits = __builtin_bit_cast(uint16_t, sh);
     return sc > 0.f ? rcp_any : 0.f;
+}
+__device__ __forceinline__ float w4_group_rcp(const float (&xh)[8], uint32_t &sbits) {
+    float amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(xh[e]));
+    return w4_rcp_of(max_over_8_lanes(amax), sbits);
 }
 
 // The codes of up to four such 8-channel runs at once, in the operand form of the GEMM's matrix instruction
@@ -82,6 +84,16 @@ __device__ __forceinline__ act_u32x6 w4_codes(const float (*const (&xh)[RUNS])[8
             ev[4 * j + i] = __builtin_amdgcn_fmed3f((*xh[j])[2 * i] * rcp[j], -7.0f, 7.0f);
             od[4 * j + i] = __builtin_amdgcn_fmed3f((*xh[j])[2 * i + 1] * rcp[j], -7.0f, 7.0f);
         }
+    return __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f);
+}
+// the codes of 32 neighbouring channels that one lane holds: a lane's operand registers as they are
+__device__ __forceinline__ act_u32x6 w4_codes32(const float (&xh)[32], float rcp) {
+    act_floatx16 ev, od;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        ev[i] = __builtin_amdgcn_fmed3f(xh[2 * i] * rcp, -7.0f, 7.0f);
+        od[i] = __builtin_amdgcn_fmed3f(xh[2 * i + 1] * rcp, -7.0f, 7.0f);
+    }
     return __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(ev, od, 8.0f);
 }
 // run j of such a result as the 48 bits (lo: bits 0-31, hi: bits 32-47) that one lane stores
@@ -145,23 +157,34 @@ __device__ __forceinline__ int w4_stage_out(int m0, int lane) {
 // (max|x| = 1.m * 2^(E - 127) <= 1.5 * 2^(e + 2)  <=>  e = E - 129, one more if 1.m > 1.5), stored as the
 // byte e + 127 (0 for an all-zero block); the codes come from the hardware conversion, which divides by
 // the scale's power of two and rounds to the nearest E2M1 element, ties to even, saturating.
-__device__ __forceinline__ void fp4_encode(const float (&xh)[8], uint32_t &word, uint32_t &sbyte) {
-    float amax = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(xh[e]));
-    amax = max_over_4_lanes(amax);
+__device__ __forceinline__ float fp4_scale_of(float amax, uint32_t &sbyte) {
     const uint32_t bits = __float_as_uint(amax);
     int byte = (int)(bits >> 23) - 2 + ((bits & 0x7fffffu) > 0x400000u ? 1 : 0);
     byte = byte < 1 ? 1 : (byte > 254 ? 254 : byte);
     const bool zero = !(amax > 0.f);
     sbyte = zero ? 0u : (uint32_t)byte;
-    const float scale = __uint_as_float((zero ? 127u : (uint32_t)byte) << 23);
+    return __uint_as_float((zero ? 127u : (uint32_t)byte) << 23);
+}
+__device__ __forceinline__ uint32_t fp4_word(float a, float b, float c, float d, float e, float f, float g, float h, float scale) {
     uint32_t w = 0u;
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[0], xh[1], scale, 0);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[2], xh[3], scale, 1);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[4], xh[5], scale, 2);
-    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, xh[6], xh[7], scale, 3);
-    word = w;
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, a, b, scale, 0);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, c, d, scale, 1);
+    w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, e, f, scale, 2);
+    return __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, g, h, scale, 3);
+}
+// a lane holds 8 channels of the block, the other 24 sit in the rest of its quad
+__device__ __forceinline__ void fp4_encode(const float (&xh)[8], uint32_t &word, uint32_t &sbyte) {
+    float amax = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(xh[e]));
+    const float scale = fp4_scale_of(max_over_4_lanes(amax), sbyte);
+    word = fp4_word(xh[0], xh[1], xh[2], xh[3], xh[4], xh[5], xh[6], xh[7], scale);
+}
+// a lane holds the whole block, `amax` its maximum
+__device__ __forceinline__ uint4 fp4_encode32(const float (&xh)[32], float amax, uint32_t &sbyte) {
+    const float scale = fp4_scale_of(amax, sbyte);
+    auto word = [&](int e) { return fp4_word(xh[e], xh[e + 1], xh[e + 2], xh[e + 3], xh[e + 4], xh[e + 5], xh[e + 6], xh[e + 7], scale); };
+    return make_uint4(word(0), word(8), word(16), word(24));
 }
 
 // Partial H [runs][Mpad][rank] in place of H: how a launch says so in H's first 16 bytes, and how a reader of H follows it.

@@ -111,6 +111,36 @@ bool wide_act(svdq::ActParams a, const svdq::ActPlan &other, const void *X, void
     return true;
 }
 
+// The forwards that run as one launch (layout.h, fused_small): not where the output lies in the input's memory, which other workgroups
+// are still reading when one stores its tile, and not under options, which name parts of the two launches.  Returns whether it was launched.
+bool fused_forward(bool int4, const svdq_layer_dev *L, const void *X, int M, void *Y, unsigned char *ws, size_t codes_off, size_t bx_off, size_t h_off, int Mpad, int kpar,
+                   hipStream_t stream, hipError_t &e) {
+    const svdq_shape &s = L->shape;
+    const uintptr_t x0 = (uintptr_t)X, x1 = x0 + (size_t)M * s.K * 2, y0 = (uintptr_t)Y, y1 = y0 + (size_t)M * s.N * 2;
+    if (g_options != 0 || (y0 < x1 && x0 < y1) || !svdq::fused_small(s.K / svdq::kGroup, s.rank, kpar)) return false;
+    if (void *ev = g_profile_event) {
+        e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);
+        if (e != hipSuccess) return true;
+    }
+    svdq::FusedSmallParams p{};
+    p.X = static_cast<const uint16_t *>(X);
+    p.rinv = static_cast<const float *>(L->rinv);
+    p.l1s = static_cast<const uint16_t *>(L->l1s);
+    p.wcodes = static_cast<const uint8_t *>(L->wcodes);
+    p.bw = static_cast<const uint8_t *>(L->wscales);
+    p.l2t = static_cast<const uint16_t *>(L->l2);
+    p.bias = static_cast<const float *>(L->bias);
+    p.Y = static_cast<uint16_t *>(Y);
+    p.codes = ws + codes_off;
+    p.bx = ws + bx_off;
+    p.H = reinterpret_cast<float *>(ws + h_off);
+    p.M = M; p.N = s.N; p.K = s.K; p.G = s.K / svdq::kGroup;
+    p.Mpad = Mpad; p.Npad = svdq::round_up(s.N, svdq::kRowPad);
+    p.rank = s.rank;
+    e = svdq::launch_fused_small(p, int4 ? 0 : 1, stream);
+    return true;
+}
+
 // The INT4 forward behind both entry points.  ksplit_force / act_force > 0 replace the K split of the GEMM / the groups
 // per activation-kernel workgroup of the calling thread's option word; lean: layout.h, workspace_layout.
 int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *workspace, size_t workspace_bytes, void *hip_stream,
@@ -158,6 +188,7 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     a.arrived = reinterpret_cast<unsigned long long *>(ws + w.aflags_off);
 
     hipError_t e;
+    if (fused_forward(true, L, X, M, Y, ws, w.codes_off, 0, w.h_off, w.Mpad, small.kpar, stream, e)) return e == hipSuccess ? SVDQ_OK : hip_fail(e);
     if (!unfused) {
         const bool one_pass = !w.act.deposit && act_force == 0 && act_override() == 0 && svdq::act_one_pass(0, M, s.K, s.rank);
         a.deposit = w.act.deposit;
@@ -382,6 +413,7 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     a.deposit = w.act.deposit;
     const bool one_pass = act_override() == 0 && !w.act.deposit && svdq::act_one_pass(1, M, s.K, s.rank);
     hipError_t e = hipSuccess;
+    if (fused_forward(false, L, X, M, Y, ws, w.codes_off, w.bx_off, w.h_off, w.Mpad, kpar, stream, e)) return e == hipSuccess ? SVDQ_OK : hip_fail(e);
     const bool wide = lowrank && !a.deposit && act_override() == 0 && wide_act(a, w.act, X, Y, s.N, ws + w.partial_off, kpar ? w.total - w.partial_off : 0, stream, e);
     if (!wide) e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);

@@ -131,6 +131,22 @@ hipError_t launch_gemm_fp4_kpar(const GemmFp4Params &p, hipStream_t stream);
 constexpr int kPeakProbeGrid = 512;
 hipError_t launch_mfma_peak(int kind, int iters, float *sink, hipStream_t stream);
 
+// ---- the forward of a small batch in one launch (fused_small_kernel.hip; INT4: fmt 0, MXFP4: fmt 1) ------------------
+struct FusedSmallParams {
+    const uint16_t *X;       // bf16 [M][K]
+    const float *rinv;       // fp32 [K]
+    const uint16_t *l1s;     // bf16, fragment order
+    const uint8_t *wcodes;   // INT4: weight blocks; MXFP4: codes
+    const uint8_t *bw;       // MXFP4: scale bytes of the weights
+    const uint16_t *l2t;     // bf16 [Npad][rank]
+    const float *bias;       // fp32 [Npad]
+    uint16_t *Y;             // bf16 [M][N]; must not share memory with X
+    uint8_t *codes, *bx;     // what the forward leaves in the workspace: activation blocks (MXFP4: codes, scale bytes),
+    float *H;                // fp32 [Mpad][rank]
+    int M, N, K, G, Mpad, Npad, rank;      // rank <= 64
+};
+hipError_t launch_fused_small(const FusedSmallParams &p, int fmt, hipStream_t stream);
+
 // ---- W4A16: 16-bit activations, INT4 weights (small batches) ---------------------------------------------------
 struct W4A16Params {
     const uint16_t *X;       // bf16 [M][K]

@@ -321,6 +321,16 @@ inline int plan_kpar_blocks(bool i8, int M, int N, int G, int ksplit_override = 
     return t128 <= 512 ? kKpar4x4 : kKparNone;
 }
 
+// INT4 and MXFP4 forwards that run as ONE launch (fused_small_kernel.hip): launches of at most one 32 x 64 tile per CU whose K is
+// short enough for every tile to quantize its tokens again.  us per forward back to back, two launches | one, rank 32:
+//   INT4   M = 1, N = 1152: K = 1024 8.6 | 7.0, 1536 8.8 | 7.9, 1792 9.2 | 8.3, 2048 9.4 | 9.2;  M = 256: K = 1024 9.6 | 7.1, 1792 10.1 | 8.6, 2304 11.1 | 10.2
+//          M = 32, N = 16384: K = 1024 9.0 | 7.3, 1792 10.6 | 9.4, 2048 11.4 | 10.9
+//   MXFP4  M = 1, N = 1152: K = 1024 9.1 | 6.5, 1792 9.1 | 7.7, 2048 9.2 | 8.3;  M = 256: K = 1024 9.2 | 6.7, 1792 9.1 | 7.9;  M = 8, N = 192: K = 1792 9.2 | 7.6
+// In a replayed graph, where no host stands between the launches, the last gain is that of K = 1792 (INT4 4 to 12 %, MXFP4 2 to 9 %;
+// K = 2048 2 % slower to 5 % faster, MXFP4 4 % slower to 3 % faster).  Wider branches lose: rank 64, M = 8, K = 1536, N = 9216 9.3 | 11.3.  K below 1024
+// keeps its two launches, whose cut has rules of its own (act_short_runs).
+inline bool fused_small(int G, int rank, int kpar) { return kpar == kKpar1x8 && rank <= 32 && G >= 16 && G <= 28; }
+
 // How the W4A4 GEMM of an M x N x (64 G) layer is launched.  Tiles are 128 x 256, two workgroups per CU (512 places).
 // The K loops of a launch with at most one workgroup per CU can be split over up to eight workgroups per tile (at least
 // twelve groups each): every one of them writes its fp32 partial tile to the workspace, and the one that finishes last
