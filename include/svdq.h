@@ -168,8 +168,8 @@ typedef struct {
 size_t svdq_workspace_bytes(int M, const svdq_shape *shape);
 
 /*
- * The hot path (Eq. 5; kernel split after Sec. 4.3 / Fig. 6b): two kernels on `hip_stream` (three for many tokens at ranks
- * above 64, where runs' partial H are added up between them)
+ * The hot path (Eq. 5; kernel split after Sec. 4.3 / Fig. 6b): two kernels on `hip_stream` (three where K is cut into runs whose
+ * partial H are added up between them)
  *   1. activation kernel: reads X once; smoothing, per-group INT4 quantization with fp16 scales,
  *      and the down projection H = X^ L1
  *   2. W4A4 GEMM: the INT4 codes go through the matrix core as exact 6-bit floats, one instruction per group of

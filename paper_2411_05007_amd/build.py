@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsvdq.so")
 
-SOURCES = ["prepare.cpp", "act_kernel.hip", "act_onepass_kernel.hip", "act_w8_small_kernel.hip", "act_wide_kernel.hip", "fused_small_kernel.hip", "gemm_w4a4_kernel.hip", "gemm_w4a4_kpar_kernel.hip", "gemm_w4a4_mid_kernel.hip", "gemm_fp4_kernel.hip", "gemm_kpar_blocks_kernel.hip", "w8a8_kernels.hip", "w4a16_kernel.hip", "peak_probe.hip", "api.hip"]
+SOURCES = ["prepare.cpp", "act_kernel.hip", "act_onepass_kernel.hip", "act_w8_small_kernel.hip", "act_wide_kernel.hip", "act_tile_kernel.hip", "fused_small_kernel.hip", "gemm_w4a4_kernel.hip", "gemm_w4a4_kpar_kernel.hip", "gemm_w4a4_mid_kernel.hip", "gemm_fp4_kernel.hip", "gemm_kpar_blocks_kernel.hip", "w8a8_kernels.hip", "w4a16_kernel.hip", "peak_probe.hip", "api.hip"]
 
 # -packed-fp32-ops is switched OFF for all device code; no fast-math, no fp contraction:
 # the quantizer's roundings must be exactly the IEEE single operations that are written.
@@ -31,7 +31,7 @@ def hipcc() -> str:
 
 # GEMM kernels only: MFMA results go to ordinary VGPRs.  The rescale consumes them on the vector ALU right away, and an
 # AGPR destination would cost one v_accvgpr_read per partial sum.
-MFMA_VGPR = {"fused_small_kernel.hip", "gemm_w4a4_kernel.hip", "gemm_w4a4_kpar_kernel.hip", "gemm_w4a4_mid_kernel.hip", "gemm_fp4_kernel.hip", "gemm_kpar_blocks_kernel.hip", "w8a8_kernels.hip", "w4a16_kernel.hip", "peak_probe.hip"}
+MFMA_VGPR = {"act_tile_kernel.hip", "fused_small_kernel.hip", "gemm_w4a4_kernel.hip", "gemm_w4a4_kpar_kernel.hip", "gemm_w4a4_mid_kernel.hip", "gemm_fp4_kernel.hip", "gemm_kpar_blocks_kernel.hip", "w8a8_kernels.hip", "w4a16_kernel.hip", "peak_probe.hip"}
 
 
 def build_library(verbose: bool = True, extra: list[str] | None = None) -> str:

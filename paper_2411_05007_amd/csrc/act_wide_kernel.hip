@@ -19,7 +19,6 @@
 
 #include "act_common.h"
 #include "buffer.h"
-#include "gemm_kpar.h"
 #include "kernels.h"
 #include "layout.h"
 #include "lds_limit.h"
@@ -222,19 +221,29 @@ hipError_t launch_wide(const ActParams &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// H and its bf16 parts from the runs' partial sums [runs][rows][rank], added in run order
-__global__ __launch_bounds__(256) void act_sum_h_kernel(const float *hpart, int runs, int M, int rows, int rank, float *H, uint8_t *hfrag) {
-    const int octets = rank / 8, idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= M * octets) return;
-    const int m = idx / octets, col = 8 * (idx - m * octets);
-    const KparH h = kpar_sum_h<8>(hpart, runs, rows, rank, m, col);
-    uint4 hi, lo;
-    kpar_split_h(h, hi, lo);
-    float4 *o = reinterpret_cast<float4 *>(H + (size_t)m * rank + col);
-    o[0] = make_float4(h.h[0], h.h[1], h.h[2], h.h[3]);
-    o[1] = make_float4(h.h[4], h.h[5], h.h[6], h.h[7]);
-    *reinterpret_cast<uint4 *>(hfrag + hfrag_offset(rank, m, col, 0)) = hi;
-    *reinterpret_cast<uint4 *>(hfrag + hfrag_offset(rank, m, col, 1)) = lo;
+// H and its bf16 parts from the runs' partial sums [runs][rows][rank], added in run order: four columns of a token per thread, one
+// wavefront per workgroup, so that a small launch reaches every CU
+__global__ __launch_bounds__(64) void act_sum_h_kernel(const float *hpart, int runs, int M, int rows, int rank, float *H, uint8_t *hfrag) {
+    const int quads = rank / 4, idx = blockIdx.x * 64 + threadIdx.x;
+    if (idx >= M * quads) return;
+    const int m = idx / quads, col = 4 * (idx - m * quads);
+    const size_t at = (size_t)m * rank + col, stride = (size_t)rows * rank;
+    float4 h = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int kBatch = 8;      // runs that are requested before the first addition waits
+    for (int c0 = 0; c0 < runs; c0 += kBatch) {
+        float4 t[kBatch];
+#pragma unroll
+        for (int c = 0; c < kBatch; ++c) t[c] = *reinterpret_cast<const float4 *>(hpart + (c0 + c < runs ? c0 + c : c0) * stride + at);
+#pragma unroll
+        for (int c = 0; c < kBatch; ++c)
+            if (c0 + c < runs) { h.x += t[c].x; h.y += t[c].y; h.z += t[c].z; h.w += t[c].w; }
+    }
+    const uint32_t hi0 = bf16_rne_pair(h.x, h.y), hi1 = bf16_rne_pair(h.z, h.w);
+    const uint32_t lo0 = bf16_rne_pair(h.x - bf16lo(hi0), h.y - bf16hi(hi0)), lo1 = bf16_rne_pair(h.z - bf16lo(hi1), h.w - bf16hi(hi1));
+    *reinterpret_cast<float4 *>(H + at) = h;
+    unsigned char *o = hfrag + 2 * (col & 7);
+    *reinterpret_cast<uint2 *>(o + hfrag_offset(rank, m, col, 0)) = make_uint2(hi0, hi1);
+    *reinterpret_cast<uint2 *>(o + hfrag_offset(rank, m, col, 1)) = make_uint2(lo0, lo1);
 }
 
 }  // namespace
@@ -250,7 +259,7 @@ hipError_t launch_act_wide(const ActParams &p, hipStream_t stream) {
 hipError_t launch_act_sum_h(const ActParams &p, int rows, hipStream_t stream) {
     if (p.M <= 0 || p.rank <= 0) return hipSuccess;
     if (!p.hpart || p.chunks < 1 || rows < p.M) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(act_sum_h_kernel, dim3((unsigned)((p.M * (p.rank / 8) + 255) / 256)), dim3(256), 0, stream, p.hpart, p.chunks, p.M, rows, p.rank, p.H, p.hfrag);
+    hipLaunchKernelGGL(act_sum_h_kernel, dim3((unsigned)(((size_t)p.M * (p.rank / 4) + 63) / 64)), dim3(64), 0, stream, p.hpart, p.chunks, p.M, rows, p.rank, p.H, p.hfrag);
     return hipGetLastError();
 }
 

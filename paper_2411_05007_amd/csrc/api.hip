@@ -94,19 +94,20 @@ int static_scratch(unsigned char **out) {
     return SVDQ_OK;
 }
 
-// The activation step of a wide branch by 64-token workgroups (layout.h, plan_act_wide).  The runs' partial H lie in Y, which the GEMM
-// writes after they have been added up, or in `spare`, room that the launch's workspace has and its GEMM does not use.  Returns
+// The activation step of a branch by workgroups of 32 or 64 tokens (layout.h, plan_act_tile and plan_act_wide).  The runs' partial H lie in Y, which the
+// GEMM writes after they have been added up, or in `spare`, room that the launch's workspace has and its GEMM does not use.  Returns
 // whether it was launched (`e`: how that went).  Not in a Y that shares memory with X, which is still being read, or is not
 // aligned for it.
-bool wide_act(svdq::ActParams a, const svdq::ActPlan &other, const void *X, void *Y, int N, void *spare, size_t spare_bytes, hipStream_t stream, hipError_t &e) {
+bool branch_act(svdq::ActParams a, const svdq::ActPlan &other, bool one_pass, const void *X, void *Y, int N, void *spare, size_t spare_bytes, hipStream_t stream, hipError_t &e) {
     const uintptr_t x0 = (uintptr_t)X, x1 = x0 + (size_t)a.M * a.K * 2, y0 = (uintptr_t)Y, y1 = y0 + (size_t)a.M * N * 2;
     const size_t one = (size_t)a.M * a.rank * 4, in_y = (y0 & 15) || (y0 < x1 && x0 < y1) || one == 0 ? 0 : (size_t)a.M * N * 2 / one, in_spare = one == 0 ? 0 : spare_bytes / one;
-    const int runs = svdq::plan_act_wide(a.fmt == 0, other, a.M, a.G, a.rank, in_y > in_spare ? in_y : in_spare);
+    const size_t room = in_y > in_spare ? in_y : in_spare;
+    const int wide = svdq::plan_act_wide(a.fmt == 0, other, a.M, a.G, a.rank, room), runs = wide ? wide : svdq::plan_act_tile(other, one_pass, a.M, a.G, a.rank, room);
     if (runs == 0) return false;
     a.chunks = runs;
     a.gchunk = (a.G + runs - 1) / runs;
     a.hpart = static_cast<float *>((size_t)runs <= in_spare ? spare : Y);
-    e = svdq::launch_act_wide(a, stream);
+    e = wide ? svdq::launch_act_wide(a, stream) : svdq::launch_act_tile(a, stream);
     if (e == hipSuccess) e = svdq::launch_act_sum_h(a, a.M, stream);
     return true;
 }
@@ -192,8 +193,8 @@ int forward_int4(const svdq_layer_dev *L, const void *X, int M, void *Y, void *w
     if (!unfused) {
         const bool one_pass = !w.act.deposit && act_force == 0 && act_override() == 0 && svdq::act_one_pass(0, M, s.K, s.rank);
         a.deposit = w.act.deposit;
-        const bool wide = lowrank && !a.deposit && act_force == 0 && act_override() == 0 && wide_act(a, w.act, X, Y, s.N, ws + w.partial_off, whole ? w.total - w.partial_off : 0, stream, e);
-        if (!wide) e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
+        const bool branch = lowrank && !a.deposit && act_force == 0 && act_override() == 0 && branch_act(a, w.act, one_pass, X, Y, s.N, ws + w.partial_off, whole ? w.total - w.partial_off : 0, stream, e);
+        if (!branch) e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
         if (e != hipSuccess) return hip_fail(e);
         if (void *ev = g_profile_event) {
             e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);
@@ -414,8 +415,8 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     const bool one_pass = act_override() == 0 && !w.act.deposit && svdq::act_one_pass(1, M, s.K, s.rank);
     hipError_t e = hipSuccess;
     if (fused_forward(false, L, X, M, Y, ws, w.codes_off, w.bx_off, w.h_off, w.Mpad, kpar, stream, e)) return e == hipSuccess ? SVDQ_OK : hip_fail(e);
-    const bool wide = lowrank && !a.deposit && act_override() == 0 && wide_act(a, w.act, X, Y, s.N, ws + w.partial_off, kpar ? w.total - w.partial_off : 0, stream, e);
-    if (!wide) e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
+    const bool branch = lowrank && !a.deposit && act_override() == 0 && branch_act(a, w.act, one_pass, X, Y, s.N, ws + w.partial_off, kpar ? w.total - w.partial_off : 0, stream, e);
+    if (!branch) e = one_pass ? svdq::launch_act_one_pass(a, lowrank ? 3 : 1, stream) : svdq::launch_act(a, lowrank ? 3 : 1, stream);
     if (e != hipSuccess) return hip_fail(e);
     if (void *ev = g_profile_event) {
         e = hipEventRecord(static_cast<hipEvent_t>(ev), stream);

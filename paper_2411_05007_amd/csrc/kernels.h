@@ -46,6 +46,8 @@ constexpr int kActW8SmallGroups = 192;      // K up to 12288: what sixteen wavef
 // INT4 and MXFP4, ranks up to 128, 64 tokens to a workgroup (act_wide_kernel.hip): quantizes and leaves the partial H of p.chunks runs of p.gchunk
 // groups in p.hpart, fp32 [p.chunks][M][rank]
 hipError_t launch_act_wide(const ActParams &p, hipStream_t stream);
+// the same by workgroups of 32 tokens (act_tile_kernel.hip)
+hipError_t launch_act_tile(const ActParams &p, hipStream_t stream);
 // H (and its bf16 parts) from such parts, [p.chunks][rows][rank], where the GEMM does not add them itself
 hipError_t launch_act_sum_h(const ActParams &p, int rows, hipStream_t stream);
 

@@ -519,6 +519,31 @@ inline int plan_act_wide(bool int4, const ActPlan &other, int M, int G, int rank
     return take ? cut : 0;
 }
 
+// INT4 and MXFP4 launches that take the kernel of 32-token workgroups (act_tile_kernel.hip): the number of runs that K is cut into (0: they do not),
+// for `room` runs' partial H.  `other`: the plan of the 16-token workgroups, which do not leave partial H for the GEMM.  Two workgroups per CU up
+// to rank 64, one beyond, runs of whole rounds of the four wavefronts, two of them at least and three of a K above 64 groups.
+// us per forward, act_kernel.hip | this, ranks above 32: INT4 M = 1440, K = 1792, N = 2336, rank 128 31.9 | 25.2; M = 1255, K = 9856, N = 528, rank 48 37.0 | 29.6; M = 512,
+// K = 12288, N = 3072, rank 128 42.7 | 39.7; M = 320 35.6 | 28.9; M = 913, K = 10624, N = 5984, rank 64 93.6 | 85.0; MXFP4 M = 131, K = 10688, N = 4352, rank 128 29.2 | 23.8; M = 3078,
+// K = 2368, N = 1936, rank 128 36.4 | 32.6.  Not taken: more than 2048 tokens, which fill the CUs with 16 to a workgroup, with a short K (INT4 M = 3246, K = 1408, N = 432,
+// rank 64 17.0 | 19.5; M = 4006, K = 2816, N = 2736, rank 64 60.6 | 62.8; MXFP4 M = 2235, K = 1664, N = 768, rank 96 19.7 | 20.8).
+// Up to rank 32 only where the runs of the other kernel meet: M = 1500, K = 8192, N = 2048, rank 16 51.7 | 45.8, M = 2300, K = 9216, rank 32 75.8 | 70.8; else
+// M = 3000, K = 6144, N = 3072, rank 16 95.2 | 96, MXFP4 M = 1500, K = 3072, N = 4608 28.3 | 28.9 (one pass).
+constexpr int kActTileTokens = 32;
+inline int plan_act_tile(const ActPlan &other, bool one_pass, int M, int G, int rank, size_t room) {
+    if (rank > 128 || G < 16 || M > 4096) return 0;
+    if (rank <= 32 && (one_pass || other.chunks <= 1 || other.whole != 0)) return 0;
+    if (rank > 32 && M > 2048 && G < (rank > 64 ? 36 : 72)) return 0;
+    const int tiles = (M + kActTileTokens - 1) / kActTileTokens;
+    size_t runs = (rank > 64 ? 256 : 512) / tiles;
+    if (runs > room) runs = room;
+    if (runs < 1) return 0;
+    int gc = (G + (int)runs - 1) / (int)runs;
+    gc = (gc + 3) / 4 * 4;
+    if (gc < (G > 64 ? 12 : 8)) gc = G > 64 ? 12 : 8;
+    const int cut = (G + gc - 1) / gc;
+    return gc <= 12 || tiles * cut >= 128 ? cut : 0;
+}
+
 // Where partial H is left for the GEMM, H itself is never made in memory; its first 16 bytes name the place of the parts instead, for
 // svdq_debug_act: two words that no sum of products gives (a NaN with this payload), the number of runs, and how many 256-byte
 // units behind H the parts [runs][Mpad][rank] start.
