@@ -20,11 +20,13 @@
 // its next group requested while it works on this one; a group's scale is one FMA per output; behind the loop the
 // wavefronts' shares of H meet in LDS, H L2 is one or two more steps of the same MFMA, and the wavefronts' sums meet in
 // LDS, both in wavefront order (deterministic).
-// Bound: a wavefront's chain of groups (about 250 vector instructions each, half of them X^'s parts, between the waits for the
-// next) and the fixed parts around the loop; by counters the vector ALU is busy 38 % of the time, the matrix core 7 to 15 %, and
-// the wavefronts wait for 60 %.  us per forward, K = 3072, rank 32, before (codes to floats, products on the vector ALU, H in a
-// launch of its own) -> now: N = 18432: 1 row 13.5 -> 11.9, 16 rows 61.7 -> 14.6;
-// N = 9216: 16 rows 44 -> 11.9; N = 3072: 1 row 11.5 -> 7.9.
+// Up to five rows the parts of X^ (and X itself, for H) are made once per workgroup and lie in LDS, where those of the rows fit it
+// (PARTS): five rows are five of a lane's sixteen operand rows, and a wavefront that makes them in its lanes makes everything three
+// times.
+// Bound: five rows by the load path (13 requests per group and wavefront: 2.7 us of a CU's time at K = 3072) and 96 vector instructions per
+// group (202 with the parts in the loop), more rows by 222 vector and 40 matrix instructions per group, and the fixed parts around the loop.  us
+// per forward, rank 32, parts of X^ in the loop -> in LDS: 1 row, K = 3072, N = 18432 11.9 -> 10.8; K = 12288, N = 3072 21.7 -> 16.1; K = N = 8192, rank 16
+// 16.4 -> 11.1; K = 4096, N = 1536 9.3 -> 6.6; 5 rows, K = 3072, N = 9216, rank 16 10.3 -> 9.1.  16 rows, K = 3072, N = 18432 14.6.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -46,10 +48,17 @@ typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 constexpr int kStackRows = 5;
 // LDS of the loop: 1 / lambda of all channels, and behind it the wavefronts' shares of H [wave][16 rows][16 RK + 4]
 constexpr int mfma_loop_bytes(int K, int rk, int waves) { return K * 4 + (rk > 0 ? waves * 16 * (16 * rk + 4) * 4 : 0); }
+// PARTS: bytes of one part of a row of X^, so that the rows of an operand read fall on distinct banks; and the loop's LDS, [part][row][K] (and, for H, X
+// itself behind them) in place of 1 / lambda
+constexpr __host__ __device__ int parts_row_bytes(int K) { return 2 * K + 16; }
+inline int mfma_parts_bytes(int M, int K, int rk, int waves) {
+    const int parts = (rk > 0 ? 4 : 3) * (M < kStackRows ? M : kStackRows) * parts_row_bytes(K), h = rk > 0 ? waves * 16 * (16 * rk + 4) * 4 : 0;
+    return parts + h <= kLdsBytesPerCU ? parts + h : parts > h ? parts : h;
+}
 constexpr int mfma_sums_bytes(int cb, int waves) { return waves * cb * 2 * 16 * 17 * 4; }
 
-// APART: all parts of X^ are made before the first is packed (split8)
-template <bool STACK, int CB, int RK, int WAVES, bool APART>
+// APART: all parts of X^ are made before the first is packed (split8).  PARTS (STACK): they are made once per workgroup, in LDS
+template <bool STACK, int CB, int RK, int WAVES, bool APART, bool PARTS>
 __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];      // 1 / lambda of all channels, later the wavefronts' sums
     constexpr int SETS = STACK ? 1 : 3, RM = STACK ? kStackRows : 16;
@@ -93,7 +102,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
     const int rb = p.rank / 16;
     const __amdgpu_buffer_rsrc_t rs_l = make_rsrc(p.l1s, (size_t)p.K * p.rank * 2);
     struct Batch { u32x4 x[2], w[CB], l[RK > 0 ? 2 * RK : 1]; uint16_t s[CB][2]; };
-    auto load = [&](int g) {
+    auto load = [&](int g, auto careful) {      // (careful: for the walk behind the loop)
         Batch t;
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
@@ -102,7 +111,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
             for (int c = 0; c < 2; ++c) t.s[cb][c] = __builtin_amdgcn_raw_buffer_load_b16(rs_s, 2 * l16, (g * p.Npad + first[cb] + 16 * c) * 2, 0);
         }
 #pragma unroll
-        for (int j = 0; j < 2; ++j) t.x[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_x, vx + 16 * j, g * 128, 0));
+        for (int j = 0; j < 2; ++j)
+            if (!PARTS || decltype(careful)::value) t.x[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_x, vx + 16 * j, g * 128, 0));
 #pragma unroll
         for (int i = 0; i < 2 * RK; ++i) {      // blocks past the rank repeat the last one; what they give is dropped
             const int c = i / 2 < rb ? i / 2 : rb - 1;
@@ -110,7 +120,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
         }
         return t;
     };
-    Batch cur = load(wave < G ? wave : G - 1);
+    Batch cur = load(wave < G ? wave : G - 1, std::false_type{});
     // Everything else that comes from memory is requested right behind: the bias of the outputs this thread will finish,
     // the operands of the wavefront's first low-rank step, 1 / lambda.
     constexpr int kOut = (RM * CB * 32 + WAVES * 64 - 1) / (WAVES * 64);
@@ -142,7 +152,56 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
     LowRank low;
     if (wave < steps) low = load_lowrank(wave);
     float *lrinv = reinterpret_cast<float *>(lds);
-    for (int k = 4 * threadIdx.x; k < p.K; k += 4 * WAVES * 64) *reinterpret_cast<float4 *>(lrinv + k) = *reinterpret_cast<const float4 *>(p.rinv + k);
+    // PARTS: eight channels of a row per thread and turn
+    const int prow = parts_row_bytes(p.K), have = p.M - m0 < RM ? p.M - m0 : RM;
+    if constexpr (PARTS) {
+        constexpr int kTurns = 4;      // requested together
+        const int chunks = have * (p.K / 8);
+        for (int c0 = threadIdx.x; c0 - (int)threadIdx.x < chunks; c0 += kTurns * WAVES * 64) {
+            uint4 w[kTurns];
+            float4 ra[kTurns], rq[kTurns];
+            int at[kTurns];
+#pragma unroll
+            for (int u = 0; u < kTurns; ++u) {
+                if (u > 0 && c0 - (int)threadIdx.x + u * WAVES * 64 >= chunks) break;
+                const int c = c0 + u * WAVES * 64 < chunks ? c0 + u * WAVES * 64 : chunks - 1;      // (past the end: the last one again, the same bits)
+                const int r = c / (p.K / 8), k = 8 * (c - r * (p.K / 8));
+                w[u] = *reinterpret_cast<const uint4 *>(p.X + (size_t)(m0 + r) * p.K + k);
+                ra[u] = *reinterpret_cast<const float4 *>(p.rinv + k);
+                rq[u] = *reinterpret_cast<const float4 *>(p.rinv + k + 4);
+                at[u] = r * prow + 2 * k;
+            }
+#pragma unroll
+            for (int u = 0; u < kTurns; ++u) {
+                if (u > 0 && c0 - (int)threadIdx.x + u * WAVES * 64 >= chunks) break;
+                const uint32_t xw[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+                const float rr[8] = {ra[u].x, ra[u].y, ra[u].z, ra[u].w, rq[u].x, rq[u].y, rq[u].z, rq[u].w};
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[2 * e] = __uint_as_float(xw[e] << 16) * rr[2 * e];
+                    x[2 * e + 1] = __uint_as_float(xw[e] & 0xffff0000u) * rr[2 * e + 1];
+                }
+#pragma unroll
+                for (int part = 0; part < 3; ++part) {
+                    u32x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        o[e] = (uint32_t)__builtin_amdgcn_perm(__float_as_uint(x[2 * e + 1]), __float_as_uint(x[2 * e]), 0x07060302);
+                        x[2 * e] -= __uint_as_float(__float_as_uint(x[2 * e]) & 0xffff0000u);
+                        x[2 * e + 1] -= __uint_as_float(__float_as_uint(x[2 * e + 1]) & 0xffff0000u);
+                    }
+                    *reinterpret_cast<u32x4 *>(lds + part * have * prow + at[u]) = o;
+                }
+                if (RK > 0) *reinterpret_cast<uint4 *>(lds + 3 * have * prow + at[u]) = w[u];      // X itself, for H
+            }
+        }
+    }
+    // (a lane's operand row: part and token; the row that carries nothing and tokens past M read one that is there)
+    const int mine = PARTS ? ((part < 3 ? part : 0) * have + (l16 % kStackRows < have ? l16 % kStackRows : have - 1)) * prow + 32 * q4 : 0;
+    const int mine_x = PARTS ? (3 * have + (l16 % kStackRows < have ? l16 % kStackRows : have - 1)) * prow + 32 * q4 : 0;
+    if constexpr (!PARTS)
+        for (int k = 4 * threadIdx.x; k < p.K; k += 4 * WAVES * 64) *reinterpret_cast<float4 *>(lrinv + k) = *reinterpret_cast<const float4 *>(p.rinv + k);
     floatx4 acc[CB][2];
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) acc[cb][0] = acc[cb][1] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -177,7 +236,11 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
         u32x4 a[2][SETS];
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const float4 *rp = reinterpret_cast<const float4 *>(lrinv + 64 * g + 16 * q4 + 8 * j);
+            if (PARTS && !decltype(careful)::value) {
+                a[j][0] = *reinterpret_cast<const u32x4 *>(lds + mine + 128 * g + 16 * j);
+                continue;
+            }
+            const float4 *rp = reinterpret_cast<const float4 *>((PARTS ? p.rinv : lrinv) + 64 * g + 16 * q4 + 8 * j);
             const float4 r0 = rp[0], r1 = rp[1];
             const u32x4 w = t.x[j];
             const float x[8] = {__uint_as_float(w.x << 16) * r0.x, __uint_as_float(w.x & 0xffff0000u) * r0.y, __uint_as_float(w.y << 16) * r0.z, __uint_as_float(w.y & 0xffff0000u) * r0.w,
@@ -218,7 +281,10 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
         }
     };
     for (int g = wave; g < G; g += WAVES) {
-        const Batch nxt = load(g + WAVES < G ? g + WAVES : g);      // past the end: this group again, loaded and ignored
+        const Batch nxt = load(g + WAVES < G ? g + WAVES : g, std::false_type{});      // past the end: this group again, loaded and ignored
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (PARTS && RK > 0) cur.x[j] = *reinterpret_cast<const u32x4 *>(lds + mine_x + 128 * g + 16 * j);
 #pragma unroll
         for (int i = 0; i < 2 * RK; ++i) hacc[RK > 0 ? i / 2 : 0] = mfma(cur.x[i % 2], cur.l[RK > 0 ? i : 0], hacc[RK > 0 ? i / 2 : 0]);
         multiply(cur, g, std::false_type{});
@@ -240,12 +306,15 @@ __global__ __launch_bounds__(WAVES * 64, 1) void w4a16_mfma_kernel(W4A16Params p
                 low = load_lowrank(s);
                 add_lowrank(s);
             }
-        for (int g = wave; g < G; g += WAVES) multiply(load(g), g, std::true_type{});
+        for (int g = wave; g < G; g += WAVES) multiply(load(g, std::true_type{}), g, std::true_type{});
     }
     // H: the wavefronts' shares meet in LDS behind 1 / lambda; the wavefront of a low-rank step adds up the 32 columns it
     // needs, in wavefront order, as it reads its operand
     constexpr int kHRow = 16 * (RK > 0 ? RK : 1) + 4;
-    float *hs = lrinv + p.K;      // [wave][16 rows][kHRow]
+    // (behind 1 / lambda or the parts of X^; in the place of the latter where LDS does not hold both)
+    const bool in_place = PARTS && 4 * have * prow + WAVES * 16 * kHRow * 4 > kLdsBytesPerCU;
+    if (RK > 0 && in_place) __syncthreads();
+    float *hs = PARTS ? reinterpret_cast<float *>(lds + (in_place ? 0 : 4 * have * prow)) : lrinv + p.K;      // [wave][16 rows][kHRow]
 #pragma unroll
     for (int c = 0; c < RK; ++c)
 #pragma unroll
@@ -339,16 +408,22 @@ __global__ __launch_bounds__(1024) void w4a16_proj_kernel(const uint16_t *X, con
 }
 
 // ---- host side ----------------------------------------------------------------------------------------------------
-template <bool STACK, int CB, int RK, int WAVES, bool APART>
-hipError_t launch_mfma_apart(const W4A16Params &p, hipStream_t stream) {
-    auto k = w4a16_mfma_kernel<STACK, CB, RK, WAVES, APART>;
+template <bool STACK, int CB, int RK, int WAVES, bool APART, bool PARTS>
+hipError_t launch_mfma_parts(const W4A16Params &p, hipStream_t stream) {
+    auto k = w4a16_mfma_kernel<STACK, CB, RK, WAVES, APART, PARTS>;
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), kLdsBytesPerCU); e != hipSuccess) return e;
     const int rows = STACK ? kStackRows : 16;
-    const int loop = mfma_loop_bytes(p.K, RK, WAVES), sums = mfma_sums_bytes(CB, WAVES), bytes = loop > sums ? loop : sums;
+    const int loop = PARTS ? mfma_parts_bytes(p.M, p.K, RK, WAVES) : mfma_loop_bytes(p.K, RK, WAVES), sums = mfma_sums_bytes(CB, WAVES), bytes = loop > sums ? loop : sums;
     if (bytes > kLdsBytesPerCU) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, dim3((p.N + 32 * CB - 1) / (32 * CB), (p.M + rows - 1) / rows), dim3(WAVES * 64), bytes, stream, p);
     return hipGetLastError();
+}
+template <bool STACK, int CB, int RK, int WAVES, bool APART>
+hipError_t launch_mfma_apart(const W4A16Params &p, hipStream_t stream) {
+    if constexpr (STACK)
+        if (mfma_parts_bytes(p.M, p.K, RK, WAVES) <= kLdsBytesPerCU) return launch_mfma_parts<true, CB, RK, WAVES, false, true>(p, stream);
+    return launch_mfma_parts<STACK, CB, RK, WAVES, APART, false>(p, stream);
 }
 // Parts of X^ apart from their packing costs registers.  Sixteen wavefronts have none for it.  Some variants of eight have two
 // workgroups on a CU without and one with it, and do it only while one is all there is (M = 54, K = 3840, N = 8960, rank 32, 560
@@ -381,10 +456,13 @@ hipError_t launch_mfma_shape(const W4A16Params &p, hipStream_t stream) {
     // 38.5 -> 35.4; K = 6144: 17.8 -> 17.6, 21.8 -> 20.6; rank 64 and three column blocks spill).  Only in one round: two workgroups of
     // eight wavefronts share a CU, where the second one of sixteen waits (eight | sixteen, us: 64 rows, K = N = 8192 46.2 | 51.3; 40 rows,
     // K = 6144, N = 10240 35.0 | 39.6; 4 rows, K = 6144, N = 30720 29.8 | 34.7; 16 rows, K = 12288, N = 30720 66.1 | 72.8)
+    // With the parts of X^ in LDS (five rows at most) two column blocks and ranks above 32 are as fast or faster with eight: 3 rows, K = 6144, N = 12288, rank 32
+    // 14.1 | 15.3, 1 row, K = N = 12288 20.6 | 21.9, 2 rows, K = 6144, N = 8192, rank 48 13.2 | 17.1; one block up to rank 32 is not: 1 row, K = N = 8192, rank 16 12.2 | 11.1.
+    const bool parts = STACK && mfma_parts_bytes(p.M, p.K, RK, 8) <= kLdsBytesPerCU;
     const bool sixteen = p.K >= 6144 && (long)((blocks + cb - 1) / cb) * passes <= 256 && mfma_loop_bytes(p.K, RK, 16) <= kLdsBytesPerCU;
-    if (sixteen && cb == 1) return launch_mfma<STACK, 1, RK, 16>(p, stream);
+    if (sixteen && cb == 1 && !(parts && RK > 2)) return launch_mfma<STACK, 1, RK, 16>(p, stream);
     if constexpr (RK <= 2)
-        if (sixteen && cb == 2) return launch_mfma<STACK, 2, RK, 16>(p, stream);
+        if (sixteen && cb == 2 && !parts) return launch_mfma<STACK, 2, RK, 16>(p, stream);
     return cb == 1 ? launch_mfma<STACK, 1, RK, 8>(p, stream) : cb == 2 ? launch_mfma<STACK, 2, RK, 8>(p, stream) : launch_mfma<STACK, 3, RK, 8>(p, stream);
 }
 template <bool STACK>
