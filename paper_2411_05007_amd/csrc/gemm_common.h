@@ -1,31 +1,14 @@
-// What the three GEMM kernels (INT4 on 6-bit operands, MXFP4, INT8) share: the order in which workgroups take the
-// output tiles, and a wavefront's way from its fp32 accumulators to the 16-bit output (arXiv 2411.05007 Eq. 5:
-// both branches and the bias meet in one output; Sec. 4.3: one store of the 16-bit result).
+// What the three GEMM kernels (INT4 on 6-bit operands, MXFP4, INT8) share: a wavefront's way from its fp32 accumulators to the
+// 16-bit output (arXiv 2411.05007 Eq. 5: both branches and the bias meet in one output; Sec. 4.3: one store of the 16-bit
+// result) and the low-rank product.  The order in which workgroups take the output tiles: layout.h, gemm_tile_of.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "act_common.h"
+#include "layout.h"
 
 namespace svdq {
-
-// XCD-aware tile order.  Workgroups are dealt round-robin to the chip's 8 XCDs, each with an L2 of its own; they are
-// renumbered so that an XCD owns a contiguous run of tiles, walked in bands of eight tile rows, column by column
-// inside a band: the 64 tiles an XCD runs at a time (two workgroups per CU) are then 8 x 8, the shape with the fewest
-// distinct operand blocks (measured on the INT4 GEMM at 1728 tiles: bands of 4, 6, 8, 12 rows miss the L2 for 260,
-// 224, 217, 239 MB per launch; bands of 2 to 18 rows run within 1 % of each other).
-// `bid`: position in the launch order, 0 <= bid < total = tiles_m * tiles_n.
-__device__ __forceinline__ void gemm_tile_of(int bid, int tiles_m, int tiles_n, int &tile_m, int &tile_n) {
-    constexpr int kBand = 8;
-    const int total = tiles_m * tiles_n;
-    const int per = (total + 7) / 8;
-    const int id = (total % 8 == 0) ? (bid % 8) * per + (bid / 8) : bid;      // a bijection only when 8 divides the count
-    const int band = id / (kBand * tiles_n);
-    const int band_rows = (tiles_m - band * kBand) < kBand ? (tiles_m - band * kBand) : kBand;
-    const int in = id - band * kBand * tiles_n;
-    tile_m = band * kBand + in % band_rows;
-    tile_n = in / band_rows;
-}
 
 // Epilogue of one wavefront that owns RB x CB blocks of 32 x 32 accumulators (the layout of the 32 x 32 MFMAs: register
 // v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32): bias, round to nearest even bf16 with the

@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256, 2) void gemm_w4a4_kernel(GemmW4Params p) {
     int gm0, gn0;      // the launch checks that every tile lies inside the padded rows and columns
     {
         int tile_m, tile_n;
-        gemm_tile_of(bid, tiles_m, tiles_n, tile_m, tile_n);
+        gemm_tile_of(bid, tiles_m, tiles_n, kXcdOrderInt4, tile_m, tile_n);
         gm0 = tile_m * T::kBM; gn0 = tile_n * T::kBN;
     }
     if (MODE == 1) {   // window export: only tiles that touch the window do any work (uniform per workgroup)
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(256, 2) void gemm_w4a4_kernel(GemmW4Params p) {
         more = wg < total;
         if (more) {
             int tile_m, tile_n;
-            gemm_tile_of(wg, tiles_m, tiles_n, tile_m, tile_n);
+            gemm_tile_of(wg, tiles_m, tiles_n, kXcdOrderInt4, tile_m, tile_n);
             gm0 = tile_m * T::kBM; gn0 = tile_n * T::kBN;
             place_pieces();
 #pragma unroll

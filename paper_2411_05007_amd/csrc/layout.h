@@ -122,6 +122,28 @@ inline __host__ __device__ int kpar_step(int wave, int KS, int i, int n) { retur
 inline __host__ __device__ int ring_offset(int j, int frags_a, int frags_b, int gm0, int gn0) {
     return j < frags_a ? gm0 * 32 + j * 1024 : j < frags_a + frags_b ? gn0 * 32 + (j - frags_a) * 1024 : 0;
 }
+// XCD-aware tile order.  Workgroups are dealt round-robin to the chip's 8 XCDs, each with an L2 of its own; they are
+// renumbered so that an XCD owns a contiguous run of tiles (their counts differ by at most one), walked in bands of eight tile
+// rows, column by column inside a band: the 64 tiles an XCD runs at a time (two workgroups per CU) are then 8 x 8, the shape with
+// the fewest distinct operand blocks (measured on the INT4 GEMM at 1728 tiles: bands of 4, 6, 8, 12 rows miss the L2 for 260,
+// 224, 217, 239 MB per launch; bands of 2 to 18 rows run within 1 % of each other).
+// Counts that 8 does not divide are renumbered from `from` tiles on.  us per forward in launch order -> renumbered: MXFP4, M = 1663, K = 7936, N = 8480
+// (476 tiles) 87.7 -> 74.5, M = 4162, K = 3392, N = 9296 (1221) 111 -> 96.3; INT8, M = 2943, K = 2560, N = 10576 112.9 -> 91.5, M = 1677,
+// K = 5888, N = 11328 155 -> 128 (33 launches of both: median 5 % faster, none slower).  The INT4 kernel, bound by power and not by the L2, gains 0 to 6 % above
+// 600 tiles (M = 4429, K = 1856, N = 10720 127.6 -> 120; M = 4169, K = 2496, N = 9472 125.6 -> 121.8) and loses 0 to 5 % below (M = 2213, K = 1536,
+// N = 6672, 486 tiles 38.4 -> 40.1).
+// `bid`: position in the launch order, 0 <= bid < total = tiles_m * tiles_n.
+constexpr int kXcdOrderInt4 = 600;
+inline __host__ __device__ void gemm_tile_of(int bid, int tiles_m, int tiles_n, int from, int &tile_m, int &tile_n) {
+    constexpr int kBand = 8;
+    const int total = tiles_m * tiles_n, per = total / 8, more = total % 8, xcd = bid % 8;      // the first `more` XCDs own a tile more than the others
+    const int id = more == 0 || total >= from ? xcd * per + (xcd < more ? xcd : more) + bid / 8 : bid;
+    const int band = id / (kBand * tiles_n);
+    const int band_rows = (tiles_m - band * kBand) < kBand ? (tiles_m - band * kBand) : kBand;
+    const int in = id - band * kBand * tiles_n;
+    tile_m = band * kBand + in % band_rows;
+    tile_n = in / band_rows;
+}
 constexpr int kGemmPlaces = 512;     // places for workgroups of the 128 x 256 tiles: two per CU
 constexpr int kFp4RowBytes = 32;     // packed bytes of one row of one 64-channel step
 constexpr int kMaxKSplitFp4 = 8;
