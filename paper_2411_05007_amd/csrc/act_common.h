@@ -145,11 +145,25 @@ struct W4Stage {
         *reinterpret_cast<uint32_t *>(stage + a2) = a2v;
         *reinterpret_cast<uint32_t *>(stage + b2) = b2v;
     }
+    // eight tokens: the first eight rows of each run
+    __device__ __forceinline__ void put(unsigned char *stage, uint32_t alo, uint32_t ahi, uint32_t sa) const {
+        uint32_t a1, b1, a2v, b2v;
+        words(alo, ahi, sa, 0u, 0u, 0u, a1, b1, a2v, b2v);
+        *reinterpret_cast<uint32_t *>(stage + a) = a1;
+        *reinterpret_cast<uint32_t *>(stage + a2) = a2v;
+    }
 };
 // where lane l's 16 bytes of such a stage belong in the group's activation blocks (lanes below kActOutStage / 16)
 __device__ __forceinline__ int w4_stage_out(int m0, int lane) {
     const int half16 = (m0 >> 4) & 1;
     return (m0 / 32) * kW4ABlock + (lane < 24 ? 384 * half16 + 16 * lane : lane < 48 ? 768 + 384 * half16 + 16 * (lane - 24) : kW4ACodes + 64 * half16 + 16 * (lane - 48));
+}
+// and of a stage of eight tokens: lanes 0-11 and 12-23 the k-halves, 24 and 25 the scales
+__device__ __forceinline__ int w4_stage_out8(int m0, int lane) {
+    const int half16 = (m0 >> 4) & 1, half8 = (m0 >> 3) & 1;
+    return (m0 / 32) * kW4ABlock + (lane < 12 ? 384 * half16 + 192 * half8 + 16 * lane
+                                    : lane < 24 ? 768 + 384 * half16 + 192 * half8 + 16 * (lane - 12)
+                                                : kW4ACodes + 64 * half16 + 32 * half8 + 16 * (lane - 24));
 }
 
 // Eq. 1 for one MXFP4 block (the 32 channels held by 4 neighbouring lanes): the scale is the smallest power

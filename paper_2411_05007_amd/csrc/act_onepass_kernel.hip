@@ -1,12 +1,13 @@
 // Activation kernel in one pass (arXiv 2411.05007 Sec. 4.3, Fig. 6b): smoothing, quantization (Eq. 1) and the down projection
-// H = X L1s, a workgroup of sixteen wavefronts to 16 tokens and all of their K.  Wavefront w has groups w, w + 16, ..., up to NG
+// H = X L1s, a workgroup of sixteen wavefronts to 16 or 8 tokens and all of their K.  Wavefront w has groups w, w + 16, ..., up to NG
 // of them, requested up to six at a time, long before they are used; nothing is parked or added up across workgroups, and
 // there is one barrier.
 //   FMT 0, 1 (INT4, MXFP4): groups are independent; what act_kernel.hip does, with more requests in flight per CU.
 //   FMT 2 (INT8, one scale per token; App. "Implementation Details"): a token's scale needs its maximum over all of K before
 //   the first code can be written, so the workgroup holds its tokens in registers from the one read to the codes.
 // Bound: one CU's rate of small requests, X and the L1 fragments that every workgroup reads (M = 4096, K = 4608, rank 32, INT4:
-// 16 us against 18 of act_kernel.hip, 38 MB of X; INT8 at M = 1337, K = 3072: 11 us, before in two launches 17).
+// 16 us against 18 of act_kernel.hip, 38 MB of X), and where the workgroups are fewer than the CUs by the vector instructions of one of them
+// (INT8, K = 3072: 250 per group and wavefront, twelve groups to a SIMD): eight tokens halve those.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -35,16 +36,17 @@ struct OnePassLds {
     static constexpr int kBytes = kMax + kWaves * kWave;
 };
 
-// RB: column blocks of 16 of the projection (0: none); NG: groups a wavefront holds
-template <int FMT, int RB, int NG>
+// RB: column blocks of 16 of the projection (0: none); NG: groups a wavefront holds; TOK: tokens of a workgroup, 16 or 8
+template <int FMT, int RB, int NG, int TOK>
 __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p) {
     using L = OnePassLds<RB>;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, blk = lane >> 4;      // MFMA operand / accumulator map
-    const int r8 = lane >> 3, c8 = lane & 7;         // load map: tokens r8 and r8 + 8, channels 8 c8 .. + 7 of a group
-    const int m0 = blockIdx.x * 16, ma = m0 + r8, mb = ma + 8;
+    constexpr bool kTwo = TOK == 16;
+    const int r8 = lane >> 3, c8 = lane & 7;         // load map: tokens r8 and (of sixteen) r8 + 8, channels 8 c8 .. + 7 of a group
+    const int m0 = blockIdx.x * TOK, ma = m0 + r8, mb = ma + 8;
     const int rb = p.rank / 16;
 
     // rows past M read the last row; what they produce lands in padding rows and is never used
@@ -58,9 +60,12 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
     const int vxb = (int)(((uint32_t)(mb < p.M ? mb : p.M - 1) * (uint32_t)p.K + 8u * (uint32_t)c8) * 2u);
     const int vca = FMT == 2 ? (int)i8_code_offset(8 * c8, p.Mpad, ma) : (int)fp4_code_offset(0, p.Mpad, ma, c8 >> 2) + 4 * (c8 & 3);
     const int vcb = FMT == 2 ? (int)i8_code_offset(8 * c8, p.Mpad, mb) : (int)fp4_code_offset(0, p.Mpad, mb, c8 >> 2) + 4 * (c8 & 3);
-    const int vsx = (int)fp4_scale_offset(0, p.Mpad, (c8 & 1) ? mb : ma, c8 >> 2);
+    const int vsx = (int)fp4_scale_offset(0, p.Mpad, kTwo && (c8 & 1) ? mb : ma, c8 >> 2);
     const W4Stage w4(r8, c8);
-    const int vout = w4_stage_out(m0, lane);
+    const int vout = kTwo ? w4_stage_out(m0, lane) : w4_stage_out8(m0, lane);
+    // (of eight tokens, the staging block's three runs are filled by half)
+    const int vstage = kTwo ? 16 * lane : lane < 12 ? 16 * lane : lane < 24 ? 384 + 16 * (lane - 12) : 768 + 16 * (lane - 24);
+    constexpr int kStageLanes = kTwo ? kActOutStage / 16 : 26;
     auto group = [&](int i) { return wave + kWaves * i; };
     auto load_b128 = [&](__amdgpu_buffer_rsrc_t rs, int v, int s, bool nt) {
         return __builtin_bit_cast(uint4, nt ? __builtin_amdgcn_raw_buffer_load_b128(rs, v, s, 2) : __builtin_amdgcn_raw_buffer_load_b128(rs, v, s, 0));
@@ -73,11 +78,13 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
         xa[i % kX] = xb[i % kX] = make_uint4(0u, 0u, 0u, 0u);
         if (group(i) < p.G) {
             xa[i % kX] = load_b128(rs_x, vxa, group(i) * 128, true);
-            xb[i % kX] = load_b128(rs_x, vxb, group(i) * 128, true);
+            if (kTwo) xb[i % kX] = load_b128(rs_x, vxb, group(i) * 128, true);
         }
     };
     float4 r0[NG], r1[NG];
-    constexpr bool kKeep = FMT == 2 && NG <= 3;      // 1 / lambda stays in registers for the second use, or is loaded again
+    // INT8: x^ stays in registers from the maximum to the codes, or X does, and 1 / lambda is loaded again
+    constexpr bool kKeep = FMT == 2 && NG * (TOK / 8) <= 6;
+    float keep[kKeep ? NG : 1][TOK / 8][8];
 #pragma unroll
     for (int i = 0; i < kX; ++i) load_x(i);
     __builtin_amdgcn_sched_barrier(0);
@@ -99,7 +106,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
         return f;
     };
 #pragma unroll
-    for (int i = 0; i < (kKeep ? NG : 2); ++i) load_rinv(i);
+    for (int i = 0; i < (kKeep && NG <= 3 ? NG : 2); ++i) load_rinv(i);
     Frags fr = load_l1(0);
     __builtin_amdgcn_sched_barrier(0);
 
@@ -121,8 +128,8 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
     for (int i = 0; i < NG; ++i) {
         float ta[8], tb[8];
         smooth(xa[i % kX], r0[i], r1[i], ta);
-        smooth(xb[i % kX], r0[i], r1[i], tb);
-        if (!kKeep) {
+        if (kTwo) smooth(xb[i % kX], r0[i], r1[i], tb);
+        if (!(kKeep && NG <= 3)) {
             __builtin_amdgcn_sched_barrier(0);
             if (i + 2 < NG) load_rinv(i + 2);
             __builtin_amdgcn_sched_barrier(0);
@@ -131,36 +138,48 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 amax_a = fmaxf(amax_a, fabsf(ta[e]));
-                amax_b = fmaxf(amax_b, fabsf(tb[e]));
+                if (kTwo) amax_b = fmaxf(amax_b, fabsf(tb[e]));
+                if (kKeep) {
+                    keep[kKeep ? i : 0][0][e] = ta[e];
+                    if (kTwo) keep[kKeep ? i : 0][TOK / 8 - 1][e] = tb[e];
+                }
             }
         } else if (group(i) < p.G) {
             if constexpr (FMT == 1) {
                 uint32_t wa, wb, ba, bb;
                 fp4_encode(ta, wa, ba);
-                fp4_encode(tb, wb, bb);
-                // the four lanes of a block write the same scale byte (an even c8 that of token r8, an odd one that of r8 + 8)
+                if (kTwo) fp4_encode(tb, wb, bb);
+                // the four lanes of a block write the same scale byte (of sixteen tokens, an even c8 that of token r8, an odd one that of r8 + 8)
                 const int sc = group(i) * p.Mpad * kFp4RowBytes;
                 __builtin_amdgcn_raw_buffer_store_b32(wa, rs_c, vca, sc, 0);
-                __builtin_amdgcn_raw_buffer_store_b32(wb, rs_c, vcb, sc, 0);
-                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((c8 & 1) ? bb : ba), rs_s, vsx, (group(i) >> 2) * p.Mpad * 8 + (group(i) & 3), 0);
+                if (kTwo) __builtin_amdgcn_raw_buffer_store_b32(wb, rs_c, vcb, sc, 0);
+                __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(kTwo && (c8 & 1) ? bb : ba), rs_s, vsx, (group(i) >> 2) * p.Mpad * 8 + (group(i) & 3), 0);
             } else {
-                uint32_t sa, sb, alo, ahi, blo, bhi;
-                const float rcp[2] = {w4_group_rcp(ta, sa), w4_group_rcp(tb, sb)};
-                const float(*const runs[2])[8] = {&ta, &tb};
-                const act_u32x6 q = w4_codes<2>(runs, rcp);
-                w4_run48(q, 0, alo, ahi);
-                w4_run48(q, 1, blo, bhi);
                 unsigned char *stage = block + L::kBlock;
-                w4.put(stage, alo, ahi, sa, blo, bhi, sb);
-                if (lane < kActOutStage / 16)
-                    buffer_store_b128<0>(__builtin_bit_cast(buffer_u32x4, *reinterpret_cast<const uint4 *>(stage + 16 * lane)), rs_c, vout, group(i) * (p.Mpad / 32) * kW4ABlock);
+                if constexpr (kTwo) {
+                    uint32_t sa, sb, alo, ahi, blo, bhi;
+                    const float rcp[2] = {w4_group_rcp(ta, sa), w4_group_rcp(tb, sb)};
+                    const float(*const runs[2])[8] = {&ta, &tb};
+                    const act_u32x6 q = w4_codes<2>(runs, rcp);
+                    w4_run48(q, 0, alo, ahi);
+                    w4_run48(q, 1, blo, bhi);
+                    w4.put(stage, alo, ahi, sa, blo, bhi, sb);
+                } else {
+                    uint32_t sa, alo, ahi;
+                    const float rcp[1] = {w4_group_rcp(ta, sa)};
+                    const float(*const runs[1])[8] = {&ta};
+                    w4_run48(w4_codes<1>(runs, rcp), 0, alo, ahi);
+                    w4.put(stage, alo, ahi, sa);
+                }
+                if (lane < kStageLanes)
+                    buffer_store_b128<0>(__builtin_bit_cast(buffer_u32x4, *reinterpret_cast<const uint4 *>(stage + vstage)), rs_c, vout, group(i) * (p.Mpad / 32) * kW4ABlock);
             }
         }
         if constexpr (RB > 0) {
             // only this wavefront touches its block, and the LDS queue of a wavefront is in order: no barrier
             *reinterpret_cast<uint4 *>(block + r8 * L::kXRow + 16 * c8) = xa[i % kX];
-            *reinterpret_cast<uint4 *>(block + (r8 + 8) * L::kXRow + 16 * c8) = xb[i % kX];
-            const uint4 *ap = reinterpret_cast<const uint4 *>(block + row * L::kXRow + 32 * blk);
+            if (kTwo) *reinterpret_cast<uint4 *>(block + (r8 + 8) * L::kXRow + 16 * c8) = xb[i % kX];
+            const uint4 *ap = reinterpret_cast<const uint4 *>(block + row % TOK * L::kXRow + 32 * blk);      // (of eight tokens: each twice)
             const uint4 x0 = ap[0], x1 = ap[1];
             const Frags now = fr;
             if (i + 1 < NG) fr = load_l1(i + 1);
@@ -178,10 +197,10 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
     float *mx = reinterpret_cast<float *>(lds);      // INT8: [16 tokens][wavefronts]
     if constexpr (FMT == 2) {
         amax_a = max_over_8_lanes(amax_a);
-        amax_b = max_over_8_lanes(amax_b);
+        if (kTwo) amax_b = max_over_8_lanes(amax_b);
         if (c8 == 0) {
             mx[r8 * kWaves + wave] = amax_a;
-            mx[(r8 + 8) * kWaves + wave] = amax_b;
+            if (kTwo) mx[(r8 + 8) * kWaves + wave] = amax_b;
         }
     }
     if constexpr (RB > 0) {
@@ -209,27 +228,28 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
             const float sc = (float)sh;
             return sc > 0.f ? 1.0f / sc : 0.f;
         };
-        _Float16 sha, shb;
-        const float rcp_a = scale_of(token_max(r8), sha), rcp_b = scale_of(token_max(r8 + 8), shb);
+        _Float16 sha, shb = 0;
+        const float rcp_a = scale_of(token_max(r8), sha), rcp_b = kTwo ? scale_of(token_max(r8 + 8), shb) : 0.f;
         if (wave == 0 && c8 == 0) {      // rows past M: padding entries of the scale vector (it has Mpad of them)
             p.sx[ma] = __builtin_bit_cast(uint16_t, sha);
-            p.sx[mb] = __builtin_bit_cast(uint16_t, shb);
+            if (kTwo) p.sx[mb] = __builtin_bit_cast(uint16_t, shb);
         }
         if (!kKeep) {
             // (or the compiler keeps what the first walk loaded and unpacked for the second, and spills it)
             asm volatile("" : "+v"(vr));
 #pragma unroll
-            for (int i = 0; i < NG; ++i)
+            for (int i = 0; i < NG; ++i)      // (sixteen tokens: fewer are kept as x^)
                 asm volatile("" : "+v"(xa[i].x), "+v"(xa[i].y), "+v"(xa[i].z), "+v"(xa[i].w), "+v"(xb[i].x), "+v"(xb[i].y), "+v"(xb[i].z), "+v"(xb[i].w));
         }
         auto codes = [&](const float (&x)[8], float rcp) {
-            uint32_t w[2] = {0u, 0u};
+            // 1.5 * 2^23 added: the sum is rounded to a whole number (to nearest, ties to even) and has it in its low bits
+            uint32_t w[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float q = fminf(127.f, fmaxf(-127.f, __builtin_rintf(x[e] * rcp)));
-                w[e >> 2] |= ((uint32_t)(int)q & 0xffu) << (8 * (e & 3));
-            }
-            return u32x2{w[0], w[1]};
+            for (int e = 0; e < 8; ++e) w[e] = __float_as_uint(__builtin_amdgcn_fmed3f(x[e] * rcp, -127.f, 127.f) + 0x1.8p23f);
+            auto low4 = [](uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+                return (uint32_t)__builtin_amdgcn_perm(__builtin_amdgcn_perm(d, c, 0x0c0c0400), __builtin_amdgcn_perm(b, a, 0x0c0c0400), 0x05040100);
+            };
+            return u32x2{low4(w[0], w[1], w[2], w[3]), low4(w[4], w[5], w[6], w[7])};
         };
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
@@ -241,11 +261,13 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
             }
             if (group(i) < p.G) {
                 float ta[8], tb[8];
-                smooth(xa[i], r0[i], r1[i], ta);
-                smooth(xb[i], r0[i], r1[i], tb);
+                if (!kKeep) {
+                    smooth(xa[i % kX], r0[i], r1[i], ta);
+                    smooth(xb[i % kX], r0[i], r1[i], tb);
+                }
                 const int sc = group(i) * p.Mpad * 64;      // a group is two 32-channel steps of operand blocks
-                __builtin_amdgcn_raw_buffer_store_b64(codes(ta, rcp_a), rs_c, vca, sc, 0);
-                __builtin_amdgcn_raw_buffer_store_b64(codes(tb, rcp_b), rs_c, vcb, sc, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(codes(kKeep ? keep[kKeep ? i : 0][0] : ta, rcp_a), rs_c, vca, sc, 0);
+                if (kTwo) __builtin_amdgcn_raw_buffer_store_b64(codes(kKeep ? keep[kKeep ? i : 0][TOK / 8 - 1] : tb, rcp_b), rs_c, vcb, sc, 0);
             }
         }
     }
@@ -256,7 +278,7 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
     if constexpr (RB > 0) {
         // the wavefronts' partial H, added in wavefront order; a thread takes two neighbouring columns of one token
         const int pairs = p.rank / 2;
-        for (int idx = threadIdx.x; idx < 16 * pairs; idx += kWaves * 64) {
+        for (int idx = threadIdx.x; idx < TOK * pairs; idx += kWaves * 64) {
             const int r = idx / pairs, col = 2 * (idx - r * pairs);
             float h0 = 0.f, h1 = 0.f;
 #pragma unroll
@@ -274,14 +296,26 @@ __global__ __launch_bounds__(kWaves * 64, 1) void act_onepass_kernel(ActParams p
     }
 }
 
-template <int FMT, int RB, int NG>
-hipError_t launch_one(const ActParams &p, hipStream_t stream) {
-    auto k = act_onepass_kernel<FMT, RB, NG>;
+// Tokens of a workgroup: eight while those are one round of the CUs.  The operand rows past the eight repeat them, and the L1 fragments
+// are read for half as many tokens, which is the smaller part.  us per forward, 16 tokens -> 8, same bits: INT8 M = 1337, K = 3072, N = 9216, rank 16 49.5 -> 46.7,
+// M = 1024, K = 1152, N = 4608 18.4 -> 17.2, M = 2000, K = N = 3072 34.7 -> 32.4, M = 2048, K = 640, N = 9216, rank 32 30.7 -> 29.5; MXFP4 M = 1500, K = 6144, N = 3072,
+// rank 32 38.9 -> 35.5, M = 2048, K = N = 3072 25.8 -> 24.8, M = 1024, K = 1152, N = 4608 15.6 -> 15.1; INT4 M = 2048, K = 4608, N = 1152 34.1 -> 32.2, M = 1337, K = 3072, N = 9216,
+// rank 16 55.5 -> 54.3, M = 1800, K = 1536, N = 9216 52.9 -> 52.7.
+int act_one_pass_tokens(int M) { return (M + 7) / 8 <= 256 ? 8 : 16; }
+
+template <int FMT, int RB, int NG, int TOK>
+hipError_t launch_tokens(const ActParams &p, hipStream_t stream) {
+    auto k = act_onepass_kernel<FMT, RB, NG, TOK>;
     constexpr int bytes = OnePassLds<RB>::kBytes;
     static LdsLimit limit;
     if (const hipError_t e = limit.raise(reinterpret_cast<const void *>(k), bytes); e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, dim3((unsigned)((p.M + 15) / 16)), dim3(kWaves * 64), bytes, stream, p);
+    hipLaunchKernelGGL(k, dim3((unsigned)((p.M + TOK - 1) / TOK)), dim3(kWaves * 64), bytes, stream, p);
     return hipGetLastError();
+}
+
+template <int FMT, int RB, int NG>
+hipError_t launch_one(const ActParams &p, hipStream_t stream) {
+    return act_one_pass_tokens(p.M) == 8 ? launch_tokens<FMT, RB, NG, 8>(p, stream) : launch_tokens<FMT, RB, NG, 16>(p, stream);
 }
 
 template <int FMT, int RB>

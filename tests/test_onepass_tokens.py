@@ -1,0 +1,69 @@
+"""One-pass activation kernel with workgroups of eight tokens (csrc/act_onepass_kernel.hip): against the oracles at the sizes where its
+indexing can go wrong, the same bits as with sixteen, and on the CPU which calls take it."""
+import numpy as np
+import pytest
+
+from oracle import svdq_oracle as O
+from paper_2411_05007_amd import svdq as S
+from tests.test_gpu_canaries import _check, _guarded
+from tests.test_gpu_parity import torch  # noqa: F401 (fixture)
+from tests.test_gpu_small_launches import _block_layer, _layer, _wide_branch
+from tests.test_gpu_w8a8 import _random_layer, _run_and_compare
+from tests.test_host_launches import FP4, INT4, W8A8, record  # noqa: F401 (fixture)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,r", [(1337, 3072, 3088, 16), (2041, 640, 2320, 32), (2000, 3072, 2320, 32), (801, 2112, 9216, 64), (797, 1088, 9216, 0), (1009, 1024, 9216, 48)])
+def test_int8_eight_tokens(torch, M, K, N, r):  # noqa: F811
+    """Tokens off 8 and off 16, groups off the sixteen wavefronts, two, three and six groups per wavefront, one, two and four column blocks of H and none."""
+    rng = np.random.default_rng(7100 + M)
+    xb, w, ax, b = _random_layer(rng, M, K, N)
+    rows = np.r_[0:24, M // 2, M - 20:M]
+    _run_and_compare(torch, xb, S.svdq_w8a8_prepare(w, ax, r, bias=b), rows=rows, what=f"w8a8 {M}x{K}x{N} r{r}")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,M,K,N,r", [("int4", 1009, 1088, 9232, 32), ("int4", 2041, 6080, 272, 16), ("int4", 1672, 2048, 9232, 32), ("fp4", 1017, 1984, 9232, 16), ("fp4", 2041, 6080, 2576, 32)])
+def test_blocks_eight_tokens(torch, fmt, M, K, N, r):  # noqa: F811
+    _wide_branch(torch, fmt, M, K, N, r)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,M,K,N,r", [("w8a8", 1337, 3072, 3088, 16), ("int4", 1009, 1088, 9232, 32), ("fp4", 1017, 1984, 9232, 16)])
+def test_eight_tokens_are_those_of_a_larger_batch(torch, fmt, M, K, N, r):  # noqa: F811
+    """A token's codes, scales and H do not depend on the tokens beside it: the first M rows of a batch whose workgroups have sixteen.  Guarded buffers;
+    rows with an infinity or a NaN leave the others' bits as they are."""
+    rng = np.random.default_rng(7200 + M)
+    if fmt == "w8a8":
+        _, w, ax, b = _random_layer(rng, 8, K, N)
+        layer = S.DeviceLayer(S.svdq_w8a8_prepare(w, ax, r, bias=b))
+    else:
+        layer = S.DeviceLayer(_layer(rng, K, N, r) if fmt == "int4" else _block_layer(rng, fmt, K, N, r))
+    large = S.bf16_tensor_from_bits(O.bf16_round(rng.standard_normal((2064, K)).astype(np.float32)))
+    layer.forward(large)
+    want = [np.asarray(t)[:M].copy() for t in layer.debug_act()]
+    x = large[:M].clone()
+    n = layer.workspace(M).numel()
+    big_ws, ws, big_y, y = _guarded(torch, layer, M, N, n)
+    for _ in range(2):
+        layer.forward(x, out=y, workspace=ws)
+    _check(torch, big_ws, n, big_y, M, f"eight tokens {fmt}")
+    layer.forward(x)
+    for a, t in zip(layer.debug_act(), want):
+        a = np.ascontiguousarray(a)
+        assert np.array_equal(a.view(np.uint8), np.ascontiguousarray(t).view(np.uint8))
+    bad, rows = x.clone(), [0, 13, M - 1]
+    for m, v in zip(rows, (float("inf"), float("nan"), float("-inf"))):
+        bad[m, (7 * m + 3) % K] = v
+    got, rest = layer.forward(bad), [m for m in range(M) if m not in rows]
+    assert torch.equal(got[rest].view(torch.int16), layer.forward(x)[rest].view(torch.int16))
+
+
+def test_which_launches_take_eight_tokens(record):  # noqa: F811
+    """While they are one round of the CUs."""
+    eight = [(0, W8A8, 1337, 3072, 9216, 16), (0, W8A8, 2000, 3072, 3072, 16), (0, INT4, 1009, 1088, 9232, 32), (0, FP4, 2048, 3072, 3072, 32)]
+    sixteen = [(0, W8A8, 2049, 3072, 9216, 16), (0, W8A8, 4608, 3072, 9216, 32), (0, INT4, 2050, 6080, 272, 32), (0, FP4, 4096, 3072, 3072, 32)]
+    for c, rec in zip(eight + sixteen, record(eight + sixteen)):
+        grids = [(r[2], int(r[3])) for r in rec if r[0] == "launch" and r[2].startswith("act_onepass_kernel<")]
+        tok = 8 if c in eight else 16
+        assert len(grids) == 1 and grids[0][0].endswith(f",{tok}>") and grids[0][1] == -(-c[2] // tok), (c, grids)
