@@ -6,8 +6,9 @@
 //   FMT 2 (INT8, one scale per token; App. "Implementation Details"): a token's scale needs its maximum over all of K before
 //   the first code can be written, so the workgroup holds its tokens in registers from the one read to the codes.
 // Bound: one CU's rate of small requests, X and the L1 fragments that every workgroup reads (M = 4096, K = 4608, rank 32, INT4:
-// 16 us against 18 of act_kernel.hip, 38 MB of X), and where the workgroups are fewer than the CUs by the vector instructions of one of them
-// (INT8, K = 3072: 250 per group and wavefront, twelve groups to a SIMD): eight tokens halve those.
+// 16 us against 18 of act_kernel.hip, 38 MB of X), and where the workgroups are fewer than the CUs by the time of one of them
+// (INT8, M = 1337, K = 3072, 16 tokens: vector instructions for a third of it, the rest waiting): eight tokens halve its loads of X, its
+// vector instructions and its stores.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -315,7 +316,8 @@ hipError_t launch_tokens(const ActParams &p, hipStream_t stream) {
 
 template <int FMT, int RB, int NG>
 hipError_t launch_one(const ActParams &p, hipStream_t stream) {
-    return act_one_pass_tokens(p.M) == 8 ? launch_tokens<FMT, RB, NG, 8>(p, stream) : launch_tokens<FMT, RB, NG, 16>(p, stream);
+    if constexpr (FMT == 1 && RB == 4) return launch_tokens<FMT, RB, NG, 8>(p, stream);
+    else return act_one_pass_tokens(p.M) == 8 ? launch_tokens<FMT, RB, NG, 8>(p, stream) : launch_tokens<FMT, RB, NG, 16>(p, stream);
 }
 
 template <int FMT, int RB>
@@ -331,7 +333,7 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
     if (!(flags & 2) || p.rank == 0) return launch_groups<FMT, 0>(p, stream);
     if (p.rank <= 16) return launch_groups<FMT, 1>(p, stream);
     if (p.rank <= 32) return launch_groups<FMT, 2>(p, stream);
-    if constexpr (FMT == 2) return launch_groups<FMT, 4>(p, stream);
+    if constexpr (FMT != 0) return launch_groups<FMT, 4>(p, stream);
     return hipErrorInvalidValue;
 }
 
@@ -347,8 +349,13 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 // least; fewer slices do better with K cut into runs, a second round undoes the gain.  INT4: M = 1337, K = 3072, N = 9216
 // 61.5 -> 60.0, M = 4096, K = 6144, N = 2048 80.5 -> 78.2, M = 4608, K = 3072, N = 3072 65.3 -> 67.8; MXFP4: M = 2048, K = N = 3072
 // 28.7 -> 27.5, M = 4608, K = 6144, N = 3072 72.4 -> 75.3; INT4 at rank 64: no difference.
+// MXFP4 with eight tokens to a workgroup, act_tile_kernel.hip -> this one: K = 1024 (below, few tokens were not measured) to 3072 from 241 tokens on, M = 270, K = 1152, N = 12288, rank 32
+// 16.4 -> 13.8, M = 397, K = 2240, N = 10208 21.0 -> 19.2, and ranks 48 and 64 (layout.h, plan_act_tile); longer rows hold six groups per wavefront, and few or
+// wide ones lose: M = 526, K = 3712, N = 7392, rank 32 24.0 | 25.3, M = 1500, K = 6144, N = 3072, rank 64 38.0 | 41.4.  INT4 (spilled registers at rank 64): M = 905, K = 3136,
+// N = 5264, rank 48 38.0 | 43.7.
 bool act_one_pass(int fmt, int M, int K, int rank) {
     const int G = K / kGroup, slices = (M + 15) / 16;
+    if (fmt == 1 && G >= 16 && G <= 3 * kWaves && act_one_pass_tokens(M) == 8) return slices >= 16 && rank <= 64;
     if (fmt != 2) return slices >= 64 && slices <= 256 && G <= 6 * kWaves && rank <= 32;
     if (G <= 8 || (slices > 256 && G <= 24)) return false;
     return (G <= 3 * kWaves && rank <= 64) || (G <= 6 * kWaves && rank <= 32);

@@ -549,10 +549,12 @@ inline int plan_act_wide(bool int4, const ActPlan &other, int M, int G, int rank
 // K = 2368, N = 1936, rank 128 36.4 | 32.6.  Not taken: more than 2048 tokens, which fill the CUs with 16 to a workgroup, with a short K (INT4 M = 3246, K = 1408, N = 432,
 // rank 64 17.0 | 19.5; M = 4006, K = 2816, N = 2736, rank 64 60.6 | 62.8; MXFP4 M = 2235, K = 1664, N = 768, rank 96 19.7 | 20.8).
 // Up to rank 32 only where the runs of the other kernel meet: M = 1500, K = 8192, N = 2048, rank 16 51.7 | 45.8, M = 2300, K = 9216, rank 32 75.8 | 70.8; else
-// M = 3000, K = 6144, N = 3072, rank 16 95.2 | 96, MXFP4 M = 1500, K = 3072, N = 4608 28.3 | 28.9 (one pass).
+// M = 3000, K = 6144, N = 3072, rank 16 95.2 | 96, MXFP4 M = 1500, K = 3072, N = 4608 28.3 | 28.9 (one pass).  Ranks of 48 and 64 give way to one pass with
+// eight tokens to a workgroup where that is taken (MXFP4 up to K = 3072): M = 2048, K = N = 3072, rank 64 29.5 | 28.0; M = 1024, K = 1536, N = 9216, rank 48 25.5 | 23.6.
 constexpr int kActTileTokens = 32;
 inline int plan_act_tile(const ActPlan &other, bool one_pass, int M, int G, int rank, size_t room) {
     if (rank > 128 || G < 16 || M > 4096) return 0;
+    if (rank <= 64 && one_pass && M <= 2048) return 0;
     if (rank <= 32 && (one_pass || other.chunks <= 1 || other.whole != 0)) return 0;
     if (rank > 32 && M > 2048 && G < (rank > 64 ? 36 : 72)) return 0;
     const int tiles = (M + kActTileTokens - 1) / kActTileTokens;
@@ -613,13 +615,16 @@ inline void act_use_small_plan(W &w, bool int4, int M, int N, int G, int rank, i
 }
 
 // INT8 batches that act_w8_small_kernel.hip takes, of those whose plan cuts K (at most 128 slices): where the GEMM adds the runs'
-// partial H itself (kpar); where a launch of its own has to, from K = 3136 on or with few slices.  us per forward, walking or one-pass
+// partial H itself (kpar); where a launch of its own has to, rows that one pass does not take or takes slower.  us per forward, walking or one-pass
 // kernel -> this one: M = 1, K = 3648, N = 5200 17.5 -> 11.3; M = 14, K = 5760, N = 1568 22.5 -> 13.8; M = 4, K = 10048, N = 1232 24.7 -> 18.7;
 // M = 3, K = 1408, N = 1584 10.6 -> 8.1; M = 664, K = 6976, N = 1824 39.7 -> 30.7; M = 1293, K = 6016, N = 1616 45.7 -> 39.5; with the launch: M = 1104, K = 7424, N = 9408
-// 108 -> 97; M = 600, K = 3072, N = 12288 40.6 -> 38.3; M = 1337, K = 3072, N = 9216 51.0 -> 51.3 and M = 1412, K = 1664, N = 10816 42.0 -> 43.9 (not taken).
+// 108 -> 97.  Where H is added by a launch of its own, one pass with eight tokens to a workgroup is the faster one (this kernel | one pass) up to K = 3072:
+// M = 270, K = 1152, N = 12288 18.8 | 17.4; M = 620, K = 2816, N = 11488 33.3 | 32.2; M = 1, K = 3072, N = 36864 28.8 | 28.7; and up to K = 6144 from 1153 tokens on: M = 1700,
+// K = 4096, N = 8192 73.8 | 70.6; M = 1337, K = 6144, N = 4096 50.3 | 49.1; below, M = 270, K = 6144, N = 12288 41.6 | 42.9, M = 594, K = 3776, N = 6896 32.3 | 32.7,
+// M = 893, K = 4224, N = 4928 34.4 | 34.3, M = 1000, K = N = 4608 41.7 | 40.3.  Few tokens of a K below 1024 keep this kernel (not measured).
 inline bool act_w8_small(int M, int K, int rank, int kpar) {
-    const int G = K / kGroup;
-    return G <= 192 && rank <= 32 && (kpar || G > 48 || (M + 15) / 16 <= 48);
+    const int G = K / kGroup, slices = (M + 15) / 16;
+    return G <= 192 && rank <= 32 && (kpar || G > 96 || (G > 48 && slices <= 72) || (G < 16 && slices <= 48));
 }
 
 // The int8 MFMA takes twice the time of the 4-bit one per step of 64 channels, so a split of the 8-bit GEMM's K loop pays
