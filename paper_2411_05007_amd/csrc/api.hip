@@ -280,7 +280,7 @@ int svdq_debug_launch_plan(const svdq_shape *s, int M, int32_t *out) {
         const svdq::GemmPlanFp4 pl = svdq::plan_gemm_fp4(M, s->N, G, ksplit_override());
         a = w.act;
         out[8] = pl.tiles; out[9] = pl.ksplit > 1 ? pl.tiles : 0; out[10] = pl.ksplit; out[11] = pl.tiles * pl.ksplit;
-        const int kpar = svdq::plan_kpar_blocks(false, M, s->N, G, ksplit_override());
+        const int kpar = svdq::plan_kpar_blocks(false, M, s->N, G, s->rank, ksplit_override());
         if (kpar) { tile_rows = svdq::kpar_rows(kpar); tile_cols = svdq::kpar_cols(kpar); }
         parked_bytes = w.total - w.hpart_off; total = w.total;
     } else if (s->group == svdq::kGroup) {
@@ -393,7 +393,7 @@ int svdq_fp4_linear_forward(const svdq_layer_dev *L, const void *X, int M, void 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     unsigned char *ws = static_cast<unsigned char *>(workspace);
     const bool lowrank = s.rank > 0 && !(g_options & SVDQ_OPT_SKIP_LOWRANK);
-    const int kpar = svdq::plan_kpar_blocks(false, M, s.N, s.K / svdq::kGroup, ksplit_override());
+    const int kpar = svdq::plan_kpar_blocks(false, M, s.N, s.K / svdq::kGroup, s.rank, ksplit_override());
 
     svdq::ActParams a{};
     a.X = static_cast<const uint16_t *>(X);
@@ -583,7 +583,7 @@ int svdq_w8a8_linear_forward(const svdq_layer_dev *L, const void *X, int M, void
     a.M = M; a.K = s.K; a.G = s.K / svdq::kGroup; a.Mpad = w.Mpad; a.rank = s.rank;
     a.fmt = 2;
     a.zero_words = reinterpret_cast<uint32_t *>(ws + w.counters_off);      // the arrival counters of the GEMM's split K loop
-    const int kpar = svdq::plan_kpar_blocks(true, M, s.N, s.K / svdq::kGroup, ksplit_override());
+    const int kpar = svdq::plan_kpar_blocks(true, M, s.N, s.K / svdq::kGroup, s.rank, ksplit_override());
     a.n_zero = kpar ? 0 : w.n_counters;
     hipError_t e;
     // small batches: tokens quantized four to a workgroup beside workgroups that project runs of K (w.act_cut: the plan has such runs)

@@ -179,40 +179,36 @@ inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, i
     while (s > 1 && (size_t)(s - 1) * (((G + s - 1) / s + 3) / 4 * 4) >= (size_t)G) --s;
     pl.ksplit = s < 1 ? 1 : s;
     pl.tile = 0;
-    // 192 x 192 tiles do nine MFMAs per step and wavefront instead of eight; they pay where they save a round of
-    // the chip's 512 workgroup places (two per CU) and fit the padded rows and columns exactly
-    if (pl.ksplit == 1 && pl.tiles > 512) {
-        const int tm = (M + 191) / 192, tn = (N + 191) / 192;
-        const long t192 = (long)tm * tn;
-        const long rounds128 = (pl.tiles + 511) / 512, rounds192 = (t192 + 511) / 512;
-        if (tm * 192 <= round_up(M, kRowPad) && tn * 192 <= round_up(N, kRowPad) && rounds192 * 9 < rounds128 * 8) {
-            pl.tile = 1;
-            pl.tiles = (int)t192;
-        }
-    }
-    // What a launch takes follows the CU with the most tiles: tiles per CU times MFMAs per step of a tile, weighted with what the
-    // tile loads per MFMA, and a fifth more where no CU has a second tile to fill the first one's waits.  192 x 128 (six
-    // MFMAs) and 128 x 128 (four) are taken where that comes out 5 % below the 128 x 256 tile (eight).
-    // us per forward, 128 x 256 | 192 x 128 | 128 x 128, the rule's choice in brackets, its losses below the line; MXFP4 rank 32, INT8 rank 16:
-    //   M = 1337, K = 3072, N = 9216 (396 | 504 | 792 tiles)   43.2 [40.4] 47.4     70.4 [59.2] 65.9
-    //   M = 2048, K = N = 3072 (192 | - | 384)                 31.8   -   [29.0]    44.4   -   [41.5]
-    //   M = 4096, K = 4608, N = 1152 (160 | - | 288)           46.0   -   [38.2]    61.0   -   [53.6]
-    //   M = 1800, K = 3072, N = 12288 (720 | 960 | 1440)       60.7  61.8 [59.2]    [89.8] 94.0  90.8
-    //   M = 4608, K = N = 3072 (432 | 576 | 864)               [43.8] 51.3  49.9    [71.0] 82.3  74.4
-    //   M = 3000, K = 3072, N = 9216 (864 | 1152 | 1728)       [70.5] 74.9  71.7    [110] 115  107
-    //   ------
-    //   M = 4608, K = 3072, N = 9216 (1296 | 1728 | 2592)      96.9 [95.7] 99.6     157.6 [152.4] 156.0 (192 x 192, 1152 tiles: 92.4, 147.9)
-    //   M = 900, K = 3072, N = 4608 (144 | 180 | 288)          29.3 [27.2] 25.4     40.2 [39.0] 35.9
-    //   M = 2304, K = 3072, N = 9216 (648 | 864 | 1296)        [59.1] 56.3  58.2    [87.1] 86.7  87.5
-    // The 192 x 192 tile has its own condition above and no place in this comparison.
-    if (pl.ksplit == 1 && pl.tile == 0) {
-        auto cost = [](long tiles, int products, double traffic) { return (double)((tiles + 255) / 256 * products) * traffic * (tiles <= 256 ? 1.2 : 1.0); };
-        const double c0 = cost(pl.tiles, 8, 1.0);
-        const long t2 = (long)((M + 191) / 192) * ((N + 127) / 128), t3 = (long)((M + 127) / 128) * ((N + 127) / 128);
-        const double c2 = (M + 191) / 192 * 192 <= round_up(M, kRowPad) ? cost(t2, 6, 1.06) : 1e30, c3 = cost(t3, 4, 1.12);
-        if ((c2 < c3 ? c2 : c3) < 0.95 * c0) {
-            pl.tile = c2 < c3 ? 2 : 3;
-            pl.tiles = (int)(c2 < c3 ? t2 : t3);
+    // The tile shape.  What a launch takes follows the CU with the most tiles, but not all the way (a CU that is done early leaves its share of
+    // the L2 to the others): the mean of the tiles per CU and of that number rounded up, times the MFMAs per step of a tile, weighted with
+    // what the tile loads per MFMA, and more where no CU has a second tile to fill the first one's waits (192 x 192 tiles, which ask for a
+    // step's operands between its products, need that least, and cost more around a short K loop: INT8, M = 1585, K = 1152, N = 4224 20.9 | 19.8 on 128 x 128,
+    // MXFP4, M = 4111, K = 1728, N = 6896 50.9 | 49.3 on 128 x 256).  192-row and 192-column tiles have to fit the padded rows and columns.  Fitted to 64 launches
+    // of all four shapes; up to two 128 x 256 tiles per CU they keep the launches that the others win by less than 3 %.
+    // us per forward, 128 x 256 | 192 x 192 | 192 x 128 | 128 x 128, the rule's choice in brackets; MXFP4 rank 32, INT8 rank 16:
+    //   M = 4608, K = 3072, N = 9216 (1296 | 1152 | 1728 | 2592 tiles)   97.8 [87.3] 95.7  98.6     157.1 [138.2] 147.5 153.9
+    //   M = 3000, K = 3072, N = 9216 (864 | 768 | 1152 | 1728)           65.7 [57.8] 68.3  65.7     101.9 [89.2] 101.9  98.8
+    //   M = 1800, K = 3072, N = 12288 (720 | 640 | 960 | 1440)           53.9 [50.9] 55.9  54.9      80.8 [78.5]  81.7  82.5
+    //   M = 4608, K = N = 3072 (432 | 384 | 576 | 864)                  [43.8] 43.1  48.8  46.0     [65.6] 64.2   75.6  68.9
+    //   M = 4178, K = 3520, N = 5744 (759 | 660 | 990 | 1485)            66.3 [63.5] 68.8  68.2
+    //   M = 4406, K = 7168, N = 2304 (315 | 276 | 414 | 630)             75.7  77.2 [70.8] 72.6
+    //   M = 907, K = 5952, N = 7216 (232 | 190 | 285 | 456)                                          58.1 [52.5]  61.9  55.8
+    //   M = 892, K = 3456, N = 7232 (203 | 190 | 285 | 399)              27.2 [26.0] 30.7  26.4
+    //   M = 2048, K = N = 3072 (192 | - | - | 384)                       31.8   -     -   [29.0]     44.4   -      -   [41.5]
+    // (the last with the activation kernel of 16-token workgroups)
+    if (pl.ksplit == 1) {
+        auto cost = [](long tiles, double per_tile, double lone) { return (tiles / 256.0 + (double)((tiles + 255) / 256)) * per_tile * (tiles <= 256 ? lone : 1.0); };
+        const int pm = round_up(M, kRowPad), pn = round_up(N, kRowPad), tm = (M + 127) / 128, tm192 = (M + 191) / 192, tn = (N + 127) / 128, tn192 = (N + 191) / 192;
+        const int tiles[4] = {pl.tiles, tm192 * 192 <= pm && tn192 * 192 <= pn ? tm192 * tn192 : 0, tm192 * 192 <= pm ? tm192 * tn : 0, tm * tn};
+        const double per_tile[4] = {8.0, 9 * (0.89 + 2.0 / (G > 18 ? G : 18)), 6 * 1.05, 4 * 1.07};
+        double best = (pl.tiles <= 512 ? 0.97 : 1.0) * cost(pl.tiles, per_tile[0], 1.2);
+        for (int t = 1; t < 4; ++t) {
+            const double c = cost(tiles[t], per_tile[t], t == 1 ? 1.03 : 1.1);
+            if (tiles[t] > 0 && c < best) {
+                best = c;
+                pl.tile = t;
+                pl.tiles = tiles[t];
+            }
         }
     }
     return pl;
@@ -328,19 +324,25 @@ inline __host__ __device__ MidPiece mid_piece(int j, int lane, int pieces, int g
 //   M = 512, K = 12288, N = 3072 (192): 38.6; 2x4 38.6, 4x8 34.9, 4x4 38.1.                  52.4; 2x4 50.4, 4x8 47.5, 4x4 52.4
 //   M = 1024, K = N = 3072 (384): 28.6; 2x4 24.6, 4x8 28.0, 4x4 24.4.                        42.8; 2x4 37.1, 4x8 39.8, 4x4 33.5
 //   M = 512, K = 3072, N = 9216 (576): 27.9; 2x4 31.0, 4x4 29.8.                             39.6; 2x4 41.6, 4x4 43.3
+//   257 to 512 tiles of 128 x 64, 4x4 | 128 x 128 (or 192 x 128) tiles, each with the activation kernel that goes with it, ranks 16 to 64: MXFP4 M = 1558, K = 1152,
+//   N = 1952 15.9 | 12.9; M = 427, K = 2112, N = 4832 17.3 | 15.4; M = 300, K = 3008, N = 8000 20.1 | 17.8; M = 1024, K = N = 3072 18.8 | 18.3; M = 1283, K = 4032, N = 2560 25.3 | 24.3;
+//   from K = 4096 on, where the large tiles would split K, M = 600, K = 4096, N = 5632 23.3 | 30.2.  Not taken: rank 128, M = 1100, K = 2624, N = 2880 27.4 | 26.9 (the sums
+//   of its cut runs lie in the smaller tiles' workspace), and ranks below 32 beyond K = 1792, which bring few columns of partial H (M = 1800, K = 3328, N = 1536 20.4 | 19.0); K below
+//   1024 was not measured.  INT8 M = 1558, K = 1152, N = 1952 17.2 | 15.1; M = 1476, K = 1024, N = 2432 17.2 | 15.0; M = 1011, K = 1536,
+//   N = 2832 16.7 | 16.7
 //   32 x 32 tiles with sixteen wavefronts, 1x8 -> narrow, ranks 16 to 128 (a launch of few tiles pulls its weights through few CUs):
 //   INT8: M = 4, K = 10048, N = 1232 (20 tiles of 32 x 64) 18.7 -> 15.8, M = 82, K = 6208, N = 1888 (90) 15.8 -> 14.1, M = 7, K = 1984, N = 4176 (66) 9.4 -> 8.8,
 //   M = 3, K = 1408, N = 1584 8.05 -> 8.05; MXFP4: M = 1, K = 5056, N = 1344 13.1 -> 12.3, M = 5, K = 8640, N = 4592 (72) 17.0 -> 15.8, M = 9, K = 2176,
 //   N = 4000 10.30 -> 10.32, M = 28, K = 1152, N = 2752 9.8 -> 10.3; beyond 128 tiles of 32 x 64 it loses (INT8, M = 99, K = 9024, N = 2864 19.8 -> 25.9);
 //   fewer than 16 were not measured
-inline int plan_kpar_blocks(bool i8, int M, int N, int G, int ksplit_override = 0) {
+inline int plan_kpar_blocks(bool i8, int M, int N, int G, int rank, int ksplit_override = 0) {
     if (ksplit_override > 0) return kKparNone;
     const long tn = (N + 63) / 64, t32 = (long)((M + 31) / 32) * tn, t64 = (long)((M + 63) / 64) * tn, t128 = (long)((M + 127) / 128) * tn;
     if (t32 <= 128 && t32 >= 16 && G >= (i8 ? 20 : 52)) return kKparNarrow;
     if (t32 <= 256) return kKpar1x8;
     if (t64 <= 256) return i8 ? kKpar2x8 : kKpar2x4;
     if (t128 <= 256) return i8 && G < 128 ? kKpar2x4 : kKpar4x8;
-    return t128 <= 512 ? kKpar4x4 : kKparNone;
+    return t128 <= 512 && (G < 16 || G > (i8 ? 18 : rank < 32 ? 28 : 63) || rank > 64) ? kKpar4x4 : kKparNone;
 }
 
 // INT4 and MXFP4 forwards that run as ONE launch (fused_small_kernel.hip): launches of at most one 32 x 64 tile per CU whose K is
@@ -686,7 +688,7 @@ inline WorkspaceFp4 workspace_layout_fp4(int M, int K, int N, int rank, int kspl
     const bool parked = ap.chunks > 1 && rank > 0;
     w.aflags_off = w.hpart_off + (parked ? align256(act_parked_floats(ap, w.Mpad, rank) * 4) : 0);
     w.total = w.aflags_off + (parked ? align256(act_arrival_words(ap, w.Mpad) * 8) : 0);
-    const int kpar = plan_kpar_blocks(false, M > 0 ? M : 1, N, G, ksplit_override);
+    const int kpar = plan_kpar_blocks(false, M > 0 ? M : 1, N, G, rank, ksplit_override);
     act_use_small_plan(w, false, M > 0 ? M : 1, N, G, rank, act_override, kpar ? kpar_rows(kpar) : 0, kpar ? kpar_cols(kpar) : 0);
     return w;
 }

@@ -343,8 +343,10 @@ hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream) {
     // per product, but nobody to work while a workgroup fills its ring or stores its tile, which a long K loop has to earn back.  us per forward,
     // 128 x 256 | 256 x 256: M = 4608, K = 12288, N = 3072 241 | 226, M = 2048, K = 9216, N = 8192 152 | 145, M = 1500, K = 8192, N = 9008 122.2 | 114.9,
     // M = 3000, K = N = 4608 83.7 | 79.6; K = 4096 (M = 1024, N = 16000) 70.4 | 70.6, K = 3072 (M = 1664, N = 8192) 56.4 | 57.8; in a second round of
-    // the CUs (M = 2048, K = 3072, N = 9216, 288 tiles) 78.1 | 99.8.
-    if (plan.tile == 0 && plan.tiles > 256 && G >= 72 && (long)((p.M + 255) / 256) * ((p.N + 255) / 256) <= 256) return launch_w8_tile<4, 4, true>(p, stream);
+    // the CUs (M = 2048, K = 3072, N = 9216, 288 tiles) 78.1 | 99.8.  Against 192 x 192 tiles, more than one per CU: M = 4608, K = 12288, N = 3072 246 | 228, M = 2328,
+    // K = 8448, N = 5136 142.7 | 134.3, M = 2119, K = 4608, N = 6960 83.4 | 81.9.
+    if ((plan.tile == 0 || plan.tile == 1) && plan.tiles > 256 && G >= 72 && (long)((p.M + 255) / 256) * ((p.N + 255) / 256) <= 256)
+        return launch_w8_tile<4, 4, true>(p, stream);
     // What a step asks of memory holds its products back where it stands in front of them and no other workgroup of the CU has products
     // meanwhile; with several workgroups it is better asked for early.  us per forward, in front | between: 192 x 192 M = 4608, K = 3072,
     // N = 12288 175 | 168; 192 x 128 up to one tile per CU M = 3129, K = 11456, N = 1648 4 % faster, beyond M = 1311, K = 8576, N = 6464 (357 tiles)

@@ -1,0 +1,64 @@
+"""Which output tiles MXFP4 and INT8 launches take (csrc/layout.h, plan_gemm_fp4 and plan_kpar_blocks), and forwards that take them."""
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2411_05007_amd import svdq as S
+from tests.test_gpu_parity import torch  # noqa: F401 (fixture)
+from tests.test_gpu_small_launches import _wide_branch
+from tests.test_gpu_w8a8 import _random_layer, _run_and_compare
+from tests.test_host_launches import FP4, HERE, W8A8, _gemm_grid, _kernels, record  # noqa: F401 (fixture)
+
+FITS = r"""
+#include <stdio.h>
+#include <initializer_list>
+#include "layout.h"
+using namespace svdq;
+int main() {
+    const int rows[4] = {128, 192, 192, 128}, cols[4] = {256, 192, 128, 128};
+    for (int M = 1; M <= 5000; M += M < 64 ? 1 : 37)
+        for (int N = 16; N <= 13000; N += N < 640 ? 16 : 208)
+            for (int G : {1, 18, 48, 192})
+                for (int want : {0, 1, 3}) {
+                    const GemmPlanFp4 p = plan_gemm_fp4(M, N, G, want);
+                    const int tm = (M + rows[p.tile] - 1) / rows[p.tile], tn = (N + cols[p.tile] - 1) / cols[p.tile];
+                    if (p.tiles != tm * tn || tm * rows[p.tile] > round_up(M, kRowPad) || tn * cols[p.tile] > round_up(N, kRowPad) || p.ksplit < 1 || (p.ksplit > 1 && p.tile != 0))
+                        return printf("M %d, N %d, G %d, %d: tile %d, %d of them, split %d\n", M, N, G, want, p.tile, p.tiles, p.ksplit), 1;
+                }
+    return printf("ok\n"), 0;
+}
+"""
+
+
+def test_tiles_fit_the_padded_rows_and_columns(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "fits.cpp", tmp_path / "fits"
+    src.write_text(FITS)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", os.path.join(os.path.dirname(HERE), "paper_2411_05007_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r,kernel,tiles", [
+    (FP4, 4608, 3072, 9216, 32, "gemm_fp4_kernel<3,3,true>", 24 * 48), (W8A8, 3000, 3072, 9216, 16, "gemm_w8a8_kernel<3,3,true>", 16 * 48), (FP4, 4608, 3072, 3072, 32, "gemm_fp4_kernel<2,4,false>", 36 * 12),
+    (FP4, 4406, 7168, 2304, 32, "gemm_fp4_kernel<3,2,false>", 23 * 18), (W8A8, 907, 5952, 7216, 16, "gemm_w8a8_kernel<3,3,true>", 5 * 38), (W8A8, 4608, 12288, 3072, 16, "gemm_w8a8_kernel<4,4,true>", 18 * 12),
+    (FP4, 1024, 3072, 3072, 32, "gemm_fp4_kernel<2,2,false>", 8 * 24), (FP4, 1024, 4096, 3072, 32, "gemm_kpar_blocks_kernel<", 8 * 48), (FP4, 1024, 3072, 3072, 128, "gemm_kpar_blocks_kernel<", 8 * 48),
+    (W8A8, 1558, 1152, 1952, 16, "gemm_w8a8_kernel<2,2,true>", 13 * 16), (W8A8, 1558, 1216, 1952, 16, "gemm_kpar_blocks_kernel<", 13 * 31)])
+def test_which_tiles_a_launch_takes(record, fmt, M, K, N, r, kernel, tiles):  # noqa: F811
+    rec = record([(0, fmt, M, K, N, r)])[0]
+    assert _kernels(rec)[-1].startswith(kernel) and _gemm_grid(rec) == tiles, (_kernels(rec), _gemm_grid(rec))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,M,K,N,r", [("fp4", 1141, 1984, 6928, 48), ("fp4", 641, 1088, 4240, 32), ("fp4", 299, 2368, 6160, 64), ("fp4", 257, 1024, 8208, 32), ("w8a8", 1900, 1984, 4528, 16), ("w8a8", 641, 1088, 4240, 32)])
+def test_tiles_of_launches_that_took_others(torch, fmt, M, K, N, r):  # noqa: F811
+    """Ragged last tiles of every shape, steps off the rounds of four, activations in one pass of eight tokens up to rank 64 and from 17 slices on."""
+    if fmt == "fp4":
+        return _wide_branch(torch, fmt, M, K, N, r)
+    xb, w, ax, b = _random_layer(np.random.default_rng(7400 + M), M, K, N)
+    _run_and_compare(torch, xb, S.svdq_w8a8_prepare(w, ax, r, bias=b), rows=np.r_[0:20, M - 140:M], what=f"w8a8 {M}x{K}x{N} r{r}")
