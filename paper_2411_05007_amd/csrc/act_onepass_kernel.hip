@@ -345,7 +345,7 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 // the wavefronts without one (1 to 4000 tokens: 1 to 13 % slower than the walking kernel at up to eight groups, 1 to 6 % faster from
 // nine on).  M = 1, K = 3072, N = 9216 15.7 -> 14.2; M = 300,
 // K = 3072, N = 2064 22.4 -> 17.9; M = 2048, K = N = 3072 40.4 -> 34.6; M = 4608, K = N = 3072 69.7 -> 64.1.
-// INT4 and MXFP4, whose groups do not wait for each other: one round of workgroups that fills a quarter of the CUs at
+// INT4 and MXFP4, whose groups do not wait for each other: what act_pass_instead names (layout.h), and else one round of workgroups that fills a quarter of the CUs at
 // least; fewer slices do better with K cut into runs, a second round undoes the gain.  INT4: M = 1337, K = 3072, N = 9216
 // 61.5 -> 60.0, M = 4096, K = 6144, N = 2048 80.5 -> 78.2, M = 4608, K = 3072, N = 3072 65.3 -> 67.8; MXFP4: M = 2048, K = N = 3072
 // 28.7 -> 27.5, M = 4608, K = 6144, N = 3072 72.4 -> 75.3; INT4 at rank 64: no difference.
@@ -356,6 +356,7 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 bool act_one_pass(int fmt, int M, int K, int rank) {
     const int G = K / kGroup, slices = (M + 15) / 16;
     if (fmt == 1 && G >= 16 && G <= 3 * kWaves && act_one_pass_tokens(M) == 8) return slices >= 16 && rank <= 64;
+    if (fmt == 0 && act_pass_instead(true, M, G, rank)) return true;
     if (fmt != 2) return slices >= 64 && slices <= 256 && G <= 6 * kWaves && rank <= 32;
     if (G <= 8 || (slices > 256 && G <= 24)) return false;
     return (G <= 3 * kWaves && rank <= 64) || (G <= 6 * kWaves && rank <= 32);

@@ -609,8 +609,17 @@ inline bool act_plan_fits(W &w, const ActPlan &a, int rank) {
 // 19.6 | 16.1; INT4 M = 119, K = 5184, N = 7712, rank 128 24.4 | 21.4, M = 2, K = 13568, N = 128, rank 96 25.3 | 23.3.  Not taken: K above 6144 beyond one
 // slice (MXFP4 M = 69, K = 7296, N = 6304, rank 112 22.9 | 28.0), more tokens or 128-row tiles (INT4 M = 323, K = 3904, N = 5824, rank 64 28.8 | 32.2).
 inline bool act_longer_runs(int M, int G, int tile_rows) { return tile_rows > 0 && tile_rows <= 64 && M <= (G <= 96 ? 256 : 16); }
+// INT4 and MXFP4 launches that leave no partial H although their tiles could add it: one pass with eight tokens to a workgroup makes H itself in
+// about the time, and the tiles are spared its reading.  us per forward, partial H | one pass: INT4 M = 1024, K = 1152, N = 4608 22.0 | 18.6; M = 1590, K = 1792, N = 2848
+// 26.7 | 22.3; M = 2048, K = N = 3072 37.4 | 34.7; M = 521, K = 1728, N = 1424 12.3 | 11.7; MXFP4 M = 1024, K = 2048,
+// N = 1536 14.1 | 13.2; M = 512, K = N = 3072 16.0 | 15.5.  Not taken: INT4 with three groups to a wavefront and few tokens (M = 512, K = N = 3072 16.8 | 17.9, on
+// 128 x 160 tiles N = 9216 31.1 | 30.1), MXFP4 with 16 columns of H; wider branches, fewer groups and fewer tokens were not measured.
+inline bool act_pass_instead(bool int4, int M, int G, int rank) {
+    return M > 368 && M <= 2048 && G >= 16 && G <= 48 && rank <= 32 && (int4 ? rank > 0 && (G <= 32 || M >= 1024) : rank > 16);
+}
 template <typename W>
 inline void act_use_small_plan(W &w, bool int4, int M, int N, int G, int rank, int act_override, int tile_rows, int tile_cols) {
+    if (act_override == 0 && act_pass_instead(int4, M, G, rank)) return;
     const bool fine = act_short_runs(int4, G, rank, tile_rows);
     if (act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, fine), rank)) return;
     if (fine && act_longer_runs(M, G, tile_rows)) act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, false), rank);

@@ -67,3 +67,23 @@ def test_which_launches_take_eight_tokens(record):  # noqa: F811
         grids = [(r[2], int(r[3])) for r in rec if r[0] == "launch" and r[2].startswith("act_onepass_kernel<")]
         tok = 8 if c in eight else 16
         assert len(grids) == 1 and grids[0][0].endswith(f",{tok}>") and grids[0][1] == -(-c[2] // tok), (c, grids)
+
+
+# launches whose tiles could add partial H: group counts off sixteen and off the rounds of the loops, ragged last workgroups and tiles
+INSTEAD = [("int4", 371, 1088, 2064, 32), ("int4", 777, 1984, 4624, 16), ("int4", 1029, 3008, 3088, 32), ("int4", 2041, 2112, 3088, 32), ("fp4", 371, 1088, 3088, 32), ("fp4", 1029, 3008, 1552, 32)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,M,K,N,r", INSTEAD)
+def test_one_pass_instead_of_partial_h(torch, fmt, M, K, N, r):  # noqa: F811
+    _wide_branch(torch, fmt, M, K, N, r)
+
+
+def test_which_launches_leave_no_partial_h(record):  # noqa: F811
+    fmts = {"int4": INT4, "fp4": FP4}
+    for c, rec in zip(INSTEAD, record([(0, fmts[f], *s) for f, *s in INSTEAD])):
+        k = [r[2] for r in rec if r[0] == "launch"]
+        assert len(k) == 2 and k[0].startswith("act_onepass_kernel<") and k[0].endswith(",8>"), (c, k)
+    other = [(0, INT4, 512, 3072, 3072, 32), (0, INT4, 368, 1152, 2064, 32), (0, INT4, 1024, 3136, 3072, 32), (0, INT4, 1024, 1152, 2064, 48), (0, FP4, 512, 1856, 3072, 16), (0, INT4, 1024, 1152, 2064, 32, 4 << 12)]
+    for c, rec in zip(other, record(other)):
+        assert not any(r[2].startswith("act_onepass") for r in rec if r[0] == "launch"), (c, rec)
