@@ -39,10 +39,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Tile configuration: 2 x 2 wavefronts, each RB x CB MFMA blocks of 32 x 32.  <2, 4>: 128 x 256 workgroup tile;
-// <3, 3>: 192 x 192 (nine MFMAs per six operand blocks instead of eight; used where it makes the tile count a whole
-// number of rounds of the chip's 512 workgroup places, e.g. 24 x 64 = 1536 tiles for M = 4608, N = 12288);
-// <3, 2>: 192 x 128 and <2, 2>: 128 x 128, which load more per MFMA and are used where they spread a launch better over
-// the CUs (layout.h, plan_gemm_fp4).
+// <3, 3>: 192 x 192 (nine MFMAs per six operand blocks instead of eight); <3, 2>: 192 x 128 and <2, 2>: 128 x 128, which load more
+// per MFMA.  Which of them a launch takes follows how they spread over the CUs (layout.h, plan_gemm_fp4).
 // 12, 12, 10, 8 operand blocks per step: two or three direct-to-LDS loads per wavefront.
 template <int RB, int CB>
 struct Fp4Tile {
