@@ -419,10 +419,27 @@ hipError_t launch_mfma_parts(const W4A16Params &p, hipStream_t stream) {
     hipLaunchKernelGGL(k, dim3((p.N + 32 * CB - 1) / (32 * CB), (p.M + rows - 1) / rows), dim3(WAVES * 64), bytes, stream, p);
     return hipGetLastError();
 }
+// Where the parts of X^ lie in LDS (PARTS): where those of the rows fit it, but for
+//  - more workgroups than CUs, two of which share a CU without the parts (CB and RK whose registers allow it) and only one with them.  us per forward, parts in the loop |
+//    in LDS: 5 rows, K = 2048, N = 36864, rank 32 18.3 | 20.6; 4 rows, K = 2560, N = 24592 14.6 | 15.3; 3 rows, K = 3072, N = 24592 15.9 | 16.7; two on a CU
+//    either way: 3 rows, K = 2048, N = 36864 17.3 | 15.1; 2 rows, K = 3072 22.1 | 18.6.  A long K in at most two rounds earns it back up to four rows (K = 4096, N =
+//    24592: 2 rows 19.5 | 18.5, 4 rows 20.3 | 20.0; K = 6144 2 rows 26.6 | 24.3), a third round does not (K = 4096, N = 36864: 3 rows 27.8 | 28.2, 4 rows 28.6 | 29.4);
+//  - loops of about one group per wavefront, where the turn through LDS and its barrier stand in front of a single step: N = 36864, rank 32, 1 row K = 128 6.8 | 7.4, K = 512
+//    7.9 | 8.2, K = 640 8.7 | 8.6; N = 9216, rank 64, 1 row K = 256 4.56 | 4.86; 2 rows, N = 24592, rank 32 K = 320 5.5 | 5.7, K = 512 6.2 | 5.9; 5 rows, N = 24592 K = 128
+//    5.6 | 5.4.  Up to 128 columns and rank 32 either does (0 to 2 %).
+template <int CB, int RK, int WAVES>
+bool parts_in_lds(const W4A16Params &p) {
+    const int loop = mfma_parts_bytes(p.M, p.K, RK, WAVES), G = p.K / 64;
+    if (loop > kLdsBytesPerCU) return false;
+    const bool brief = G <= 8 && (RK > 2 ? p.M * G < 18 : p.M < 4 && p.M * G < 16 && p.N > 128);
+    constexpr bool kTwoWithout = WAVES == 8 && (RK == 0 || CB == 1 || (CB == 2 && RK == 2));
+    const long wgs = (p.N + 32 * CB - 1) / (32 * CB);
+    return !brief && (!kTwoWithout || wgs <= 256 || 2 * loop <= kLdsBytesPerCU || (p.K >= 4096 && p.M <= 4 && wgs <= 512));
+}
 template <bool STACK, int CB, int RK, int WAVES, bool APART>
 hipError_t launch_mfma_apart(const W4A16Params &p, hipStream_t stream) {
     if constexpr (STACK)
-        if (mfma_parts_bytes(p.M, p.K, RK, WAVES) <= kLdsBytesPerCU) return launch_mfma_parts<true, CB, RK, WAVES, false, true>(p, stream);
+        if (parts_in_lds<CB, RK, WAVES>(p)) return launch_mfma_parts<true, CB, RK, WAVES, false, true>(p, stream);
     return launch_mfma_parts<STACK, CB, RK, WAVES, APART, false>(p, stream);
 }
 // Parts of X^ apart from their packing costs registers.  Sixteen wavefronts have none for it.  Some variants of eight have two

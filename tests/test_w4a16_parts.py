@@ -45,3 +45,14 @@ def test_which_calls_keep_the_parts_in_lds(record):  # noqa: F811
     calls = [(*s, True) for s in EDGES if s[0] <= 5] + [(5, 4160, 1040, 32, False), (2, 12288, 272, 16, False), (6, 1088, 272, 32, False), (16, 3072, 18432, 32, False)]
     for (M, K, N, r, parts), rec in zip(calls, record([(0, W4A16, M, K, N, r) for M, K, N, r, _ in calls])):
         assert _kernels(rec)[-1].endswith(",true>") == parts, (M, K, N, r, _kernels(rec))
+
+
+def test_where_parts_in_lds_would_cost(record):  # noqa: F811
+    """More workgroups than CUs, two of which share a CU only without the parts; loops of one group per wavefront and few rows."""
+    calls = [(5, 2048, 36864, 32, False), (4, 2560, 24592, 16, False), (3, 3072, 27648, 32, False), (5, 3072, 36864, 0, False), (3, 4096, 36864, 32, False), (5, 4096, 30720, 0, False),
+             (3, 2048, 36864, 32, True), (2, 3072, 36864, 16, True), (4, 3072, 30720, 0, True), (4, 4096, 24592, 32, True), (2, 6144, 30720, 32, True), (5, 3072, 24576, 32, True),
+             (5, 2048, 27648, 64, True), (3, 3072, 36864, 48, True), (2, 3072, 17408, 64, True),
+             (1, 512, 36864, 16, False), (2, 448, 9216, 32, False), (3, 320, 18432, 0, False), (1, 128, 272, 16, False), (1, 512, 80, 64, False), (2, 512, 9216, 48, False),
+             (1, 576, 36864, 16, True), (2, 512, 9216, 32, True), (3, 384, 18432, 64, True), (4, 64, 18432, 32, True), (1, 512, 128, 32, True)]
+    for (M, K, N, r, parts), rec in zip(calls, record([(0, W4A16, M, K, N, r) for M, K, N, r, _ in calls])):
+        assert _kernels(rec)[-1].endswith(",true>") == parts, (M, K, N, r, _kernels(rec))
