@@ -438,7 +438,7 @@ bool parts_in_lds(const W4A16Params &p) {
 }
 template <bool STACK, int CB, int RK, int WAVES, bool APART>
 hipError_t launch_mfma_apart(const W4A16Params &p, hipStream_t stream) {
-    if constexpr (STACK)
+    if constexpr (STACK && (WAVES == 8 || (CB == 1 && RK <= 2)))      // (launch_mfma_shape: other launches of sixteen wavefronts are those whose parts do not fit)
         if (parts_in_lds<CB, RK, WAVES>(p)) return launch_mfma_parts<true, CB, RK, WAVES, false, true>(p, stream);
     return launch_mfma_parts<STACK, CB, RK, WAVES, APART, false>(p, stream);
 }
