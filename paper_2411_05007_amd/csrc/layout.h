@@ -329,7 +329,11 @@ inline __host__ __device__ MidPiece mid_piece(int j, int lane, int pieces, int g
 //   from K = 4096 on, where the large tiles would split K, M = 600, K = 4096, N = 5632 23.3 | 30.2.  Not taken: rank 128, M = 1100, K = 2624, N = 2880 27.4 | 26.9 (the sums
 //   of its cut runs lie in the smaller tiles' workspace), and ranks below 32 beyond K = 1792, which bring few columns of partial H (M = 1800, K = 3328, N = 1536 20.4 | 19.0); K below
 //   1024 was not measured.  INT8 M = 1558, K = 1152, N = 1952 17.2 | 15.1; M = 1476, K = 1024, N = 2432 17.2 | 15.0; M = 1011, K = 1536,
-//   N = 2832 16.7 | 16.7
+//   N = 2832 16.7 | 16.7.  Nor few tokens, whose runs' partial H these tiles add by themselves while the large ones need a launch for it: MXFP4 up to 240 tokens (M = 16, K = 3072,
+//   N = 18432, rank 64 17.5 | 19.4; M = 1, N = 32000, rank 32 17.9 | 19.2; M = 129, K = 1024, N = 16000 14.1 | 15.2; M = 200, K = 1792, N = 12800, rank 16 15.1 | 16.3; M = 256, K = 1792, N = 8640,
+//   one pass of eight tokens, 15.5 | 13.6), but ranks 48 and 64 from 97 tokens and K = 1152 on (M = 129, K = 3072, N = 12800, rank 48 20.7 | 19.8; M = 128, K = 1792, N = 25600, rank 64
+//   19.2 | 17.8; K = 1024, M = 200, N = 12800 15.6 | 15.9) and no branch at all (M = 1, K = 1152, N = 25600 10.6 | 9.3); INT8 without a branch (M = 500, K = 1152, N = 6400 12.6 | 13.4)
+//   and with one of more than 16 columns up to 64 tokens (M = 4, K = 1024, N = 25600, rank 32 13.4 | 14.0; M = 100 15.3 | 14.9)
 //   32 x 32 tiles with sixteen wavefronts, 1x8 -> narrow, ranks 16 to 128 (a launch of few tiles pulls its weights through few CUs):
 //   INT8: M = 4, K = 10048, N = 1232 (20 tiles of 32 x 64) 18.7 -> 15.8, M = 82, K = 6208, N = 1888 (90) 15.8 -> 14.1, M = 7, K = 1984, N = 4176 (66) 9.4 -> 8.8,
 //   M = 3, K = 1408, N = 1584 8.05 -> 8.05; MXFP4: M = 1, K = 5056, N = 1344 13.1 -> 12.3, M = 5, K = 8640, N = 4592 (72) 17.0 -> 15.8, M = 9, K = 2176,
@@ -342,7 +346,8 @@ inline int plan_kpar_blocks(bool i8, int M, int N, int G, int rank, int ksplit_o
     if (t32 <= 256) return kKpar1x8;
     if (t64 <= 256) return i8 ? kKpar2x8 : kKpar2x4;
     if (t128 <= 256) return i8 && G < 128 ? kKpar2x4 : kKpar4x8;
-    return t128 <= 512 && (G < 16 || G > (i8 ? 18 : rank < 32 ? 28 : 63) || rank > 64) ? kKpar4x4 : kKparNone;
+    const bool few = i8 ? rank == 0 || (rank > 16 && M <= 64) : rank > 0 && M <= (rank >= 48 && G >= 18 ? 96 : 240);
+    return t128 <= 512 && (G < 16 || G > (i8 ? 18 : rank < 32 ? 28 : 63) || rank > 64 || few) ? kKpar4x4 : kKparNone;
 }
 
 // INT4 and MXFP4 forwards that run as ONE launch (fused_small_kernel.hip): launches of at most one 32 x 64 tile per CU whose K is

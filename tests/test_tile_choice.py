@@ -62,3 +62,13 @@ def test_tiles_of_launches_that_took_others(torch, fmt, M, K, N, r):  # noqa: F8
         return _wide_branch(torch, fmt, M, K, N, r)
     xb, w, ax, b = _random_layer(np.random.default_rng(7400 + M), M, K, N)
     _run_and_compare(torch, xb, S.svdq_w8a8_prepare(w, ax, r, bias=b), rows=np.r_[0:20, M - 140:M], what=f"w8a8 {M}x{K}x{N} r{r}")
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r,kpar", [
+    (FP4, 16, 3072, 18432, 64, True), (FP4, 1, 3072, 32768, 32, True), (FP4, 129, 1024, 12800, 16, True), (FP4, 240, 1792, 8640, 32, True), (FP4, 96, 3072, 18432, 48, True), (FP4, 200, 1024, 12800, 64, True),
+    (FP4, 241, 1792, 8640, 32, False), (FP4, 97, 3072, 18432, 48, False), (FP4, 200, 1152, 12800, 64, False), (FP4, 1, 1152, 25600, 0, False),
+    (W8A8, 500, 1152, 6400, 0, True), (W8A8, 4, 1024, 16448, 32, True), (W8A8, 64, 1152, 18432, 32, True), (W8A8, 65, 1152, 18432, 32, False), (W8A8, 4, 1024, 16448, 16, False)])
+def test_few_tokens_share_k(record, fmt, M, K, N, r, kpar):  # noqa: F811
+    """257 to 512 tiles of 128 x 64: few tokens whose runs' partial H the K-sharing tiles add by themselves, and INT8 without a branch."""
+    rec = record([(0, fmt, M, K, N, r)])[0]
+    assert _kernels(rec)[-1].startswith("gemm_kpar_blocks_kernel<") == kpar, _kernels(rec)
