@@ -352,10 +352,11 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 // MXFP4 with eight tokens to a workgroup, act_tile_kernel.hip -> this one: K = 1024 (below, few tokens were not measured) to 3072 from 241 tokens on, M = 270, K = 1152, N = 12288, rank 32
 // 16.4 -> 13.8, M = 397, K = 2240, N = 10208 21.0 -> 19.2, and ranks 48 and 64 (layout.h, plan_act_tile); longer rows hold six groups per wavefront, and few or
 // wide ones lose: M = 526, K = 3712, N = 7392, rank 32 24.0 | 25.3, M = 1500, K = 6144, N = 3072, rank 64 38.0 | 41.4.  INT4 (spilled registers at rank 64): M = 905, K = 3136,
-// N = 5264, rank 48 38.0 | 43.7.
+// N = 5264, rank 48 38.0 | 43.7.  Without a branch cut runs cost no second launch (act_kernel.hip | this): M = 667, K = 3008, N = 64 9.5 | 10.2, M = 300, K = 2240, N = 2800 8.6 | 8.9, M = 500,
+// K = 3072, N = 6400 16.1 | 17.1; M = 257, K = 1024, N = 3072 9.6 | 9.3, M = 1000, K = 1536, N = 1024 10.4 | 10.1.
 bool act_one_pass(int fmt, int M, int K, int rank) {
     const int G = K / kGroup, slices = (M + 15) / 16;
-    if (fmt == 1 && G >= 16 && G <= 3 * kWaves && act_one_pass_tokens(M) == 8) return slices >= 16 && rank <= 64;
+    if (fmt == 1 && G >= 16 && G <= 3 * kWaves && act_one_pass_tokens(M) == 8) return slices >= (rank > 0 || G <= 24 ? 16 : 64) && rank <= 64;
     if (fmt == 0 && act_pass_instead(true, M, G, rank)) return true;
     if (fmt != 2) return slices >= 64 && slices <= 256 && G <= 6 * kWaves && rank <= 32;
     if (G <= 8 || (slices > 256 && G <= 24)) return false;

@@ -87,3 +87,10 @@ def test_which_launches_leave_no_partial_h(record):  # noqa: F811
     other = [(0, INT4, 512, 3072, 3072, 32), (0, INT4, 368, 1152, 2064, 32), (0, INT4, 1024, 3136, 3072, 32), (0, INT4, 1024, 1152, 2064, 48), (0, FP4, 512, 1856, 3072, 16), (0, INT4, 1024, 1152, 2064, 32, 4 << 12)]
     for c, rec in zip(other, record(other)):
         assert not any(r[2].startswith("act_onepass") for r in rec if r[0] == "launch"), (c, rec)
+
+
+@pytest.mark.parametrize("M,K,N,one_pass", [(667, 3008, 64, False), (300, 2240, 2800, False), (500, 3072, 6400, False), (1008, 2048, 1536, False), (1009, 2048, 1536, True), (300, 1536, 3072, True), (300, 1600, 3072, False)])
+def test_mxfp4_without_a_branch(record, M, K, N, one_pass):  # noqa: F811
+    """Nothing has to meet over K, so cut runs cost no second launch: one pass of rows up to K = 1536, and where workgroups of sixteen tokens would fill a quarter of the CUs."""
+    k = [r[2] for r in record([(0, FP4, M, K, N, 0)])[0] if r[0] == "launch"]
+    assert k[0].startswith("act_onepass_kernel<") == one_pass, k
