@@ -357,7 +357,7 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 bool act_one_pass(int fmt, int M, int K, int rank) {
     const int G = K / kGroup, slices = (M + 15) / 16;
     if (fmt == 1 && G >= 16 && G <= 3 * kWaves && act_one_pass_tokens(M) == 8) return slices >= (rank > 0 || G <= 24 ? 16 : 64) && rank <= 64;
-    if (fmt == 0 && act_pass_instead(true, M, G, rank)) return true;
+    if (fmt == 0 && act_pass_instead(true, M, 0, G, rank, 0)) return true;
     if (fmt != 2) return slices >= 64 && slices <= 256 && G <= 6 * kWaves && rank <= 32;
     if (G <= 8 || (slices > 256 && G <= 24)) return false;
     return (G <= 3 * kWaves && rank <= 64) || (G <= 6 * kWaves && rank <= 32);

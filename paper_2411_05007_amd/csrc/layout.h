@@ -617,14 +617,17 @@ inline bool act_longer_runs(int M, int G, int tile_rows) { return tile_rows > 0 
 // INT4 and MXFP4 launches that leave no partial H although their tiles could add it: one pass with eight tokens to a workgroup makes H itself in
 // about the time, and the tiles are spared its reading.  us per forward, partial H | one pass: INT4 M = 1024, K = 1152, N = 4608 22.0 | 18.6; M = 1590, K = 1792, N = 2848
 // 26.7 | 22.3; M = 2048, K = N = 3072 37.4 | 34.7; M = 521, K = 1728, N = 1424 12.3 | 11.7; MXFP4 M = 1024, K = 2048,
-// N = 1536 14.1 | 13.2; M = 512, K = N = 3072 16.0 | 15.5.  Not taken: INT4 with three groups to a wavefront and few tokens (M = 512, K = N = 3072 16.8 | 17.9, on
-// 128 x 160 tiles N = 9216 31.1 | 30.1), MXFP4 with 16 columns of H; wider branches, fewer groups and fewer tokens were not measured.
-inline bool act_pass_instead(bool int4, int M, int G, int rank) {
-    return M > 368 && M <= 2048 && G >= 16 && G <= 48 && rank <= 32 && (int4 ? rank > 0 && (G <= 32 || M >= 1024) : rank > 16);
+// N = 1536 14.1 | 13.2; M = 512, K = N = 3072 16.0 | 15.5.  With three groups to a wavefront up to 1024 tokens, which the runs' workgroups take in one round, not for INT4 (M = 512, K =
+// N = 3072 16.8 | 17.9, on 128 x 160 tiles N = 9216 31.1 | 30.1; M = 1024, K = 3072, N = 1536 16.9 | 18.2, N = 4096 25.7 | 26.1, but N = 4608 30.9 | 29.6 and K = 2112, N = 4608 26.5 | 24.0), and for MXFP4 not on tiles of 32 or 64 rows, which are few and read
+// little (M = 371, K = 2560, N = 256 9.9 | 10.6, M = 512, K = 2560, N = 1024 11.0 | 11.5, M = 1024, K = 3072, N = 1024 13.3 | 14.1; tiles of 128 rows M = 771, N = 1536 7 and 2 % faster at K = 2560 and 3072).
+// Nor MXFP4 with 16 columns of H; wider branches, fewer groups and fewer tokens were not measured.
+inline bool act_pass_instead(bool int4, int M, int N, int G, int rank, int tile_rows) {
+    if (M <= 368 || M > 2048 || G < 16 || G > 48 || rank > 32) return false;
+    return int4 ? rank > 0 && (G <= 32 || M > 1024 || (M == 1024 && (G <= 40 || N > 4096))) : rank > 16 && (G <= 32 || M > 1024 || tile_rows > 64);
 }
 template <typename W>
 inline void act_use_small_plan(W &w, bool int4, int M, int N, int G, int rank, int act_override, int tile_rows, int tile_cols) {
-    if (act_override == 0 && act_pass_instead(int4, M, G, rank)) return;
+    if (act_override == 0 && act_pass_instead(int4, M, N, G, rank, tile_rows)) return;
     const bool fine = act_short_runs(int4, G, rank, tile_rows);
     if (act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, fine), rank)) return;
     if (fine && act_longer_runs(M, G, tile_rows)) act_plan_fits(w, plan_act_small(M, N, G, rank, act_override, tile_rows, tile_cols, false), rank);

@@ -94,3 +94,12 @@ def test_mxfp4_without_a_branch(record, M, K, N, one_pass):  # noqa: F811
     """Nothing has to meet over K, so cut runs cost no second launch: one pass of rows up to K = 1536, and where workgroups of sixteen tokens would fill a quarter of the CUs."""
     k = [r[2] for r in record([(0, FP4, M, K, N, 0)])[0] if r[0] == "launch"]
     assert k[0].startswith("act_onepass_kernel<") == one_pass, k
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r,one_pass", [
+    (FP4, 371, 2560, 2560, 32, False), (FP4, 512, 2112, 2048, 32, False), (FP4, 1024, 3072, 1024, 32, False), (FP4, 771, 3072, 64, 32, False), (INT4, 1024, 3072, 1536, 32, False),
+    (FP4, 371, 2560, 3072, 32, True), (FP4, 771, 2560, 1536, 32, True), (FP4, 1025, 3072, 1024, 32, True), (FP4, 371, 2048, 64, 32, True), (INT4, 1025, 3072, 1536, 32, True), (INT4, 1024, 2560, 1536, 32, True), (INT4, 1024, 3072, 4608, 32, True), (INT4, 512, 2048, 512, 16, True)])
+def test_partial_h_stays_where_few_tiles_read_it(record, fmt, M, K, N, r, one_pass):  # noqa: F811
+    """Three groups to a wavefront: tiles of 32 or 64 rows (MXFP4), and up to 1024 tokens, which the runs' workgroups take in one round."""
+    k = [r[2] for r in record([(0, fmt, M, K, N, r)])[0] if r[0] == "launch"]
+    assert len(k) == 2 and k[0].startswith("act_onepass_kernel<") == one_pass, k
