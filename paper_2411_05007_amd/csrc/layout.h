@@ -556,13 +556,15 @@ inline int plan_act_wide(bool int4, const ActPlan &other, int M, int G, int rank
 // K = 2368, N = 1936, rank 128 36.4 | 32.6.  Not taken: more than 2048 tokens, which fill the CUs with 16 to a workgroup, with a short K (INT4 M = 3246, K = 1408, N = 432,
 // rank 64 17.0 | 19.5; M = 4006, K = 2816, N = 2736, rank 64 60.6 | 62.8; MXFP4 M = 2235, K = 1664, N = 768, rank 96 19.7 | 20.8).
 // Up to rank 32 only where the runs of the other kernel meet: M = 1500, K = 8192, N = 2048, rank 16 51.7 | 45.8, M = 2300, K = 9216, rank 32 75.8 | 70.8; else
-// M = 3000, K = 6144, N = 3072, rank 16 95.2 | 96, MXFP4 M = 1500, K = 3072, N = 4608 28.3 | 28.9 (one pass).  Ranks of 48 and 64 give way to one pass with
+// M = 3000, K = 6144, N = 3072, rank 16 95.2 | 96, MXFP4 M = 1500, K = 3072, N = 4608 28.3 | 28.9 (one pass); and from 257 tokens on (below, the sum's launch is the larger part: MXFP4 M = 128,
+// K = 1024, N = 36864, rank 16 15.5 | 16.7, M = 171, K = 8192, N = 23408 36.0 | 37.9, INT4 M = 256, K = 1024, N = 36864 27.6 | 28.5, M = 64, K = 8192, N = 23408, rank 32 40.8 | 41.4; INT4 M = 400,
+// K = 4096, N = 23408, rank 32 66.1 | 66.3).  Ranks of 48 and 64 give way to one pass with
 // eight tokens to a workgroup where that is taken (MXFP4 up to K = 3072): M = 2048, K = N = 3072, rank 64 29.5 | 28.0; M = 1024, K = 1536, N = 9216, rank 48 25.5 | 23.6.
 constexpr int kActTileTokens = 32;
 inline int plan_act_tile(const ActPlan &other, bool one_pass, int M, int G, int rank, size_t room) {
     if (rank > 128 || G < 16 || M > 4096) return 0;
     if (rank <= 64 && one_pass && M <= 2048) return 0;
-    if (rank <= 32 && (one_pass || other.chunks <= 1 || other.whole != 0)) return 0;
+    if (rank <= 32 && (M <= 256 || one_pass || other.chunks <= 1 || other.whole != 0)) return 0;
     if (rank > 32 && M > 2048 && G < (rank > 64 ? 36 : 72)) return 0;
     const int tiles = (M + kActTileTokens - 1) / kActTileTokens;
     size_t runs = (rank > 64 ? 256 : 512) / tiles;

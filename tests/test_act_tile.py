@@ -73,3 +73,11 @@ def test_which_launches_take_tiles_of_32_tokens(record):  # noqa: F811
         assert len(k) == 3 and k[0].startswith("act_tile_kernel<") and k[1] == "act_sum_h_kernel", (c, k)
     for c, rec in zip(other, recs[len(took):]):
         assert not any(k.startswith("act_tile") for k in _kernels(rec)), (c, _kernels(rec))
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r,tile", [("fp4", 128, 1024, 36864, 16, False), ("fp4", 171, 8192, 23408, 16, False), ("int4", 256, 1024, 36864, 16, False), ("int4", 64, 8192, 23408, 32, False),
+                                              ("fp4", 400, 8192, 23408, 32, True), ("fp4", 16, 2048, 36864, 64, True), ("int4", 1, 4096, 36864, 128, True)])
+def test_few_tokens_with_a_narrow_branch_keep_their_launches(record, fmt, M, K, N, r, tile):  # noqa: F811
+    """Up to 256 tokens at ranks 16 and 32 the runs that meet in one launch are the faster ones."""
+    k = _kernels(record([(0, {"int4": INT4, "fp4": FP4}[fmt], M, K, N, r)])[0])
+    assert k[0].startswith("act_tile_kernel<") == tile, k
