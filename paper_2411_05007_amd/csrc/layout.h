@@ -642,10 +642,12 @@ inline void act_use_small_plan(W &w, bool int4, int M, int N, int G, int rank, i
 // 108 -> 97.  Where H is added by a launch of its own, one pass with eight tokens to a workgroup is the faster one (this kernel | one pass) up to K = 3072:
 // M = 270, K = 1152, N = 12288 18.8 | 17.4; M = 620, K = 2816, N = 11488 33.3 | 32.2; M = 1, K = 3072, N = 36864 28.8 | 28.7; and up to K = 6144 from 1153 tokens on: M = 1700,
 // K = 4096, N = 8192 73.8 | 70.6; M = 1337, K = 6144, N = 4096 50.3 | 49.1; below, M = 270, K = 6144, N = 12288 41.6 | 42.9, M = 594, K = 3776, N = 6896 32.3 | 32.7,
-// M = 893, K = 4224, N = 4928 34.4 | 34.3, M = 1000, K = N = 4608 41.7 | 40.3.  Few tokens of a K below 1024 keep this kernel (not measured).
+// M = 893, K = 4224, N = 4928 34.4 | 34.3, M = 1000, K = N = 4608 41.7 | 40.3.  Few tokens of a K below 1024 keep this kernel (not measured), and so do two kinds of launches that one pass is slower for: without
+// a branch, where nothing has to be added (M = 16, K = 2048, N = 39936 20.3 | 21.5, M = 512, K = 1536, N = 9984 17.9 | 18.7, M = 400, K = 3072, N = 9984 26.1 | 27.4), and up to 256 tokens of a K above 2560 with more
+// than 16 columns of H (M = 4, K = 3072, N = 33024, rank 32 28.1 | 29.3, rank 16 27.4 | 27.5; M = 200, N = 19968 30.5 | 31.0; M = 400, N = 9984 30.2 | 30.4).
 inline bool act_w8_small(int M, int K, int rank, int kpar) {
     const int G = K / kGroup, slices = (M + 15) / 16;
-    return G <= 192 && rank <= 32 && (kpar || G > 96 || (G > 48 && slices <= 72) || (G < 16 && slices <= 48));
+    return G <= 192 && rank <= 32 && (kpar || G > 96 || (G > 48 && slices <= 72) || ((G < 16 || rank == 0) && slices <= 48) || (rank > 16 && G > 40 && slices <= 16));
 }
 
 // The int8 MFMA takes twice the time of the 4-bit one per step of 64 channels, so a split of the 8-bit GEMM's K loop pays

@@ -103,3 +103,11 @@ def test_partial_h_stays_where_few_tiles_read_it(record, fmt, M, K, N, r, one_pa
     """Three groups to a wavefront: tiles of 32 or 64 rows (MXFP4), and up to 1024 tokens, which the runs' workgroups take in one round."""
     k = [r[2] for r in record([(0, fmt, M, K, N, r)])[0] if r[0] == "launch"]
     assert len(k) == 2 and k[0].startswith("act_onepass_kernel<") == one_pass, k
+
+
+@pytest.mark.parametrize("M,K,N,r,one_pass", [(16, 2048, 39936, 0, False), (512, 1536, 9984, 0, False), (768, 3072, 9984, 0, False), (4, 3072, 33024, 32, False), (256, 2624, 19968, 32, False),
+                                              (4, 3072, 33024, 16, True), (257, 3072, 19968, 32, True), (4, 2560, 33024, 32, True), (769, 3072, 9984, 0, True)])
+def test_int8_launches_that_quantize_beside_the_projection(record, M, K, N, r, one_pass):  # noqa: F811
+    """Large tiles: without a branch there is no sum to make; few tokens of a K above 2560 with more than 16 columns of H."""
+    k = [x[2] for x in record([(0, W8A8, M, K, N, r)])[0] if x[0] == "launch"]
+    assert k[-1].startswith("gemm_w8a8_kernel<") and k[0].startswith("act_onepass_kernel<" if one_pass else "act_w8_small_kernel<"), k
