@@ -165,7 +165,7 @@ struct GemmPlanFp4 {
     int tile;        // 0: 128 x 256, 1: 192 x 192, 2: 192 x 128, 3: 128 x 128
     int tiles, ksplit;
 };
-inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, int min_steps = 32) {
+inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, int min_steps = 32, bool i8 = false) {
     GemmPlanFp4 pl;
     pl.tiles = ((M + 127) / 128) * ((N + 255) / 256);
     int s = 1;
@@ -183,8 +183,11 @@ inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, i
     // the L2 to the others): the mean of the tiles per CU and of that number rounded up, times the MFMAs per step of a tile, weighted with
     // what the tile loads per MFMA, and more where no CU has a second tile to fill the first one's waits (192 x 192 tiles, which ask for a
     // step's operands between its products, need that least, and cost more around a short K loop: INT8, M = 1585, K = 1152, N = 4224 20.9 | 19.8 on 128 x 128,
-    // MXFP4, M = 4111, K = 1728, N = 6896 50.9 | 49.3 on 128 x 256).  192-row and 192-column tiles have to fit the padded rows and columns.  Fitted to 64 launches
-    // of all four shapes; up to two 128 x 256 tiles per CU they keep the launches that the others win by less than 3 %.
+    // MXFP4, M = 4111, K = 1728, N = 6896 50.9 | 49.3 on 128 x 256; more so where they are at most one per CU: INT8, M = 527, K = 640, N = 11136 17.6 | 15.8 on 128 x 128, M = 2080, K = 1664,
+    // N = 2976 23.7 | 22.2; less so where a CU has more than four of them and the K loop is longer than their start: INT8, M = 4493, K = 1152, N = 19904 136.8 on 128 x 256 | 124.3, MXFP4, M = 2571, K = 1024, N = 25232
+    // 65.9 | 61.2, but M = 4012, K = 384, N = 19552 56.7 | 62.4).  Large INT8 launches of up to seven groups are stores of 16-bit results before all else, which small tiles
+    // spread better (M = 3728, K = 64, N = 34544 81.6 on 192 x 192 | 73.3 on 128 x 128).  192-row and 192-column tiles have to fit the padded rows and columns.  Fitted to 1400 launches, G = 1 to 192,
+    // of two to four shapes each; up to two 128 x 256 tiles per CU they keep the launches that the others win by less than 3 %.
     // us per forward, 128 x 256 | 192 x 192 | 192 x 128 | 128 x 128, the rule's choice in brackets; MXFP4 rank 32, INT8 rank 16:
     //   M = 4608, K = 3072, N = 9216 (1296 | 1152 | 1728 | 2592 tiles)   97.8 [87.3] 95.7  98.6     157.1 [138.2] 147.5 153.9
     //   M = 3000, K = 3072, N = 9216 (864 | 768 | 1152 | 1728)           65.7 [57.8] 68.3  65.7     101.9 [89.2] 101.9  98.8
@@ -200,10 +203,11 @@ inline GemmPlanFp4 plan_gemm_fp4(int M, int N, int G, int ksplit_override = 0, i
         auto cost = [](long tiles, double per_tile, double lone) { return (tiles / 256.0 + (double)((tiles + 255) / 256)) * per_tile * (tiles <= 256 ? lone : 1.0); };
         const int pm = round_up(M, kRowPad), pn = round_up(N, kRowPad), tm = (M + 127) / 128, tm192 = (M + 191) / 192, tn = (N + 127) / 128, tn192 = (N + 191) / 192;
         const int tiles[4] = {pl.tiles, tm192 * 192 <= pm && tn192 * 192 <= pn ? tm192 * tn192 : 0, tm192 * 192 <= pm ? tm192 * tn : 0, tm * tn};
-        const double per_tile[4] = {8.0, 9 * (0.89 + 2.0 / (G > 18 ? G : 18)), 6 * 1.05, 4 * 1.07};
+        const double per_tile[4] = {8.0, 9 * (0.89 + (G >= 12 && tiles[1] > 1024 ? 1.2 : 2.0) / (G > 18 ? G : 18)), 6 * 1.05, 4 * (i8 && G < 8 && tiles[3] > 1280 ? 0.95 : 1.07)};
+        const double lone192 = G < 67 ? 1.0 + 2.0 / (G > 12 ? G : 12) : 1.03;
         double best = (pl.tiles <= 512 ? 0.97 : 1.0) * cost(pl.tiles, per_tile[0], 1.2);
         for (int t = 1; t < 4; ++t) {
-            const double c = cost(tiles[t], per_tile[t], t == 1 ? 1.03 : 1.1);
+            const double c = cost(tiles[t], per_tile[t], t == 1 ? lone192 : 1.1);
             if (tiles[t] > 0 && c < best) {
                 best = c;
                 pl.tile = t;

@@ -338,7 +338,7 @@ hipError_t launch_gemm_w8a8(const GemmW8Params &p, hipStream_t stream) {
     if (p.ksplit > 1 && (size_t)(p.ksplit - 1) * (((G + p.ksplit - 1) / p.ksplit + 3) / 4 * 4) >= (size_t)G) return hipErrorInvalidValue;
     if (p.ksplit > 1) return launch_w8_tile<2, 4, false>(p, stream);
     // the tile shape follows the MXFP4 GEMM's rule
-    const GemmPlanFp4 plan = plan_gemm_fp4(p.M, p.N, G, 1);
+    const GemmPlanFp4 plan = plan_gemm_fp4(p.M, p.N, G, 1, 32, true);
     // 256 x 256 tiles, one per CU, where a CU has two of 128 x 256: two thirds of the bytes from the L2 and of the LDS reads
     // per product, but nobody to work while a workgroup fills its ring or stores its tile, which a long K loop has to earn back.  us per forward,
     // 128 x 256 | 256 x 256: M = 4608, K = 12288, N = 3072 241 | 226, M = 2048, K = 9216, N = 8192 152 | 145, M = 1500, K = 8192, N = 9008 122.2 | 114.9,

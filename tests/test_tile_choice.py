@@ -72,3 +72,12 @@ def test_few_tokens_share_k(record, fmt, M, K, N, r, kpar):  # noqa: F811
     """257 to 512 tiles of 128 x 64: few tokens whose runs' partial H the K-sharing tiles add by themselves, and INT8 without a branch."""
     rec = record([(0, fmt, M, K, N, r)])[0]
     assert _kernels(rec)[-1].startswith("gemm_kpar_blocks_kernel<") == kpar, _kernels(rec)
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r,tile", [
+    (W8A8, 4493, 1152, 19904, 16, "3,3"), (FP4, 2571, 1024, 25232, 32, "3,3"), (W8A8, 527, 640, 11136, 16, "2,2"), (W8A8, 2080, 1664, 2976, 16, "2,2"), (FP4, 3592, 1280, 1712, 32, "2,2"), (W8A8, 3728, 64, 34544, 16, "2,2"),
+    (W8A8, 907, 5952, 7216, 16, "3,3"), (FP4, 892, 3456, 7232, 32, "3,3"), (FP4, 1800, 3072, 12288, 32, "3,3"), (W8A8, 2379, 320, 7008, 16, "3,3")])
+def test_tiles_of_short_loops(record, fmt, M, K, N, r, tile):  # noqa: F811
+    """192 x 192 tiles where a CU has several of them, 128 x 128 ones where it would have a single large one with a short loop, and for large INT8 launches of a few groups."""
+    k = _kernels(record([(0, fmt, M, K, N, r)])[0])
+    assert k[-1].startswith(("gemm_fp4_kernel<" if fmt == FP4 else "gemm_w8a8_kernel<") + tile + ","), k
