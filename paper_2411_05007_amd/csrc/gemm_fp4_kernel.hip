@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : 2) void gemm_fp4_kernel(Gem
     const int g_begin = split * g_per;
     const int g_end = g_begin + g_per < p.G ? g_begin + g_per : p.G;
     int tile_m, tile_n;
-    gemm_tile_of((int)blockIdx.x - split * total, tiles_m, tiles_n, 0, tile_m, tile_n);
+    gemm_tile_of((int)blockIdx.x - split * total, tiles_m, tiles_n, xcd_order_from(false, p.G, p.N), tile_m, tile_n);
     const int gm0 = tile_m * kBM, gn0 = tile_n * kBN;      // the launch checks that every tile lies inside the padded rows and columns
 
     // the accumulators start as the bias (in the split that also carries the low-rank product): loaded here, it shares

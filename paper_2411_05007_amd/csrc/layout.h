@@ -132,8 +132,12 @@ inline __host__ __device__ int ring_offset(int j, int frags_a, int frags_b, int 
 // K = 5888, N = 11328 155 -> 128 (33 launches of both: median 5 % faster, none slower).  The INT4 kernel, bound by power and not by the L2, gains 0 to 6 % above
 // 600 tiles (M = 4429, K = 1856, N = 10720 127.6 -> 120; M = 4169, K = 2496, N = 9472 125.6 -> 121.8) and loses 0 to 5 % below (M = 2213, K = 1536,
 // N = 6672, 486 tiles 38.4 -> 40.1).
+// MXFP4 and INT8 launches below 600 tiles with short rows and up to 4096 columns stay in launch order too, in which the eight rows of a band fall on the eight XCDs, each of which then
+// reads its own: 1.7 % faster in the geometric mean of 162 launches (MXFP4, K up to 1536, M = 3270, K = 1536, N = 1872 15.0 in launch order, 15.5 renumbered; INT8, K up to 1024, M = 1823, K = 384,
+// N = 2272 13.5 | 14.0).  Longer rows gain by the numbering at every width (K = 2560, 1 to 2.5 %), and so do wider launches (more than 5000 columns 0 to 7 %: INT8, M = 1703, K = 384, N = 8304 21.6 | 20.3).
 // `bid`: position in the launch order, 0 <= bid < total = tiles_m * tiles_n.
 constexpr int kXcdOrderInt4 = 600;
+inline __host__ __device__ int xcd_order_from(bool i8, int G, int N) { return N <= 4096 && G <= (i8 ? 16 : 24) ? 600 : 0; }
 inline __host__ __device__ void gemm_tile_of(int bid, int tiles_m, int tiles_n, int from, int &tile_m, int &tile_n) {
     constexpr int kBand = 8;
     const int total = tiles_m * tiles_n, per = total / 8, more = total % 8, xcd = bid % 8;      // the first `more` XCDs own a tile more than the others

@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256, RB * CB <= 4 ? 3 : RB * CB <= 9 ? 2 : 1) void 
     const int g_begin = split * g_per;
     const int g_end = g_begin + g_per < p.K / 32 ? g_begin + g_per : p.K / 32;
     int tile_m, tile_n;
-    gemm_tile_of((int)blockIdx.x - split * total, tiles_m, tiles_n, 0, tile_m, tile_n);
+    gemm_tile_of((int)blockIdx.x - split * total, tiles_m, tiles_n, xcd_order_from(true, p.K / 64, p.N), tile_m, tile_n);
     const int gm0 = tile_m * kBM, gn0 = tile_n * kBN;      // the launch checks that every tile lies inside the padded rows and columns
 
     intx16 iacc[kRB][kCB];
