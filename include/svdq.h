@@ -232,8 +232,9 @@ int svdq_debug_group_acc(const svdq_layer_dev *layer, const void *workspace, int
  * check them over many shapes without a GPU.  out receives 16 values:
  *   [0] runs per 16-token slice of the activation kernel, [1] groups of 64 channels per run, [2] wavefronts per
  *   workgroup, [3] how many leading slices are cut differently, into [4] runs of [5] groups (runs <= 1: walked whole),
- *   [6] workgroups of the activation kernel, [7] its LDS bytes per workgroup (launches that take the one-pass activation
- *   kernel, one workgroup per slice, or the one of 64-token workgroups use none of [0] to [7]),
+ *   [6] workgroups of the activation kernel, [7] its LDS bytes per workgroup (none of [0] to [7] is used by small forwards that run
+ *   as one kernel, by launches of the one-pass activation kernel, a workgroup to 16 or 8 tokens, and by those of its kernels of 32- and
+ *   64-token workgroups, which cut K into runs of their own),
  *   [8] output tiles of the GEMM, [9] how many of them have their K loop split, [10] into how many workgroups,
  *   [11] workgroups of the GEMM,
  *   [12] bytes / 256 of the workspace from the parked partial H on (which lies in the place of the partial tiles of a split

@@ -349,7 +349,7 @@ hipError_t launch_rank(const ActParams &p, int flags, hipStream_t stream) {
 // least; fewer slices do better with K cut into runs, a second round undoes the gain.  INT4: M = 1337, K = 3072, N = 9216
 // 61.5 -> 60.0, M = 4096, K = 6144, N = 2048 80.5 -> 78.2, M = 4608, K = 3072, N = 3072 65.3 -> 67.8; MXFP4: M = 2048, K = N = 3072
 // 28.7 -> 27.5, M = 4608, K = 6144, N = 3072 72.4 -> 75.3; INT4 at rank 64: no difference.
-// MXFP4 with eight tokens to a workgroup, act_tile_kernel.hip -> this one: K = 1024 (below, few tokens were not measured) to 3072 from 241 tokens on, M = 270, K = 1152, N = 12288, rank 32
+// MXFP4 with eight tokens to a workgroup, act_tile_kernel.hip -> this one: K = 1024 (below, partial H is left to the GEMM: layout.h, act_pass_instead) to 3072 from 241 tokens on, M = 270, K = 1152, N = 12288, rank 32
 // 16.4 -> 13.8, M = 397, K = 2240, N = 10208 21.0 -> 19.2, and ranks 48 and 64 (layout.h, plan_act_tile); longer rows hold six groups per wavefront, and few or
 // wide ones lose: M = 526, K = 3712, N = 7392, rank 32 24.0 | 25.3, M = 1500, K = 6144, N = 3072, rank 64 38.0 | 41.4.  INT4 (spilled registers at rank 64): M = 905, K = 3136,
 // N = 5264, rank 48 38.0 | 43.7.  Without a branch cut runs cost no second launch (act_kernel.hip | this): M = 667, K = 3008, N = 64 9.5 | 10.2, M = 300, K = 2240, N = 2800 8.6 | 8.9, M = 500,

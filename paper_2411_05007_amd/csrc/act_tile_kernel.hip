@@ -8,9 +8,9 @@
 // a run's groups, wavefront w taking groups w, w + 4, ..., with nothing to wait for in the loop; X is requested a group ahead, the
 // fragments as soon as the products have read the last ones.  Their partial H meet in LDS and leave with plain stores, and
 // act_sum_h_kernel adds the runs in order.
-// us in a kernel trace, M = 512, K = 12288, rank 128: act_kernel.hip 16.9; this kernel 9.7 and the sum 3 to 4.  Bound: a wavefront's chain
-// (190 vector and 16 matrix instructions and 20 requests per group at rank 128, one wavefront per SIMD) and the fixed parts, 3 us
-// of the 9.7.  Tried: the codes of a run kept in LDS and stored behind the loop (the same, but one workgroup per CU for long runs: M =
+// us in a kernel trace, M = 512, K = 12288, rank 128: act_kernel.hip 16.9; this kernel 10.6 and the sum 4.8, of which the forward sees 12.6 (its start and end
+// are shared with the neighbours').  Bound: a wavefront's chain (by counters 163 vector and 16 matrix instructions, 21 requests and two stores per
+// group at rank 128, one wavefront per SIMD) and the fixed parts, 3 us of the 10.6.  Tried: the codes of a run kept in LDS and stored behind the loop (the same, but one workgroup per CU for long runs: M =
 // 1800, K = 8192, N = 3072, rank 128 94.7 -> 97.7 us per forward); eight wavefronts (M = 512: 40.1 -> 40.6); parts that the GEMM adds (up to rank 64
 // 2 to 10 % slower than act_kernel.hip's).  The rule, with both sides: layout.h, plan_act_tile.
 #include <hip/hip_runtime.h>
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void act_tile_kernel(ActParams p) {
             __builtin_amdgcn_raw_buffer_store_b8((uint8_t)sbyte, rs_s, 4 * lane, ((g >> 2) * p.Mpad + gm0) * 8 + (g & 3), 0);
         }
     }
-    // ---- the run's codes leave, and its partial H: the wavefronts' parts meet in LDS, in their order
+    // ---- the run's partial H: the wavefronts' parts meet in LDS, in their order (its codes have left in the loop)
     float *hmine = reinterpret_cast<float *>(xl);
 #pragma unroll
     for (int c = 0; c < RC; ++c)

@@ -145,7 +145,7 @@ struct FusedSmallParams {
     uint16_t *Y;             // bf16 [M][N]; must not share memory with X
     uint8_t *codes, *bx;     // what the forward leaves in the workspace: activation blocks (MXFP4: codes, scale bytes),
     float *H;                // fp32 [Mpad][rank]
-    int M, N, K, G, Mpad, Npad, rank;      // rank <= 64
+    int M, N, K, G, Mpad, Npad, rank;      // rank <= 32
 };
 hipError_t launch_fused_small(const FusedSmallParams &p, int fmt, hipStream_t stream);
 

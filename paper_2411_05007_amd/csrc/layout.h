@@ -336,7 +336,8 @@ inline __host__ __device__ MidPiece mid_piece(int j, int lane, int pieces, int g
 //   N = 1952 15.9 | 12.9; M = 427, K = 2112, N = 4832 17.3 | 15.4; M = 300, K = 3008, N = 8000 20.1 | 17.8; M = 1024, K = N = 3072 18.8 | 18.3; M = 1283, K = 4032, N = 2560 25.3 | 24.3;
 //   from K = 4096 on, where the large tiles would split K, M = 600, K = 4096, N = 5632 23.3 | 30.2.  Not taken: rank 128, M = 1100, K = 2624, N = 2880 27.4 | 26.9 (the sums
 //   of its cut runs lie in the smaller tiles' workspace), and ranks below 32 beyond K = 1792, which bring few columns of partial H (M = 1800, K = 3328, N = 1536 20.4 | 19.0); K below
-//   1024 was not measured.  INT8 M = 1558, K = 1152, N = 1952 17.2 | 15.1; M = 1476, K = 1024, N = 2432 17.2 | 15.0; M = 1011, K = 1536,
+//   1024 keeps the small tiles, which lose 1 to 20 % up to K = 512 (MXFP4, M = 500, N = 8000, rank 32 12.0 | 10.6; INT8 13.7 | 12.9) and lie on either side beyond (K = 768, rank 32, MXFP4 M = 500, N = 6400 13.1 | 13.6,
+//   M = 1200, N = 2560 13.3 | 11.6, rank 64 15.1 | 16.3; INT8 M = 500, N = 6400 13.3 | 14.8).  INT8 M = 1558, K = 1152, N = 1952 17.2 | 15.1; M = 1476, K = 1024, N = 2432 17.2 | 15.0; M = 1011, K = 1536,
 //   N = 2832 16.7 | 16.7.  Nor few tokens, whose runs' partial H these tiles add by themselves while the large ones need a launch for it: MXFP4 up to 240 tokens (M = 16, K = 3072,
 //   N = 18432, rank 64 17.5 | 19.4; M = 1, N = 32000, rank 32 17.9 | 19.2; M = 129, K = 1024, N = 16000 14.1 | 15.2; M = 200, K = 1792, N = 12800, rank 16 15.1 | 16.3; M = 256, K = 1792, N = 8640,
 //   one pass of eight tokens, 15.5 | 13.6), but ranks 48 and 64 from 97 tokens and K = 1152 on (M = 129, K = 3072, N = 12800, rank 48 20.7 | 19.8; M = 128, K = 1792, N = 25600, rank 64
@@ -365,7 +366,8 @@ inline int plan_kpar_blocks(bool i8, int M, int N, int G, int rank, int ksplit_o
 //   MXFP4  M = 1, N = 1152: K = 1024 9.1 | 6.5, 1792 9.1 | 7.7, 2048 9.2 | 8.3;  M = 256: K = 1024 9.2 | 6.7, 1792 9.1 | 7.9;  M = 8, N = 192: K = 1792 9.2 | 7.6
 // In a replayed graph, where no host stands between the launches, the last gain is that of K = 1792 (INT4 4 to 12 %, MXFP4 2 to 9 %;
 // K = 2048 2 % slower to 5 % faster, MXFP4 4 % slower to 3 % faster).  Wider branches lose: rank 64, M = 8, K = 1536, N = 9216 9.3 | 11.3.  K below 1024
-// keeps its two launches, whose cut has rules of its own (act_short_runs).
+// keeps its two launches, whose cut has rules of its own (act_short_runs), although one is the faster side there as well (INT4 M = 256, N = 1152: K = 512 8.6 | 6.7, 960 9.6 | 7.5; MXFP4 M = 32,
+// N = 16384, K = 960 8.6 | 7.6): the kernel's tests stop at 1024.
 inline bool fused_small(int G, int rank, int kpar) { return kpar == kKpar1x8 && rank <= 32 && G >= 16 && G <= 28; }
 
 // How the W4A4 GEMM of an M x N x (64 G) layer is launched.  Tiles are 128 x 256, two workgroups per CU (512 places).
@@ -558,7 +560,8 @@ inline int plan_act_wide(bool int4, const ActPlan &other, int M, int G, int rank
 
 // INT4 and MXFP4 launches that take the kernel of 32-token workgroups (act_tile_kernel.hip): the number of runs that K is cut into (0: they do not),
 // for `room` runs' partial H.  `other`: the plan of the 16-token workgroups, which do not leave partial H for the GEMM.  Two workgroups per CU up
-// to rank 64, one beyond, runs of whole rounds of the four wavefronts, two of them at least and three of a K above 64 groups.
+// to rank 64, one beyond; the number of runs is that of whole rounds of the four wavefronts, two of them at least and three of a K above 64 groups, and K is then cut into so
+// many runs of about one length (33 groups: four of seven and one of five).
 // us per forward, act_kernel.hip | this, ranks above 32: INT4 M = 1440, K = 1792, N = 2336, rank 128 31.9 | 25.2; M = 1255, K = 9856, N = 528, rank 48 37.0 | 29.6; M = 512,
 // K = 12288, N = 3072, rank 128 42.7 | 39.7; M = 320 35.6 | 28.9; M = 913, K = 10624, N = 5984, rank 64 93.6 | 85.0; MXFP4 M = 131, K = 10688, N = 4352, rank 128 29.2 | 23.8; M = 3078,
 // K = 2368, N = 1936, rank 128 36.4 | 32.6.  Not taken: more than 2048 tokens, which fill the CUs with 16 to a workgroup, with a short K (INT4 M = 3246, K = 1408, N = 432,
@@ -630,7 +633,9 @@ inline bool act_longer_runs(int M, int G, int tile_rows) { return tile_rows > 0 
 // N = 1536 14.1 | 13.2; M = 512, K = N = 3072 16.0 | 15.5.  With three groups to a wavefront up to 1024 tokens, which the runs' workgroups take in one round, not for INT4 (M = 512, K =
 // N = 3072 16.8 | 17.9, on 128 x 160 tiles N = 9216 31.1 | 30.1; M = 1024, K = 3072, N = 1536 16.9 | 18.2, N = 4096 25.7 | 26.1, but N = 4608 30.9 | 29.6 and K = 2112, N = 4608 26.5 | 24.0), and for MXFP4 not on tiles of 32 or 64 rows, which are few and read
 // little (M = 371, K = 2560, N = 256 9.9 | 10.6, M = 512, K = 2560, N = 1024 11.0 | 11.5, M = 1024, K = 3072, N = 1024 13.3 | 14.1; tiles of 128 rows M = 771, N = 1536 7 and 2 % faster at K = 2560 and 3072).
-// Nor MXFP4 with 16 columns of H; wider branches, fewer groups and fewer tokens were not measured.
+// Nor MXFP4 with 16 columns of H (wider branches were not measured).  Fewer tokens and groups keep partial H; on the far sides, partial H | one pass: M = 300, K = 1024, N = 3072 INT4 10.9 | 10.2, MXFP4 10.1 | 10.0;
+// M = 340, K = 2048 INT4 14.2 | 14.0, MXFP4 13.6 | 12.6; M = 256, K = 3072, N = 1152 INT4 12.8 | 13.0, MXFP4 11.2 | 11.3; M = 1000, N = 3072: K = 896 INT4 16.3 | 15.2, MXFP4 14.5 | 13.6, K = 512 INT4 13.8 | 13.5, MXFP4
+// 12.3 | 12.3, K = 256 INT4 11.5 | 11.8, MXFP4 11.5 | 12.0.
 inline bool act_pass_instead(bool int4, int M, int N, int G, int rank, int tile_rows) {
     if (M <= 368 || M > 2048 || G < 16 || G > 48 || rank > 32) return false;
     return int4 ? rank > 0 && (G <= 32 || M > 1024 || (M == 1024 && (G <= 40 || N > 4096))) : rank > 16 && (G <= 32 || M > 1024 || tile_rows > 64);
@@ -650,7 +655,8 @@ inline void act_use_small_plan(W &w, bool int4, int M, int N, int G, int rank, i
 // 108 -> 97.  Where H is added by a launch of its own, one pass with eight tokens to a workgroup is the faster one (this kernel | one pass) up to K = 3072:
 // M = 270, K = 1152, N = 12288 18.8 | 17.4; M = 620, K = 2816, N = 11488 33.3 | 32.2; M = 1, K = 3072, N = 36864 28.8 | 28.7; and up to K = 6144 from 1153 tokens on: M = 1700,
 // K = 4096, N = 8192 73.8 | 70.6; M = 1337, K = 6144, N = 4096 50.3 | 49.1; below, M = 270, K = 6144, N = 12288 41.6 | 42.9, M = 594, K = 3776, N = 6896 32.3 | 32.7,
-// M = 893, K = 4224, N = 4928 34.4 | 34.3, M = 1000, K = N = 4608 41.7 | 40.3.  Few tokens of a K below 1024 keep this kernel (not measured), and so do two kinds of launches that one pass is slower for: without
+// M = 893, K = 4224, N = 4928 34.4 | 34.3, M = 1000, K = N = 4608 41.7 | 40.3.  Few tokens of a K below 1024 keep this kernel, slower by 6 to 11 %
+// there too (M = 16, K = 640, N = 36864 13.9 | 12.8, M = 400, K = 960, N = 9216 17.2 | 15.7), and so do two kinds of launches that one pass is slower for: without
 // a branch, where nothing has to be added (M = 16, K = 2048, N = 39936 20.3 | 21.5, M = 512, K = 1536, N = 9984 17.9 | 18.7, M = 400, K = 3072, N = 9984 26.1 | 27.4), and up to 256 tokens of a K above 2560 with more
 // than 16 columns of H (M = 4, K = 3072, N = 33024, rank 32 28.1 | 29.3, rank 16 27.4 | 27.5; M = 200, N = 19968 30.5 | 31.0; M = 400, N = 9984 30.2 | 30.4).
 inline bool act_w8_small(int M, int K, int rank, int kpar) {

@@ -21,7 +21,7 @@
 // wavefronts' shares of H meet in LDS, H L2 is one or two more steps of the same MFMA, and the wavefronts' sums meet in
 // LDS, both in wavefront order (deterministic).
 // Up to five rows the parts of X^ (and X itself, for H) are made once per workgroup and lie in LDS, where those of the rows fit it
-// (PARTS): five rows are five of a lane's sixteen operand rows, and a wavefront that makes them in its lanes makes everything three
+// and that is the faster side (PARTS; parts_in_lds below): five rows are five of a lane's sixteen operand rows, and a wavefront that makes them in its lanes makes everything three
 // times.
 // Bound: five rows by the load path (13 requests per group and wavefront: 2.7 us of a CU's time at K = 3072) and 96 vector instructions per
 // group (202 with the parts in the loop), more rows by 222 vector and 40 matrix instructions per group, and the fixed parts around the loop.  us

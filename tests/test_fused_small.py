@@ -35,7 +35,7 @@ def test_one_launch_at_its_edges(torch, fmt, M, K, N, r):  # noqa: F811
 @pytest.mark.parametrize("fmt", ["int4", "fp4"])
 def test_one_launch_stays_in_its_buffers_and_rows(torch, fmt):  # noqa: F811
     """Guarded output and workspace; a row with an infinity or a NaN becomes NaN, the others keep their bits; an output in the input's
-    memory (two launches) differs by summation order only: 2e-5 in the 2-norm (perf/cases.py)."""
+    memory (two launches) differs by summation order only, 2e-6 to 3.5e-5 in the 2-norm: held to 1.5e-4, the tolerance of perf/cases.py."""
     M, K, N, r = 70, 1152, 1152, 32
     rng = np.random.default_rng(6200)
     layer = S.DeviceLayer(_layer(rng, K, N, r) if fmt == "int4" else _block_layer(rng, fmt, K, N, r))
