@@ -8,9 +8,9 @@ import pytest
 
 from paper_2411_05007_amd import svdq as S
 from tests.test_gpu_parity import torch  # noqa: F401 (fixture)
-from tests.test_gpu_small_launches import _wide_branch
+from tests.test_gpu_small_launches import _block_format, _wide_branch
 from tests.test_gpu_w8a8 import _random_layer, _run_and_compare
-from tests.test_host_launches import FP4, HERE, W8A8, _gemm_grid, _kernels, record  # noqa: F401 (fixture)
+from tests.test_host_launches import FP4, HERE, INT4, W8A8, _gemm_grid, _kernels, record  # noqa: F401 (fixture)
 
 FITS = r"""
 #include <stdio.h>
@@ -81,3 +81,37 @@ def test_tiles_of_short_loops(record, fmt, M, K, N, r, tile):  # noqa: F811
     """192 x 192 tiles where a CU has several of them, 128 x 128 ones where it would have a single large one with a short loop, and for large INT8 launches of a few groups."""
     k = _kernels(record([(0, fmt, M, K, N, r)])[0])
     assert k[-1].startswith(("gemm_fp4_kernel<" if fmt == FP4 else "gemm_w8a8_kernel<") + tile + ","), k
+
+
+# calls beside the lines that the tables of layout.h draw, with the activation kernel and the tiles that they take: ragged tokens, columns and groups
+LINES = [("fp4", 17, 1088, 16464, 48, "act_kernel<", "gemm_kpar_blocks_kernel<"), ("fp4", 129, 1088, 8272, 32, "act_kernel<", "gemm_kpar_blocks_kernel<"), ("fp4", 97, 1216, 16464, 64, "act_tile_kernel<", "gemm_fp4_kernel<2,2,"),
+         ("fp4", 301, 2112, 1040, 0, "act_kernel<", "gemm_kpar_blocks_kernel<"), ("fp4", 371, 2176, 528, 32, "act_kernel<", "gemm_kpar_blocks_kernel<"), ("fp4", 131, 1088, 23440, 16, "act_kernel<", "gemm_fp4_kernel<3,2,"),
+         ("fp4", 257, 1088, 2064, 0, "act_onepass_kernel<", "gemm_kpar_blocks_kernel<"), ("int4", 1024, 2624, 1040, 32, "act_kernel<", "gemm_w4a4_kpar_kernel<"),
+         ("w8a8", 33, 1088, 16464, 32, "act_w8_small_kernel<", "gemm_kpar_blocks_kernel<"), ("w8a8", 397, 1152, 5200, 0, "act_w8_small_kernel<", "gemm_kpar_blocks_kernel<"), ("w8a8", 201, 1088, 19984, 0, "act_w8_small_kernel<", "gemm_w8a8_kernel<2,2,"),
+         ("w8a8", 201, 2624, 16528, 32, "act_w8_small_kernel<", "gemm_w8a8_kernel<"), ("w8a8", 2049, 192, 10768, 16, "act_kernel<", "gemm_w8a8_kernel<2,2,")]
+
+
+@pytest.mark.parametrize("fmt,M,K,N,r,act,gemm", LINES)
+def test_which_kernels_the_lines_choose(record, fmt, M, K, N, r, act, gemm):  # noqa: F811
+    k = _kernels(record([(0, {"int4": INT4, "fp4": FP4, "w8a8": W8A8}[fmt], M, K, N, r)])[0])
+    assert k[0].startswith(act) and k[-1].startswith(gemm), k
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fmt,M,K,N,r", [s[:5] for s in LINES])
+def test_forwards_beside_the_lines(torch, fmt, M, K, N, r):  # noqa: F811
+    """Codes and scales exact, H and Y to the bounds of the formats' own tests."""
+    if fmt == "int4":
+        return _wide_branch(torch, fmt, M, K, N, r)
+    _block_format(torch, fmt, M, K, N, r, None)
+
+
+def test_int8_tiles_fit_the_padded_rows_and_columns(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host compiler")
+    src, exe = tmp_path / "fits8.cpp", tmp_path / "fits8"
+    src.write_text(FITS.replace("plan_gemm_fp4(M, N, G, want)", "plan_gemm_fp4(M, N, G, want, 32, true)").replace("{1, 18, 48, 192}", "{1, 7, 8, 18}"))
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", os.path.join(os.path.dirname(HERE), "paper_2411_05007_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout

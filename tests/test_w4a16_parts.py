@@ -56,3 +56,13 @@ def test_where_parts_in_lds_would_cost(record):  # noqa: F811
              (1, 576, 36864, 16, True), (2, 512, 9216, 32, True), (3, 384, 18432, 64, True), (4, 64, 18432, 32, True), (1, 512, 128, 32, True)]
     for (M, K, N, r, parts), rec in zip(calls, record([(0, W4A16, M, K, N, r) for M, K, N, r, _ in calls])):
         assert _kernels(rec)[-1].endswith(",true>") == parts, (M, K, N, r, _kernels(rec))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,K,N,r", [(5, 2048, 24656, 16), (4, 2112, 24592, 0), (1, 128, 272, 16), (2, 448, 1040, 48), (3, 64, 144, 64)])
+def test_parts_in_the_loop_where_lds_would_cost(torch, M, K, N, r):  # noqa: F811
+    """Bound: as for the parts in LDS."""
+    from tests.test_gpu_w4a16 import _run
+    rng = np.random.default_rng(6700 + M + K + N)
+    print(f"w4a16 parts in the loop: M={M} K={K} N={N} r={r}", flush=True)
+    _run(torch, O.bf16_round(rng.standard_normal((M, K)).astype(np.float32)), _layer(rng, K, N, min(r, N, K)), f"w4a16 {M}x{K}x{N} r{r}")
